@@ -26,38 +26,15 @@ if ROOT not in sys.path:
 
 METRIC = "logL evals/sec (full-band & heterodyned) vs FP64 plain at |dlogL|<1e-3"
 
-# Algorithmic FP64 flops per (proposal, frequency bin) of the fused kernel, FMA
-# counted as 2.  FP64 form: TaylorF2 phase by Horner in f^(1/3) (11 FMA + 1 mul
-# = 23), reduction to a fraction of a cycle (1), detector-0 complex MAC (4 FMA
-# = 8), two detectors' rotation-Horner steps (2 x (2 mul + 6 FMA) = 28), and
-# the FP64 sin/cos polynomial (47): 107.  Mixed form: the phase comes from a
-# cubic recurrence in runs of bins (gw_full_phase_runs): a recurrence bin
-# costs 3 additions, a directly evaluated one (the first four of a run, and
-# every bin below the lowest level) the phase without its constant and
-# linear terms (9 FMA + 3 mul = 21), the linear term (1 mul + 1 FMA = 3), the
-# difference update (3) and the sum (1); both then add 1 + 8 + 28.  The FP32
-# sin/cos of the mixed form are not counted as FP64 flops.
-FLOPS_PER_BIN = {"fp64": 107.0, "mixed_recurrence": 40.0, "mixed_direct": 65.0}
+# FP64 flops per (proposal, node) of the fused kernel at three detectors, FMA
+# counted as 2: the TaylorF2 phase by Horner in f^(1/3) less the reference (12
+# FMA = 24), two detectors' delays (2 FMA = 4), three phasors (mixed: reduction
+# 1, square 1, 14 FMA, 1 mul = 31 each; FP64: 48 each) and three complex
+# multiply-adds (12 FMA = 24).  The nodes stand for all n_freq bins
+# (gw_full_nodes).
+FLOPS_PER_NODE = {"fp64": 24 + 4 + 3 * 48 + 24, "mixed": 24 + 4 + 3 * 31 + 24}
 
 
-def mixed_flops_per_bin(gw, ctx, n_freq):
-    """Average mixed-form flops per bin over the band.  Runs are aligned
-    blocks, and a chunk that starts inside one also re-evaluates the run's
-    first bins, which adds under 0.2 % at 128 chunks and is not counted."""
-    k_min, lens = gw.gw_full_phase_runs(ctx.handle)
-    direct, k = 0, n_freq - 1
-    while k >= 0:
-        run, s = 0, 0
-        for km, ln in zip(k_min, lens):
-            if k & ~(ln - 1) >= km:
-                run, s = ln, k & ~(ln - 1)
-                break
-        if run == 0:  # every lower bin is evaluated directly
-            direct += k + 1
-            break
-        direct += min(min(s + run - 1, n_freq - 1) - s + 1, 4)
-        k = s - 1
-    return (FLOPS_PER_BIN["mixed_recurrence"] * (n_freq - direct) + FLOPS_PER_BIN["mixed_direct"] * direct) / n_freq
 PEAK_FP64_TFLOPS = 78.6  # MI355X FP64 vector, dense
 
 # HBM bytes per launch from two rocprofv3 PMC runs (FETCH_SIZE, WRITE_SIZE)
@@ -258,12 +235,13 @@ def cfg1_leg(gw, torch, steps, warmup):
     with gw.Context(prob) as ctx:
         for name, prec in (("fp64", gw.GW_PREC_FP64), ("mixed", gw.GW_PREC_MIXED)):
             dt, k_ms = time_steps(ctx, theta, out, steps, warmup, prec, gw.GW_MARG_NONE, torch, gw, profile=True)
-            fpb = FLOPS_PER_BIN["fp64"] if name == "fp64" else mixed_flops_per_bin(gw, ctx, int(prob.n_freq))
-            ach = fpb * n * prob.n_freq / (k_ms * 1e-3) / 1e12
+            nodes = gw.gw_full_nodes(ctx.handle)[0]
+            ach = FLOPS_PER_NODE[name] * n * nodes / (k_ms * 1e-3) / 1e12
             res[name] = {"value": n * steps / dt, "ms_per_batch": dt / steps * 1e3, "kernel_ms": k_ms,
                          "roofline": {"kernel": f"k_full<3,{0 if name == 'fp64' else 1}>", "bound": "alu",
                                       "achieved": ach, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                                      "frac": ach / PEAK_FP64_TFLOPS, "flops_per_bin": fpb}}
+                                      "frac": ach / PEAK_FP64_TFLOPS, "n_nodes": nodes,
+                                      "flops_per_node": FLOPS_PER_NODE[name]}}
     res.update({"unit": "logL evals/s", "batch": n, "n_freq": int(prob.n_freq),
                 "workload": "plain FP64 batch likelihood: T=8 s, 20-512 Hz, df=1/8 Hz (3937 bins x 3 detectors), "
                             "1024 prior draws, no marginalisation"})
@@ -880,7 +858,7 @@ def main():
         dt_fp, k_fp = time_steps(ctx, theta, out, fp_steps, 2, gw.GW_PREC_FP64, marg, torch, gw, profile=True)
         fp = out.clone()
         dlogl = float(torch.max(torch.abs(mix - fp)).item())
-        fpb_mixed = mixed_flops_per_bin(gw, ctx, int(prob.n_freq))
+        nodes = gw.gw_full_nodes(ctx.handle)[0]
         tm = None
         if "tmarg" in set(args.legs.split(",")):
             tm = tmarg_leg(gw, torch, ctx, theta, max(5, args.steps // 2), 2, n * args.steps / dt_mix)
@@ -892,9 +870,9 @@ def main():
             ml = mlp_leg(gw, torch, ctx, max(10, args.steps))
     value = n * args.steps / dt_mix
     fp_value = n * fp_steps / dt_fp
-    units = n * prob.n_freq
-    ach = fpb_mixed * units / (k_mix * 1e-3) / 1e12
-    ach_fp = FLOPS_PER_BIN["fp64"] * units / (k_fp * 1e-3) / 1e12
+    flops_mix, flops_fp = (FLOPS_PER_NODE[k] * n * nodes for k in ("mixed", "fp64"))
+    ach = flops_mix / (k_mix * 1e-3) / 1e12
+    ach_fp = flops_fp / (k_fp * 1e-3) / 1e12
     res = {
         "metric": METRIC,
         "value": value,
@@ -910,8 +888,9 @@ def main():
         "data": "synthetic",
         "config": {"workload": "full-band BNS likelihood: TaylorF2 3.5PN aligned-spin+tidal, 3 detectors, "
                                "T=128 s, 20-2048 Hz, df=1/128 Hz (259,585 bins/detector), batch 4096 prior "
-                               "draws, phase+distance marginalised; mixed form (FP64 phase by a cubic "
-                               "recurrence in runs of bins, FP32 sin/cos, FP64 sums)",
+                               "draws, phase+distance marginalised; mixed form (sums over interpolation nodes that "
+                               "stand for all bins to 1e-13, FP64 phase and sums, sin/cos to 1e-10, FP32 terms in "
+                               "the distance marginal)",
                    "batch": n, "n_freq": int(prob.n_freq), "n_det": 3, "marg": "phase+distance",
                    "prec": "mixed"},
         "roofline": {"bound": "alu", "achieved": ach, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
@@ -919,7 +898,7 @@ def main():
                      "hbm_gbs": (traffic_bytes() / (k_mix * 1e-3) / 1e9) if traffic_bytes() else None,
                      "hbm_peak_gbs": 8000.0,
                      "kernel": "k_full<3,1> (mixed)", "kernel_ms": k_mix,
-                     "flops_per_launch": fpb_mixed * units, "flops_per_bin": fpb_mixed},
+                     "flops_per_launch": flops_mix, "n_nodes": nodes, "flops_per_node": FLOPS_PER_NODE["mixed"]},
         "fp64_plain": {"value": fp_value, "ms_per_step": dt_fp / fp_steps * 1e3, "kernel_ms": k_fp,
                        "roofline_frac": ach_fp / PEAK_FP64_TFLOPS},
         "speedup_vs_fp64": value / fp_value,

@@ -686,16 +686,25 @@ gw_status gw_autotune(gw_ctx* ctx, const double* theta, int64_t n, int32_t like,
 gw_status gw_set_full_shape(gw_ctx* ctx, int32_t tpb, int32_t n_chunks);
 
 /*
- * Reduction used by the mixed-precision full band: 0 automatic (currently the
- * vector-ALU form, the faster one at a batch of 4096), 1 vector ALUs (one sin/cos per bin, per-detector delay
- * rotation by recurrence), 2 matrix cores (block moments: the delay rotation
+ * Reduction used by the full band: 0 automatic (the interpolation nodes, see
+ * gw_full_nodes, and the vector-ALU form for the rows they do not cover), 1
+ * vector ALUs over every bin (one sin/cos per bin, per-detector delay rotation
+ * by recurrence), 2 matrix cores (block moments: the delay rotation
  * of detectors 1.. is expanded within blocks of B bins in powers of the bin
  * offset, truncated where the first dropped term is below 1e-9, and the block
  * moments are an FP32 contraction on v_mfma_f32_16x16x4_f32, folded into FP64
  * per block).  Kind 2 on a context where the form is unavailable makes
- * loglike_batch return GW_ENOTSUP.  The FP64 form always uses kind 1.
+ * loglike_batch return GW_ENOTSUP.  The FP64 form takes kind 2 as 0.
  */
 gw_status gw_set_full_kernel(gw_ctx* ctx, int32_t kind);
+/* Kinds 0 and 2 sum the rows that the context's interpolation nodes cover over
+ * the nodes (FP64, and mixed for kind 0); kind 1 sums every row over every bin.
+ * A node stands for a block of bins over which the template is smooth: n_nodes
+ * samples reproduce the sums over n_freq bins to 1e-13 of the sum of |u_ik|
+ * for every row whose d Psi / d f lies within the range of the sampler's prior
+ * (chirp masses from 1.05 Msun up) and whose |t_c + dt_i| is at most tau_max
+ * (s); the others are summed over every bin.  Either output may be NULL. */
+gw_status gw_full_nodes(const gw_ctx* ctx, int32_t* n_nodes, double* tau_max);
 /* Block length B of the matrix-core form (0 when the detectors are too far
  * apart for a block of 8 bins at this frequency spacing). */
 gw_status gw_full_info(const gw_ctx* ctx, int32_t* mom_blk);

@@ -12,8 +12,8 @@ from ._lib import (  # noqa: F401
     GwError, gw_ctx_create, gw_ctx_destroy, gw_data_inner, gw_last_error, gw_set_full_shape, gw_template,
     gw_version, loglike_batch, heterodyne_setup, gw_het_info, loglike_batch_uneven, gw_set_het_shape,
     gw_graph_info, gw_profile_enable, gw_profile_read, slice_step, slice_sweep, gw_prior_transform, Mlp,
-    gw_set_full_kernel, gw_full_info, gw_full_phase_runs, gw_phasor_gain, WaveformCache, gw_set_time_window,
-    gw_time_grid_info, gw_set_het_tm_split, gw_reconstruct, slice_uniforms_fixed, GW_MAX_BLOCK, gw_set_sky_frame,
+    gw_set_full_kernel, gw_full_info, gw_full_nodes, gw_full_phase_runs, gw_phasor_gain, WaveformCache,
+    gw_set_time_window, gw_time_grid_info, gw_set_het_tm_split, gw_reconstruct, slice_uniforms_fixed, GW_MAX_BLOCK, gw_set_sky_frame,
     gw_fiducial_search, gw_set_time_oversample, loglike_batch_noalloc, noalloc_max_rows, GW_NOALLOC_DOUBLES,
 )
 
@@ -51,7 +51,7 @@ class Context:
         return gw_data_inner(self._ctx)
 
     def set_full_kernel(self, kind: int = 0):
-        """0 automatic, 1 vector-ALU reduction, 2 matrix-core reduction (mixed precision)."""
+        """0 automatic, 1 vector-ALU reduction over every bin, 2 matrix-core reduction (mixed precision)."""
         gw_set_full_kernel(self._ctx, kind)
 
     @property

@@ -167,6 +167,7 @@ _SIGS = {
     "gw_prior_transform_marg": (ctypes.c_int, [_P, _P, ctypes.c_int64, ctypes.c_int32, _P, _P]),
     "gw_set_full_kernel": (ctypes.c_int, [_P, ctypes.c_int32]),
     "gw_full_info": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32)]),
+    "gw_full_nodes": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_double)]),
     "gw_full_phase_runs": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
     "gw_phasor_gain": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double)]),
     "gw_mlp_create": (ctypes.c_int, [_P, ctypes.c_uint64, ctypes.POINTER(_P)]),
@@ -355,6 +356,13 @@ def gw_full_phase_runs(ctx):
     n = (ctypes.c_int32 * 4)()
     check(load().gw_full_phase_runs(ctx, k, n), "gw_full_phase_runs")
     return list(k), list(n)
+
+
+def gw_full_nodes(ctx):
+    """(number of interpolation nodes, largest |t_c + dt_i| they cover in s)."""
+    n, tau = ctypes.c_int32(), ctypes.c_double()
+    check(load().gw_full_nodes(ctx, ctypes.byref(n), ctypes.byref(tau)), "gw_full_nodes")
+    return n.value, tau.value
 
 
 def gw_full_info(ctx) -> int:

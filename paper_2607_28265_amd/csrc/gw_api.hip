@@ -222,6 +222,7 @@ gw_status gw_ctx_create(const gw_problem* pr, int32_t device, gw_ctx** out) {
   if (st == GW_OK) st = build_moment_table(ctx, rec, pr->det_pos);
   if (st == GW_OK) st = wmom_init(ctx);
   if (st == GW_OK) st = calibrate_phasor(ctx);
+  if (st == GW_OK) st = nodes_init(ctx);
   if (st != GW_OK) {
     gw_ctx_destroy(ctx);
     return st;
@@ -236,6 +237,7 @@ gw_status gw_ctx_destroy(gw_ctx* ctx) {
   het_free(ctx);
   graphs_free(ctx);
   slice_free(ctx);
+  nodes_free(ctx);
   for (hipEvent_t e : ctx->prof_ev)
     if (e) (void)hipEventDestroy(e);
   double* bufs[] = {ctx->bins,   ctx->dist_tab, ctx->coef,   ctx->partial, ctx->zbuf,
@@ -284,7 +286,8 @@ gw_status loglike_batch(gw_ctx* ctx, const double* theta, int64_t n, int32_t lik
     s = launch_full(ctx, ctx->coef, ld, n, prec, tpb, nch, ctx->partial, st);
     prof_end(ctx, slot, st);
   }
-  if (s == GW_OK) s = launch_epilogue(ctx, ctx->partial, nch, ctx->coef, ld, n, marg, prec, logl, st);
+  if (s == GW_OK)
+    s = launch_epilogue(ctx, ctx->partial, nch, node_chunks(ctx, n, prec, nch), ctx->coef, ld, n, marg, prec, logl, st);
   return s;
 }
 
@@ -296,7 +299,7 @@ gw_status gw_template(gw_ctx* ctx, const double* theta, int64_t n, double* h, vo
   hipStream_t st = (hipStream_t)stream;
   gw_status s = check_hip(hipSetDevice(ctx->device), "hipSetDevice");
   if (s == GW_OK) s = ensure_buffer(&ctx->coef, &ctx->coef_cap, (int64_t)C_NCOEF * n, "coefficient workspace");
-  if (s == GW_OK) s = launch_prologue(ctx, theta, n, 0, ctx->coef, n, st);
+  if (s == GW_OK) s = launch_prologue(ctx, theta, n, 0, ctx->coef, n, st, false);
   if (s == GW_OK) s = launch_template(ctx, ctx->coef, n, n, h, st);
   return s;
 }

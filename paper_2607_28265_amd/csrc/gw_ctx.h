@@ -9,11 +9,18 @@
 #include <vector>
 
 #include "gw_device.h"
+#include "gw_nodes.h"
 #include "gwswig.h"
 
 struct gw_het_state;
 struct gw_graph_cache;
 struct gw_slice_ws;
+
+// Interpolation nodes (gw_nodes.h): records [n][node_rs] on the device.
+struct NodeTable {
+  double* rec = nullptr;
+  int n = 0;
+};
 
 struct gw_ctx {
   int device = 0;
@@ -24,6 +31,11 @@ struct gw_ctx {
   //   x = f^(1/3), x^2, f^(-5/3), ln f, then Re/Im of u_ik per detector
   double* bins = nullptr;
   int rec_stride = 0;
+  // interpolation nodes of the full-band sums, and the row check that admits
+  // a row to them (host and device copies)
+  NodeTable nodes;
+  gw::NodeCheck node_check{};
+  gw::NodeCheck* node_check_dev = nullptr;
   // distance grid
   double* dist_tab = nullptr;      // [n_dist][4]: d, 1/d, 1/(2 d^2), ln w
   int32_t n_dist = 0;
@@ -92,12 +104,17 @@ gw_status check_hip(hipError_t e, const char* what);
 gw_status ensure_buffer(double** buf, int64_t* cap, int64_t need, const char* what);
 
 // Launch helpers (all asynchronous on ``st``).
+// ``nodes``: with the row check of the node tables (column C_NODE, else 0).
 gw_status launch_prologue(gw_ctx* ctx, const double* theta, int64_t n, int marg, double* coef,
-                          int64_t ld, hipStream_t st);
+                          int64_t ld, hipStream_t st, bool nodes = true);
 gw_status launch_full(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, int prec,
                       int tpb, int n_chunks, double* partial, hipStream_t st);
+// Chunks (the first of n_chunks) that hold the partial sums of the rows summed
+// over the nodes, for a launch of n rows; 0 when every row takes the sums over
+// the bins.
+int node_chunks(const gw_ctx* ctx, int64_t n, int prec, int n_chunks);
 // The partials may be overwritten (small batches reduce them in place first).
-gw_status launch_epilogue(gw_ctx* ctx, double* partial, int n_chunks, const double* coef,
+gw_status launch_epilogue(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef,
                           int64_t ld, int64_t n, int marg, int prec, double* logl, hipStream_t st);
 gw_status launch_template(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, double* h,
                           hipStream_t st);
@@ -122,13 +139,13 @@ int64_t wmom_slot_f2(const gw_ctx* ctx);
 gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, int tpb, int n_chunks,
                         const int32_t* slow_rows, const int32_t* fast_rows, const int32_t* counts, int rows_per_slot,
                         const int32_t* slot_of, const float2* mom, double* zfast, double* partial, hipStream_t st);
-gw_status launch_epilogue_cached(gw_ctx* ctx, double* partial, int n_chunks, const double* coef, int64_t ld,
-                                 int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc,
+gw_status launch_epilogue_cached(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef,
+                                 int64_t ld, int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc,
                                  double* zrow, hipStream_t st);
 // As launch_epilogue_cached, with the distance marginal's (|Z_1|, <h|h>_1)
 // staging buffer [2][n] given explicitly instead of the context's.
-gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, const double* coef, int64_t ld, int64_t n,
-                            int marg, int prec, double* logl, const int32_t* zsrc, const double* zc, double* zrow,
+gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef,
+                            int64_t ld, int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc, double* zrow,
                             double* zbuf, hipStream_t st);
 gw_status launch_wmom_build(gw_ctx* ctx, const double* coef, int64_t ld, const int32_t* slots, const int32_t* count,
                             int64_t max_count, int rows_per_slot, const int32_t* src, int prec, float2* mom,
@@ -139,11 +156,16 @@ gw_status wmom_init(gw_ctx* ctx);
 // and the workspace it needs for n rows.
 void cached_shape(const gw_ctx* ctx, int* tpb, int* nch);
 gw_status cached_reserve(gw_ctx* ctx, int64_t n);
+// As node_chunks, for launch_cached.
+int cached_node_chunks(const gw_ctx* ctx, int n_chunks);
 void full_launch_shape(const gw_ctx* ctx, int64_t n, int* tpb, int* n_chunks);
 // Block-moment table of the matrix-core reduction from the per-bin records
 // (host [n_freq][4 + 2 n_det]); leaves the form unavailable (mom_blk = 0) when
 // the detector delays are too long for a block of 8 bins.
 gw_status build_moment_table(gw_ctx* ctx, const std::vector<double>& rec, const double* det_pos);
+// Build the node tables and the row check (needs the bin records on the device).
+gw_status nodes_init(gw_ctx* ctx);
+void nodes_free(gw_ctx* ctx);
 // Measure the hardware phasor bias and set ctx->pgain_re / pgain_im.
 gw_status calibrate_phasor(gw_ctx* ctx);
 

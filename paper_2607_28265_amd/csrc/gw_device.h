@@ -36,6 +36,7 @@ enum CoefCol {
   C_HH = 24,         // <h|h> summed over detectors (closed form)
   C_TAU0 = 25,       // total time shift of detector 0 (t_c + dt_0), s
   C_AMP = 26,        // amplitude A
+  C_NODE = 27,       // full band: what of the row the node tables cover (gw_nodes.h)
   C_NCOEF = 32
 };
 
@@ -53,90 +54,126 @@ struct Geom {
 
 __device__ inline bool finite_d(double v) { return __builtin_isfinite(v); }
 
-// Per-proposal prologue.  Writes C_NCOEF values into out[] (stride ``ld``).
+// Phase in cycles of the template at one frequency, from the coefficient
+// registers: xm5 * P(x) + (b5 + b6 x) ln f.
+struct PhaseCoef {
+  double a0, a2, a3, a4, a5, a6, a7, a8, a10, a12, b5, b6;
+};
+
+// Per-proposal prologue in two halves that share nothing but the row, so that
+// two waves can take one each: the phase coefficients (masses, spins, tides),
+// and the sky, delays and amplitude.  Together they write every column but
+// C_NODE into out[] (stride ``ld``); a row that is not physical gets zeros.
 // marg: 0 plain, 1 phase-marginalised (phi_c := 0), 2 phase+distance
 // (phi_c := 0, d_L := 1 Mpc), 3 phase+time (phi_c := 0, t_c := 0).
-__device__ inline void prologue(const double* __restrict__ th, int marg, const Geom& g,
-                                double* out, int64_t ld) {
+struct Row {
   double v[13];
+  bool ok;  // finite and physical
+};
+
+__device__ inline Row load_row(const double* __restrict__ th, int marg) {
+  Row r;
 #pragma unroll
-  for (int j = 0; j < 13; ++j) v[j] = th[j];
-  bool ok = true;
+  for (int j = 0; j < 13; ++j) r.v[j] = th[j];
+  r.ok = true;
 #pragma unroll
-  for (int j = 0; j < 13; ++j) ok = ok && finite_d(v[j]);
-  const double mc = v[0], q = v[1], c1 = v[2], c2 = v[3], l1 = v[4], l2 = v[5];
-  double dl = v[6];
-  const double iota = v[7], ra = v[8], dec = v[9], psi = v[10];
-  double phic = v[11];
-  double tc = v[12];
-  ok = ok && mc > 0.0 && q > 0.0 && q <= 1.0 && fabs(c1) < 1.0 && fabs(c2) < 1.0;
-  if (marg != 2) ok = ok && dl > 0.0;
-  if (!ok) {
-#pragma unroll
-    for (int c = 0; c < C_NCOEF; ++c) out[c * ld] = 0.0;
-    return;
+  for (int j = 0; j < 13; ++j) r.ok = r.ok && finite_d(r.v[j]);
+  r.ok = r.ok && r.v[0] > 0.0 && r.v[1] > 0.0 && r.v[1] <= 1.0 && fabs(r.v[2]) < 1.0 && fabs(r.v[3]) < 1.0;
+  if (marg != 2) r.ok = r.ok && r.v[6] > 0.0;
+  return r;
+}
+
+// Phase coefficients but the delay of detector 0 (a8), written and returned.
+__device__ inline PhaseCoef prologue_phase(const Row& row, int marg, double* out, int64_t ld) {
+  PhaseCoef c{};
+  if (row.ok) {
+    const double mc = row.v[0], q = row.v[1], c1 = row.v[2], c2 = row.v[3], l1 = row.v[4], l2 = row.v[5];
+    const double phic = marg != 0 ? 0.0 : row.v[11];
+    // Masses: X1 = m1/M >= X2, eta = X1 X2, delta = X1 - X2.
+    const double x1 = 1.0 / (1.0 + q);
+    const double x2 = q * x1;
+    const double eta = x1 * x2;
+    const double dlt = x1 - x2;
+    const double mtot = mc * pow(eta, -0.6);
+    const double eta2 = eta * eta, eta3 = eta2 * eta;
+
+    // Aligned-spin combinations.
+    const double sl = x1 * x1 * c1 + x2 * x2 * c2;
+    const double dsl = dlt * (x2 * c2 - x1 * c1);
+
+    // Post-Newtonian coefficients of sum_j (p_j + l_j ln v) v^j.
+    const double p0 = 1.0;
+    const double p2 = 3715.0 / 756.0 + 55.0 / 9.0 * eta;
+    const double p3 = -16.0 * kPi + 188.0 / 3.0 * sl + 25.0 * dsl;
+    const double sig = 79.0 / 8.0 * eta * c1 * c2 + 81.0 / 16.0 * (x1 * x1 * c1 * c1 + x2 * x2 * c2 * c2);
+    const double p4 = 15293365.0 / 508032.0 + 27145.0 / 504.0 * eta + 3085.0 / 72.0 * eta2 - 10.0 * sig;
+    const double gam = (554345.0 / 1134.0 + 110.0 / 9.0 * eta) * sl + (13915.0 / 84.0 - 10.0 / 3.0 * eta) * dsl;
+    const double p5 = kPi * (38645.0 / 756.0 - 65.0 / 9.0 * eta) - gam;
+    const double l5 = 3.0 * p5;
+    const double p6 = 11583231236531.0 / 4694215680.0 - 640.0 / 3.0 * kPi * kPi
+                      - 6848.0 / 21.0 * (kEulerGamma + kLog4)
+                      + (-15737765635.0 / 3048192.0 + 2255.0 / 12.0 * kPi * kPi) * eta
+                      + 76055.0 / 1728.0 * eta2 - 127825.0 / 1296.0 * eta3
+                      + kPi * (3760.0 * sl + 1490.0 * dsl) / 3.0;
+    const double l6 = -6848.0 / 21.0;
+    const double p7 = kPi * (77096675.0 / 254016.0 + 378515.0 / 1512.0 * eta - 74045.0 / 756.0 * eta2)
+                      + (-8980424995.0 / 762048.0 + 6586595.0 / 756.0 * eta - 305.0 / 36.0 * eta2) * sl
+                      - (170978035.0 / 48384.0 - 2876425.0 / 672.0 * eta - 4735.0 / 144.0 * eta2) * dsl;
+    // Tidal (Lambda-tilde at 5PN, delta-Lambda-tilde at 6PN).
+    const double lp = l1 + l2, lm = l1 - l2;
+    const double ltil = 8.0 / 13.0 * ((1.0 + 7.0 * eta - 31.0 * eta2) * lp + dlt * (1.0 + 9.0 * eta - 11.0 * eta2) * lm);
+    const double dltil = 0.5 * (dlt * (1.0 - 13272.0 / 1319.0 * eta + 8944.0 / 1319.0 * eta2) * lp
+                                + (1.0 - 15910.0 / 1319.0 * eta + 32850.0 / 1319.0 * eta2 + 3380.0 / 1319.0 * eta3) * lm);
+    const double t10 = -19.5 * ltil;
+    const double t12 = -3115.0 / 64.0 * ltil + 6595.0 / 364.0 * dlt * dltil;
+
+    // v = kappa x with kappa = (pi M)^(1/3), x = f^(1/3); ln v = ln kappa + ln f / 3.
+    const double kap = cbrt(kPi * mtot * kMsunSec);
+    const double lk = log(kap);
+    const double ki = 1.0 / kap;
+    const double ki2 = ki * ki, ki3 = ki2 * ki, ki5 = ki3 * ki2;
+    const double pref = 3.0 / (128.0 * eta) * kInvTwoPi;  // cycles
+    double a[13];
+    a[0] = pref * ki5 * p0;
+    a[2] = pref * ki3 * p2;
+    a[3] = pref * ki2 * p3;
+    a[4] = pref * ki * p4;
+    a[5] = pref * (p5 + l5 * lk) + (-phic - 0.25 * kPi) * kInvTwoPi;
+    a[6] = pref * kap * (p6 + l6 * lk);
+    a[7] = pref * kap * kap * p7;
+    const double kap5 = kap * kap * kap * kap * kap;
+    a[10] = pref * kap5 * t10;
+    a[12] = pref * kap5 * kap * kap * t12;
+    const double b5 = pref * l5 / 3.0;
+    const double b6 = pref * l6 * kap / 3.0;
+    c = PhaseCoef{a[0], a[2], a[3], a[4], a[5], a[6], a[7], 0.0, a[10], a[12], b5, b6};
   }
-  if (marg != 0) phic = 0.0;
-  if (marg == 2) dl = 1.0;
-  if (marg == 3) tc = 0.0;
+  out[C_A0 * ld] = c.a0;
+  out[C_A2 * ld] = c.a2;
+  out[C_A3 * ld] = c.a3;
+  out[C_A4 * ld] = c.a4;
+  out[C_A5 * ld] = c.a5;
+  out[C_A6 * ld] = c.a6;
+  out[C_A7 * ld] = c.a7;
+  out[C_A10 * ld] = c.a10;
+  out[C_A12 * ld] = c.a12;
+  out[C_B5 * ld] = c.b5;
+  out[C_B6 * ld] = c.b6;
+  return c;
+}
 
-  // Masses: X1 = m1/M >= X2, eta = X1 X2, delta = X1 - X2.
-  const double x1 = 1.0 / (1.0 + q);
-  const double x2 = q * x1;
-  const double eta = x1 * x2;
-  const double dlt = x1 - x2;
-  const double mtot = mc * pow(eta, -0.6);
-  const double eta2 = eta * eta, eta3 = eta2 * eta;
-
-  // Aligned-spin combinations.
-  const double sl = x1 * x1 * c1 + x2 * x2 * c2;
-  const double dsl = dlt * (x2 * c2 - x1 * c1);
-
-  // Post-Newtonian coefficients of sum_j (p_j + l_j ln v) v^j.
-  const double p0 = 1.0;
-  const double p2 = 3715.0 / 756.0 + 55.0 / 9.0 * eta;
-  const double p3 = -16.0 * kPi + 188.0 / 3.0 * sl + 25.0 * dsl;
-  const double sig = 79.0 / 8.0 * eta * c1 * c2 + 81.0 / 16.0 * (x1 * x1 * c1 * c1 + x2 * x2 * c2 * c2);
-  const double p4 = 15293365.0 / 508032.0 + 27145.0 / 504.0 * eta + 3085.0 / 72.0 * eta2 - 10.0 * sig;
-  const double gam = (554345.0 / 1134.0 + 110.0 / 9.0 * eta) * sl + (13915.0 / 84.0 - 10.0 / 3.0 * eta) * dsl;
-  const double p5 = kPi * (38645.0 / 756.0 - 65.0 / 9.0 * eta) - gam;
-  const double l5 = 3.0 * p5;
-  const double p6 = 11583231236531.0 / 4694215680.0 - 640.0 / 3.0 * kPi * kPi
-                    - 6848.0 / 21.0 * (kEulerGamma + kLog4)
-                    + (-15737765635.0 / 3048192.0 + 2255.0 / 12.0 * kPi * kPi) * eta
-                    + 76055.0 / 1728.0 * eta2 - 127825.0 / 1296.0 * eta3
-                    + kPi * (3760.0 * sl + 1490.0 * dsl) / 3.0;
-  const double l6 = -6848.0 / 21.0;
-  const double p7 = kPi * (77096675.0 / 254016.0 + 378515.0 / 1512.0 * eta - 74045.0 / 756.0 * eta2)
-                    + (-8980424995.0 / 762048.0 + 6586595.0 / 756.0 * eta - 305.0 / 36.0 * eta2) * sl
-                    - (170978035.0 / 48384.0 - 2876425.0 / 672.0 * eta - 4735.0 / 144.0 * eta2) * dsl;
-  // Tidal (Lambda-tilde at 5PN, delta-Lambda-tilde at 6PN).
-  const double lp = l1 + l2, lm = l1 - l2;
-  const double ltil = 8.0 / 13.0 * ((1.0 + 7.0 * eta - 31.0 * eta2) * lp + dlt * (1.0 + 9.0 * eta - 11.0 * eta2) * lm);
-  const double dltil = 0.5 * (dlt * (1.0 - 13272.0 / 1319.0 * eta + 8944.0 / 1319.0 * eta2) * lp
-                              + (1.0 - 15910.0 / 1319.0 * eta + 32850.0 / 1319.0 * eta2 + 3380.0 / 1319.0 * eta3) * lm);
-  const double t10 = -19.5 * ltil;
-  const double t12 = -3115.0 / 64.0 * ltil + 6595.0 / 364.0 * dlt * dltil;
-
-  // v = kappa x with kappa = (pi M)^(1/3), x = f^(1/3); ln v = ln kappa + ln f / 3.
-  const double kap = cbrt(kPi * mtot * kMsunSec);
-  const double lk = log(kap);
-  const double ki = 1.0 / kap;
-  const double ki2 = ki * ki, ki3 = ki2 * ki, ki5 = ki3 * ki2;
-  const double pref = 3.0 / (128.0 * eta) * kInvTwoPi;  // cycles
-  double a[13];
-  a[0] = pref * ki5 * p0;
-  a[2] = pref * ki3 * p2;
-  a[3] = pref * ki2 * p3;
-  a[4] = pref * ki * p4;
-  a[5] = pref * (p5 + l5 * lk) + (-phic - 0.25 * kPi) * kInvTwoPi;
-  a[6] = pref * kap * (p6 + l6 * lk);
-  a[7] = pref * kap * kap * p7;
-  const double kap5 = kap * kap * kap * kap * kap;
-  a[10] = pref * kap5 * t10;
-  a[12] = pref * kap5 * kap * kap * t12;
-  const double b5 = pref * l5 / 3.0;
-  const double b6 = pref * l6 * kap / 3.0;
+// The other columns; returns the largest |t_c + dt_i|.
+__device__ inline double prologue_sky(const Row& row, int marg, const Geom& g, double* out, int64_t ld) {
+  double ta = 0.0;
+  if (!row.ok) {
+    out[C_A8 * ld] = 0.0;
+#pragma unroll
+    for (int c = C_DT1; c < C_NCOEF; ++c)
+      if (c != C_NODE) out[c * ld] = 0.0;
+    return ta;
+  }
+  const double mc = row.v[0], iota = row.v[7], ra = row.v[8], dec = row.v[9], psi = row.v[10];
+  const double dl = marg == 2 ? 1.0 : row.v[6], tc = marg == 3 ? 0.0 : row.v[12];
 
   // Detector frame: phi = ra - gmst.
   const double ph = ra - g.gmst;
@@ -175,6 +212,7 @@ __device__ inline void prologue(const double* __restrict__ th, int marg, const G
     }
     const double tau = tc + dt;
     if (i == 0) tau0 = tau;
+    if (i < g.n_det) ta = fmax(ta, fabs(tau));
     const double apr = amp * fp * pp;
     const double api = -amp * fx * ci;
     out[(C_APRE + i) * ld] = apr;
@@ -182,32 +220,15 @@ __device__ inline void prologue(const double* __restrict__ th, int marg, const G
     if (i >= 1 && i < 4) out[(C_DT1 + i - 1) * ld] = (i < g.n_det) ? tau - tau0 : 0.0;
     if (i < g.n_det) hh += (apr * apr + api * api) * g.hhw[i];
   }
-  a[8] = tau0;
-  out[C_A0 * ld] = a[0];
-  out[C_A2 * ld] = a[2];
-  out[C_A3 * ld] = a[3];
-  out[C_A4 * ld] = a[4];
-  out[C_A5 * ld] = a[5];
-  out[C_A6 * ld] = a[6];
-  out[C_A7 * ld] = a[7];
-  out[C_A8 * ld] = a[8];
-  out[C_A10 * ld] = a[10];
-  out[C_A12 * ld] = a[12];
-  out[C_B5 * ld] = b5;
-  out[C_B6 * ld] = b6;
+  out[C_A8 * ld] = tau0;
   out[C_VALID * ld] = 1.0;
   out[C_HH * ld] = hh;
   out[C_TAU0 * ld] = tau0;
   out[C_AMP * ld] = amp;
 #pragma unroll
-  for (int c = C_AMP + 1; c < C_NCOEF; ++c) out[c * ld] = 0.0;
+  for (int c = C_NODE + 1; c < C_NCOEF; ++c) out[c * ld] = 0.0;
+  return ta;
 }
-
-// Phase in cycles of the template at one frequency, from the coefficient
-// registers: xm5 * P(x) + (b5 + b6 x) ln f.
-struct PhaseCoef {
-  double a0, a2, a3, a4, a5, a6, a7, a8, a10, a12, b5, b6;
-};
 
 __device__ inline double phase_cycles(const PhaseCoef& c, double x, double x2, double xm5, double lnf) {
   double t = fma(x2, c.a12, c.a10);

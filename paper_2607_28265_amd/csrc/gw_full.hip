@@ -26,11 +26,62 @@
 
 namespace gw {
 
+// Per-row coefficients, 64 rows to a workgroup: wave 0 takes the phase half,
+// wave 1 the sky half (each a serial chain of several FP64 functions, which is
+// what a launch of few rows waits for), then all four waves share the row
+// check of the node tables (gw_nodes.h), a quarter of its frequencies each.
+// At 250 rows 5 us, 6.5 us with one wave doing both halves and no check.
 __global__ void __launch_bounds__(256) k_prologue(const double* __restrict__ theta, int64_t n, int marg,
-                                                  Geom geom, double* __restrict__ coef, int64_t ld) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  prologue(theta + p * 13, marg, geom, coef + p, ld);
+                                                  Geom geom, double* __restrict__ coef, int64_t ld,
+                                                  const NodeCheck* __restrict__ chk) {
+  __shared__ double pc[11][64];
+  __shared__ double tau[64];
+  __shared__ int in[4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t p = (int64_t)blockIdx.x * 64 + lane;
+  const bool live = p < n;
+  if (wave < 2 && live) {
+    const Row row = load_row(theta + p * 13, marg);
+    if (wave == 0) {
+      const PhaseCoef c = prologue_phase(row, marg, coef + p, ld);
+      const double v[11] = {c.a0, c.a2, c.a3, c.a4, c.a6, c.a7, c.a10, c.a12, c.b5, c.b6, row.ok ? 1.0 : 0.0};
+#pragma unroll
+      for (int j = 0; j < 11; ++j) pc[j][lane] = v[j];
+    } else {
+      tau[lane] = prologue_sky(row, marg, geom, coef + p, ld);
+    }
+  }
+  if (!chk) {
+    if (wave == 0 && live) coef[C_NODE * ld + p] = 0.0;
+    return;
+  }
+  __syncthreads();
+  if (live) {
+    // a row that is not physical has zero coefficients: any table takes it
+    PhaseCoef c{};
+    c.a0 = pc[0][lane];
+    c.a2 = pc[1][lane];
+    c.a3 = pc[2][lane];
+    c.a4 = pc[3][lane];
+    c.a6 = pc[4][lane];
+    c.a7 = pc[5][lane];
+    c.a10 = pc[6][lane];
+    c.a12 = pc[7][lane];
+    c.b5 = pc[8][lane];
+    c.b6 = pc[9][lane];
+    bool good = true;
+#pragma unroll
+    for (int j = 0; j < kNodeCheck / 4; ++j) {
+      const double* __restrict__ v = chk->v[wave * (kNodeCheck / 4) + j];
+      good = good && fabs(phase_slope(c, v[0], v[1], v[2], v[3]) - v[4]) <= v[5];
+    }
+    in[wave][lane] = good || pc[10][lane] == 0.0;
+  }
+  __syncthreads();
+  if (wave == 0 && live) {
+    const bool good = in[0][lane] && in[1][lane] && in[2][lane] && in[3][lane];
+    coef[C_NODE * ld + p] = !good ? 0.0 : (tau[lane] > chk->tau_max ? kNodePhase : kNodeFull);
+  }
 }
 
 // Decode a workgroup index into (chunk, proposal tile).  Workgroups are
@@ -90,36 +141,46 @@ __device__ inline void phasor(double r, const TrigConsts& T, double* gr, double*
   }
 }
 
-// LIST (small batches, e.g. the sampler's rounds): the rows are
-// rows[0 .. *count) (at most n, in any order) instead of 0 .. n - 1, 64 to a
-// workgroup, and the workgroup's waves split the chunk's bins between them
-// (each with its own start phase), their sums added in wave order; workgroups
-// past the count exit at once.
-template <int ND, int PREC, bool LIST>
+// SPLIT (the automatic launch shape, and row lists): 64 rows to a workgroup,
+// whose four waves split the chunk's nodes or bins between them (each with its
+// own start phase), their sums added in wave order: a quarter of the partial
+// sums for the same number of waves.  With ``rows`` the rows are
+// rows[0 .. *count) (at most n, in any order) instead of 0 .. n - 1, and
+// workgroups past the count exit at once.
+template <int ND, int PREC, bool SPLIT>
 __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, int64_t ld, int64_t n,
                                               const double* __restrict__ bins, int64_t k0, double df,
                                               int n_freq, int chunk_len, int n_chunks, TrigConsts T, PhaseRuns R,
                                               double pg_re, double pg_im, const int32_t* __restrict__ rows,
-                                              const int32_t* __restrict__ count, double* __restrict__ partial) {
+                                              const int32_t* __restrict__ count, const double* __restrict__ nodes,
+                                              int n_node, int nch_node, TrigFit F, double* __restrict__ partial) {
   constexpr int RS = 4 + 2 * ND;
-  const int tpb = LIST ? 64 : blockDim.x;
+  const int tpb = SPLIT ? 64 : blockDim.x;
   const int nptile = (int)((n + tpb - 1) / tpb);
   int chunk, ptile;
   decode_block(blockIdx.x, nptile, n_chunks, &chunk, &ptile);
   int64_t p, pc;
   bool live;
-  if constexpr (LIST) {
-    const int cnt = *count;
-    if (ptile * tpb >= cnt) return;  // uniform over the workgroup
-    const int idx = ptile * tpb + (threadIdx.x & 63);
+  if constexpr (SPLIT) {
+    const int64_t cnt = rows ? *count : n;
+    if ((int64_t)ptile * tpb >= cnt) return;  // uniform over the workgroup
+    const int64_t idx = (int64_t)ptile * tpb + (threadIdx.x & 63);
     live = idx < cnt;
-    p = rows[live ? idx : cnt - 1];
+    p = live ? idx : cnt - 1;
+    if (rows) p = rows[p];
     pc = p;
   } else {
     p = (int64_t)ptile * tpb + threadIdx.x;
     pc = p < n ? p : n - 1;
     live = p < n;
   }
+
+  // Rows that the node tables cover (gw_nodes.h) take the sums over the nodes,
+  // in the first nch_node chunks; the others the walk over every bin below.
+  // A wave with rows of both kinds does both.
+  const bool on_nodes = nch_node > 0 && coef[C_NODE * ld + pc] >= kNodeFull;
+  const bool any_node = chunk < nch_node && __any(on_nodes), any_bins = __any(!on_nodes);
+  if (!any_node && !any_bins) return;  // the waves of a SPLIT workgroup share their rows
 
   PhaseCoef c;
   c.a0 = coef[C_A0 * ld + pc];
@@ -137,7 +198,7 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
 
   int kb = chunk * chunk_len;
   int ke = kb + chunk_len < n_freq ? kb + chunk_len : n_freq;
-  if constexpr (LIST) {
+  if constexpr (SPLIT) {
     // wave index made visibly wave-uniform, so that the bin walk stays scalar
     const int nw = blockDim.x >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = ((ke > kb ? ke - kb : 0) + nw - 1) / nw;
@@ -147,197 +208,257 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
   }
 
   double zr[ND], zi[ND];
-  double rr[ND], ri[ND];  // rho_i
 #pragma unroll
   for (int i = 0; i < ND; ++i) {
     zr[i] = 0.0;
     zi[i] = 0.0;
-    rr[i] = 1.0;
-    ri[i] = 0.0;
   }
+  if (any_bins) {
+    double rr[ND], ri[ND];  // rho_i
 #pragma unroll
-  for (int i = 1; i < ND; ++i) {
-    const double dt = coef[(C_DT1 + i - 1) * ld + pc];
-    double s, co;
-    sincos_cycles(df * dt, T, &s, &co);
-    rr[i] = co;
-    ri[i] = -s;
-  }
-
-  // Descending walk so that the Horner recurrence leaves rho^0 on the first
-  // bin.  Records alternate between two register sets: while one bin is
-  // processed the next one's record is already in flight.
-  auto accumulate = [&](const double* __restrict__ u, double gr, double gi) {
-    {
-      const double ur = u[0], ui = u[1];
-      zr[0] = fma(ur, gr, zr[0]);
-      zr[0] = fma(-ui, gi, zr[0]);
-      zi[0] = fma(ur, gi, zi[0]);
-      zi[0] = fma(ui, gr, zi[0]);
+    for (int i = 0; i < ND; ++i) {
+      rr[i] = 1.0;
+      ri[i] = 0.0;
     }
 #pragma unroll
     for (int i = 1; i < ND; ++i) {
-      const double ur = u[2 * i], ui = u[2 * i + 1];
-      double tr = zr[i] * rr[i];
-      tr = fma(-zi[i], ri[i], tr);
-      tr = fma(ur, gr, tr);
-      tr = fma(-ui, gi, tr);
-      double ti = zr[i] * ri[i];
-      ti = fma(zi[i], rr[i], ti);
-      ti = fma(ur, gi, ti);
-      ti = fma(ui, gr, ti);
-      zr[i] = tr;
-      zi[i] = ti;
+      const double dt = coef[(C_DT1 + i - 1) * ld + pc];
+      double s, co;
+      sincos_cycles(df * dt, T, &s, &co);
+      rr[i] = co;
+      ri[i] = -s;
     }
-  };
-  if constexpr (PREC == 0) {
-    auto step = [&](const double* __restrict__ rec) {
-      const double r = phase_cycles(c, rec[0], rec[1], rec[2], rec[3]);
-      double gr, gi;
-      phasor<PREC>(r, T, &gr, &gi);
-      accumulate(rec + 4, gr, gi);
+
+    // Descending walk so that the Horner recurrence leaves rho^0 on the first
+    // bin.  Records alternate between two register sets: while one bin is
+    // processed the next one's record is already in flight.
+    auto accumulate = [&](const double* __restrict__ u, double gr, double gi) {
+      {
+        const double ur = u[0], ui = u[1];
+        zr[0] = fma(ur, gr, zr[0]);
+        zr[0] = fma(-ui, gi, zr[0]);
+        zi[0] = fma(ur, gi, zi[0]);
+        zi[0] = fma(ui, gr, zi[0]);
+      }
+#pragma unroll
+      for (int i = 1; i < ND; ++i) {
+        const double ur = u[2 * i], ui = u[2 * i + 1];
+        double tr = zr[i] * rr[i];
+        tr = fma(-zi[i], ri[i], tr);
+        tr = fma(ur, gr, tr);
+        tr = fma(-ui, gi, tr);
+        double ti = zr[i] * ri[i];
+        ti = fma(zi[i], rr[i], ti);
+        ti = fma(ur, gi, ti);
+        ti = fma(ui, gr, ti);
+        zr[i] = tr;
+        zi[i] = ti;
+      }
     };
-    if (ke > kb) {
-      // bins in pairs with one loop exit (see the mixed form below)
-      double ra[RS], rb[RS];
+    if constexpr (PREC == 0) {
+      auto step = [&](const double* __restrict__ rec) {
+        const double r = phase_cycles(c, rec[0], rec[1], rec[2], rec[3]);
+        double gr, gi;
+        phasor<PREC>(r, T, &gr, &gi);
+        accumulate(rec + 4, gr, gi);
+      };
+      if (ke > kb) {
+        // bins in pairs with one loop exit (see the mixed form below)
+        double ra[RS], rb[RS];
 #pragma unroll
-      for (int j = 0; j < RS; ++j) ra[j] = bins[(int64_t)(ke - 1) * RS + j];
-      int k = ke - 1, left = ke - kb;
-      for (; left >= 2; left -= 2, k -= 2) {
+        for (int j = 0; j < RS; ++j) ra[j] = bins[(int64_t)(ke - 1) * RS + j];
+        int k = ke - 1, left = ke - kb;
+        for (; left >= 2; left -= 2, k -= 2) {
 #pragma unroll
-        for (int j = 0; j < RS; ++j) rb[j] = bins[(int64_t)(k - 1) * RS + j];
-        step(ra);
-        const int k2 = k - 2 >= kb ? k - 2 : kb;
+          for (int j = 0; j < RS; ++j) rb[j] = bins[(int64_t)(k - 1) * RS + j];
+          step(ra);
+          const int k2 = k - 2 >= kb ? k - 2 : kb;
 #pragma unroll
-        for (int j = 0; j < RS; ++j) ra[j] = bins[(int64_t)k2 * RS + j];
-        step(rb);
-      }
-      if (left) step(ra);
-    }
-  } else {
-    // runs of the cubic phase recurrence (see PhaseRuns).  A walk that
-    // starts inside a run (a chunk, or a wave's share of one) first advances
-    // the run's table down to its own first bin without accumulating.
-    const double lin_step = -c.a8 * df;  // linear phase change per bin of the descending walk
-    constexpr int US = 2 * ND;
-    int k = ke - 1;
-    while (k >= kb) {
-      int L = 0, s = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int sj = k & ~(R.len[j] - 1);
-        if (L == 0 && sj >= R.k_min[j]) {
-          L = R.len[j];
-          s = sj;
+          for (int j = 0; j < RS; ++j) ra[j] = bins[(int64_t)k2 * RS + j];
+          step(rb);
         }
+        if (left) step(ra);
       }
-      if (L == 0) {
-        // below the lowest level: every bin evaluated directly
-        const int nd = k - kb + 1 < 4 ? k - kb + 1 : 4;
+    } else {
+      // runs of the cubic phase recurrence (see PhaseRuns).  A walk that
+      // starts inside a run (a chunk, or a wave's share of one) first advances
+      // the run's table down to its own first bin without accumulating.
+      const double lin_step = -c.a8 * df;  // linear phase change per bin of the descending walk
+      constexpr int US = 2 * ND;
+      int k = ke - 1;
+      while (k >= kb) {
+        int L = 0, s = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int sj = k & ~(R.len[j] - 1);
+          if (L == 0 && sj >= R.k_min[j]) {
+            L = R.len[j];
+            s = sj;
+          }
+        }
+        if (L == 0) {
+          // below the lowest level: every bin evaluated directly
+          const int nd = k - kb + 1 < 4 ? k - kb + 1 : 4;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (j < nd) {
+              const double* __restrict__ rc = bins + (int64_t)(k - j) * RS;
+              const double r = phase_nonlinear(c, rc[0], rc[1], rc[2], rc[3]) + fma(c.a8, rc[0] * rc[1], c.a5);
+              double gr, gi;
+              phasor<PREC>(r, T, &gr, &gi);
+              accumulate(rc + 4, gr, gi);
+            }
+          }
+          k -= nd;
+          continue;
+        }
+        const int top = s + L - 1 < n_freq - 1 ? s + L - 1 : n_freq - 1;
+        const int nd = top - s + 1 < 4 ? top - s + 1 : 4;
+        // the run's first (up to) four bins, evaluated directly; their
+        // nonlinear parts build the backward differences n0..n3
+        double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0, lin = 0.0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (j < nd) {
-            const double* __restrict__ rc = bins + (int64_t)(k - j) * RS;
-            const double r = phase_nonlinear(c, rc[0], rc[1], rc[2], rc[3]) + fma(c.a8, rc[0] * rc[1], c.a5);
-            double gr, gi;
-            phasor<PREC>(r, T, &gr, &gi);
-            accumulate(rc + 4, gr, gi);
+            const int kk = top - j;
+            const double* __restrict__ rc = bins + (int64_t)kk * RS;
+            const double nl = phase_nonlinear(c, rc[0], rc[1], rc[2], rc[3]);
+            lin = fma(c.a8, rc[0] * rc[1], c.a5);
+            const double d1 = nl - n0;
+            const double d2 = d1 - n1;
+            n3 = d2 - n2;
+            n2 = d2;
+            n1 = d1;
+            n0 = nl;
+            if (kk <= k && kk >= kb) {
+              double gr, gi;
+              phasor<PREC>(nl + lin, T, &gr, &gi);
+              accumulate(rc + 4, gr, gi);
+            }
           }
         }
-        k -= nd;
-        continue;
-      }
-      const int top = s + L - 1 < n_freq - 1 ? s + L - 1 : n_freq - 1;
-      const int nd = top - s + 1 < 4 ? top - s + 1 : 4;
-      // the run's first (up to) four bins, evaluated directly; their
-      // nonlinear parts build the backward differences n0..n3
-      double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0, lin = 0.0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (j < nd) {
-          const int kk = top - j;
-          const double* __restrict__ rc = bins + (int64_t)kk * RS;
-          const double nl = phase_nonlinear(c, rc[0], rc[1], rc[2], rc[3]);
-          lin = fma(c.a8, rc[0] * rc[1], c.a5);
-          const double d1 = nl - n0;
-          const double d2 = d1 - n1;
-          n3 = d2 - n2;
-          n2 = d2;
-          n1 = d1;
-          n0 = nl;
-          if (kk <= k && kk >= kb) {
-            double gr, gi;
-            phasor<PREC>(nl + lin, T, &gr, &gi);
-            accumulate(rc + 4, gr, gi);
+        const int lo = s > kb ? s : kb;  // the run's last bin in this walk
+        int kk = top - nd;
+        if (kk >= lo) {
+          // the remaining bins from the table of the full phase
+          double p0 = n0 + lin, p1 = n1 + lin_step, p2 = n2;
+          const double p3 = n3;
+          for (; kk > k; --kk) {  // above the walk's first bin: advance only
+            p2 += p3;
+            p1 += p2;
+            p0 += p1;
           }
+          auto step = [&](const double* __restrict__ u) {
+            p2 += p3;
+            p1 += p2;
+            p0 += p1;
+            double gr, gi;
+            phasor<PREC>(p0, T, &gr, &gi);
+            accumulate(u, gr, gi);
+          };
+          // bins in pairs, one loop exit, so that the accumulators of the
+          // two steps can alternate registers; the next record is in flight
+          // while one is processed
+          double ua[US], ub[US];
+#pragma unroll
+          for (int j = 0; j < US; ++j) ua[j] = bins[(int64_t)kk * RS + 4 + j];
+          int left = kk - lo + 1;
+          for (; left >= 2; left -= 2, kk -= 2) {
+#pragma unroll
+            for (int j = 0; j < US; ++j) ub[j] = bins[(int64_t)(kk - 1) * RS + 4 + j];
+            step(ua);
+            const int k2 = kk - 2 >= lo ? kk - 2 : lo;
+#pragma unroll
+            for (int j = 0; j < US; ++j) ua[j] = bins[(int64_t)k2 * RS + 4 + j];
+            step(ub);
+          }
+          if (left) step(ua);
         }
+        k = s - 1;
       }
-      const int lo = s > kb ? s : kb;  // the run's last bin in this walk
-      int kk = top - nd;
-      if (kk >= lo) {
-        // the remaining bins from the table of the full phase
-        double p0 = n0 + lin, p1 = n1 + lin_step, p2 = n2;
-        const double p3 = n3;
-        for (; kk > k; --kk) {  // above the walk's first bin: advance only
-          p2 += p3;
-          p1 += p2;
-          p0 += p1;
-        }
-        auto step = [&](const double* __restrict__ u) {
-          p2 += p3;
-          p1 += p2;
-          p0 += p1;
-          double gr, gi;
-          phasor<PREC>(p0, T, &gr, &gi);
-          accumulate(u, gr, gi);
-        };
-        // bins in pairs, one loop exit, so that the accumulators of the
-        // two steps can alternate registers; the next record is in flight
-        // while one is processed
-        double ua[US], ub[US];
+    }
+    // Apply exp(-2 pi i f_kb (tau_i - tau_0)) to the recurrences.
 #pragma unroll
-        for (int j = 0; j < US; ++j) ua[j] = bins[(int64_t)kk * RS + 4 + j];
-        int left = kk - lo + 1;
-        for (; left >= 2; left -= 2, kk -= 2) {
+    for (int i = 1; i < ND; ++i) {
+      const double dt = coef[(C_DT1 + i - 1) * ld + pc];
+      const double fb = (double)(k0 + kb) * df;
+      double s, co;
+      sincos_cycles(fb * dt, T, &s, &co);
+      const double er = co, ei = -s;
+      const double tr = zr[i] * er - zi[i] * ei;
+      const double ti = zr[i] * ei + zi[i] * er;
+      zr[i] = tr;
+      zi[i] = ti;
+    }
+    if (PREC == 1) {
+      // remove the mean bias of the hardware phasor (every sum is linear in it)
 #pragma unroll
-          for (int j = 0; j < US; ++j) ub[j] = bins[(int64_t)(kk - 1) * RS + 4 + j];
-          step(ua);
-          const int k2 = kk - 2 >= lo ? kk - 2 : lo;
-#pragma unroll
-          for (int j = 0; j < US; ++j) ua[j] = bins[(int64_t)k2 * RS + 4 + j];
-          step(ub);
-        }
-        if (left) step(ua);
+      for (int i = 0; i < ND; ++i) {
+        const double tr = zr[i] * pg_re - zi[i] * pg_im;
+        zi[i] = zr[i] * pg_im + zi[i] * pg_re;
+        zr[i] = tr;
       }
-      k = s - 1;
     }
   }
-  // Apply exp(-2 pi i f_kb (tau_i - tau_0)) to the recurrences.
-#pragma unroll
-  for (int i = 1; i < ND; ++i) {
-    const double dt = coef[(C_DT1 + i - 1) * ld + pc];
-    const double fb = (double)(k0 + kb) * df;
-    double s, co;
-    sincos_cycles(fb * dt, T, &s, &co);
-    const double er = co, ei = -s;
-    const double tr = zr[i] * er - zi[i] * ei;
-    const double ti = zr[i] * ei + zi[i] * er;
-    zr[i] = tr;
-    zi[i] = ti;
-  }
-  if (PREC == 1) {
-    // remove the mean bias of the hardware phasor (every sum is linear in it)
+  if (any_node) {
+    // the nodes of this wave's share of the chunk, in pairs with the next
+    // record in flight, as for the bins below
+    constexpr int NS = node_rs(ND);
+    const int per = (n_node + nch_node - 1) / nch_node;
+    int jb = chunk * per;
+    int je = jb + per < n_node ? jb + per : n_node;
+    if constexpr (SPLIT) {
+      const int nw = blockDim.x >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      const int sub = ((je > jb ? je - jb : 0) + nw - 1) / nw;
+      const int b2 = jb + wv * sub;
+      je = b2 + sub < je ? b2 + sub : je;
+      jb = b2;
+    }
+    double sr[ND], si[ND], dt[ND];
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
-      const double tr = zr[i] * pg_re - zi[i] * pg_im;
-      zi[i] = zr[i] * pg_im + zi[i] * pg_re;
-      zr[i] = tr;
+      sr[i] = si[i] = 0.0;
+      dt[i] = i == 0 ? 0.0 : coef[(C_DT1 + i - 1) * ld + pc];
+    }
+    auto step = [&](const double* __restrict__ rec) {
+      const double r0 = node_phase(c, rec[0], rec[1], rec[2], rec[3], rec[5]);
+#pragma unroll
+      for (int i = 0; i < ND; ++i) {
+        double gr, gi;
+        node_phasor<PREC>(i == 0 ? r0 : fma(rec[4], dt[i], r0), T, F, &gr, &gi);
+        const double wr = rec[6 + 2 * i], wi = rec[7 + 2 * i];
+        sr[i] = fma(wr, gr, sr[i]);
+        sr[i] = fma(-wi, gi, sr[i]);
+        si[i] = fma(wr, gi, si[i]);
+        si[i] = fma(wi, gr, si[i]);
+      }
+    };
+    if (je > jb) {
+      double ra[NS], rb[NS];
+#pragma unroll
+      for (int q = 0; q < NS; ++q) ra[q] = nodes[(int64_t)jb * NS + q];
+      int j = jb;
+      for (; j + 2 <= je; j += 2) {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) rb[q] = nodes[(int64_t)(j + 1) * NS + q];
+        step(ra);
+        const int j2 = j + 2 < je ? j + 2 : je - 1;
+#pragma unroll
+        for (int q = 0; q < NS; ++q) ra[q] = nodes[(int64_t)j2 * NS + q];
+        step(rb);
+      }
+      if (j < je) step(ra);
+    }
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      zr[i] = on_nodes ? sr[i] : zr[i];
+      zi[i] = on_nodes ? si[i] : zi[i];
     }
   }
-  if constexpr (LIST) {
+  if constexpr (SPLIT) {
     if (!wave_sums_combine<ND>(zr, zi)) return;
   }
-  if (live) {
+  if (live && (!on_nodes || chunk < nch_node)) {
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       partial[((int64_t)chunk * 2 * ND + 2 * i) * n + p] = zr[i];
@@ -1041,9 +1162,14 @@ __global__ void __launch_bounds__(256) k_full_mfma(const double* __restrict__ co
 // zsrc[p] of zc ([slot][2 nd]) instead of the partials (moves that change only
 // A P_i), and zrow (when not NULL) receives every row's z_i ([n][2 nd]).
 // The partials of chunk c are read at chunk index c * cstride (1, or the
-// group length after k_partial_reduce).
+// group length after k_partial_reduce).  A row summed over the nodes has
+// partials in the first nch_node chunks only.
+__device__ inline int row_chunks(const double* __restrict__ coef, int64_t ld, int64_t p, int n_chunks, int nch_node) {
+  return nch_node > 0 && coef[C_NODE * ld + p] >= kNodeFull ? nch_node : n_chunks;
+}
+
 __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ partial, int n_chunks, int cstride,
-                                                  int nd, const double* __restrict__ coef, int64_t ld, int64_t n,
+                                                  int nch_node, int nd, const double* __restrict__ coef, int64_t ld, int64_t n,
                                                   double dd, int marg, double* __restrict__ logl,
                                                   double* __restrict__ zbuf, const int32_t* __restrict__ zsrc,
                                                   const double* __restrict__ zc, double* __restrict__ zrow) {
@@ -1054,10 +1180,13 @@ __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ pa
   double z[2 * kMaxDet];
 #pragma unroll
   for (int j = 0; j < 2 * kMaxDet; ++j) z[j] = 0.0;
-  for (int c = wave; c < n_chunks; c += 16) {
+  const int own = row_chunks(coef, ld, pc, n_chunks * cstride, nch_node);
+  for (int c = wave; c < n_chunks && __any(c * cstride < own); c += 16) {
+    if (c * cstride < own) {
 #pragma unroll
-    for (int j = 0; j < 2 * kMaxDet; ++j)
-      if (j < 2 * nd) z[j] += partial[((int64_t)c * cstride * 2 * nd + j) * n + pc];
+      for (int j = 0; j < 2 * kMaxDet; ++j)
+        if (j < 2 * nd) z[j] += partial[((int64_t)c * cstride * 2 * nd + j) * n + pc];
+    }
   }
   __shared__ double red[15][2 * kMaxDet][64];
   if (wave > 0) {
@@ -1117,13 +1246,16 @@ __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ pa
 // chunks): workgroup (tile, g) adds chunks g cpg .. (g + 1) cpg - 1 of its 64
 // rows (its 4 waves interleaved, then in wave order) and stores the sum in
 // chunk g cpg of the same buffer, which no other workgroup reads.
-__global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ partial, int n_chunks, int cpg, int nd,
-                                                        int64_t n) {
+__global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ partial, int n_chunks, int cpg,
+                                                        int nch_node, int nd, const double* __restrict__ coef,
+                                                        int64_t ld, int64_t n) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t p = (int64_t)blockIdx.x * 64 + lane;
   const int64_t pc = p < n ? p : n - 1;
   const int c0 = blockIdx.y * cpg;
-  const int c1 = c0 + cpg < n_chunks ? c0 + cpg : n_chunks;
+  const int own = row_chunks(coef, ld, pc, n_chunks, nch_node);
+  if (!__any(c0 < own)) return;  // the four waves hold the same rows
+  const int c1 = c0 + cpg < own ? c0 + cpg : own;
   double z[2 * kMaxDet];
 #pragma unroll
   for (int j = 0; j < 2 * kMaxDet; ++j) z[j] = 0.0;
@@ -1233,28 +1365,34 @@ __global__ void __launch_bounds__(256) k_template(const double* __restrict__ coe
 // Launch helpers
 
 gw_status launch_prologue(gw_ctx* ctx, const double* theta, int64_t n, int marg, double* coef, int64_t ld,
-                          hipStream_t st) {
+                          hipStream_t st, bool nodes) {
   if (n == 0) return GW_OK;
-  const int tpb = 256;
-  const int64_t blocks = (n + tpb - 1) / tpb;
-  hipLaunchKernelGGL(k_prologue, dim3((unsigned)blocks), dim3(tpb), 0, st, theta, n, marg, ctx->geom, coef, ld);
+  const int64_t blocks = (n + 63) / 64;
+  hipLaunchKernelGGL(k_prologue, dim3((unsigned)blocks), dim3(256), 0, st, theta, n, marg, ctx->geom, coef, ld,
+                     nodes ? (const NodeCheck*)ctx->node_check_dev : nullptr);
   return check_hip(hipGetLastError(), "prologue launch");
 }
 
+// The automatic shape splits a chunk over the four waves of a 64-row
+// workgroup; a shape set by the caller and the matrix-core form keep their
+// rows per workgroup, whose waves walk the chunk in step.
+static bool full_split(const gw_ctx* ctx) { return ctx->full_tpb <= 0 && ctx->full_kernel != 2; }
+
 void full_launch_shape(const gw_ctx* ctx, int64_t n, int* tpb_out, int* chunks_out) {
-  int tpb = ctx->full_tpb;
+  const bool split = full_split(ctx);
+  const int tpb = ctx->full_tpb > 0 ? ctx->full_tpb : (split || n >= 2048 ? 256 : 64);
   int ch = ctx->full_chunks;
-  if (tpb <= 0) tpb = n >= 2048 ? 256 : 64;
-  const int64_t nptile = (n + tpb - 1) / tpb;
+  const int64_t nptile = split ? (n + 63) / 64 : (n + tpb - 1) / tpb;
   if (ch <= 0) {
-    // Aim for ~4096 workgroups of 4 waves (~2048 of 1), keep at least 32 bins
-    // per chunk.  At 4096 x 259,585 with 4-wave workgroups, 256 chunks (16,384
-    // waves) ran 12 % faster than 128: several waves per SIMD in flight, and a
-    // short tail.
-    const int64_t target = tpb >= 256 ? 4096 : 2048;
+    // For the rows that walk every bin: aim for ~4096 workgroups of 4 waves
+    // (~2048 waves for under 2048 rows), keep at least 32 bins per wave.  At
+    // 4096 x 259,585 with 4-wave workgroups, 16,384 waves ran 12 % faster than
+    // 8192: several waves per SIMD in flight, and a short tail.
+    const int64_t target = split ? (n >= 2048 ? 4096 : 512) : (tpb >= 256 ? 4096 : 2048);
+    const int64_t least = split ? 128 : 32;
     int64_t want = (target + nptile - 1) / nptile;
     want = (want + 7) / 8 * 8;
-    const int64_t maxc = ctx->geom.n_freq / 32 > 8 ? ctx->geom.n_freq / 32 : 8;
+    const int64_t maxc = ctx->geom.n_freq / least > 8 ? ctx->geom.n_freq / least : 8;
     if (want > maxc) want = maxc / 8 * 8 > 0 ? maxc / 8 * 8 : 8;
     if (want < 8) want = 8;
     ch = (int)want;
@@ -1263,6 +1401,8 @@ void full_launch_shape(const gw_ctx* ctx, int64_t n, int* tpb_out, int* chunks_o
   *chunks_out = ch;
 }
 
+bool use_mfma(const gw_ctx* ctx, int prec);
+
 template <int ND>
 static gw_status launch_full_nd(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, int prec, int tpb,
                                 int n_chunks, double* partial, hipStream_t st) {
@@ -1270,17 +1410,23 @@ static gw_status launch_full_nd(gw_ctx* ctx, const double* coef, int64_t ld, int
   const int chunk_len = (int)((nf + n_chunks - 1) / n_chunks);
   const TrigConsts T = make_trig_consts();
   const PhaseRuns PR = make_phase_runs(ctx->geom);
-  const int64_t nptile = (n + tpb - 1) / tpb;
+  const TrigFit F = make_trig_fit();
+  const int nch_node = node_chunks(ctx, n, prec, n_chunks);
+  const bool split = full_split(ctx);
+  const int64_t nptile = split ? (n + 63) / 64 : (n + tpb - 1) / tpb;
   const int64_t blocks = nptile * n_chunks;
   if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
-  if (prec == GW_PREC_FP64) {
-    hipLaunchKernelGGL((k_full<ND, 0, false>), dim3((unsigned)blocks), dim3(tpb), 0, st, coef, ld, n, ctx->bins,
-                       ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, 1.0, 0.0, nullptr, nullptr, partial);
-  } else {
-    hipLaunchKernelGGL((k_full<ND, 1, false>), dim3((unsigned)blocks), dim3(tpb), 0, st, coef, ld, n, ctx->bins,
-                       ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, ctx->pgain_re, ctx->pgain_im,
-                       nullptr, nullptr, partial);
-  }
+  auto launch = [&](auto kernel, double pg_re, double pg_im) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(split ? 256 : tpb), 0, st, coef, ld, n, ctx->bins,
+                       ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, pg_re, pg_im, nullptr, nullptr,
+                       (const double*)ctx->nodes.rec, ctx->nodes.n, nch_node, F, partial);
+  };
+  if (prec == GW_PREC_FP64)
+    split ? launch(k_full<ND, 0, true>, 1.0, 0.0) : launch(k_full<ND, 0, false>, 1.0, 0.0);
+  else if (split)
+    launch(k_full<ND, 1, true>, ctx->pgain_re, ctx->pgain_im);
+  else
+    launch(k_full<ND, 1, false>, ctx->pgain_re, ctx->pgain_im);
   return check_hip(hipGetLastError(), "full-band kernel launch");
 }
 
@@ -1304,6 +1450,32 @@ static gw_status launch_mfma_nd(gw_ctx* ctx, const double* coef, int64_t ld, int
 // benchmark shape); the matrix-core form on request.
 bool use_mfma(const gw_ctx* ctx, int prec) {
   return prec == GW_PREC_MIXED && ctx->mom_blk > 0 && ctx->full_kernel == 2;
+}
+
+// Chunks of the node sums: about kNodeWaves waves in flight (four per SIMD,
+// which all start and end together), about kNodeWaveMin nodes a wave at least
+// (its start costs about ten), and a multiple of 8, since a chunk's workgroups
+// share an XCD: 4096 rows took 100 us a call with 16 or 24 chunks and 113 to
+// 122 us with 12, 18 or 20.  At 250 rows 36 us with 28 to 40 nodes a wave,
+// 40 us with 24 or 64.
+constexpr int64_t kNodeWaves = 4096;
+constexpr int kNodeWaveMin = 28;
+
+int node_chunks(const gw_ctx* ctx, int64_t n, int prec, int n_chunks) {
+  if (ctx->nodes.n <= 0 || ctx->full_kernel == 1 || use_mfma(ctx, prec)) return 0;
+  const int split = full_split(ctx) ? 4 : 1;
+  int64_t c = kNodeWaves / ((n + 63) / 64 * split);
+  if (c > ctx->nodes.n / (kNodeWaveMin * split)) c = ctx->nodes.n / (kNodeWaveMin * split);
+  c = (c + 4) / 8 * 8;
+  if (c < 8) c = 8;
+  return (int)(c < n_chunks ? c : n_chunks);
+}
+
+int cached_node_chunks(const gw_ctx* ctx, int n_chunks) {
+  if (ctx->nodes.n <= 0 || ctx->full_kernel == 1) return 0;
+  int c = ctx->nodes.n / 64 / 8 * 8;
+  if (c < 8) c = 8;
+  return c < n_chunks ? c : n_chunks;
 }
 
 gw_status launch_full(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, int prec, int tpb, int n_chunks,
@@ -1452,35 +1624,37 @@ gw_status build_moment_table(gw_ctx* ctx, const std::vector<double>& rec, const 
   return GW_OK;
 }
 
-gw_status launch_epilogue(gw_ctx* ctx, double* partial, int n_chunks, const double* coef, int64_t ld,
+gw_status launch_epilogue(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef, int64_t ld,
                           int64_t n, int marg, int prec, double* logl, hipStream_t st) {
-  return launch_epilogue_cached(ctx, partial, n_chunks, coef, ld, n, marg, prec, logl, nullptr, nullptr, nullptr, st);
+  return launch_epilogue_cached(ctx, partial, n_chunks, nch_node, coef, ld, n, marg, prec, logl, nullptr, nullptr,
+                                nullptr, st);
 }
 
-gw_status launch_epilogue_cached(gw_ctx* ctx, double* partial, int n_chunks, const double* coef, int64_t ld,
-                                 int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc,
-                                 double* zrow, hipStream_t st) {
-  return launch_epilogue_z(ctx, partial, n_chunks, coef, ld, n, marg, prec, logl, zsrc, zc, zrow, ctx->zbuf, st);
+gw_status launch_epilogue_cached(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef,
+                                 int64_t ld, int64_t n, int marg, int prec, double* logl, const int32_t* zsrc,
+                                 const double* zc, double* zrow, hipStream_t st) {
+  return launch_epilogue_z(ctx, partial, n_chunks, nch_node, coef, ld, n, marg, prec, logl, zsrc, zc, zrow, ctx->zbuf,
+                           st);
 }
 
-gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, const double* coef, int64_t ld, int64_t n,
-                            int marg, int prec, double* logl, const int32_t* zsrc, const double* zc, double* zrow,
+gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef, int64_t ld,
+                            int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc, double* zrow,
                             double* zbuf, hipStream_t st) {
   if (n == 0) return GW_OK;
   const int64_t blocks = (n + 63) / 64;
   const LogI0Consts* C = ctx->i0c;  // device copy, r1max from the distance grid
   int groups = n_chunks, cstride = 1;
-  if (n <= 2048 && n_chunks >= 64) {
+  if (n <= 2048 && n_chunks >= 64 && nch_node <= 0) {
     // few rows, many chunks: reduce groups of 8 chunks across the chip first
     cstride = 8;
     groups = (n_chunks + cstride - 1) / cstride;
     hipLaunchKernelGGL(k_partial_reduce, dim3((unsigned)blocks, (unsigned)groups), dim3(256), 0, st, partial, n_chunks,
-                       cstride, ctx->n_det, n);
+                       cstride, nch_node, ctx->n_det, coef, ld, n);
     gw_status s = check_hip(hipGetLastError(), "partial reduction launch");
     if (s != GW_OK) return s;
   }
-  hipLaunchKernelGGL(k_epilogue, dim3((unsigned)blocks), dim3(1024), 0, st, partial, groups, cstride, ctx->n_det, coef,
-                     ld, n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow);
+  hipLaunchKernelGGL(k_epilogue, dim3((unsigned)blocks), dim3(1024), 0, st, partial, groups, cstride, nch_node,
+                     ctx->n_det, coef, ld, n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow);
   gw_status s = check_hip(hipGetLastError(), "epilogue launch");
   if (s != GW_OK || marg != 2) return s;
   // large batches: lane = row (grid records are scalar loads shared by 64
@@ -1527,6 +1701,8 @@ static gw_status launch_cached_nd(gw_ctx* ctx, const double* coef, int64_t n, in
   const int nf = (int)ctx->geom.n_freq;
   const TrigConsts T = make_trig_consts();
   const PhaseRuns PR = make_phase_runs(ctx->geom);
+  const TrigFit F = make_trig_fit();
+  const int nch_node = cached_node_chunks(ctx, n_chunks);
   const int64_t nptile = (n + 63) / 64;  // 64 rows per workgroup; tpb / 64 waves split each chunk
   const int64_t blocks = nptile * n_chunks;
   if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
@@ -1535,11 +1711,12 @@ static gw_status launch_cached_nd(gw_ctx* ctx, const double* coef, int64_t n, in
   if (slow_rows) {
     if (prec == GW_PREC_FP64)
       hipLaunchKernelGGL((k_full<ND, 0, true>), dim3((unsigned)blocks), dim3(tpb), 0, st, coef, n, n, ctx->bins,
-                         ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, 1.0, 0.0, slow_rows, counts, partial);
+                         ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, 1.0, 0.0, slow_rows, counts,
+                         (const double*)ctx->nodes.rec, ctx->nodes.n, nch_node, F, partial);
     else
       hipLaunchKernelGGL((k_full<ND, 1, true>), dim3((unsigned)blocks), dim3(tpb), 0, st, coef, n, n, ctx->bins,
                          ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, ctx->pgain_re, ctx->pgain_im,
-                         slow_rows, counts, partial);
+                         slow_rows, counts, (const double*)ctx->nodes.rec, ctx->nodes.n, nch_node, F, partial);
     s = check_hip(hipGetLastError(), "full-band list kernel launch");
   }
   if (s != GW_OK || !mom) return s;  // no cache, no fast rows
@@ -1549,6 +1726,9 @@ static gw_status launch_cached_nd(gw_ctx* ctx, const double* coef, int64_t n, in
   int cm = n_blk / 8 < n_chunks ? n_blk / 8 : n_chunks;
   if (cm < 1) cm = 1;
   if (cm > 8) cm = cm / 8 * 8;
+  // rows of the common epilogue that the node tables cover are summed over
+  // nch_node chunks
+  if (!zfast && nch_node > 0 && cm > nch_node) cm = nch_node;
   const int slot = prof_begin(ctx, st, 1);
   hipLaunchKernelGGL((k_wmom<ND>), dim3((unsigned)(nptile * cm)), dim3(256), 0, st, coef, n, n, ctx->geom.k0,
                      ctx->geom.df, blk, n_blk, cm, zfast ? cm : n_chunks, T, fast_rows, counts + 1, rows_per_slot,

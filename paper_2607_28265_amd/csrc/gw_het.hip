@@ -297,20 +297,22 @@ __device__ inline bool tile_rows(const HetArgs* __restrict__ ab, const int64_t* 
   return *row0 < *row_end;
 }
 
-// Per-row prologue over the work list (same tiles as the evaluation kernel).
-__global__ void __launch_bounds__(256) k_het_prologue(const HetArgs* __restrict__ ab,
+// Per-row prologue over the work list (same tiles as the evaluation kernel): a
+// workgroup per 64-row tile, wave 0 taking the phase half of the prologue and
+// wave 1 the sky half (see k_prologue).
+__global__ void __launch_bounds__(128) k_het_prologue(const HetArgs* __restrict__ ab,
                                                       const int64_t* __restrict__ pre, int marg, Geom geom) {
-  const int lane = threadIdx.x & 63;
-  const int wpb = blockDim.x >> 6;
-  const int64_t wid = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6);
-  const int64_t nwaves = (int64_t)gridDim.x * wpb;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t total = pre[ab->n_sub];
   const int64_t ld = ab->ld;
-  for (int64_t t = wid; t < total; t += nwaves) {
+  for (int64_t t = blockIdx.x; t < total; t += gridDim.x) {
     int64_t row0, row_end;
     if (!tile_rows(ab, pre, t, &row0, &row_end)) continue;
-    const int64_t row = row0 + lane;
-    if (row < row_end) prologue(ab->theta + row * 13, marg, geom, ab->coef + row, ld);
+    const int64_t p = row0 + lane;
+    if (p >= row_end) continue;
+    const Row row = load_row(ab->theta + p * 13, marg);
+    if (wave == 0) prologue_phase(row, marg, ab->coef + p, ld);
+    else prologue_sky(row, marg, geom, ab->coef + p, ld);
   }
 }
 
@@ -806,7 +808,7 @@ static gw_status launch_het_nd(gw_ctx* ctx, int marg, int prec, int n_ech, hipSt
 static gw_status enqueue_het(gw_ctx* ctx, int marg, int prec, int n_ech, hipStream_t st) {
   gw_het_state* h = ctx->het;
   const bool small = h->n_rows_last < kDistRowsPerLane;
-  hipLaunchKernelGGL(k_het_prologue, dim3(small ? 32 : 256 * 4), dim3(256), 0, st, h->args, h->tile_pre, marg,
+  hipLaunchKernelGGL(k_het_prologue, dim3(small ? 128 : 256 * 4), dim3(128), 0, st, h->args, h->tile_pre, marg,
                      ctx->geom);
   gw_status s = check_hip(hipGetLastError(), "heterodyne prologue launch");
   if (s != GW_OK) return s;
@@ -1239,7 +1241,7 @@ gw_status loglike_het_tmarg_staged(gw_ctx* ctx, const double* theta, int64_t n, 
   double2* hpart = part + (int64_t)h->tm_nslot * K * chunk;
   double* hhc = (double*)(hpart + (int64_t)h->tm_nch * chunk * mh);
   double* zpart = zp > 0 ? hhc + (chunk + 1) / 2 * 2 : nullptr;
-  s = launch_prologue(ctx, theta, n, GW_MARG_PHASE_TIME, ctx->coef, n, st);
+  s = launch_prologue(ctx, theta, n, GW_MARG_PHASE_TIME, ctx->coef, n, st, false);
   if (s != GW_OK) return s;
   HetConst hc;
   for (int i = 0; i < kMaxDet; ++i) {
@@ -1383,7 +1385,7 @@ gw_status heterodyne_setup(gw_ctx* ctx, const double* theta0, int32_t n_bins, in
   if (s == GW_OK)
     s = check_hip(hipMemcpy(d_edges, edges.data(), ne * sizeof(int64_t), hipMemcpyHostToDevice), "copy");
   if (s == GW_OK) s = check_hip(hipMemset(h->rec, 0, (size_t)ne * h->rs * sizeof(double)), "memset");
-  if (s == GW_OK) s = launch_prologue(ctx, d_th, 1, 0, d_coef0, 1, nullptr);
+  if (s == GW_OK) s = launch_prologue(ctx, d_th, 1, 0, d_coef0, 1, nullptr, false);
   const TrigConsts T = make_trig_consts();
   if (s == GW_OK) {
     hipLaunchKernelGGL(k_het_edges, dim3((ne + 255) / 256), dim3(256), 0, nullptr, ctx->bins, ctx->rec_stride,

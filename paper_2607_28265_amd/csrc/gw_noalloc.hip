@@ -103,7 +103,8 @@ gw_status loglike_batch_noalloc(gw_ctx* ctx, const double* theta, int64_t n, int
   s = launch_prologue(ctx, theta, n, marg, coef, n, st);
   if (s == GW_OK) s = launch_full(ctx, coef, n, n, prec, tpb, nch, partial, st);
   if (s == GW_OK)
-    s = launch_epilogue_z(ctx, partial, nch, coef, n, n, marg, prec, logl, nullptr, nullptr, nullptr, zbuf, st);
+    s = launch_epilogue_z(ctx, partial, nch, node_chunks(ctx, n, prec, nch), coef, n, n, marg, prec, logl, nullptr,
+                          nullptr, nullptr, zbuf, st);
   return s;
 }
 

@@ -1,0 +1,112 @@
+// Interpolation nodes of the full-band sums.
+//
+// Every full-band sum is linear in samples of a smooth function of frequency,
+//   z_i = sum_k u_ik G_i(f_k),   G_i(f) = exp(-2 pi i (Psi(f) + f tau_i)),
+// with weights u_ik that depend on the data alone.  Relative to a fixed
+// reference phase R(f), G_i turns by at most S(f) = |Psi' + tau_i - R'| cycles
+// per Hz, and on a long segment that is far below one turn per bin over most
+// of the band (a 128 s segment samples every 1/128 Hz what a signal of under
+// two seconds does above 100 Hz).  On a block of bins on which
+// G_i exp(2 pi i R) turns by omega radians to either side of the centre, its
+// polynomial interpolant at n Chebyshev nodes errs by less than about
+// 2 (omega / 2)^n / n!, so with
+//   W_ij = sum_k l_j(f_k) u_ik exp(-2 pi i R(f_k))
+// (l_j the Lagrange polynomials of the block's nodes)
+//   z_i = sum_j W_ij G_i(f_j) exp(2 pi i R(f_j))
+// to 1e-13 of the block's sum of |u_ik|: the same sums from n samples a block
+// instead of one per bin.  The weights are computed once per context.  A block
+// on which that saves less than a tenth keeps its bins (a node per bin).
+//
+// R is half the phase of a reference waveform of chirp mass kNodeMc: chirp
+// times run from 0 (heavy binaries) to that waveform's, so half of it halves
+// the largest S.  S is the largest of a set of waveforms around the sampler's
+// prior (kNodeMc and 1.45 Msun, the prior's mass ratios and tides, aligned
+// spins of 0.1), times 1.02, plus 1 ms.  k_prologue compares each row's
+// Psi' - R' with S at kNodeCheck frequencies (Psi' - R' is a sum of a dozen
+// powers of f, too smooth to exceed S between them by more than that margin)
+// and its delays with tau_max; a row that exceeds either takes the sums over
+// every bin instead.
+#pragma once
+
+#include "gw_device.h"
+#include "gw_trig_fit.h"
+
+namespace gw {
+
+constexpr double kNodeMc = 1.05;   // Msun
+constexpr double kNodeTol = 1e-13; // interpolation error per unit sum of |u|
+constexpr int kNodeMax = 128;      // most nodes of a block
+constexpr int kNodeCheck = 24;     // frequencies of the row check
+
+// Values of the coefficient column C_NODE: the row's phase alone, or its phase
+// and its delays, lie within what the node tables are built for.
+constexpr double kNodePhase = 1.0, kNodeFull = 2.0;
+
+// The row check's frequencies: x = f^(1/3), ln f, x^-8, x^-3, R'(f), S(f).
+struct NodeCheck {
+  double v[kNodeCheck][6];
+  double tau_max;  // s
+};
+
+// Record of one node: x, x^2, f^(-5/3), ln f, f, R (cycles), then Re, Im W_i
+// per detector.
+__host__ __device__ constexpr int node_rs(int nd) { return 6 + 2 * nd; }
+
+// d Psi / d f without the linear time term, in cycles per Hz.
+__device__ inline double phase_slope(const PhaseCoef& c, double x, double lnf, double xm8, double xm3) {
+  // sum_j a_j (j - 5) / 3 x^(j - 8) + (b5 + b6 x) / f + b6 ln f / (3 x^2)
+  double t = fma(x * x, c.a12 * (7.0 / 3.0), c.a10 * (5.0 / 3.0));
+  t = x * x * t;
+  t = fma(x, t, c.a7 * (2.0 / 3.0));
+  t = fma(x, t, c.a6 * (1.0 / 3.0));
+  t = x * t;
+  t = fma(x, t, c.a4 * (-1.0 / 3.0));
+  t = fma(x, t, c.a3 * (-2.0 / 3.0));
+  t = fma(x, t, -c.a2);
+  t = fma(x * x, t, c.a0 * (-5.0 / 3.0));
+  const double l = fma(c.b6 * x, fma(lnf, 1.0 / 3.0, 1.0), c.b5);
+  return fma(l, xm3, t * xm8);
+}
+
+// exp(-2 pi i r) at a node.  FP64 form: the full-accuracy pair.  Mixed form:
+// FP64 polynomials good to 2e-11 / 1.2e-10, where the walk over bins takes the
+// FP32 hardware pair (6e-8): with tens of bins behind each node the rounding
+// of the phasors averages over that many fewer samples, and the difference
+// costs 5 of the 84 instructions of a node.
+template <int PREC>
+__device__ inline void node_phasor(double r, const TrigConsts& T, const TrigFit& F, double* gr, double* gi) {
+  if (PREC == 0) {
+    double s, c;
+    sincos_cycles(r, T, &s, &c);
+    *gr = c;
+    *gi = -s;
+  } else {
+    const double t = r - rint(r);
+    const double s = t * t;
+    double a = F.s[7], b = F.c[7];
+#pragma unroll
+    for (int k = 6; k >= 0; --k) {
+      a = fma(a, s, F.s[k]);
+      b = fma(b, s, F.c[k]);
+    }
+    *gr = b;
+    *gi = -(t * a);
+  }
+}
+
+// Phase at a node relative to the reference, cycles.
+__device__ inline double node_phase(const PhaseCoef& c, double x, double x2, double xm5, double lnf, double ref) {
+  double t = fma(x2, c.a12, c.a10);
+  t = fma(x2, t, c.a8);
+  t = fma(x, t, c.a7);
+  t = fma(x, t, c.a6);
+  t = fma(x, t, c.a5);
+  t = fma(x, t, c.a4);
+  t = fma(x, t, c.a3);
+  t = fma(x, t, c.a2);
+  t = fma(x2, t, c.a0);
+  const double lg = fma(c.b6, x, c.b5);
+  return fma(lg, lnf, fma(t, xm5, -ref));
+}
+
+}  // namespace gw

@@ -166,7 +166,8 @@ gw_status stage_overlaps(gw_ctx* ctx, const double* theta, int64_t n, int like, 
   if (s == GW_OK) s = launch_prologue(ctx, theta, n, marg, ctx->coef, n, st);
   if (s == GW_OK) s = launch_full(ctx, ctx->coef, n, n, prec, tpb, nch, ctx->partial, st);
   if (s == GW_OK)
-    s = launch_epilogue_cached(ctx, ctx->partial, nch, ctx->coef, n, n, marg, prec, ll, nullptr, nullptr, zrow, st);
+    s = launch_epilogue_cached(ctx, ctx->partial, nch, node_chunks(ctx, n, prec, nch), ctx->coef, n, n, marg, prec,
+                               ll, nullptr, nullptr, zrow, st);
   if (s != GW_OK) return s;
   hipLaunchKernelGGL(k_recon_stage, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, zrow, nd, ctx->coef, n, n,
                      zc3);

@@ -190,8 +190,8 @@ gw_status gw_wcache_update(gw_wcache* c, const double* theta, const int32_t* slo
     s = launch_cached(ctx, ctx->coef, n, prec, tpb, nch, c->rows, nullptr, c->counts, 1, nullptr, nullptr, nullptr,
                       ctx->partial, st);
   if (s == GW_OK)
-    s = launch_epilogue_cached(ctx, ctx->partial, nch, ctx->coef, n, n, marg, prec, logl, nullptr, nullptr, c->zrow,
-                               st);
+    s = launch_epilogue_cached(ctx, ctx->partial, nch, cached_node_chunks(ctx, nch), ctx->coef, n, n, marg, prec, logl,
+                               nullptr, nullptr, c->zrow, st);
   if (s == GW_OK) {
     hipLaunchKernelGGL(k_wc_store_z, dim3(blocks), dim3(256), 0, st, c->zrow, c->sl, c->owner, n, ctx->n_det, c->zc);
     s = check_hip(hipGetLastError(), "cached sums launch");
@@ -225,13 +225,13 @@ gw_status gw_wcache_loglike(gw_wcache* c, const double* theta, const int32_t* sl
   hipLaunchKernelGGL(k_wc_rows, dim3(blocks), dim3(256), 0, st, c->rows, n, c->counts, 1);
   s = check_hip(hipGetLastError(), "row list launch");
   if (s == GW_OK && kind == 2) {  // the slots' sums, no reduction
-    s = launch_epilogue_cached(ctx, ctx->partial, 0, ctx->coef, n, n, marg, prec, logl, c->sl, c->zc, nullptr, st);
+    s = launch_epilogue_cached(ctx, ctx->partial, 0, 0, ctx->coef, n, n, marg, prec, logl, c->sl, c->zc, nullptr, st);
   } else if (s == GW_OK) {
     // complete sums into zrow, then the epilogue takes them from there
     s = launch_cached(ctx, ctx->coef, n, prec, tpb, nch, nullptr, c->rows, c->counts, 1, c->sl, c->wc, c->zrow,
                       ctx->partial, st);
     if (s == GW_OK)
-      s = launch_epilogue_cached(ctx, ctx->partial, 0, ctx->coef, n, n, marg, prec, logl, c->rows, c->zrow, nullptr,
+      s = launch_epilogue_cached(ctx, ctx->partial, 0, 0, ctx->coef, n, n, marg, prec, logl, c->rows, c->zrow, nullptr,
                                  st);
   }
   if (s == GW_OK) {
