@@ -33,7 +33,7 @@ struct gw_ctx {
   int rec_stride = 0;
   // interpolation nodes of the full-band sums, and the row check that admits
   // a row to them (host and device copies)
-  NodeTable nodes;
+  NodeTable nodes, nodes_wide;
   gw::NodeCheck node_check{};
   gw::NodeCheck* node_check_dev = nullptr;
   // distance grid
@@ -121,14 +121,16 @@ gw_status launch_template(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n
 // Waveform-cache forms (fast/slow blocks of the sampler).  A cache slot holds
 // the block moments of one intrinsic waveform (float2 [n_blk][n_det][12],
 // wmom_slot_f2 entries; block length wmom_block bins).  launch_cached runs the
-// full reduction on rows slow_rows[0 .. counts[0]) (none when slow_rows is
-// NULL) into partials of n_chunks chunks and row stride n (coefficients with
-// ld = n), and, when mom is not NULL, the moment reduction on rows
-// fast_rows[0 .. counts[1]) (row p uses slot slot_of[p], or p / rows_per_slot
-// when slot_of is NULL), whose complete sums go to zfast[p][2 n_det] (rows
-// whose |t_c + dt_i| exceeds the cache's range get NaN), or, when zfast is
-// NULL, into the same n_chunks partials as the full reduction (summed by the
-// epilogue like any other row).
+// full reduction on rows slow_rows[0 .. counts[0]) into partials of n_chunks
+// chunks and row stride n (coefficients with ld = n), and, when mom is not
+// NULL, the moment reduction on rows fast_rows[0 .. counts[1]) (row p uses
+// slot p / 2; rows whose |t_c + dt_i| exceeds the cache's range get NaN) into
+// the same partials.
+// launch_wcache_slow: the full reduction on all n rows, on the vector ALUs.
+// launch_wcache_fast: rows that a node table covers (C_NODE at least
+// kNodeWide) summed over its nodes into nch_node chunks, the others over the
+// moments of slot slot_of[p] (slot 0 when that is outside 0 .. n_slots - 1)
+// into n_chunks = wcache_fast_chunks chunks; the epilogue is told kNodeWide.
 // launch_epilogue_cached combines partials (rows with zsrc[p] >= 0 take their
 // sums from zc[zsrc[p]]) and writes every row's sums to zrow when not NULL.
 // launch_wmom_build rebuilds the slots slots[i] >= 0, i < *count <= max_count,
@@ -136,17 +138,24 @@ gw_status launch_template(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n
 // the phase and phasor of precision prec.
 int wmom_block(const gw_ctx* ctx);
 int64_t wmom_slot_f2(const gw_ctx* ctx);
-gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, int tpb, int n_chunks,
-                        const int32_t* slow_rows, const int32_t* fast_rows, const int32_t* counts, int rows_per_slot,
-                        const int32_t* slot_of, const float2* mom, double* zfast, double* partial, hipStream_t st);
+gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, const int32_t* slow_rows,
+                        const int32_t* fast_rows, const int32_t* counts, const float2* mom, double* partial,
+                        hipStream_t st);
+gw_status launch_wcache_slow(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, double* partial,
+                             hipStream_t st);
+int wcache_fast_chunks(const gw_ctx* ctx, int n_chunks);
+gw_status launch_wcache_fast(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
+                             const int32_t* slot_of, int64_t n_slots, const float2* mom, double* partial,
+                             hipStream_t st);
 gw_status launch_epilogue_cached(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef,
                                  int64_t ld, int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc,
                                  double* zrow, hipStream_t st);
 // As launch_epilogue_cached, with the distance marginal's (|Z_1|, <h|h>_1)
 // staging buffer [2][n] given explicitly instead of the context's.
 gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef,
-                            int64_t ld, int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc, double* zrow,
-                            double* zbuf, hipStream_t st);
+                            int64_t ld, int64_t n, int marg, int prec, double* logl, const int32_t* zsrc,
+                            const double* zc, double* zrow, double* zbuf, hipStream_t st,
+                            double node_from = gw::kNodeFull);
 gw_status launch_wmom_build(gw_ctx* ctx, const double* coef, int64_t ld, const int32_t* slots, const int32_t* count,
                             int64_t max_count, int rows_per_slot, const int32_t* src, int prec, float2* mom,
                             hipStream_t st);
@@ -156,8 +165,9 @@ gw_status wmom_init(gw_ctx* ctx);
 // and the workspace it needs for n rows.
 void cached_shape(const gw_ctx* ctx, int* tpb, int* nch);
 gw_status cached_reserve(gw_ctx* ctx, int64_t n);
-// As node_chunks, for launch_cached.
-int cached_node_chunks(const gw_ctx* ctx, int n_chunks);
+// As node_chunks, for the row-list and cache launches; ``always``: whatever
+// reduction gw_set_full_kernel asks for.
+int cached_node_chunks(const gw_ctx* ctx, int64_t n, int n_chunks, bool always = false);
 void full_launch_shape(const gw_ctx* ctx, int64_t n, int* tpb, int* n_chunks);
 // Block-moment table of the matrix-core reduction from the per-bin records
 // (host [n_freq][4 + 2 n_det]); leaves the form unavailable (mom_blk = 0) when
@@ -165,6 +175,8 @@ void full_launch_shape(const gw_ctx* ctx, int64_t n, int* tpb, int* n_chunks);
 gw_status build_moment_table(gw_ctx* ctx, const std::vector<double>& rec, const double* det_pos);
 // Build the node tables and the row check (needs the bin records on the device).
 gw_status nodes_init(gw_ctx* ctx);
+// The table for delays up to kTauCap (once per context).
+gw_status nodes_wide_init(gw_ctx* ctx);
 void nodes_free(gw_ctx* ctx);
 // Measure the hardware phasor bias and set ctx->pgain_re / pgain_im.
 gw_status calibrate_phasor(gw_ctx* ctx);

@@ -80,7 +80,9 @@ __global__ void __launch_bounds__(256) k_prologue(const double* __restrict__ the
   __syncthreads();
   if (wave == 0 && live) {
     const bool good = in[0][lane] && in[1][lane] && in[2][lane] && in[3][lane];
-    coef[C_NODE * ld + p] = !good ? 0.0 : (tau[lane] > chk->tau_max ? kNodePhase : kNodeFull);
+    const double t = tau[lane];
+    coef[C_NODE * ld + p] =
+        !good ? 0.0 : (t <= chk->tau_max ? kNodeFull : (t <= kTauCap ? kNodeWide : kNodePhase));
   }
 }
 
@@ -146,15 +148,21 @@ __device__ inline void phasor(double r, const TrigConsts& T, double* gr, double*
 // own start phase), their sums added in wave order: a quarter of the partial
 // sums for the same number of waves.  With ``rows`` the rows are
 // rows[0 .. *count) (at most n, in any order) instead of 0 .. n - 1, and
-// workgroups past the count exit at once.
+// workgroups past the count exit at once.  Rows with C_NODE = tabs.row are
+// summed over the nodes (of table blockIdx.y), the others over the bins, or
+// with nodes_only not at all (the caller sums them its own way).
 template <int ND, int PREC, bool SPLIT>
 __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, int64_t ld, int64_t n,
                                               const double* __restrict__ bins, int64_t k0, double df,
                                               int n_freq, int chunk_len, int n_chunks, TrigConsts T, PhaseRuns R,
                                               double pg_re, double pg_im, const int32_t* __restrict__ rows,
-                                              const int32_t* __restrict__ count, const double* __restrict__ nodes,
-                                              int n_node, int nch_node, TrigFit F, double* __restrict__ partial) {
+                                              const int32_t* __restrict__ count, NodeTabs tabs, int nch_node,
+                                              bool nodes_only, TrigFit F, double* __restrict__ partial) {
   constexpr int RS = 4 + 2 * ND;
+  // (chosen by selects: an indexed kernel argument would be a second load)
+  const double* __restrict__ nodes = blockIdx.y ? tabs.rec[1] : tabs.rec[0];
+  const int n_node = blockIdx.y ? tabs.n[1] : tabs.n[0];
+  const double node_row = blockIdx.y ? tabs.row[1] : tabs.row[0];
   const int tpb = SPLIT ? 64 : blockDim.x;
   const int nptile = (int)((n + tpb - 1) / tpb);
   int chunk, ptile;
@@ -178,8 +186,8 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
   // Rows that the node tables cover (gw_nodes.h) take the sums over the nodes,
   // in the first nch_node chunks; the others the walk over every bin below.
   // A wave with rows of both kinds does both.
-  const bool on_nodes = nch_node > 0 && coef[C_NODE * ld + pc] >= kNodeFull;
-  const bool any_node = chunk < nch_node && __any(on_nodes), any_bins = __any(!on_nodes);
+  const bool on_nodes = nch_node > 0 && coef[C_NODE * ld + pc] == node_row;
+  const bool any_node = chunk < nch_node && __any(on_nodes), any_bins = !nodes_only && __any(!on_nodes);
   if (!any_node && !any_bins) return;  // the waves of a SPLIT workgroup share their rows
 
   PhaseCoef c;
@@ -458,7 +466,7 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
   if constexpr (SPLIT) {
     if (!wave_sums_combine<ND>(zr, zi)) return;
   }
-  if (live && (!on_nodes || chunk < nch_node)) {
+  if (live && (on_nodes ? chunk < nch_node : !nodes_only)) {
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       partial[((int64_t)chunk * 2 * ND + 2 * i) * n + p] = zr[i];
@@ -470,7 +478,6 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
 constexpr int kWMom = 12;          // Chebyshev orders per block and detector
 static_assert(kWMom % 2 == 0, "the few-slot build reads the orders in pairs");
 constexpr int64_t kWBuildManyRows = 512;  // builds listing fewer slots use k_wmom_build_few
-constexpr double kTauCap = 0.25;    // largest |t_c + dt_i| (s) the moment cache is built for
 
 // Extrinsic moves with a cached waveform (Sec. III.B: the fast blocks reuse
 // the waveform of the chain's intrinsic parameters and only redo the
@@ -813,18 +820,23 @@ __global__ void __launch_bounds__(256) k_wmom(const double* __restrict__ coef, i
                                               double df, int blk, int n_blk, int n_chunks, int n_out, TrigConsts T,
                                               const int32_t* __restrict__ rows, const int32_t* __restrict__ count,
                                               int rows_per_slot, const int32_t* __restrict__ slot_of,
-                                              const float2* __restrict__ mom, int64_t slot_f2,
+                                              int64_t n_slots, const float2* __restrict__ mom, int64_t slot_f2,
+                                              bool skip_nodes,
                                               double* __restrict__ partial) {
   const int nptile = (int)((n + 63) / 64);
   int chunk, ptile;
   decode_block(blockIdx.x, nptile, n_chunks, &chunk, &ptile);
-  const int cnt = *count;
-  if (ptile * 64 >= cnt) return;  // uniform over the workgroup
-  const int idx = ptile * 64 + (threadIdx.x & 63);
+  const int64_t cnt = rows ? *count : n;
+  if ((int64_t)ptile * 64 >= cnt) return;  // uniform over the workgroup
+  const int64_t idx = (int64_t)ptile * 64 + (threadIdx.x & 63);
   const bool live = idx < cnt;
-  const int64_t p = rows[live ? idx : cnt - 1];
+  int64_t p = live ? idx : cnt - 1;
+  if (rows) p = rows[p];
+  // rows that the caller sums over the nodes (the workgroup's waves share their rows)
+  const bool mine = live && !(skip_nodes && coef[C_NODE * ld + p] >= kNodeWide);
+  if (!__any(mine)) return;
   int64_t slot = slot_of ? (int64_t)slot_of[p] : p / rows_per_slot;
-  if (slot < 0) slot = 0;  // a row without a valid slot (the caller discards it)
+  if (slot < 0 || slot >= n_slots) slot = 0;  // a row without a valid slot (the caller discards it)
   const float4* __restrict__ ms = reinterpret_cast<const float4*>(mom + slot * slot_f2);
 
   // this wave's blocks
@@ -888,7 +900,7 @@ __global__ void __launch_bounds__(256) k_wmom(const double* __restrict__ coef, i
     for (int i = 0; i < ND; ++i) zr[i] = zi[i] = __builtin_nan("");
   }
   if (!wave_sums_combine<ND>(zr, zi)) return;
-  if (live) {
+  if (mine) {
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       partial[((int64_t)chunk * 2 * ND + 2 * i) * n + p] = zr[i];
@@ -898,27 +910,6 @@ __global__ void __launch_bounds__(256) k_wmom(const double* __restrict__ coef, i
 #pragma unroll
       for (int j = 0; j < 2 * ND; ++j) partial[((int64_t)c * 2 * ND + j) * n + p] = 0.0;
   }
-}
-
-// Sum the fast rows' chunk partials (fixed order) into zout[p][2 nd]: one
-// lane per (listed row, component).
-__global__ void __launch_bounds__(256) k_wmom_sum(const double* __restrict__ partial, int n_chunks, int nd, int64_t n,
-                                                  const int32_t* __restrict__ rows,
-                                                  const int32_t* __restrict__ count, double* __restrict__ zout) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int idx = t / (2 * nd), j = t - idx * (2 * nd);
-  if (idx >= *count) return;
-  const int64_t p = rows[idx];
-  double acc[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.0;
-  int c = 0;
-  for (; c + 8 <= n_chunks; c += 8) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] += partial[((int64_t)(c + q) * 2 * nd + j) * n + p];
-  }
-  for (int q = 0; c + q < n_chunks; ++q) acc[q] += partial[((int64_t)(c + q) * 2 * nd + j) * n + p];
-  zout[p * 2 * nd + j] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
 }
 
 // Matrix-core form of the mixed reduction.
@@ -1162,17 +1153,19 @@ __global__ void __launch_bounds__(256) k_full_mfma(const double* __restrict__ co
 // zsrc[p] of zc ([slot][2 nd]) instead of the partials (moves that change only
 // A P_i), and zrow (when not NULL) receives every row's z_i ([n][2 nd]).
 // The partials of chunk c are read at chunk index c * cstride (1, or the
-// group length after k_partial_reduce).  A row summed over the nodes has
-// partials in the first nch_node chunks only.
-__device__ inline int row_chunks(const double* __restrict__ coef, int64_t ld, int64_t p, int n_chunks, int nch_node) {
-  return nch_node > 0 && coef[C_NODE * ld + p] >= kNodeFull ? nch_node : n_chunks;
+// group length after k_partial_reduce).  A row summed over the nodes (C_NODE
+// at least node_from) has partials in the first nch_node chunks only.
+__device__ inline int row_chunks(const double* __restrict__ coef, int64_t ld, int64_t p, int n_chunks, int nch_node,
+                                 double node_from = kNodeFull) {
+  return nch_node > 0 && coef[C_NODE * ld + p] >= node_from ? nch_node : n_chunks;
 }
 
 __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ partial, int n_chunks, int cstride,
                                                   int nch_node, int nd, const double* __restrict__ coef, int64_t ld, int64_t n,
                                                   double dd, int marg, double* __restrict__ logl,
                                                   double* __restrict__ zbuf, const int32_t* __restrict__ zsrc,
-                                                  const double* __restrict__ zc, double* __restrict__ zrow) {
+                                                  const double* __restrict__ zc, double* __restrict__ zrow,
+                                                  double node_from) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int64_t p = (int64_t)blockIdx.x * 64 + lane;
@@ -1180,7 +1173,7 @@ __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ pa
   double z[2 * kMaxDet];
 #pragma unroll
   for (int j = 0; j < 2 * kMaxDet; ++j) z[j] = 0.0;
-  const int own = row_chunks(coef, ld, pc, n_chunks * cstride, nch_node);
+  const int own = row_chunks(coef, ld, pc, n_chunks * cstride, nch_node, node_from);
   for (int c = wave; c < n_chunks && __any(c * cstride < own); c += 16) {
     if (c * cstride < own) {
 #pragma unroll
@@ -1373,6 +1366,20 @@ gw_status launch_prologue(gw_ctx* ctx, const double* theta, int64_t n, int marg,
   return check_hip(hipGetLastError(), "prologue launch");
 }
 
+// The context's own node table, and with ``wide`` the one for longer delays.
+static NodeTabs node_tabs(const gw_ctx* ctx, bool wide = false) {
+  NodeTabs t{};
+  t.rec[0] = ctx->nodes.rec;
+  t.n[0] = ctx->nodes.n;
+  t.row[0] = kNodeFull;
+  if (wide) {
+    t.rec[1] = ctx->nodes_wide.rec;
+    t.n[1] = ctx->nodes_wide.n;
+    t.row[1] = kNodeWide;
+  }
+  return t;
+}
+
 // The automatic shape splits a chunk over the four waves of a 64-row
 // workgroup; a shape set by the caller and the matrix-core form keep their
 // rows per workgroup, whose waves walk the chunk in step.
@@ -1416,17 +1423,17 @@ static gw_status launch_full_nd(gw_ctx* ctx, const double* coef, int64_t ld, int
   const int64_t nptile = split ? (n + 63) / 64 : (n + tpb - 1) / tpb;
   const int64_t blocks = nptile * n_chunks;
   if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
-  auto launch = [&](auto kernel, double pg_re, double pg_im) {
+  const NodeTabs tabs = node_tabs(ctx);
+  const bool fp64 = prec == GW_PREC_FP64;
+  auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(split ? 256 : tpb), 0, st, coef, ld, n, ctx->bins,
-                       ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, pg_re, pg_im, nullptr, nullptr,
-                       (const double*)ctx->nodes.rec, ctx->nodes.n, nch_node, F, partial);
+                       ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, fp64 ? 1.0 : ctx->pgain_re,
+                       fp64 ? 0.0 : ctx->pgain_im, nullptr, nullptr, tabs, nch_node, false, F, partial);
   };
-  if (prec == GW_PREC_FP64)
-    split ? launch(k_full<ND, 0, true>, 1.0, 0.0) : launch(k_full<ND, 0, false>, 1.0, 0.0);
-  else if (split)
-    launch(k_full<ND, 1, true>, ctx->pgain_re, ctx->pgain_im);
+  if (split)
+    fp64 ? launch(k_full<ND, 0, true>) : launch(k_full<ND, 1, true>);
   else
-    launch(k_full<ND, 1, false>, ctx->pgain_re, ctx->pgain_im);
+    fp64 ? launch(k_full<ND, 0, false>) : launch(k_full<ND, 1, false>);
   return check_hip(hipGetLastError(), "full-band kernel launch");
 }
 
@@ -1461,9 +1468,7 @@ bool use_mfma(const gw_ctx* ctx, int prec) {
 constexpr int64_t kNodeWaves = 4096;
 constexpr int kNodeWaveMin = 28;
 
-int node_chunks(const gw_ctx* ctx, int64_t n, int prec, int n_chunks) {
-  if (ctx->nodes.n <= 0 || ctx->full_kernel == 1 || use_mfma(ctx, prec)) return 0;
-  const int split = full_split(ctx) ? 4 : 1;
+static int node_chunk_count(const gw_ctx* ctx, int64_t n, int n_chunks, int split) {
   int64_t c = kNodeWaves / ((n + 63) / 64 * split);
   if (c > ctx->nodes.n / (kNodeWaveMin * split)) c = ctx->nodes.n / (kNodeWaveMin * split);
   c = (c + 4) / 8 * 8;
@@ -1471,11 +1476,14 @@ int node_chunks(const gw_ctx* ctx, int64_t n, int prec, int n_chunks) {
   return (int)(c < n_chunks ? c : n_chunks);
 }
 
-int cached_node_chunks(const gw_ctx* ctx, int n_chunks) {
-  if (ctx->nodes.n <= 0 || ctx->full_kernel == 1) return 0;
-  int c = ctx->nodes.n / 64 / 8 * 8;
-  if (c < 8) c = 8;
-  return c < n_chunks ? c : n_chunks;
+int node_chunks(const gw_ctx* ctx, int64_t n, int prec, int n_chunks) {
+  if (ctx->nodes.n <= 0 || ctx->full_kernel == 1 || use_mfma(ctx, prec)) return 0;
+  return node_chunk_count(ctx, n, n_chunks, full_split(ctx) ? 4 : 1);
+}
+
+int cached_node_chunks(const gw_ctx* ctx, int64_t n, int n_chunks, bool always) {
+  if (ctx->nodes.n <= 0 || (ctx->full_kernel == 1 && !always)) return 0;
+  return node_chunk_count(ctx, n, n_chunks, 4);
 }
 
 gw_status launch_full(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, int prec, int tpb, int n_chunks,
@@ -1639,7 +1647,7 @@ gw_status launch_epilogue_cached(gw_ctx* ctx, double* partial, int n_chunks, int
 
 gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_node, const double* coef, int64_t ld,
                             int64_t n, int marg, int prec, double* logl, const int32_t* zsrc, const double* zc, double* zrow,
-                            double* zbuf, hipStream_t st) {
+                            double* zbuf, hipStream_t st, double node_from) {
   if (n == 0) return GW_OK;
   const int64_t blocks = (n + 63) / 64;
   const LogI0Consts* C = ctx->i0c;  // device copy, r1max from the distance grid
@@ -1654,7 +1662,7 @@ gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_
     if (s != GW_OK) return s;
   }
   hipLaunchKernelGGL(k_epilogue, dim3((unsigned)blocks), dim3(1024), 0, st, partial, groups, cstride, nch_node,
-                     ctx->n_det, coef, ld, n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow);
+                     ctx->n_det, coef, ld, n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow, node_from);
   gw_status s = check_hip(hipGetLastError(), "epilogue launch");
   if (s != GW_OK || marg != 2) return s;
   // large batches: lane = row (grid records are scalar loads shared by 64
@@ -1693,70 +1701,106 @@ int64_t wmom_slot_f2(const gw_ctx* ctx) {
   return n_blk * ctx->n_det * kWMom;
 }
 
+// Row-list launches: the SPLIT reduction of the rows listed in rows[0 .. *count)
+// (all n when rows is NULL), and the moment reduction of the waveform cache.
 template <int ND>
-static gw_status launch_cached_nd(gw_ctx* ctx, const double* coef, int64_t n, int prec, int tpb, int n_chunks,
-                                  const int32_t* slow_rows, const int32_t* fast_rows, const int32_t* counts,
-                                  int rows_per_slot, const int32_t* slot_of, const float2* mom, double* zfast,
-                                  double* partial, hipStream_t st) {
+static gw_status launch_rows_nd(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
+                                const int32_t* rows, const int32_t* count, bool wide, double* partial,
+                                hipStream_t st) {
   const int nf = (int)ctx->geom.n_freq;
-  const TrigConsts T = make_trig_consts();
-  const PhaseRuns PR = make_phase_runs(ctx->geom);
-  const TrigFit F = make_trig_fit();
-  const int nch_node = cached_node_chunks(ctx, n_chunks);
-  const int64_t nptile = (n + 63) / 64;  // 64 rows per workgroup; tpb / 64 waves split each chunk
-  const int64_t blocks = nptile * n_chunks;
+  const int64_t blocks = (n + 63) / 64 * n_chunks;
   if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
   const int chunk_len = (int)((nf + n_chunks - 1) / n_chunks);
-  gw_status s = GW_OK;
-  if (slow_rows) {
-    if (prec == GW_PREC_FP64)
-      hipLaunchKernelGGL((k_full<ND, 0, true>), dim3((unsigned)blocks), dim3(tpb), 0, st, coef, n, n, ctx->bins,
-                         ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, 1.0, 0.0, slow_rows, counts,
-                         (const double*)ctx->nodes.rec, ctx->nodes.n, nch_node, F, partial);
-    else
-      hipLaunchKernelGGL((k_full<ND, 1, true>), dim3((unsigned)blocks), dim3(tpb), 0, st, coef, n, n, ctx->bins,
-                         ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, T, PR, ctx->pgain_re, ctx->pgain_im,
-                         slow_rows, counts, (const double*)ctx->nodes.rec, ctx->nodes.n, nch_node, F, partial);
-    s = check_hip(hipGetLastError(), "full-band list kernel launch");
-  }
-  if (s != GW_OK || !mom) return s;  // no cache, no fast rows
-  const int blk = wmom_block(ctx);
-  const int n_blk = (nf + blk - 1) / blk;
-  // chunks of at least 8 blocks, at most the partials' chunk count
-  int cm = n_blk / 8 < n_chunks ? n_blk / 8 : n_chunks;
-  if (cm < 1) cm = 1;
-  if (cm > 8) cm = cm / 8 * 8;
-  // rows of the common epilogue that the node tables cover are summed over
-  // nch_node chunks
-  if (!zfast && nch_node > 0 && cm > nch_node) cm = nch_node;
-  const int slot = prof_begin(ctx, st, 1);
-  hipLaunchKernelGGL((k_wmom<ND>), dim3((unsigned)(nptile * cm)), dim3(256), 0, st, coef, n, n, ctx->geom.k0,
-                     ctx->geom.df, blk, n_blk, cm, zfast ? cm : n_chunks, T, fast_rows, counts + 1, rows_per_slot,
-                     slot_of, mom, wmom_slot_f2(ctx), partial);
-  prof_end(ctx, slot, st);
-  s = check_hip(hipGetLastError(), "cached-waveform kernel launch");
-  if (s != GW_OK || !zfast) return s;  // without zfast the epilogue sums the fast rows' partials
-  hipLaunchKernelGGL(k_wmom_sum, dim3((unsigned)((n * 2 * ND + 255) / 256)), dim3(256), 0, st, partial, cm, ND, n,
-                     fast_rows, counts + 1, zfast);
-  return check_hip(hipGetLastError(), "cached-waveform sum launch");
+  const bool fp64 = prec == GW_PREC_FP64;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, wide ? 2 : 1), dim3(256), 0, st, coef, n, n, ctx->bins,
+                       ctx->geom.k0, ctx->geom.df, nf, chunk_len, n_chunks, make_trig_consts(),
+                       make_phase_runs(ctx->geom), fp64 ? 1.0 : ctx->pgain_re, fp64 ? 0.0 : ctx->pgain_im, rows,
+                       count, node_tabs(ctx, wide), nch_node, wide, make_trig_fit(), partial);
+  };
+  fp64 ? launch(k_full<ND, 0, true>) : launch(k_full<ND, 1, true>);
+  return check_hip(hipGetLastError(), "full-band list kernel launch");
 }
 
-gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, int tpb, int n_chunks,
-                        const int32_t* slow_rows, const int32_t* fast_rows, const int32_t* counts, int rows_per_slot,
-                        const int32_t* slot_of, const float2* mom, double* zfast, double* partial, hipStream_t st) {
-  if (n == 0) return GW_OK;
-  if (tpb != 64 && tpb != 128 && tpb != 256) return set_error(GW_EINVAL, "tpb must be 64, 128 or 256");
+static gw_status launch_rows(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
+                             const int32_t* rows, const int32_t* count, bool wide, double* partial, hipStream_t st) {
   switch (ctx->n_det) {
-    case 1: return launch_cached_nd<1>(ctx, coef, n, prec, tpb, n_chunks, slow_rows, fast_rows, counts,
-                                       rows_per_slot, slot_of, mom, zfast, partial, st);
-    case 2: return launch_cached_nd<2>(ctx, coef, n, prec, tpb, n_chunks, slow_rows, fast_rows, counts,
-                                       rows_per_slot, slot_of, mom, zfast, partial, st);
-    case 3: return launch_cached_nd<3>(ctx, coef, n, prec, tpb, n_chunks, slow_rows, fast_rows, counts,
-                                       rows_per_slot, slot_of, mom, zfast, partial, st);
-    case 4: return launch_cached_nd<4>(ctx, coef, n, prec, tpb, n_chunks, slow_rows, fast_rows, counts,
-                                       rows_per_slot, slot_of, mom, zfast, partial, st);
+    case 1: return launch_rows_nd<1>(ctx, coef, n, prec, n_chunks, nch_node, rows, count, wide, partial, st);
+    case 2: return launch_rows_nd<2>(ctx, coef, n, prec, n_chunks, nch_node, rows, count, wide, partial, st);
+    case 3: return launch_rows_nd<3>(ctx, coef, n, prec, n_chunks, nch_node, rows, count, wide, partial, st);
+    case 4: return launch_rows_nd<4>(ctx, coef, n, prec, n_chunks, nch_node, rows, count, wide, partial, st);
     default: return set_error(GW_ENOTSUP, "n_det %d not supported", ctx->n_det);
   }
+}
+
+// Chunks of the moment reduction: at least 8 blocks each, at most ``most``.
+static int wmom_chunks(const gw_ctx* ctx, int most) {
+  const int blk = wmom_block(ctx);
+  const int n_blk = (int)((ctx->geom.n_freq + blk - 1) / blk);
+  int cm = n_blk / 8 < most ? n_blk / 8 : most;
+  if (cm < 1) cm = 1;
+  return cm > 8 ? cm / 8 * 8 : cm;
+}
+
+static gw_status launch_wmom(gw_ctx* ctx, const double* coef, int64_t n, int cm, int n_out, const int32_t* rows,
+                             const int32_t* count, int rows_per_slot, const int32_t* slot_of, int64_t n_slots,
+                             const float2* mom, bool skip_nodes, double* partial, hipStream_t st) {
+  const int blk = wmom_block(ctx);
+  const int n_blk = (int)((ctx->geom.n_freq + blk - 1) / blk);
+  const int64_t blocks = (n + 63) / 64 * cm;
+  if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, coef, n, n, ctx->geom.k0, ctx->geom.df, blk,
+                       n_blk, cm, n_out, make_trig_consts(), rows, count, rows_per_slot, slot_of, n_slots, mom,
+                       wmom_slot_f2(ctx), skip_nodes, partial);
+  };
+  const int slot = prof_begin(ctx, st, 1);
+  switch (ctx->n_det) {
+    case 1: launch(k_wmom<1>); break;
+    case 2: launch(k_wmom<2>); break;
+    case 3: launch(k_wmom<3>); break;
+    case 4: launch(k_wmom<4>); break;
+    default: return set_error(GW_ENOTSUP, "n_det %d not supported", ctx->n_det);
+  }
+  prof_end(ctx, slot, st);
+  return check_hip(hipGetLastError(), "cached-waveform kernel launch");
+}
+
+gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, const int32_t* slow_rows,
+                        const int32_t* fast_rows, const int32_t* counts, const float2* mom, double* partial,
+                        hipStream_t st) {
+  if (n == 0) return GW_OK;
+  const int nch_node = cached_node_chunks(ctx, n, n_chunks);
+  gw_status s = launch_rows(ctx, coef, n, prec, n_chunks, nch_node, slow_rows, counts, false, partial, st);
+  if (s != GW_OK || !mom) return s;
+  // the epilogue sums rows that the node tables cover over nch_node chunks,
+  // the fast ones among them
+  const int cm = wmom_chunks(ctx, nch_node > 0 ? nch_node : n_chunks);
+  return launch_wmom(ctx, coef, n, cm, n_chunks, fast_rows, counts + 1, 2, nullptr, n, mom, false, partial, st);
+}
+
+// The cache's slow rows: all n.
+gw_status launch_wcache_slow(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, double* partial,
+                             hipStream_t st) {
+  if (n == 0) return GW_OK;
+  return launch_rows(ctx, coef, n, prec, n_chunks, cached_node_chunks(ctx, n, n_chunks), nullptr, nullptr, false,
+                     partial, st);
+}
+
+// The cache's fast rows.  Summing a row over its own nodes costs less than
+// reading its slot's moments (2048 rows of 512 slots: 45 us against 96), so
+// only the rows that no node table covers read them.
+int wcache_fast_chunks(const gw_ctx* ctx, int n_chunks) { return wmom_chunks(ctx, n_chunks); }
+
+gw_status launch_wcache_fast(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
+                             const int32_t* slot_of, int64_t n_slots, const float2* mom, double* partial,
+                             hipStream_t st) {
+  if (n == 0) return GW_OK;
+  gw_status s = GW_OK;
+  if (nch_node > 0) s = launch_rows(ctx, coef, n, prec, nch_node, nch_node, nullptr, nullptr, true, partial, st);
+  if (s != GW_OK) return s;
+  return launch_wmom(ctx, coef, n, n_chunks, n_chunks, nullptr, nullptr, 1, slot_of, n_slots, mom, nch_node > 0,
+                     partial, st);
 }
 
 template <int ND>

@@ -38,14 +38,24 @@ constexpr double kNodeTol = 1e-13; // interpolation error per unit sum of |u|
 constexpr int kNodeMax = 128;      // most nodes of a block
 constexpr int kNodeCheck = 24;     // frequencies of the row check
 
-// Values of the coefficient column C_NODE: the row's phase alone, or its phase
-// and its delays, lie within what the node tables are built for.
-constexpr double kNodePhase = 1.0, kNodeFull = 2.0;
+constexpr double kTauCap = 0.25;   // s, delays of the wide table and of the waveform cache
+
+// Values of the coefficient column C_NODE: the row's phase lies within what
+// the tables are built for, and its delays within neither table's, the wide
+// table's (kTauCap) or the context's own (tau_max).  Zero: the phase does not.
+constexpr double kNodePhase = 1.0, kNodeWide = 2.0, kNodeFull = 3.0;
 
 // The row check's frequencies: x = f^(1/3), ln f, x^-8, x^-3, R'(f), S(f).
 struct NodeCheck {
   double v[kNodeCheck][6];
   double tau_max;  // s
+};
+
+// The tables of a reduction and the C_NODE value of the rows each covers.
+struct NodeTabs {
+  const double* rec[2];
+  int n[2];
+  double row[2];
 };
 
 // Record of one node: x, x^2, f^(-5/3), ln f, f, R (cycles), then Re, Im W_i

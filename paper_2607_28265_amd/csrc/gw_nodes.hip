@@ -224,7 +224,7 @@ gw_status nodes_init(gw_ctx* ctx) {
   double rmax = 0.0;
   for (int i = 0; i < g.n_det; ++i)
     rmax = fmax(rmax, sqrt(g.pos[i][0] * g.pos[i][0] + g.pos[i][1] * g.pos[i][1] + g.pos[i][2] * g.pos[i][2]));
-  c.tau_max = fmin(0.1 + 2.0 * rmax / kLightSpeed, 0.25);
+  c.tau_max = fmin(0.1 + 2.0 * rmax / kLightSpeed, kTauCap);
   std::vector<NodePlace> place;
   partition(ctx, w, c.tau_max, &place);
   s = check_hip(hipMalloc((void**)&ctx->node_check_dev, sizeof(NodeCheck)), "node check");
@@ -233,7 +233,19 @@ gw_status nodes_init(gw_ctx* ctx) {
   return s;
 }
 
+gw_status nodes_wide_init(gw_ctx* ctx) {
+  if (ctx->nodes_wide.rec) return GW_OK;
+  std::vector<PhaseCoef> w;
+  std::vector<NodePlace> place;
+  const gw_status s = node_waveforms(ctx, &w);
+  if (s != GW_OK) return s;
+  partition(ctx, w, kTauCap, &place);
+  return node_table(ctx, w[0], place, &ctx->nodes_wide);
+}
+
 void nodes_free(gw_ctx* ctx) {
+  if (ctx->nodes_wide.rec) (void)hipFree(ctx->nodes_wide.rec);
+  ctx->nodes_wide = NodeTable{};
   if (ctx->nodes.rec) (void)hipFree(ctx->nodes.rec);
   if (ctx->node_check_dev) (void)hipFree(ctx->node_check_dev);
   ctx->nodes = NodeTable{};

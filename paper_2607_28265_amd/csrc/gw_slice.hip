@@ -726,10 +726,10 @@ static gw_status eval_rows(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, const SweepC
   s = check_hip(hipGetLastError(), "row list launch");
   if (s == GW_OK) s = launch_prologue(ctx, ws->cand, n, a.marg, ctx->coef, n, st);
   if (s == GW_OK)
-    s = launch_cached(ctx, ctx->coef, n, a.prec, tpb, nch, ws->S.slow_rows, ws->S.stream_rows, ws->S.counts, 2,
-                      nullptr, a.cache ? ws->wc : nullptr, nullptr, ctx->partial, st);
+    s = launch_cached(ctx, ctx->coef, n, a.prec, nch, ws->S.slow_rows, ws->S.stream_rows, ws->S.counts,
+                      a.cache ? ws->wc : nullptr, ctx->partial, st);
   if (s == GW_OK)
-    s = launch_epilogue_cached(ctx, ctx->partial, nch, cached_node_chunks(ctx, nch), ctx->coef, n, n, a.marg, a.prec, ws->cand_logl, ws->S.zsrc,
+    s = launch_epilogue_cached(ctx, ctx->partial, nch, cached_node_chunks(ctx, n, nch), ctx->coef, n, n, a.marg, a.prec, ws->cand_logl, ws->S.zsrc,
                                ws->S.zc, ws->S.zrow, st);
   return s;
 }

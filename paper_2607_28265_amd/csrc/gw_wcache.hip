@@ -16,74 +16,77 @@ struct gw_wcache {
   float2* wc = nullptr;  // [n_slots][slot_f2] block moments (FP32 complex)
   double* zc = nullptr;  // [n_slots][2 n_det] sums z_i of each slot's point
   int32_t* owner = nullptr;  // [n_slots]: -1 between calls
-  // per-call workspace: zrow [cap][2 kMaxDet], rows [cap] (0 .. n - 1),
-  // sl [cap] (checked slots), counts [2]
+  // per-call workspace: zrow [cap][2 kMaxDet], sl [cap] (checked slots), and
+  // the slots whose moments are wanted with their rows, bslot and brow [cap],
+  // bcount of them
   int64_t cap = 0;
   char* mem = nullptr;
   double* zrow = nullptr;
-  int32_t* rows = nullptr;
   int32_t* sl = nullptr;
-  int32_t* counts = nullptr;
+  int32_t* bslot = nullptr;
+  int32_t* brow = nullptr;
+  int32_t* bcount = nullptr;
 };
 
 namespace {
-
-// rows[i] = i for i < n; counts = (n, 0) for the full list, (0, n) for the
-// cached-waveform list.
-__global__ void k_wc_rows(int32_t* __restrict__ rows, int64_t n, int32_t* __restrict__ counts, int which) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) rows[i] = (int32_t)i;
-  if (i == 0) {
-    counts[0] = which == 0 ? (int32_t)n : 0;
-    counts[1] = which == 1 ? (int32_t)n : 0;
-  }
-}
 
 __global__ void k_wc_fill(int32_t* __restrict__ a, int64_t n, int32_t v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = v;
 }
 
-// sl[r] = slots[r] when 0 <= slots[r] < n_slots, else -1; with owner, the
-// largest row naming each slot claims it.
+// sl[r] = slots[r] when 0 <= slots[r] < n_slots, else -1; the largest row
+// naming each slot claims it.  Clears the list of moments to build.
 __global__ void k_wc_slots(const int32_t* __restrict__ slots, int64_t n, int64_t n_slots, int32_t* __restrict__ sl,
-                           int32_t* __restrict__ owner) {
+                           int32_t* __restrict__ owner, int32_t* __restrict__ bcount) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r == 0) *bcount = 0;
   if (r >= n) return;
   const int32_t s = slots[r];
   const bool ok = s >= 0 && s < n_slots;
   sl[r] = ok ? s : -1;
-  if (ok && owner) atomicMax(&owner[s], (int32_t)r);
+  if (ok) atomicMax(&owner[s], (int32_t)r);
 }
 
-// Keep only the claiming row of each slot (sl[r] = -2 for the others: their
-// log L stands, they store nothing), store its sums: zc[sl[r]] = zrow[r].
-__global__ void k_wc_store_z(const double* __restrict__ zrow, int32_t* __restrict__ sl,
-                             const int32_t* __restrict__ owner, int64_t n, int nd, double* __restrict__ zc) {
+// The claiming row of each slot stores its sums, zc[sl[r]] = zrow[r], and asks
+// for the slot's moments when no node table covers its phase: the fast rows of
+// the other slots are summed over the nodes.  (The list's order does not
+// matter: each slot's moments come from its own row.)
+__global__ void k_wc_store(const double* __restrict__ zrow, const int32_t* __restrict__ sl,
+                           const int32_t* __restrict__ owner, const double* __restrict__ coef, int64_t n, int nd,
+                           bool nodes, double* __restrict__ zc, int32_t* __restrict__ bslot,
+                           int32_t* __restrict__ brow, int32_t* __restrict__ bcount) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n) return;
   const int32_t s = sl[r];
-  if (s < 0) return;
-  if (owner[s] != (int32_t)r) {
-    sl[r] = -2;
-    return;
-  }
+  if (s < 0 || owner[s] != (int32_t)r) return;
   for (int j = 0; j < 2 * nd; ++j) zc[(int64_t)s * 2 * nd + j] = zrow[r * 2 * nd + j];
+  if (nodes && coef[C_NODE * n + r] >= kNodePhase) return;
+  const int32_t q = atomicAdd(bcount, 1);
+  bslot[q] = s;
+  brow[q] = (int32_t)r;
 }
 
-// Release the claims (owner back to -1) once the slots are written.
-__global__ void k_wc_release(const int32_t* __restrict__ slots, int64_t n, int64_t n_slots,
-                             int32_t* __restrict__ owner) {
+// Release the claims (owner back to -1) once the slots are written; rows whose
+// slot is out of range get log L = NaN.
+__global__ void k_wc_release(const int32_t* __restrict__ sl, int64_t n, int32_t* __restrict__ owner,
+                             double* __restrict__ logl) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n) return;
-  const int32_t s = slots[r];
-  if (s >= 0 && s < n_slots) owner[s] = -1;
+  if (sl[r] >= 0) owner[sl[r]] = -1;
+  else logl[r] = __builtin_nan("");
 }
 
-// Rows whose slot is out of range (sl[r] == -1) get log L = NaN.
-__global__ void k_wc_mark(const int32_t* __restrict__ sl, int64_t n, double* __restrict__ logl) {
+// sl[r] = slots[r], or -1 when that is no slot.
+__global__ void k_wc_clip(const int32_t* __restrict__ slots, int64_t n, int64_t n_slots, int32_t* __restrict__ sl) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n && sl[r] == -1) logl[r] = __builtin_nan("");
+  if (r < n) sl[r] = slots[r] >= 0 && slots[r] < n_slots ? slots[r] : -1;
+}
+
+// Rows whose slot is out of range get log L = NaN.
+__global__ void k_wc_mark(const int32_t* __restrict__ slots, int64_t n, int64_t n_slots, double* __restrict__ logl) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r < n && (slots[r] < 0 || slots[r] >= n_slots)) logl[r] = __builtin_nan("");
 }
 
 gw_status wc_reserve(gw_wcache* c, int64_t n) {
@@ -92,13 +95,14 @@ gw_status wc_reserve(gw_wcache* c, int64_t n) {
   if (c->mem) (void)hipFree(c->mem);
   c->mem = nullptr;
   c->cap = 0;
-  const size_t bytes = (size_t)n * 2 * kMaxDet * sizeof(double) + 2 * (size_t)n * sizeof(int32_t) + 2 * sizeof(int32_t);
+  const size_t bytes = (size_t)n * 2 * kMaxDet * sizeof(double) + 3 * (size_t)n * sizeof(int32_t) + sizeof(int32_t);
   s = check_hip(hipMalloc((void**)&c->mem, bytes), "waveform cache workspace");
   if (s != GW_OK) return s;
   c->zrow = (double*)c->mem;
-  c->rows = (int32_t*)(c->mem + (size_t)n * 2 * kMaxDet * sizeof(double));
-  c->sl = c->rows + n;
-  c->counts = c->sl + n;
+  c->sl = (int32_t*)(c->mem + (size_t)n * 2 * kMaxDet * sizeof(double));
+  c->bslot = c->sl + n;
+  c->brow = c->bslot + n;
+  c->bcount = c->brow + n;
   c->cap = n;
   return GW_OK;
 }
@@ -130,6 +134,7 @@ gw_status gw_wcache_create(gw_ctx* ctx, int64_t n_slots, gw_wcache** out) {
     return set_error(GW_EINVAL, "gw_wcache_create: %lld slots of %lld bytes exceed 128 GiB", (long long)n_slots,
                      (long long)(f2 * sizeof(float2)));
   gw_status s = check_hip(hipSetDevice(ctx->device), "hipSetDevice");
+  if (s == GW_OK) s = nodes_wide_init(ctx);
   if (s != GW_OK) return s;
   gw_wcache* c = new (std::nothrow) gw_wcache();
   if (!c) return set_error(GW_ENOMEM, "gw_wcache_create");
@@ -182,24 +187,21 @@ gw_status gw_wcache_update(gw_wcache* c, const double* theta, const int32_t* slo
   const unsigned blocks = (unsigned)((n + 255) / 256);
   s = launch_prologue(ctx, theta, n, marg, ctx->coef, n, st);
   if (s == GW_OK) {
-    hipLaunchKernelGGL(k_wc_rows, dim3(blocks), dim3(256), 0, st, c->rows, n, c->counts, 0);
-    hipLaunchKernelGGL(k_wc_slots, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, c->sl, c->owner);
-    s = check_hip(hipGetLastError(), "row list launch");
+    hipLaunchKernelGGL(k_wc_slots, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, c->sl, c->owner, c->bcount);
+    s = check_hip(hipGetLastError(), "slot check launch");
   }
+  if (s == GW_OK) s = launch_wcache_slow(ctx, ctx->coef, n, prec, nch, ctx->partial, st);
   if (s == GW_OK)
-    s = launch_cached(ctx, ctx->coef, n, prec, tpb, nch, c->rows, nullptr, c->counts, 1, nullptr, nullptr, nullptr,
-                      ctx->partial, st);
-  if (s == GW_OK)
-    s = launch_epilogue_cached(ctx, ctx->partial, nch, cached_node_chunks(ctx, nch), ctx->coef, n, n, marg, prec, logl,
-                               nullptr, nullptr, c->zrow, st);
+    s = launch_epilogue_cached(ctx, ctx->partial, nch, cached_node_chunks(ctx, n, nch), ctx->coef, n, n, marg, prec,
+                               logl, nullptr, nullptr, c->zrow, st);
   if (s == GW_OK) {
-    hipLaunchKernelGGL(k_wc_store_z, dim3(blocks), dim3(256), 0, st, c->zrow, c->sl, c->owner, n, ctx->n_det, c->zc);
+    hipLaunchKernelGGL(k_wc_store, dim3(blocks), dim3(256), 0, st, c->zrow, c->sl, c->owner, ctx->coef, n, ctx->n_det,
+                       ctx->nodes.n > 0, c->zc, c->bslot, c->brow, c->bcount);
     s = check_hip(hipGetLastError(), "cached sums launch");
   }
-  if (s == GW_OK) s = launch_wmom_build(ctx, ctx->coef, n, c->sl, c->counts, n, 1, c->rows, prec, c->wc, st);
+  if (s == GW_OK) s = launch_wmom_build(ctx, ctx->coef, n, c->bslot, c->bcount, n, 1, c->brow, prec, c->wc, st);
   if (s == GW_OK) {
-    hipLaunchKernelGGL(k_wc_release, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, c->owner);
-    hipLaunchKernelGGL(k_wc_mark, dim3(blocks), dim3(256), 0, st, c->sl, n, logl);
+    hipLaunchKernelGGL(k_wc_release, dim3(blocks), dim3(256), 0, st, c->sl, n, c->owner, logl);
     s = check_hip(hipGetLastError(), "slot release launch");
   }
   return s;
@@ -221,21 +223,20 @@ gw_status gw_wcache_loglike(gw_wcache* c, const double* theta, const int32_t* sl
   s = launch_prologue(ctx, theta, n, marg, ctx->coef, n, st);
   if (s != GW_OK) return s;
   // out-of-range slots read slot 0 and are marked NaN afterwards
-  hipLaunchKernelGGL(k_wc_slots, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, c->sl, nullptr);
-  hipLaunchKernelGGL(k_wc_rows, dim3(blocks), dim3(256), 0, st, c->rows, n, c->counts, 1);
-  s = check_hip(hipGetLastError(), "row list launch");
-  if (s == GW_OK && kind == 2) {  // the slots' sums, no reduction
-    s = launch_epilogue_cached(ctx, ctx->partial, 0, 0, ctx->coef, n, n, marg, prec, logl, c->sl, c->zc, nullptr, st);
-  } else if (s == GW_OK) {
-    // complete sums into zrow, then the epilogue takes them from there
-    s = launch_cached(ctx, ctx->coef, n, prec, tpb, nch, nullptr, c->rows, c->counts, 1, c->sl, c->wc, c->zrow,
-                      ctx->partial, st);
+  if (kind == 2) {  // the slots' sums, no reduction
+    hipLaunchKernelGGL(k_wc_clip, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, c->sl);
+    s = check_hip(hipGetLastError(), "slot check launch");
     if (s == GW_OK)
-      s = launch_epilogue_cached(ctx, ctx->partial, 0, 0, ctx->coef, n, n, marg, prec, logl, c->rows, c->zrow, nullptr,
-                                 st);
+      s = launch_epilogue_cached(ctx, ctx->partial, 0, 0, ctx->coef, n, n, marg, prec, logl, c->sl, c->zc, nullptr, st);
+  } else {
+    const int cm = wcache_fast_chunks(ctx, nch), nn = cached_node_chunks(ctx, n, nch, true);
+    s = launch_wcache_fast(ctx, ctx->coef, n, prec, cm, nn, slots, c->n_slots, c->wc, ctx->partial, st);
+    if (s == GW_OK)
+      s = launch_epilogue_z(ctx, ctx->partial, cm, nn, ctx->coef, n, n, marg, prec, logl, nullptr, nullptr, nullptr,
+                            ctx->zbuf, st, kNodeWide);
   }
   if (s == GW_OK) {
-    hipLaunchKernelGGL(k_wc_mark, dim3(blocks), dim3(256), 0, st, c->sl, n, logl);
+    hipLaunchKernelGGL(k_wc_mark, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, logl);
     s = check_hip(hipGetLastError(), "slot check launch");
   }
   return s;

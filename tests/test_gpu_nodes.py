@@ -84,3 +84,35 @@ def test_node_sums_independent_of_launch_shape(gw, tpb, chunks):
     ok = np.isfinite(want)
     assert np.array_equal(np.isfinite(got), ok)
     assert np.max(np.abs(got[ok] - want[ok])) < 512 * np.finfo(float).eps * np.max(np.abs(want[ok]))
+
+
+@pytest.mark.parametrize("n_slots,n", [(1, 1), (70, 65), (600, 700)])
+def test_cache_mixes_node_and_moment_rows(gw, n_slots, n):
+    # slots in and out of the tables' phase range, and extrinsic moves with
+    # delays on either side of each table's and of the cache's own limit
+    prob = with_injection(gwsynth.make_problem(8.0, 20.0, 512.0, psd_scale=1e-47),
+                          gwsynth.prior_draws(gwsynth.SEEDS["injection"], 1)[0])
+    rng = np.random.default_rng(3)
+    base = gwsynth.prior_draws(21, n_slots)
+    base[1::3, 0] = 0.9
+    slots = rng.integers(0, n_slots, n)
+    th = base[slots].copy()
+    ext = gwsynth.prior_draws(22, n)
+    th[:, 6:11], th[:, 12] = ext[:, 6:11], ext[:, 12]
+    th[3::7, 12] = 0.19
+    th[5::9, 12] = -0.2
+    th[4::11, 12] = 0.31
+    dt = np.array([[abs(t[12] + d) for d in (-np.array([math.cos(t[9]) * math.cos(t[8]), math.cos(t[9]) * math.sin(t[8]),
+                                                        math.sin(t[9])]) @ prob.det_pos.T / 299792458.0)] for t in th])
+    beyond = dt.max(axis=1) > 0.25
+    with gw.Context(prob) as ctx:
+        cache = gw.WaveformCache(ctx.handle, n_slots)
+        cache.update(torch.from_numpy(base).cuda(), torch.arange(n_slots, dtype=torch.int32, device="cuda"))
+        got = cache.loglike(torch.from_numpy(th).cuda(), torch.from_numpy(slots.astype(np.int32)).cuda(), 1).cpu().numpy()
+        ctx.set_full_kernel(1)
+        want = ctx.loglike(torch.from_numpy(th).cuda(), marg=L.PHASE_DIST).cpu().numpy()
+        cache.close()
+    assert np.array_equal(np.isnan(got), beyond)
+    # FP32 moments carry 6e-8 of the overlap, which is at most sqrt(<d|d> <h|h>)
+    # and enters the distance marginal with slope below sqrt(<d|d>)-sized SNR^2
+    assert np.max(np.abs(got - want)[~beyond]) < 6e-8 * L.data_inner(prob)
