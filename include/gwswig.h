@@ -342,8 +342,10 @@ gw_status gw_graph_info(const gw_ctx* ctx, int32_t* n_graphs, double* last_insta
  * else Philox4x64-10 (Salmon et al. 2011): uniform j of chain c is word j % 4
  * of the block at counter (counter, c, j / 4, 0) under key (seed, 0), mapped
  * to ((w >> 11) + 0.5) 2^-53.
- * Blocks until done (the host checks progress every four rounds; rounds
- * after every chain has finished change nothing).
+ * Blocks until done (the host checks progress every few rounds; rounds
+ * after every chain has finished change nothing).  A round may evaluate
+ * candidates of several steps of a chain at once; the moves and n_evals are
+ * those of the walk described above.
  */
 #define GW_MAX_BLOCK 11
 #define GW_SLICE_UNI_FIXED(bd) (((bd) <= 4 ? 4 : 2 * (((bd) + 1) / 2)) + 2)
@@ -367,7 +369,7 @@ typedef struct {
   int32_t prec;           /* GW_PREC_FP64 or GW_PREC_MIXED */
   int32_t* n_evals;       /* device [k] likelihood calls per chain, or NULL */
   int32_t* status;        /* device [k] 0 moved, 1 kept, or NULL */
-  int32_t use_graph;      /* 1: replay a captured graph of 4 rounds (captured on
+  int32_t use_graph;      /* 1: replay a captured graph of a few rounds (captured on
                              first use and again when k, like, marg, prec, the
                              launch shapes, the time grid (window, oversampling,
                              edge split), the heterodyne setup, a workspace,

@@ -126,7 +126,8 @@ gw_status launch_template(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n
 // NULL, the moment reduction on rows fast_rows[0 .. counts[1]) (row p uses
 // slot p / 2; rows whose |t_c + dt_i| exceeds the cache's range get NaN) into
 // the same partials.
-// launch_wcache_slow: the full reduction on all n rows, on the vector ALUs.
+// launch_all_rows: the full reduction on all n rows, on the vector ALUs, with
+// the same sums as launch_cached's slow rows at the same chunk counts.
 // launch_wcache_fast: rows that a node table covers (C_NODE at least
 // kNodeWide) summed over its nodes into nch_node chunks, the others over the
 // moments of slot slot_of[p] (slot 0 when that is outside 0 .. n_slots - 1)
@@ -141,8 +142,8 @@ int64_t wmom_slot_f2(const gw_ctx* ctx);
 gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, const int32_t* slow_rows,
                         const int32_t* fast_rows, const int32_t* counts, const float2* mom, double* partial,
                         hipStream_t st);
-gw_status launch_wcache_slow(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, double* partial,
-                             hipStream_t st);
+gw_status launch_all_rows(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
+                          double* partial, hipStream_t st);
 int wcache_fast_chunks(const gw_ctx* ctx, int n_chunks);
 gw_status launch_wcache_fast(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
                              const int32_t* slot_of, int64_t n_slots, const float2* mom, double* partial,

@@ -1779,12 +1779,10 @@ gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, in
   return launch_wmom(ctx, coef, n, cm, n_chunks, fast_rows, counts + 1, 2, nullptr, n, mom, false, partial, st);
 }
 
-// The cache's slow rows: all n.
-gw_status launch_wcache_slow(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, double* partial,
-                             hipStream_t st) {
+gw_status launch_all_rows(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
+                          double* partial, hipStream_t st) {
   if (n == 0) return GW_OK;
-  return launch_rows(ctx, coef, n, prec, n_chunks, cached_node_chunks(ctx, n, n_chunks), nullptr, nullptr, false,
-                     partial, st);
+  return launch_rows(ctx, coef, n, prec, n_chunks, nch_node, nullptr, nullptr, false, partial, st);
 }
 
 // The cache's fast rows.  Summing a row over its own nodes costs less than

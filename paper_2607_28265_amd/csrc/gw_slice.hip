@@ -109,6 +109,14 @@ struct SliceState {
   int32_t* tot_evals;
   int32_t* n_caps;   // blocks whose shrink cap was hit
   int32_t* n_active;  // [2] chains still moving after a round (the fused rounds alternate)
+  // look-ahead rounds (k_sweep_round), per candidate row: what it is (0 none,
+  // 1 lower end, 2 upper end, 3 shrink draw), where, and for a shrink draw the
+  // bracket and draw count it was made at
+  int32_t* look_kind;
+  int32_t* look_ns;
+  double* look_t;
+  double* look_lo;
+  double* look_hi;
   // row lists and waveform cache bookkeeping (list mode only)
   int32_t* rkind;      // [2k]: 0 no likelihood, 1 full, 2 cached waveform, 3 cached sums
   int32_t* zsrc;       // [2k]: slot whose cached sums the row uses, or -1
@@ -542,18 +550,328 @@ __global__ void __launch_bounds__(kSweepThreads) k_sweep_update(const SweepParam
   count_active(S.n_active, update_chain(P, S, cand_logl, c));
 }
 
-// One round's update followed by the next round's proposals, for calls with
-// no waveform cache, prescreen or record: the same per-chain steps in the same
-// order as k_sweep_update then k_sweep_propose, in one launch.  Moving chains
-// are counted in n_active[slot]; n_active[slot ^ 1], which the next round
-// counts into, is cleared here.
-__global__ void __launch_bounds__(kSweepThreads) k_sweep_step(const SweepParams* __restrict__ D, SliceState S, const double* __restrict__ cand_logl, double* __restrict__ cand, int slot) {
+// One round for calls with no waveform cache, prescreen or record: the update
+// from the last round's log L (unless ``first``), then the next proposals, with
+// R lanes and R candidate rows per chain (rows c R .. c R + R - 1).
+//
+// A round costs the latency of its four kernels whatever its few hundred rows,
+// so each chain looks ahead: while stepping out, lane i of an end proposes the
+// point i steps beyond it, and while shrinking, lane i proposes the draw that
+// follows if the i before it are rejected (the bracket those rejections leave
+// is known in advance).  The update takes the rows in that order and stops
+// where the one-candidate walk would have, so the moves and the counts of
+// likelihood calls are those of that walk, and rows beyond it are ignored.  A
+// heterodyned sweep of seven blocks at 125 chains takes 1.42 ms with 8 rows a
+// chain, 4.2 ms with two (76 rounds of 46 us and their gaps).  The lanes also
+// share the pairs of normals of a new block's direction.
+//
+// Moving chains are counted in n_active[slot]; n_active[slot ^ 1], which the
+// next round counts into, is cleared here.
+
+// The lanes of a chain: lane ``i`` of R, all R in one wave.
+template <int R>
+struct Lanes {
+  int i;
+  __device__ double get(double v, int from) const { return __shfl(v, from, R); }
+  __device__ int get(int v, int from) const { return __shfl(v, from, R); }
+  // bit j: the predicate of lane j
+  __device__ unsigned bits(bool p) const {
+    const unsigned long long m = __ballot(p);
+    return (unsigned)(m >> (__lane_id() & ~(R - 1))) & (unsigned)((1u << R) - 1u);
+  }
+};
+
+// A chain's state in registers (the same in each of its lanes).
+struct Chain {
+  int fl, b, bd;
+  double t_lo, t_hi, d[kMaxBlock];
+  int left[2], n_shrink, n_evals, tot_evals, n_caps;
+};
+
+// start_block with the pairs of normals dealt over the lanes.
+template <int R>
+__device__ inline void start_chain(const SweepParams& P, int64_t c, int b, const Lanes<R>& ln, Chain& C) {
+  C.b = b;
+  C.bd = P.bd[b];
+  const int bd = C.bd, nfix = uni_fixed(bd);
+  // uniforms 2 p and 2 p + 1: one half of a Philox block, or table entries
+  auto pair = [&](int p, double* u0, double* u1) {
+    if (P.uniforms) {
+      const double* t = P.uniforms + c * (nfix + P.max_shrink) + 2 * p;
+      *u0 = t[0];
+      *u1 = t[1];
+      return;
+    }
+    uint64_t ctr[4] = {P.counter + (uint64_t)b, (uint64_t)c, (uint64_t)(p >> 1), 0ull};
+    philox4x64(ctr, P.seed, 0ull);
+    *u0 = philox_unit(p & 1 ? ctr[2] : ctr[0]);
+    *u1 = philox_unit(p & 1 ? ctr[3] : ctr[1]);
+  };
+  constexpr int kPairs = (kMaxBlock + 1) / 2;
+  double z[2 * kPairs];
+#pragma unroll
+  for (int p0 = 0; p0 < kPairs; p0 += R) {
+    double a = 0.0, e = 0.0;
+    if (2 * (p0 + ln.i) < bd) {
+      double u0, u1;
+      pair(p0 + ln.i, &u0, &u1);
+      const double r = sqrt(-2.0 * log(u0));
+      double sn, cs;
+      sincos(kTwoPi * u1, &sn, &cs);
+      a = r * cs;
+      e = r * sn;
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (p0 + q < kPairs) {
+        z[2 * (p0 + q)] = ln.get(a, q);
+        z[2 * (p0 + q) + 1] = ln.get(e, q);
+      }
+  }
+  double nrm = 0.0;
+#pragma unroll
+  for (int j = 0; j < kMaxBlock; ++j)
+    if (j < bd) nrm += z[j] * z[j];
+  nrm = sqrt(nrm);
+#pragma unroll
+  for (int j = 0; j < kMaxBlock; ++j) z[j] = z[j] / nrm;
+  const double* L = P.chol + P.choff[b];
+#pragma unroll
+  for (int a = 0; a < kMaxBlock; ++a) {
+    double v = 0.0;
+    if (a < bd) {
+#pragma unroll
+      for (int q = 0; q < kMaxBlock; ++q)
+        if (q < bd) v += L[a * bd + q] * z[q];
+    }
+    C.d[a] = v;
+  }
+  double off, vsplit;
+  pair(nfix / 2 - 1, &off, &vsplit);
+  C.t_lo = -off * P.w;
+  C.t_hi = (1.0 - off) * P.w;
+  const int budget = 2 * P.max_out + 1;
+  C.left[0] = (int)floor((double)budget * vsplit);
+  C.left[1] = budget - 1 - C.left[0];
+  C.n_shrink = 0;
+  C.n_evals = 0;
+  C.fl = (C.left[0] > 0 ? 1 : 0) | (C.left[1] > 0 ? 2 : 0);
+}
+
+// The current block ends: count it and start the next, or mark the sweep done.
+template <int R>
+__device__ inline void end_chain_block(const SweepParams& P, int64_t c, bool capped, const Lanes<R>& ln, Chain& C) {
+  C.tot_evals += C.n_evals;
+  C.n_evals = 0;
+  if (capped) C.n_caps += 1;
+  if (C.b + 1 < P.nb) start_chain(P, c, C.b + 1, ln, C);
+  else C.fl = 4;
+}
+
+// Lanes per workgroup: a quarter of a wave, so that few chains' diverging
+// paths share one (64 lanes: 1.10 against 1.04 ms a sweep at 25 chains, equal
+// at 125).
+constexpr int kLookLanes = 16;
+
+template <int R>
+__global__ void __launch_bounds__(kLookLanes) k_sweep_round(const SweepParams* __restrict__ D, SliceState S,
+                                                    const double* __restrict__ cand_logl, double* __restrict__ cand,
+                                                    int slot, int first) {
   const SweepParams& P = *D;
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c == 0) S.n_active[slot ^ 1] = 0;
-  if (c >= P.k) return;
-  count_active(S.n_active + slot, update_chain(P, S, cand_logl, c));
-  propose_chain(P, S, cand, c);
+  const int64_t row = (int64_t)blockIdx.x * kLookLanes + threadIdx.x;
+  const int64_t c = row / R;
+  if (row == 0) S.n_active[slot ^ 1] = 0;
+  if (c >= P.k) return;  // all lanes of a chain together
+  const Lanes<R> ln{(int)(threadIdx.x & (R - 1))};
+  Chain C;
+  C.fl = S.flags[c];
+  C.b = S.cur[c];
+  C.t_lo = S.t_lo[c];
+  C.t_hi = S.t_hi[c];
+  C.left[0] = S.n_out[2 * c];
+  C.left[1] = S.n_out[2 * c + 1];
+  C.n_shrink = S.n_shrink[c];
+  C.n_evals = S.n_evals[c];
+  C.tot_evals = S.tot_evals[c];
+  C.n_caps = S.n_caps[c];
+#pragma unroll
+  for (int a = 0; a < kMaxBlock; ++a) C.d[a] = S.d[c * kMaxBlock + a];
+  C.bd = P.bd[C.b];
+  const bool was_done = !first && (C.fl & 4);
+  if (!first && !was_done) {
+    const int kind = S.look_kind[row];  // 0 none, 1 lower end, 2 upper end, 3 shrink draw
+    const double v = cand_logl[row];
+    const double t = S.look_t[row];
+    const unsigned in = ln.bits(v > P.logl_star);
+    if (C.fl & 3) {
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        const unsigned on = ln.bits(kind == side + 1);  // consecutive lanes, in order
+        if (!on) continue;
+        const int l0 = __ffs((int)on) - 1, n = __popc(on);
+        const unsigned hit = (in >> l0) & ((n < 32 ? 1u << n : 0u) - 1u);
+        const int ok = __ffs((int)~hit) - 1;  // leading candidates inside, <= n
+        C.n_evals += ok < n ? ok + 1 : n;
+        for (int q = 0; q < ok; ++q) {
+          if (side == 0) C.t_lo -= P.w;
+          else C.t_hi += P.w;
+        }
+        C.left[side] -= ok;
+        if (ok < n || C.left[side] == 0) C.fl &= ~(1 << side);
+      }
+    } else {
+      const int n = __popc(ln.bits(kind == 3));
+      const unsigned hit = in & ((1u << n) - 1u);
+      const double ts = t;
+      if (hit) {
+        const int j = __ffs((int)hit) - 1;
+        const double tj = ln.get(ts, j), vj = ln.get(v, j);
+        C.n_evals += j + 1;
+        if (ln.i == 0) {
+          for (int a = 0; a < C.bd; ++a) P.x[c * kSliceDim + P.block[C.b][a]] += tj * S.d[c * kMaxBlock + a];
+          P.logl[c] = vj;
+        }
+        end_chain_block(P, c, false, ln, C);
+      } else {
+        const double tl = ln.get(ts, n - 1);
+        C.t_lo = ln.get(S.look_lo[row], n - 1);
+        C.t_hi = ln.get(S.look_hi[row], n - 1);
+        C.n_shrink = ln.get(S.look_ns[row], n - 1) + 1;
+        C.n_evals += n;
+        if (tl < 0.0) C.t_lo = tl;
+        else C.t_hi = tl;
+        if (C.n_shrink >= P.max_shrink) end_chain_block(P, c, true, ln, C);
+      }
+    }
+  }
+  // the chain's point: written above by lane 0, read back by all its lanes
+  __threadfence_block();
+  double x[kSliceDim];
+#pragma unroll
+  for (int j = 0; j < kSliceDim; ++j) x[j] = __hip_atomic_load(P.x + c * kSliceDim + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+
+  // this lane's candidate
+  int kind = 0, ns0 = 0;
+  double t = 0.0, lo0 = 0.0, hi0 = 0.0, u[kSliceDim];
+  // the block's coordinates of the chain's point
+  int idx[kMaxBlock];
+  double xb[kMaxBlock];
+  auto take_block = [&]() {
+#pragma unroll
+    for (int a = 0; a < kMaxBlock; ++a) idx[a] = P.block[C.b][a];
+#pragma unroll
+    for (int a = 0; a < kMaxBlock; ++a) {
+      xb[a] = x[0];
+#pragma unroll
+      for (int q = 1; q < kSliceDim; ++q) xb[a] = idx[a] == q ? x[q] : xb[a];
+    }
+  };
+  // the point at tt: inside the cube?
+  auto inside = [&](double tt) {
+    bool ok = true;
+#pragma unroll
+    for (int a = 0; a < kMaxBlock; ++a) {
+      const double w = xb[a] + tt * C.d[a];
+      ok = ok && (a >= C.bd || (w >= 0.0 && w <= 1.0));
+    }
+    return ok;
+  };
+  take_block();
+  bool any = false;
+  for (int guard = 0; guard <= kMaxBlocks && !(C.fl & 4) && !any; ++guard) {
+    if (C.fl & 3) {
+      const bool both = (C.fl & 3) == 3;
+      const int side = both ? (ln.i >= R / 2 ? 1 : 0) : (C.fl & 1 ? 0 : 1);
+      const int i = both ? (ln.i & (R / 2 - 1)) : ln.i;
+      double tt = side == 0 ? C.t_lo : C.t_hi;
+      for (int q = 0; q < i; ++q) tt = side == 0 ? tt - P.w : tt + P.w;
+      const unsigned good = ln.bits(i < (side == 0 ? C.left[0] : C.left[1]) && inside(tt));
+      // candidates up to the first that the walk would not evaluate
+      const int l0 = both && side == 1 ? R / 2 : 0;
+      const int n = __ffs((int)~(good >> l0)) - 1;
+      if (i < n) {
+        kind = side + 1;
+        t = tt;
+        any = true;
+      }
+      if (both) {
+        // an end whose next point lies outside the cube stops there
+        if (!(good & 1u)) C.fl &= ~1;
+        if (!((good >> (R / 2)) & 1u)) C.fl &= ~2;
+      } else if (!(good & 1u)) {
+        C.fl &= ~3;
+      }
+      any = ln.bits(any) != 0;
+    }
+    if (!(C.fl & 3)) {
+      double lo = C.t_lo, hi = C.t_hi;
+      int ns = C.n_shrink, got = 0;
+      const int nfix = uni_fixed(C.bd);
+      while (ns < P.max_shrink && got < R) {
+        const int left = P.max_shrink - ns;
+        const double um = ln.i < left ? slice_uniform(P, C.b, c, nfix + ns + ln.i) : 0.0;
+        const int m = left < R ? left : R;
+        for (int q = 0; q < m && got < R; ++q) {
+          const double tt = lo + ln.get(um, q) * (hi - lo);
+          if (inside(tt)) {
+            if (got == ln.i) {
+              kind = 3;
+              t = tt;
+              lo0 = lo;
+              hi0 = hi;
+              ns0 = ns;
+            }
+            ++got;
+          }
+          if (tt < 0.0) lo = tt;
+          else hi = tt;
+          ++ns;
+        }
+      }
+      if (got) {
+        any = true;
+      } else {  // cap reached: keep the point
+        end_chain_block(P, c, true, ln, C);
+        take_block();
+      }
+    }
+  }
+  double* __restrict__ th = cand + row * 13;
+  if (kind) {
+#pragma unroll
+    for (int j = 0; j < kSliceDim; ++j) u[j] = x[j];
+#pragma unroll
+    for (int a = 0; a < kMaxBlock; ++a) {
+      const double w = xb[a] + t * C.d[a];
+#pragma unroll
+      for (int q = 0; q < kSliceDim; ++q) u[q] = a < C.bd && idx[a] == q ? w : u[q];
+    }
+    prior_transform(u, th, P.cm);
+  } else if (!was_done) {  // an unphysical vector (cheap -inf); done chains keep theirs
+    for (int j = 0; j < 13; ++j) th[j] = 0.0;
+    th[1] = -1.0;
+  }
+  if (was_done) return;
+  S.look_kind[row] = kind;
+  S.look_t[row] = t;
+  S.look_lo[row] = lo0;
+  S.look_hi[row] = hi0;
+  S.look_ns[row] = ns0;
+  if (ln.i == 0) {
+    S.flags[c] = C.fl;
+    S.cur[c] = C.b;
+    S.t_lo[c] = C.t_lo;
+    S.t_hi[c] = C.t_hi;
+    S.n_out[2 * c] = C.left[0];
+    S.n_out[2 * c + 1] = C.left[1];
+    S.n_shrink[c] = C.n_shrink;
+    S.n_evals[c] = C.n_evals;
+    S.tot_evals[c] = C.tot_evals;
+    S.n_caps[c] = C.n_caps;
+#pragma unroll
+    for (int a = 0; a < kMaxBlock; ++a) S.d[c * kMaxBlock + a] = C.d[a];
+  }
+  count_active(S.n_active + slot, ln.i == 0 ? C.fl : 4);
 }
 
 // Row lists of the cached likelihood: rows of kind 1 and 2 in ascending
@@ -651,7 +969,7 @@ using namespace gw;
 
 // What a captured round group bakes in: any change means a new capture.
 struct SliceGraphKey {
-  int64_t k;
+  int64_t k, n;
   int32_t like, marg, prec, cache;
   const void *ws_mem, *coef, *partial, *zbuf, *het, *wc, *mlp;
   uint64_t mlp_scale, gen;
@@ -682,6 +1000,7 @@ struct gw_slice_ws {
 };
 
 static gw_status slice_ws(gw_ctx* ctx, int64_t k, gw_slice_ws** out);
+constexpr int64_t kLookRows = 1024;
 static gw_status slice_wcache(gw_ctx* ctx, gw_slice_ws* ws, int64_t k);
 
 struct SweepCall {
@@ -714,14 +1033,24 @@ gw_status gw::cached_reserve(gw_ctx* ctx, int64_t n) {
   return s;
 }
 
-// Likelihood of the round's 2k candidate rows into ws->cand_logl.
-static gw_status eval_rows(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, const SweepCall& a, hipStream_t st) {
-  const int64_t n = 2 * k;
-  if (!a.lists) return loglike_batch(ctx, ws->cand, n, a.like, a.marg, a.prec, ws->cand_logl, st);
+// Likelihood of the round's n candidate rows into ws->cand_logl.  The full band
+// sums in the chunks of a 2 k-row list launch whether the rows are listed or
+// not, so that a candidate's log L does not depend on the look-ahead.
+static gw_status eval_rows(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, int64_t n, const SweepCall& a, hipStream_t st) {
+  if (a.like != GW_FULL || a.marg != GW_MARG_PHASE_DIST)
+    return loglike_batch(ctx, ws->cand, n, a.like, a.marg, a.prec, ws->cand_logl, st);
   gw_status s = cached_reserve(ctx, n);
   if (s != GW_OK) return s;
   int tpb, nch;
   cached_shape(ctx, &tpb, &nch);
+  const int nn = cached_node_chunks(ctx, 2 * k, nch);
+  if (!a.lists) {
+    s = launch_prologue(ctx, ws->cand, n, a.marg, ctx->coef, n, st);
+    if (s == GW_OK) s = launch_all_rows(ctx, ctx->coef, n, a.prec, nch, nn, ctx->partial, st);
+    if (s == GW_OK)
+      s = launch_epilogue(ctx, ctx->partial, nch, nn, ctx->coef, n, n, a.marg, a.prec, ws->cand_logl, st);
+    return s;
+  }
   hipLaunchKernelGGL(k_sweep_lists, dim3(1), dim3(1024), 0, st, (const SweepParams*)ws->dev, ws->S);
   s = check_hip(hipGetLastError(), "row list launch");
   if (s == GW_OK) s = launch_prologue(ctx, ws->cand, n, a.marg, ctx->coef, n, st);
@@ -729,8 +1058,8 @@ static gw_status eval_rows(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, const SweepC
     s = launch_cached(ctx, ctx->coef, n, a.prec, nch, ws->S.slow_rows, ws->S.stream_rows, ws->S.counts,
                       a.cache ? ws->wc : nullptr, ctx->partial, st);
   if (s == GW_OK)
-    s = launch_epilogue_cached(ctx, ctx->partial, nch, cached_node_chunks(ctx, n, nch), ctx->coef, n, n, a.marg, a.prec, ws->cand_logl, ws->S.zsrc,
-                               ws->S.zc, ws->S.zrow, st);
+    s = launch_epilogue_cached(ctx, ctx->partial, nch, nn, ctx->coef, n, n, a.marg, a.prec, ws->cand_logl,
+                               ws->S.zsrc, ws->S.zc, ws->S.zrow, st);
   return s;
 }
 
@@ -738,15 +1067,15 @@ static gw_status eval_rows(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, const SweepC
 // changes) on the workspace's own capture stream.  Buffers the likelihood
 // would grow are reserved first: no allocation may happen during capture.
 template <class Group>
-static gw_status slice_graph(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, const SweepCall& a, bool fused, bool pinned,
-                             Group group) {
-  const int64_t n = 2 * k;
-  gw_status s = a.lists ? cached_reserve(ctx, n) : a.like == GW_HET ? het_reserve(ctx, n) : full_reserve(ctx, n);
+static gw_status slice_graph(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, int64_t n, const SweepCall& a, bool fused,
+                             bool pinned, Group group) {
+  gw_status s = a.like == GW_HET ? het_reserve(ctx, n) : cached_reserve(ctx, n);
   if (s == GW_OK && a.marg == GW_MARG_PHASE_TIME) s = tmarg_reserve(ctx, n, a.like);
   if (s != GW_OK) return s;
   SliceGraphKey key;
   memset(&key, 0, sizeof(key));
   key.k = k;
+  key.n = n;
   key.like = a.like;
   key.marg = a.marg;
   key.prec = a.prec;
@@ -930,6 +1259,26 @@ static gw_status set_block(const char* who, SweepParams& P, int b, const int32_t
   return GW_OK;
 }
 
+// Calls with no waveform cache, prescreen or record run the look-ahead rounds;
+// of the others, the full band's rows go to the likelihood as lists.
+static bool look_ahead(const SweepParams& P) { return !P.cache && !P.screen && !P.record; }
+
+static int32_t use_lists(int32_t like, int32_t marg, const SweepParams& P) {
+  return like == GW_FULL && marg == GW_MARG_PHASE_DIST && !look_ahead(P);
+}
+
+// Candidate rows per chain of the look-ahead rounds: the most of 2, 4, 8 and 16
+// that keep a round within kLookRows rows.  One sweep of 125 heterodyned chains
+// takes 2.48, 1.62, 1.41 and 1.48 ms with 2, 4, 8 and 16 rows a chain, of 250
+// chains 2.47, 1.74 and 1.91 ms with 2, 4 and 8; 125 full-band chains 2.88,
+// 1.93, 1.82 and 1.91 ms with 2 to 16.
+
+static int look_rows(int64_t k) {
+  int r = 2;
+  while (r < 16 && 2 * r * k <= kLookRows) r *= 2;
+  return r;
+}
+
 // Run one sweep of P.nb blocks for all chains to completion.
 static gw_status run_sweep(gw_ctx* ctx, const SweepParams& P, const SweepCall& a, hipStream_t st) {
   gw_status s = check_hip(hipSetDevice(ctx->device), "hipSetDevice");
@@ -939,6 +1288,9 @@ static gw_status run_sweep(gw_ctx* ctx, const SweepParams& P, const SweepCall& a
   if (s == GW_OK && a.cache) s = slice_wcache(ctx, ws, P.k);
   if (s != GW_OK) return s;
   const int64_t k = P.k;
+  const bool fused = look_ahead(P);
+  const int R = fused ? look_rows(k) : 2;
+  const int64_t n = R * k;  // candidate rows of a round
   const int tpb = kSweepThreads;
   const unsigned blocks = (unsigned)((k + tpb - 1) / tpb);
   if (a.mlp) {
@@ -952,13 +1304,13 @@ static gw_status run_sweep(gw_ctx* ctx, const SweepParams& P, const SweepCall& a
     // seed every chain's cached sums from a full evaluation of its current point
     hipLaunchKernelGGL(k_cache_init0, dim3(blocks), dim3(tpb), 0, st, (const SweepParams*)ws->dev, ws->S, ws->cand);
     s = check_hip(hipGetLastError(), "cache init launch");
-    if (s == GW_OK) s = eval_rows(ctx, ws, k, a, st);
+    if (s == GW_OK) s = eval_rows(ctx, ws, k, n, a, st);
     if (s == GW_OK) {
       hipLaunchKernelGGL(k_cache_init1, dim3(blocks), dim3(tpb), 0, st, (const SweepParams*)ws->dev, ws->S);
       s = check_hip(hipGetLastError(), "cache init launch");
     }
   }
-  // One group = 4 rounds of (propose, batched likelihood, update); after a
+  // A group is a few rounds of (propose, batched likelihood, update); after a
   // group the number of chains still moving is copied back.  A block takes at
   // most 2 max_out stepping rounds (both ends in parallel, their shares
   // summing to 2 max_out) and max_shrink shrink rounds, so after max_rounds
@@ -966,49 +1318,57 @@ static gw_status run_sweep(gw_ctx* ctx, const SweepParams& P, const SweepCall& a
   // chain is done change nothing, so the next group is queued before the
   // previous group's count is read: the host waits on group g while group
   // g + 1 runs, and at most one group of idle rounds follows the last move.
+  // The look-ahead rounds are few, so their groups are shorter; a round's
+  // update and the next round's proposals run as one kernel there, and the
+  // first proposals are launched once before the groups.
   const int max_rounds = P.nb * (2 * P.max_out + 1 + P.max_shrink + 1);
-  // Without a cache, prescreen or record, a round's update and the next
-  // round's proposals run as one kernel (k_sweep_step) and the first
-  // proposals are launched once before the groups.
-  const bool fused = !a.cache && !a.mlp && !P.record;
-  if (s == GW_OK && fused) {
-    hipLaunchKernelGGL(k_sweep_propose, dim3(blocks), dim3(tpb), 0, st, (const SweepParams*)ws->dev, ws->S,
-                       ws->cand);
-    s = check_hip(hipGetLastError(), "slice propose launch");
-  }
+  const int per_group = fused ? 2 : 4;
+  auto round = [&](hipStream_t rs, int slot, int first) -> gw_status {
+    const dim3 grid((unsigned)((n + kLookLanes - 1) / kLookLanes)), blk(kLookLanes);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, blk, 0, rs, (const SweepParams*)ws->dev, ws->S, (const double*)ws->cand_logl,
+                         ws->cand, slot, first);
+    };
+    switch (R) {
+      case 2: go(k_sweep_round<2>); break;
+      case 4: go(k_sweep_round<4>); break;
+      case 8: go(k_sweep_round<8>); break;
+      default: go(k_sweep_round<16>); break;
+    }
+    return check_hip(hipGetLastError(), "slice round launch");
+  };
+  if (s == GW_OK && fused) s = round(st, 1, 1);
   auto group = [&](hipStream_t gs) -> gw_status {
     gw_status g = GW_OK;
-    for (int r = 0; r < 4 && g == GW_OK; ++r) {
+    for (int r = 0; r < per_group && g == GW_OK; ++r) {
       if (!fused) {
         hipLaunchKernelGGL(k_sweep_propose, dim3(blocks), dim3(tpb), 0, gs, (const SweepParams*)ws->dev, ws->S,
                            ws->cand);
         g = check_hip(hipGetLastError(), "slice propose launch");
       }
       if (g == GW_OK && a.mlp) {
-        g = mlp_infer(a.mlp, ws->S.ucand, 2 * k, ws->S.pred, gs);
+        g = mlp_infer(a.mlp, ws->S.ucand, n, ws->S.pred, gs);
         if (g == GW_OK) {
-          hipLaunchKernelGGL(k_sweep_screen, dim3((unsigned)((2 * k + tpb - 1) / tpb)), dim3(tpb), 0, gs,
+          hipLaunchKernelGGL(k_sweep_screen, dim3((unsigned)((n + tpb - 1) / tpb)), dim3(tpb), 0, gs,
                              (const SweepParams*)ws->dev, ws->S, ws->cand);
           g = check_hip(hipGetLastError(), "slice screen launch");
         }
       }
-      if (g == GW_OK) g = eval_rows(ctx, ws, k, a, gs);
+      if (g == GW_OK) g = eval_rows(ctx, ws, k, n, a, gs);
       if (g == GW_OK && fused) {
-        hipLaunchKernelGGL(k_sweep_step, dim3(blocks), dim3(tpb), 0, gs, (const SweepParams*)ws->dev, ws->S,
-                           (const double*)ws->cand_logl, ws->cand, r & 1);
-        g = check_hip(hipGetLastError(), "slice step launch");
+        g = round(gs, r & 1, 0);
       } else if (g == GW_OK) {
         hipLaunchKernelGGL(k_sweep_update, dim3(blocks), dim3(tpb), 0, gs, (const SweepParams*)ws->dev, ws->S,
                            (const double*)ws->cand_logl);
         g = check_hip(hipGetLastError(), "slice update launch");
       }
       if (g == GW_OK && a.cache)
-        g = launch_wmom_build(ctx, ctx->coef, 2 * k, ws->S.build_list, ws->S.counts + 2, k, 2, ws->S.build_src,
+        g = launch_wmom_build(ctx, ctx->coef, n, ws->S.build_list, ws->S.counts + 2, k, 2, ws->S.build_src,
                               a.prec, ws->wc, gs);
     }
     return g;
   };
-  // the heterodyned rounds all evaluate the same 2k candidate rows: their
+  // the heterodyned rounds all evaluate the same n candidate rows: their
   // argument block is written once here instead of by every round
   struct Unpin {
     gw_ctx* c = nullptr;
@@ -1018,16 +1378,16 @@ static gw_status run_sweep(gw_ctx* ctx, const SweepParams& P, const SweepCall& a
   } unpin;
   const bool pin = a.like == GW_HET && a.marg != GW_MARG_PHASE_TIME;
   if (s == GW_OK && pin) {
-    s = het_pin_args(ctx, ws->cand, 2 * k, ws->cand_logl, st);
+    s = het_pin_args(ctx, ws->cand, n, ws->cand_logl, st);
     if (s == GW_OK) unpin.c = ctx;
   }
-  if (s == GW_OK && a.use_graph) s = slice_graph(ctx, ws, k, a, fused, pin, group);
+  if (s == GW_OK && a.use_graph) s = slice_graph(ctx, ws, k, n, a, fused, pin, group);
   int cur = 0, prev = -1;
-  for (int rounds = 0; s == GW_OK && rounds < max_rounds; rounds += 4) {
+  for (int rounds = 0; s == GW_OK && rounds < max_rounds; rounds += per_group) {
     if (a.use_graph) s = check_hip(hipGraphLaunch(ws->exec, st), "slice graph launch");
     else s = group(st);
     if (s != GW_OK) break;
-    // a group's last round (r = 3) counts into n_active[1] when fused
+    // a group's last round counts into n_active[1] when fused
     s = check_hip(hipMemcpyAsync(ws->h_active + cur, ws->S.n_active + (fused ? 1 : 0), sizeof(int32_t),
                                  hipMemcpyDeviceToHost, st),
                   "copy");
@@ -1088,11 +1448,11 @@ gw_status slice_step(gw_ctx* ctx, const gw_slice_args* a, void* stream) {
   P.k = a->k;
   P.x = a->x;
   P.logl = a->logl;
-  P.lists = a->like == GW_FULL && a->marg == GW_MARG_PHASE_DIST;
   s = cube_map(ctx, a->marg, &P.cm);
   if (s == GW_OK) s = set_screen("slice_step", ctx, a->mlp, a->margin, a->audit_frac, P);
   if (s == GW_OK) s = set_record("slice_step", a->rec_x, a->rec_logl, a->rec_cap, a->rec_count, P);
   if (s != GW_OK) return s;
+  P.lists = use_lists(a->like, a->marg, P);
   const int32_t graph = a->use_graph;
   const SweepCall c{a->like, a->marg, a->prec, graph, a->n_evals, a->status, 0, nullptr, P.lists,
                     P.screen ? a->mlp : nullptr, a->screen_stats};
@@ -1145,11 +1505,11 @@ gw_status slice_sweep(gw_ctx* ctx, const gw_sweep_args* a, void* stream) {
     P.cache = 1;
     P.n_det = ctx->n_det;
   }
-  P.lists = a->like == GW_FULL && a->marg == GW_MARG_PHASE_DIST;
   s = cube_map(ctx, a->marg, &P.cm);
   if (s == GW_OK) s = set_screen("slice_sweep", ctx, a->mlp, a->margin, a->audit_frac, P);
   if (s == GW_OK) s = set_record("slice_sweep", a->rec_x, a->rec_logl, a->rec_cap, a->rec_count, P);
   if (s != GW_OK) return s;
+  P.lists = use_lists(a->like, a->marg, P);
   const int32_t graph = a->use_graph;
   const SweepCall c{a->like, a->marg, a->prec, graph, a->n_evals, a->status, P.cache, a->eval_kinds, P.lists,
                     P.screen ? a->mlp : nullptr, a->screen_stats};
@@ -1224,13 +1584,16 @@ static gw_status slice_ws(gw_ctx* ctx, int64_t k, gw_slice_ws** out) {
   if (ws->mem) (void)hipFree(ws->mem);
   ws->mem = nullptr;
   ws->cap = 0;
-  // doubles: t_lo, t_hi, d[kMaxBlock], cand_t[2], cand[26], cand_logl[2], zrow[2][2 kMaxDet],
+  // per candidate row (at most ``rows``): cand[13], cand_logl, look_t, look_lo, look_hi; look_kind, look_ns;
+  // per chain, doubles: t_lo, t_hi, d[kMaxBlock], cand_t[2], zrow[2][2 kMaxDet],
   // zc[3][2 kMaxDet], ucand[2][11], pred[2];
   // ints: flags, n_out[2], n_shrink, n_evals, slot_ok[2], cur, tot_evals, n_caps, rkind[2], zsrc[2],
   // build_list, build_src, dirty, slow_rows[2], stream_rows[2], scr[2], side_tests[2], then the two active
   // counters and the three list counts
-  const size_t nd = (size_t)k * (1 + 1 + kMaxBlock + 2 + 26 + 2 + 4 * kMaxDet + 6 * kMaxDet + 2 * kSliceDim + 2);
-  const size_t ni = (size_t)k * (1 + 2 + 1 + 1 + 2 + 3 + 2 + 2 + 1 + 1 + 1 + 2 + 2 + 2 + 2) + 5;
+  const int64_t rows = 2 * k > kLookRows ? 2 * k : kLookRows;
+  const size_t nd = (size_t)rows * (13 + 4)
+                    + (size_t)k * (1 + 1 + kMaxBlock + 2 + 4 * kMaxDet + 6 * kMaxDet + 2 * kSliceDim + 2);
+  const size_t ni = (size_t)k * (1 + 2 + 1 + 1 + 2 + 3 + 2 + 2 + 1 + 1 + 1 + 2 + 2 + 2 + 2) + 2 * (size_t)rows + 5;
   char* m = nullptr;
   // six 64-bit counters first (evaluation kinds, prescreen counts), then the doubles and the ints
   gw_status s = check_hip(hipMalloc((void**)&m, 64 + nd * sizeof(double) + ni * sizeof(int32_t)), "slice workspace");
@@ -1242,13 +1605,18 @@ static gw_status slice_ws(gw_ctx* ctx, int64_t k, gw_slice_ws** out) {
   ws->S.t_hi = dp; dp += k;
   ws->S.d = dp; dp += k * kMaxBlock;
   ws->S.cand_t = dp; dp += 2 * k;
-  ws->cand = dp; dp += 26 * k;
-  ws->cand_logl = dp; dp += 2 * k;
+  ws->cand = dp; dp += 13 * rows;
+  ws->cand_logl = dp; dp += rows;
+  ws->S.look_t = dp; dp += rows;
+  ws->S.look_lo = dp; dp += rows;
+  ws->S.look_hi = dp; dp += rows;
   ws->S.zrow = dp; dp += 4 * kMaxDet * k;
   ws->S.zc = dp; dp += 6 * kMaxDet * k;
   ws->S.ucand = dp; dp += 2 * kSliceDim * k;
   ws->S.pred = dp; dp += 2 * k;
   int32_t* ip = (int32_t*)dp;
+  ws->S.look_kind = ip; ip += rows;
+  ws->S.look_ns = ip; ip += rows;
   ws->S.flags = ip; ip += k;
   ws->S.n_out = ip; ip += 2 * k;
   ws->S.n_shrink = ip; ip += k;

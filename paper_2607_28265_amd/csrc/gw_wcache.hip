@@ -190,9 +190,10 @@ gw_status gw_wcache_update(gw_wcache* c, const double* theta, const int32_t* slo
     hipLaunchKernelGGL(k_wc_slots, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, c->sl, c->owner, c->bcount);
     s = check_hip(hipGetLastError(), "slot check launch");
   }
-  if (s == GW_OK) s = launch_wcache_slow(ctx, ctx->coef, n, prec, nch, ctx->partial, st);
+  const int nn = cached_node_chunks(ctx, n, nch);
+  if (s == GW_OK) s = launch_all_rows(ctx, ctx->coef, n, prec, nch, nn, ctx->partial, st);
   if (s == GW_OK)
-    s = launch_epilogue_cached(ctx, ctx->partial, nch, cached_node_chunks(ctx, n, nch), ctx->coef, n, n, marg, prec,
+    s = launch_epilogue_cached(ctx, ctx->partial, nch, nn, ctx->coef, n, n, marg, prec,
                                logl, nullptr, nullptr, c->zrow, st);
   if (s == GW_OK) {
     hipLaunchKernelGGL(k_wc_store, dim3(blocks), dim3(256), 0, st, c->zrow, c->sl, c->owner, ctx->coef, n, ctx->n_det,
