@@ -22,6 +22,16 @@ struct NodeTable {
   int n = 0;
 };
 
+// Node tables of the time marginal's block moments: records of node_rs + 1
+// columns (the node's offset s in [-1, 1] in its block), idx = first node of each block
+// [n_blk + 1]; the first n_heavy blocks are split over a workgroup's waves.
+struct TmNodes {
+  NodeTable tab;
+  int32_t* idx = nullptr;
+  int n_heavy = 0, blk = 0, K = 0;
+  double phi_max = -1.0;
+};
+
 struct gw_ctx {
   int device = 0;
   gw::Geom geom{};
@@ -34,6 +44,7 @@ struct gw_ctx {
   // interpolation nodes of the full-band sums, and the row check that admits
   // a row to them (host and device copies)
   NodeTable nodes, nodes_wide;
+  TmNodes tm_nodes;
   gw::NodeCheck node_check{};
   gw::NodeCheck* node_check_dev = nullptr;
   // distance grid
@@ -178,6 +189,13 @@ gw_status build_moment_table(gw_ctx* ctx, const std::vector<double>& rec, const 
 gw_status nodes_init(gw_ctx* ctx);
 // The table for delays up to kTauCap (once per context).
 gw_status nodes_wide_init(gw_ctx* ctx);
+// The tables of a time grid's moments (rebuilt when the grid changes).
+constexpr int kTmWaveNodes = 48;  // a block of more nodes, or twice as many bins, is split over four waves
+// Up to this many blocks (8 s segments: 62) every block is split: 48 us against
+// 58 for 50 rows, 66 against 74 for 250, equal from 1000 on.
+constexpr int kTmFewBlocks = 128;
+gw_status tm_nodes_init(gw_ctx* ctx, int blk, int n_blk, int K, double phi_max);
+void tm_nodes_free(gw_ctx* ctx);
 void nodes_free(gw_ctx* ctx);
 // Measure the hardware phasor bias and set ctx->pgain_re / pgain_im.
 gw_status calibrate_phasor(gw_ctx* ctx);

@@ -26,7 +26,7 @@ struct NodePlace {
 // per context: 1.1 ms at 259,585 bins.
 __global__ void __launch_bounds__(256) k_node_weights(const NodePlace* __restrict__ place,
                                                       const double* __restrict__ bins, int nd, PhaseCoef ref,
-                                                      TrigConsts T, double* __restrict__ rec) {
+                                                      TrigConsts T, int node_stride, double* __restrict__ rec) {
   const NodePlace P = place[blockIdx.x];
   const int rs = 4 + 2 * nd, nb = P.ke - P.kb;
   double acc[2 * kMaxDet];
@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(256) k_node_weights(const NodePlace* __restric
       for (int i = 0; i < 2 * nd; ++i) red[i][threadIdx.x] += red[i][threadIdx.x + o];
     __syncthreads();
   }
-  double* __restrict__ r = rec + (int64_t)blockIdx.x * node_rs(nd);
+  double* __restrict__ r = rec + (int64_t)blockIdx.x * node_stride;
   if ((int)threadIdx.x < 2 * nd) r[6 + threadIdx.x] = red[threadIdx.x][0];
   if (threadIdx.x == 0) r[5] = phase_cycles(ref, r[0], r[1], r[2], r[3]);
 }
@@ -134,6 +134,25 @@ static double envelope(const std::vector<PhaseCoef>& w, double f) {
   return 1.02 * s + 1e-3;
 }
 
+// S(f) by bin: the envelope on a grid fine enough for the larger of two
+// neighbours to bound what lies between (power laws; 64 points an octave).
+struct SlopeBound {
+  std::vector<double> e;
+  double k0;
+  SlopeBound(const Geom& g, const std::vector<PhaseCoef>& w) : k0((double)g.k0) {
+    const double f0 = k0 * g.df, top = (k0 + (double)(g.n_freq - 1)) / k0;
+    const int n = 2 + (int)(64.0 * log2(top > 1.0 ? top : 1.0));
+    e.resize(n + 1);
+    for (int j = 0; j <= n; ++j) e[j] = envelope(w, f0 * exp2(j / 64.0));
+  }
+  double at(int k) const {
+    const int j = std::min((int)(64.0 * log2((k0 + k) / k0)), (int)e.size() - 2);
+    return fmax(e[j], e[j + 1]);
+  }
+  // bins [k, l]: the envelope falls, then rises, so its ends bound a range
+  double over(int k, int l) const { return fmax(at(k), at(l)); }
+};
+
 // Partition of the band: from the lowest bin up, the block length (growing by
 // a quarter at a time, at most a sixth of its frequency, at most kNodeMax
 // nodes) with the fewest nodes per bin.
@@ -141,23 +160,14 @@ static void partition(const gw_ctx* ctx, const std::vector<PhaseCoef>& w, double
   const Geom& g = ctx->geom;
   const int nf = (int)g.n_freq;
   const NodeCount node_count;
-  // the envelope on a grid fine enough to interpolate (power laws): 1/64 octave
-  const double f0 = (double)g.k0 * g.df, f1 = (double)(g.k0 + nf - 1) * g.df;
-  const int ng = 2 + (int)(64.0 * log2(f1 / f0 > 1.0 ? f1 / f0 : 1.0));
-  std::vector<double> e(ng + 1);
-  for (int j = 0; j <= ng; ++j) e[j] = envelope(w, f0 * exp2(j / 64.0)) + tau;
-  auto slope = [&](int k) {
-    const double t = 64.0 * log2((double)(g.k0 + k) / (double)g.k0);
-    const int j = std::min((int)t, ng - 1);
-    return fmax(e[j], e[j + 1]);
-  };
+  const SlopeBound slope(g, w);
   for (int k = 0; k < nf;) {
     double best = 0.9;
     int bl = std::min(8, nf - k), bn = bl;  // a node per bin
     for (int L = 8; L <= nf - k; L = std::min(L + L / 4 + 1, L < nf - k ? nf - k : L + 1)) {
       const double f = (double)(g.k0 + k) * g.df, h = 0.5 * (L - 1) * g.df;
       if (L > 8 && 6.0 * L * g.df > f) break;
-      const int n = node_count(kTwoPi * h * fmax(slope(k), slope(k + L - 1)));
+      const int n = node_count(kTwoPi * h * (slope.over(k, k + L - 1) + tau));
       if (n > kNodeMax) break;
       if ((double)n < best * L) {
         best = (double)n / L;
@@ -170,41 +180,59 @@ static void partition(const gw_ctx* ctx, const std::vector<PhaseCoef>& w, double
   }
 }
 
-static gw_status node_table(gw_ctx* ctx, const PhaseCoef& ref, const std::vector<NodePlace>& place, NodeTable* out) {
+// A node's offset from its block's first bin, in bins.
+static double node_offset(const NodePlace& P) {
+  if (P.n == P.ke - P.kb) return (double)P.j;
+  return 0.5 * (double)(P.ke - 1 - P.kb) * (1.0 + cos((double)(2 * P.j + 1) * kPi / (double)(2 * P.n)));
+}
+
+// Records of the places, with ``extra`` further columns filled by the caller's
+// ``fill(node, columns)``.
+template <class Fill>
+static gw_status node_table(gw_ctx* ctx, const PhaseCoef& ref, const std::vector<NodePlace>& place, int extra,
+                            Fill fill, NodeTable* out) {
   const Geom& g = ctx->geom;
-  const int nd = ctx->n_det, rs = node_rs(nd);
+  const int nd = ctx->n_det, rs = node_rs(nd) + extra;
   const size_t n = place.size();
-  std::vector<double> rec(n * rs, 0.0);
+  std::vector<double> rec(std::max<size_t>(n, 1) * rs, 0.0);
   for (size_t q = 0; q < n; ++q) {
-    const NodePlace& P = place[q];
-    double f;
-    if (P.n == P.ke - P.kb)
-      f = (double)(g.k0 + P.kb + P.j) * g.df;
-    else
-      f = 0.5 * ((double)(2 * g.k0 + P.kb + P.ke - 1)
-                 + (double)(P.ke - 1 - P.kb) * cos((double)(2 * P.j + 1) * kPi / (double)(2 * P.n))) * g.df;
+    const double f = ((double)(g.k0 + place[q].kb) + node_offset(place[q])) * g.df;
     double* r = &rec[q * rs];
     r[0] = cbrt(f);
     r[1] = r[0] * r[0];
     r[2] = pow(f, -5.0 / 3.0);
     r[3] = log(f);
     r[4] = f;
+    fill(q, r + node_rs(nd));
   }
-  NodePlace* d = nullptr;
-  gw_status s = check_hip(hipMalloc((void**)&d, n * sizeof(NodePlace)), "node places");
-  if (s == GW_OK) s = check_hip(hipMalloc((void**)&out->rec, rec.size() * sizeof(double)), "node records");
-  if (s == GW_OK) s = check_hip(hipMemcpy(d, place.data(), n * sizeof(NodePlace), hipMemcpyHostToDevice), "places");
+  gw_status s = check_hip(hipMalloc((void**)&out->rec, rec.size() * sizeof(double)), "node records");
   if (s == GW_OK)
     s = check_hip(hipMemcpy(out->rec, rec.data(), rec.size() * sizeof(double), hipMemcpyHostToDevice), "records");
+  if (s != GW_OK || n == 0) return s;
+  NodePlace* d = nullptr;
+  s = check_hip(hipMalloc((void**)&d, n * sizeof(NodePlace)), "node places");
+  if (s == GW_OK) s = check_hip(hipMemcpy(d, place.data(), n * sizeof(NodePlace), hipMemcpyHostToDevice), "places");
   if (s == GW_OK) {
     hipLaunchKernelGGL(k_node_weights, dim3((unsigned)n), dim3(256), 0, nullptr, (const NodePlace*)d,
-                       (const double*)ctx->bins, nd, ref, make_trig_consts(), out->rec);
+                       (const double*)ctx->bins, nd, ref, make_trig_consts(), rs, out->rec);
     s = check_hip(hipGetLastError(), "node weights launch");
   }
   if (s == GW_OK) s = check_hip(hipStreamSynchronize(nullptr), "node weights");
   if (d) (void)hipFree(d);
   if (s == GW_OK) out->n = (int)n;
   return s;
+}
+
+static gw_status node_table(gw_ctx* ctx, const PhaseCoef& ref, const std::vector<NodePlace>& place, NodeTable* out) {
+  return node_table(ctx, ref, place, 0, [](size_t, double*) {}, out);
+}
+
+// Largest light travel time from the geocentre to a detector.
+static double travel_time(const Geom& g) {
+  double rmax = 0.0;
+  for (int i = 0; i < g.n_det; ++i)
+    rmax = fmax(rmax, sqrt(g.pos[i][0] * g.pos[i][0] + g.pos[i][1] * g.pos[i][1] + g.pos[i][2] * g.pos[i][2]));
+  return rmax / kLightSpeed;
 }
 
 gw_status nodes_init(gw_ctx* ctx) {
@@ -221,10 +249,7 @@ gw_status nodes_init(gw_ctx* ctx) {
   }
   // the sampler's |t_c| <= 0.1 s prior at the geocentre or at any detector,
   // plus the light travel times; at most a quarter second
-  double rmax = 0.0;
-  for (int i = 0; i < g.n_det; ++i)
-    rmax = fmax(rmax, sqrt(g.pos[i][0] * g.pos[i][0] + g.pos[i][1] * g.pos[i][1] + g.pos[i][2] * g.pos[i][2]));
-  c.tau_max = fmin(0.1 + 2.0 * rmax / kLightSpeed, kTauCap);
+  c.tau_max = fmin(0.1 + 2.0 * travel_time(g), kTauCap);
   std::vector<NodePlace> place;
   partition(ctx, w, c.tau_max, &place);
   s = check_hip(hipMalloc((void**)&ctx->node_check_dev, sizeof(NodeCheck)), "node check");
@@ -243,7 +268,64 @@ gw_status nodes_wide_init(gw_ctx* ctx) {
   return node_table(ctx, w[0], place, &ctx->nodes_wide);
 }
 
+// Tables of the time marginal's moments.  Within a block the samples of
+// exp(-i phi s) G_i, |phi| <= phi_max (the shifts the moments are expanded
+// for), are what the sums over the grid see, so n nodes serve all K moments.
+// A node costs about twice what a bin of the walk does; a block on which that
+// saves nothing keeps its bins (no nodes).
+gw_status tm_nodes_init(gw_ctx* ctx, int blk, int n_blk, int K, double phi_max) {
+  TmNodes& t = ctx->tm_nodes;
+  if (t.tab.rec && t.blk == blk && t.K == K && t.phi_max == phi_max) return GW_OK;
+  tm_nodes_free(ctx);
+  const Geom& g = ctx->geom;
+  const int nf = (int)g.n_freq;
+  std::vector<PhaseCoef> w;
+  gw_status s = node_waveforms(ctx, &w);
+  if (s != GW_OK) return s;
+  const SlopeBound slope(g, w);
+  const NodeCount node_count;
+  const double tau = travel_time(g);
+  std::vector<NodePlace> place;
+  std::vector<int32_t> idx(n_blk + 1, 0);  // first node of each block
+  for (int b = 0; b < n_blk; ++b) {
+    const int kb = b * blk, ke = std::min(kb + blk, nf);
+    const int n = node_count(kPi * (ke - 1 - kb) * g.df * (slope.over(kb, ke - 1) + tau) + phi_max);
+    if (n <= kNodeMax && 2 * n < ke - kb)
+      for (int j = 0; j < n; ++j) place.push_back(NodePlace{kb, ke, n, j});
+    idx[b + 1] = (int32_t)place.size();
+  }
+  // blocks of many samples are split over a workgroup's waves (the lowest ones:
+  // the slopes fall with frequency), all of them where there are few
+  for (int b = 0; b < n_blk; ++b) {
+    const int bins = std::min((b + 1) * blk, nf) - b * blk, nodes = idx[b + 1] - idx[b];
+    if (nodes > kTmWaveNodes || (nodes == 0 && bins > 2 * kTmWaveNodes)) t.n_heavy = b + 1;
+    if (n_blk <= kTmFewBlocks) t.n_heavy = n_blk;
+  }
+  const double cen = 0.5 * (blk - 1), hinv = 2.0 / blk;
+  s = node_table(ctx, w[0], place, 1, [&](size_t q, double* v) {
+    *v = (node_offset(place[q]) - cen) * hinv;
+  }, &t.tab);
+  if (s == GW_OK) s = check_hip(hipMalloc((void**)&t.idx, idx.size() * sizeof(int32_t)), "time-moment units");
+  if (s == GW_OK)
+    s = check_hip(hipMemcpy(t.idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice), "units");
+  if (s != GW_OK) {
+    tm_nodes_free(ctx);
+    return s;
+  }
+  t.blk = blk;
+  t.K = K;
+  t.phi_max = phi_max;
+  return GW_OK;
+}
+
+void tm_nodes_free(gw_ctx* ctx) {
+  if (ctx->tm_nodes.tab.rec) (void)hipFree(ctx->tm_nodes.tab.rec);
+  if (ctx->tm_nodes.idx) (void)hipFree(ctx->tm_nodes.idx);
+  ctx->tm_nodes = TmNodes{};
+}
+
 void nodes_free(gw_ctx* ctx) {
+  tm_nodes_free(ctx);
   if (ctx->nodes_wide.rec) (void)hipFree(ctx->nodes_wide.rec);
   ctx->nodes_wide = NodeTable{};
   if (ctx->nodes.rec) (void)hipFree(ctx->nodes.rec);

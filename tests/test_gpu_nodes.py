@@ -116,3 +116,33 @@ def test_cache_mixes_node_and_moment_rows(gw, n_slots, n):
     # FP32 moments carry 6e-8 of the overlap, which is at most sqrt(<d|d> <h|h>)
     # and enters the distance marginal with slope below sqrt(<d|d>)-sized SNR^2
     assert np.max(np.abs(got - want)[~beyond]) < 6e-8 * L.data_inner(prob)
+
+
+@pytest.mark.parametrize("n_det,grid,n,window,over", [
+    (3, (64.0, 20.0, 2048.0), 65, 0.0, 0), (2, (32.0, 10.0, 1024.0), 64, 0.05, 1), (4, (16.0, 20.0, 1024.0), 63, 0.0, 2),
+    (1, (8.0, 20.0, 512.0), 130, 0.12, 4), (3, (4.0, 30.0, 256.0), 1, 0.0, 0), (3, (128.0, 20.0, 512.0), 513, 0.0, 0)])
+def test_time_moments_over_nodes(gw, n_det, grid, n, window, over):
+    """Time marginal: nodes against bins, rows in and beyond the tables mixed
+    (one launch holds both).  A grid value carries the interpolation error of
+    the block moments' nodes, which log L follows with slope at most 1."""
+    prob = gwsynth.make_problem(*grid, psd_scale=1e-47, n_det=n_det)
+    prob = with_injection(prob, gwsynth.prior_draws(gwsynth.SEEDS["injection"], 1)[0])
+    th = _rows(prob, n)
+    t = torch.from_numpy(th).cuda()
+    with gw.Context(prob) as ctx:
+        if window:
+            gw.gw_set_time_window(ctx.handle, window)
+        if over:
+            gw.gw_set_time_oversample(ctx.handle, over)
+        got = {}
+        for prec in (0, 1):
+            for kind in (0, 1):
+                ctx.set_full_kernel(kind)
+                got[prec, kind] = ctx.loglike(t, marg=L.PHASE_TIME, prec=prec).cpu().numpy()
+        ref = got[0, 1]
+        ok = np.isfinite(ref)
+        assert all(np.array_equal(np.isfinite(v), ok) for v in got.values())
+        tol = _tol(prob, th, ref)
+        assert np.max(np.abs(got[0, 0] - ref)[ok]) < 2 * tol
+        assert np.max(np.abs(got[1, 0] - ref)[ok]) < 1e-3
+        assert np.max(np.abs(got[1, 1] - ref)[ok]) < 1e-3
