@@ -153,26 +153,25 @@ gw_status loglike_batch(gw_ctx* ctx, const double* theta, int64_t n, int32_t lik
  * integral by tens of nats for loud signals):
  *   log L = -<d|d>/2 - <h|h>/2 + ln[ (1/N_t) sum_j I0(|Z(t_j)|) ],
  * Z(t) the overlap of the template shifted by t (template at t_c = 0).  The
- * library cuts the band into blocks of N / P bins (P the smallest power of two
- * >= 2 J + 1, and at least 16 / R), within which the time shift is expanded in
- * Chebyshev polynomials of the bin's offset (Jacobi-Anger: K = 12 terms when
- * the dropped ones stay below 2e-11 of the block's sum of |overlap weight|,
- * every grid of the default window, else 16), and evaluates every grid point
- * with one FFT of length P R per term over the blocks.  W defaults to 0.1 s;
+ * library spreads the overlap's samples onto a frequency grid of cells of
+ * N / (2 P) bins (P the smallest power of two >= 2 J + 1, and at least 16 / R)
+ * with a Kaiser-Bessel window of 14 points, and evaluates every grid point with
+ * one transform of 2 P R points; the window's images stay below 6e-13 of the
+ * sum of |overlap weight| (5e-14 at the default window).  W defaults to 0.1 s;
  * gw_set_time_window changes it (GW_ENOTSUP if P would exceed 2048); a grid
- * whose transform P R would exceed 4096 points is GW_ENOTSUP at evaluation.
+ * whose P R would exceed 4096 is GW_ENOTSUP at evaluation.
  * gw_time_grid_info reports the grid step delta / R, the number of points
- * N_t = 2 J R + 1, P and the block length.  Work space: n x (n_freq / B) x
- * 16 K bytes per call (in row chunks of at most 1 GiB).
+ * N_t = 2 J R + 1, P and N / P.  Work space: about n x (n_freq P / N) x 240
+ * bytes per call (in row chunks of at most 1 GiB).
  * With like = GW_HET the same grid sum runs on the binned likelihood, the
  * appendix's direct summation on the heterodyned bins: at every t_j the
  * phase-marginal binned log L of the template shifted by t_j (the binned
  * <h|h> depends on t_j through the bin widths).  The library forms per-row
- * edge weights, takes their block moments (the edges lie on the fine grid) into
- * the same FFTs as the full band, and expands the bin-width phasors
+ * edge weights, spreads them (the edges lie on the fine grid) onto the same
+ * frequency grid as the full band, and expands the bin-width phasors
  * exp(-2 pi i (f_e - f_e-1) t_j) about the widths' centre (as many terms as
  * keep the first dropped one below 1e-13 of the norm sum; GW_ENOTSUP beyond
- * 48).  Work space up to 1 GiB of moments per chunk of rows (about 8,000 rows
+ * 48).  Work space up to 1 GiB of grid sums per chunk of rows (about 8,000 rows
  * at 128 s).
  */
 gw_status gw_set_time_window(gw_ctx* ctx, double window);

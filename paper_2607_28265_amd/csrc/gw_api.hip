@@ -241,7 +241,7 @@ gw_status gw_ctx_destroy(gw_ctx* ctx) {
   for (hipEvent_t e : ctx->prof_ev)
     if (e) (void)hipEventDestroy(e);
   double* bufs[] = {ctx->bins,   ctx->dist_tab, ctx->coef,   ctx->partial, ctx->zbuf,
-                    ctx->tm_ccoef, ctx->tm_basis, ctx->tm_mom, ctx->recon, ctx->wc_basis};
+                    ctx->tm_dec, ctx->tm_mom, ctx->recon, ctx->wc_basis};
   for (double* b : bufs)
     if (b) (void)hipFree(b);
   if (ctx->wtab) (void)hipFree(ctx->wtab);

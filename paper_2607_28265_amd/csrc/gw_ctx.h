@@ -22,14 +22,29 @@ struct NodeTable {
   int n = 0;
 };
 
-// Node tables of the time marginal's block moments: records of node_rs + 1
-// columns (the node's offset s in [-1, 1] in its block), idx = first node of each block
-// [n_blk + 1]; the first n_heavy blocks are split over a workgroup's waves.
-struct TmNodes {
+// Which of a row's points a grid point is the sum of, in order (tgrid_cover in
+// gw_tgrid.h; device memory).
+struct TgCover {
+  const int4* pts = nullptr;
+  const int32_t* shift = nullptr;
+  int n_many = 0;
+};
+
+// Time marginal of the full band: interpolation nodes of the window's delays
+// in order of frequency, records of node_rs + kTgW columns (the grid weights),
+// each node's grid cell, and the chunks of nodes (first node, end, first grid
+// point, place of their points); the first n_dense chunks are one cell each,
+// split over a workgroup's waves.  bins_w [cell][kTgW]: grid weights of the
+// bins of a cell.  cov: chunks of nodes, of blocks.
+struct TmGrid {
   NodeTable tab;
+  double* bins_w = nullptr;
   int32_t* idx = nullptr;
-  int n_heavy = 0, blk = 0, K = 0;
-  double phi_max = -1.0;
+  const int32_t* cell = nullptr;
+  const int4* chunk = nullptr;
+  TgCover cov[2];
+  int n_chunk = 0, n_dense = 0, n_pts = 0;  // n_pts: points of a row, the larger of the two covers
+  int blk = 0, L = 0, jmax = -1;
 };
 
 struct gw_ctx {
@@ -44,7 +59,7 @@ struct gw_ctx {
   // interpolation nodes of the full-band sums, and the row check that admits
   // a row to them (host and device copies)
   NodeTable nodes, nodes_wide;
-  TmNodes tm_nodes;
+  TmGrid tm_grid;
   gw::NodeCheck node_check{};
   gw::NodeCheck* node_check_dev = nullptr;
   // distance grid
@@ -81,15 +96,13 @@ struct gw_ctx {
   int prof = 0;                     // 0 off, 1 the dominant kernel, 2 the time-grid kernel
   std::vector<hipEvent_t> prof_ev;  // pairs (start, stop)
   int prof_used = 0;
-  // time marginal: window half-width (s), FFT twiddles and moment workspace
+  // time marginal: window half-width (s), tables and workspace
   double tm_window = 0.1;
   int tm_R = 4;                    // grid points per sampling interval of the segment
   int tm_nsk = 0;                  // edge chunks of the heterodyned time marginal's moments (0 = heuristic)
   double* wc_basis = nullptr;      // [wmom_block][12] Chebyshev values for the waveform cache
-  double* tm_ccoef = nullptr;      // [K][256][16] expansion coefficients of the grid (tm_cc_L, tm_cc_jmax, tm_cc_K)
-  int tm_cc_L = 0, tm_cc_jmax = 0, tm_cc_K = 0;
-  double* tm_basis = nullptr;      // [blk][K] Chebyshev values of the in-block offset for the moments
-  int tm_basis_blk = 0, tm_basis_K = 0;
+  double* tm_dec = nullptr;        // [jmax + 1] 1 / psi_hat of the time grid (tm_dec_L, tm_dec_jmax)
+  int tm_dec_L = 0, tm_dec_jmax = 0;
   double* tm_mom = nullptr;
   int64_t tm_mom_cap = 0;
   // bumped by every setter that changes what a captured likelihood launch
@@ -189,27 +202,25 @@ gw_status build_moment_table(gw_ctx* ctx, const std::vector<double>& rec, const 
 gw_status nodes_init(gw_ctx* ctx);
 // The table for delays up to kTauCap (once per context).
 gw_status nodes_wide_init(gw_ctx* ctx);
-// The tables of a time grid's moments (rebuilt when the grid changes).
-constexpr int kTmWaveNodes = 48;  // a block of more nodes, or twice as many bins, is split over four waves
-// Up to this many blocks (8 s segments: 62) every block is split: 48 us against
-// 58 for 50 rows, 66 against 74 for 250, equal from 1000 on.
-constexpr int kTmFewBlocks = 128;
-gw_status tm_nodes_init(gw_ctx* ctx, int blk, int n_blk, int K, double phi_max);
-void tm_nodes_free(gw_ctx* ctx);
+// The tables of the full band's time marginal (rebuilt when the grid changes).
+struct TimeGridShape;
+gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g);
+void tm_grid_free(gw_ctx* ctx);
 void nodes_free(gw_ctx* ctx);
 // Measure the hardware phasor bias and set ctx->pgain_re / pgain_im.
 gw_status calibrate_phasor(gw_ctx* ctx);
 
-// Time-grid sums from block moments (gw_tgrid.hip), shared by the full-band
-// and heterodyned time marginals: moments [n][K][n_blk] complex (K expansion
-// orders, 12 or 16), one FFT of length L = P R per order, the grid
-// t_j = j delta / R, |j| <= jmax.
+// Time-grid sums from samples spread onto a frequency grid (gw_tgrid.hip),
+// shared by the full-band and heterodyned time marginals: t_j = j delta / R,
+// |j| <= jmax.
 constexpr int kTgHMax = 48;  // most norm moments of the heterodyned form
 struct TGridArgs {
-  const double* mom;   // complex moment (row p, order m, block b) at p rs + (m n_blk + b) es
-  int64_t mom_rs, mom_es;  // (K n_blk, 1): row-major, one row's moments contiguous; (1, n): row fastest
+  const double* part;  // complex [n][pitch]: the rows' chunks of grid sums
+  int64_t pitch;
+  TgCover cov[2];      // of the rows whose C_NODE is at least node_from, of the others
+  double node_from;
   int64_t n;
-  int n_blk, L, jmax, K;
+  int n_g, L, jmax;
   const double* coef;  // prologue coefficients of the n rows (stride ld)
   int64_t ld;
   double* logl;
@@ -221,26 +232,22 @@ struct TGridArgs {
   int64_t c2, cden;    // exp(-2 pi i c u_j) = exp(-2 pi i (c2 j mod cden) / cden)
   double* zout;        // or NULL: [n][2 jmax + 1][3] staged grid values
   double f0_num, f0_den;  // f_0 t_j = j f0_num / f0_den cycles
-  double* zpart;       // [tgrid_split(n, K)][n][2 jmax + 1] complex when the split exceeds 1
 };
 // The context's time grid: segment length N (samples), J and R (|j| <= jmax =
-// J R), P, blocks of blk = N / P fine bins (n_blk of them), L = P R.
+// J R), P, blocks of blk = N / P fine bins (n_blk of them), L = P R; cells of
+// half a block, n_g grid points, the first f0 bins from the band's lowest bin.
 struct TimeGridShape {
   int64_t N;
   double delta;  // the segment's sampling interval; the grid step is delta / R
-  int J, R, P, blk, n_blk, L, jmax;
+  int J, R, P, blk, n_blk, L, jmax, n_g;
+  double cell, beta;  // bins per cell, shape of the window
+  double f0_num, f0_den;  // f_0 t_j = j f0_num / f0_den cycles
 };
 gw_status time_grid_shape(const gw_ctx* ctx, TimeGridShape* g);
-// The context's coefficient table for a grid (rebuilt when L, jmax or K
-// change), and the rows per chunk whose moments fit the bounded workspace.
-gw_status tgrid_tables(gw_ctx* ctx, int L, int jmax, int K);
-int64_t tgrid_chunk_rows(int64_t n, int n_blk, int K);
-// Order groups per row of a launch of n rows (1, 2 or 4); above 1 the launch
-// needs zpart.
-int tgrid_split(int64_t n, int K);
-// Complex elements of zpart needed by the launches of n rows in chunks of
-// chunk rows on a grid of nt points.
-int64_t tgrid_zpart_elems(int64_t n, int64_t chunk, int K, int nt);
+// The context's table for a grid (rebuilt when L or jmax change), and the rows
+// per chunk of pitch points each that fit the bounded workspace.
+gw_status tgrid_tables(gw_ctx* ctx, int L, int jmax);
+int64_t tgrid_chunk_rows(int64_t n, int64_t pitch);
 gw_status launch_tgrid(const gw_ctx* ctx, const TGridArgs& a, hipStream_t st);
 
 // Record the device address of ``device``'s copy of the allocation-free
@@ -278,7 +285,7 @@ void het_unpin_args(gw_ctx* ctx);
 void het_shape_key(const gw_ctx* ctx, int32_t* wpb, int32_t* grid, int32_t* ech);
 // The heterodyned time marginal's table and index addresses and plan sizes
 // (zeros without heterodyne state), for keying captured graphs.
-void het_tm_key(const gw_ctx* ctx, const void** tab, const void** idx, int32_t* nch, int32_t* nslot, int32_t* nsplit);
+void het_tm_key(const gw_ctx* ctx, const void** tab, const void** idx, int32_t* nch);
 
 // Heterodyne and graph state owned by the context.
 void het_free(gw_ctx* ctx);

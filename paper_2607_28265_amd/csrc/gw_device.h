@@ -13,6 +13,7 @@ namespace gw {
 constexpr double kPi = 3.141592653589793238462643383279502884;
 constexpr double kTwoPi = 6.283185307179586476925286766559005768;
 constexpr double kInvTwoPi = 0.159154943091895335768883763372514362;
+constexpr double kInvSqrtTwoPi = 0.3989422804014327;
 constexpr double kLog2E = 1.44269504088896340735992468100189214;
 constexpr double kMsunSec = 4.925490947641267e-6;     // G Msun / c^3 (s)
 constexpr double kLightSpeed = 299792458.0;            // m / s

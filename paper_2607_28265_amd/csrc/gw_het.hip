@@ -72,18 +72,19 @@ struct gw_het_state {
   const double* pin_logl = nullptr;
   int64_t pin_rows = 0;
   // time marginal: row-independent tables for the current grid (built on
-  // first use): per block b < n_blk the edges [bs[b], bs[b + 1]) in it, per
-  // edge the Chebyshev values T_m(s_e) of its offset in the block (m < tm_K)
-  // and the powers sigma_e^m of its bin width about the widths' centre
-  // (m < tm_mh), and the moment kernel's chunks (gw_hetplan.h)
-  double* tm_tab = nullptr;      // [n_edges][tm_K + tm_mh]
-  // bs [n_blk + 1], then the plan: e0 [nch + 1], blo, bhi, sfirst, slast
-  // [nch] each, then per cut block fb, fs, fc [tm_nsplit] each
+  // first use): per edge the kTgW grid weights and the powers sigma_e^m of its
+  // bin width about the widths' centre (m < tm_mh), and the moment kernel's
+  // chunks (gw_hetplan.h)
+  double* tm_tab = nullptr;      // [n_edges][kTgW + tm_mh]
+  // the cover's points (gw_tgrid.h), the cell of each edge [n_edges] (tm_cell),
+  // the chunks' first edge [nch + 1], first cell, end cell and first point
+  // [nch] each, the cover's shifts
   int32_t* tm_idx = nullptr;
-  int tm_blk = 0, tm_nblk = 0, tm_mh = 0, tm_nch = 0, tm_nch_req = -1, tm_K = 0;
-  int tm_nslot = 0, tm_nsplit = 0;  // piece slots and cut blocks of the plan
+  const int32_t* tm_cell = nullptr;
+  TgCover tm_cov;
+  int tm_blk = 0, tm_nblk = 0, tm_mh = 0, tm_nch = 0, tm_nch_req = -1, tm_L = 0, tm_jmax = -1;
+  int tm_npts = 0;               // grid points of a row's chunks
   double tm_hw = 0.0;            // half-range of the bin widths (fine bins)
-  double tm_umax = -1.0;         // the window's largest |u| the norm series was sized for
   int64_t tm_c2 = 0;             // smallest + largest bin width (fine bins)
 };
 
@@ -917,13 +918,11 @@ void het_shape_key(const gw_ctx* ctx, int32_t* wpb, int32_t* grid, int32_t* ech)
   *ech = ctx->het ? ctx->het->ech : 0;
 }
 
-void het_tm_key(const gw_ctx* ctx, const void** tab, const void** idx, int32_t* nch, int32_t* nslot, int32_t* nsplit) {
+void het_tm_key(const gw_ctx* ctx, const void** tab, const void** idx, int32_t* nch) {
   const gw_het_state* h = ctx->het;
   *tab = h ? h->tm_tab : nullptr;
   *idx = h ? h->tm_idx : nullptr;
   *nch = h ? h->tm_nch : 0;
-  *nslot = h ? h->tm_nslot : 0;
-  *nsplit = h ? h->tm_nsplit : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -935,7 +934,7 @@ void het_tm_key(const gw_ctx* ctx, const void** tab, const void** idx, int32_t* 
 // q_i = (A P_i) / (A0 P0_i), the binned overlap and norm at t_j are
 //   Z(t_j)  = sum_e W_e exp(-2 pi i f_e t_j),
 //   hh(t_j) = sum_i |q_i|^2 hh0_i + Re sum_e V_e exp(-2 pi i (f_e - f_e-1) t_j).
-// The edges lie on the fine grid, so Z goes through the block moments of the
+// The edges lie on the fine grid, so Z goes through the frequency grid of the
 // full band's time marginal with W_e in place of the per-bin weights
 // (gw_tgrid.hip); the widths f_e - f_e-1 = dk_e df span a short range, and
 // exp(-2 pi i dk_e u) about the widths' centre c, dk_e = c + hw sigma_e, is a
@@ -943,22 +942,24 @@ void het_tm_key(const gw_ctx* ctx, const void** tab, const void** idx, int32_t* 
 // grid kernel sums (tm_mh terms, the first dropped one below 1e-13 of
 // sum_e |V_e| at the window's edge).
 
-// Edge-weight moments of one (64-row tile, chunk): lane = row, the chunk's
+// Sums over the edges of one (64-row tile, chunk): lane = row, the chunk's
 // edges e0[c] .. e0[c + 1] in order (edge records and tables wave-uniform).
-// what = 0: the K block moments of W for the blocks the chunk emits, into mom
-// [K][n_blk][rows] (rows fastest, so the stores of a wave are contiguous), or
-// for a block the plan cuts, the chunk's piece into part [slot][K][rows];
-// what = 1: S_m, m0 <= m < m0 + K (m < mh), over the
-// chunk's edges into hpart [chunk][rows][mh]; chunk 0 also writes the
-// constant norm part hhc [rows].
-template <int ND, int PREC, int K, int WHAT>
+// GRID: W spread onto the grid, the window of kTgW points sliding over the
+// chunk's cells (a point that no later edge reaches is stored), into part
+// [rows][pitch]; chunk 0 also writes the constant norm part hhc [rows].  Both
+// forms: S_m, m0 <= m < m0 + MH (m < mh), over the chunk's edges into hpart
+// [chunk][rows][mh].  The GRID form takes the first moments along, which
+// spares their phases and phasors (mixed, 5000 bins: 32 us for both at 128 rows,
+// 36 + 21 in two passes).
+template <int ND, int PREC, bool GRID, int MH>
 __global__ void __launch_bounds__(64) k_het_tmom(const double* __restrict__ coef, int64_t ld, int64_t n,
                                                  const double* __restrict__ rec, int n_bins,
                                                  const double* __restrict__ tab, int mh,
-                                                 const int32_t* __restrict__ bs, const int32_t* __restrict__ plan,
-                                                 int nch, int n_blk, int m0, HetConst hc, TrigConsts T,
-                                                 double2* __restrict__ mom, double2* __restrict__ part,
-                                                 double2* __restrict__ hpart, double* __restrict__ hhc) {
+                                                 const int32_t* __restrict__ cell, const int32_t* __restrict__ plan,
+                                                 int nch, int m0, HetConst hc, TrigConsts T, int64_t pitch,
+                                                 double2* __restrict__ part, double2* __restrict__ hpart,
+                                                 double* __restrict__ hhc) {
+  constexpr int K = kTgW;
   constexpr int RS = het_rs(ND);
   constexpr int BO = het_bin_off(ND);
   const int64_t p = (int64_t)blockIdx.x * 64 + threadIdx.x;
@@ -981,11 +982,11 @@ __global__ void __launch_bounds__(64) k_het_tmom(const double* __restrict__ coef
     hconst = fma(q2[i], hc.hh0[i], hconst);
     pr[i] = pim[i] = 0.0;
   }
-  if (WHAT == 0 && ch == 0 && p < n) hhc[p] = hconst;
+  if (GRID && ch == 0 && p < n) hhc[p] = hconst;
   const int32_t* __restrict__ e0 = plan;
   const int e_lo = e0[ch], e_hi = e0[ch + 1];
   const int tw_ = K + mh;  // table row length
-  if (WHAT == 1 && e_lo > 0) {  // the norm term needs the previous edge's phasors
+  if (e_lo > 0) {  // the norm term needs the previous edge's phasors
     const double* r = rec + (int64_t)(e_lo - 1) * RS;
     const double d0 = phase_cycles(c, r[H_X], r[H_X2], r[H_XM5], r[H_LNF]) - r[H_PHI0];
 #pragma unroll
@@ -994,148 +995,126 @@ __global__ void __launch_bounds__(64) k_het_tmom(const double* __restrict__ coef
       het_phasor<PREC>(di, T, &pr[i], &pim[i]);
     }
   }
-  double ar_[K], ai_[K];
+  double ar_[K], ai_[K], hr[MH], hi[MH];
 #pragma unroll
   for (int m = 0; m < K; ++m) ar_[m] = ai_[m] = 0.0;
-  // one edge: its weight (W_e for WHAT = 0, V_e for WHAT = 1) into the moments
+#pragma unroll
+  for (int m = 0; m < MH; ++m) hr[m] = hi[m] = 0.0;
+  double2* out = part + p * pitch;
+  int cur = 0;  // the window's first grid point
+  auto slide = [&](int to) {
+    for (; cur < to; ++cur, ++out) {
+      if (p < n) *out = make_double2(ar_[0], ai_[0]);
+#pragma unroll
+      for (int m = 0; m + 1 < K; ++m) {
+        ar_[m] = ar_[m + 1];
+        ai_[m] = ai_[m + 1];
+      }
+      ar_[K - 1] = ai_[K - 1] = 0.0;
+    }
+  };
+  // one edge: W_e onto the grid, V_e into the moments
   auto edge = [&](int e) {
     const double* r = rec + (int64_t)e * RS;
     const double d0 = phase_cycles(c, r[H_X], r[H_X2], r[H_XM5], r[H_LNF]) - r[H_PHI0];
     const double f = r[H_F];
-    double wr = 0.0, wi = 0.0;
+    double wr = 0.0, wi = 0.0, vr = 0.0, vi = 0.0;
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       const double di = i == 0 ? d0 : fma(f, dt[i], d0) - r[H_PHI0 + i];
       double gr, gi;
       het_phasor<PREC>(di, T, &gr, &gi);
       const double* w = r + BO + 1 + 6 * i;
-      if constexpr (WHAT == 0) {
+      if constexpr (GRID) {
         // summed-by-parts weights; the first and last edges take one side
         const double kr = e == 0 ? w[0] - w[2] : (e == n_bins ? w[2] : w[0]);
         const double ki = e == 0 ? w[1] - w[3] : (e == n_bins ? w[3] : w[1]);
         const double kgr = kr * gr - ki * gi, kgi = kr * gi + ki * gr;  // q K g
         wr = fma(qr[i], kgr, fma(-qi[i], kgi, wr));
         wi = fma(qr[i], kgi, fma(qi[i], kgr, wi));
-      } else {
-        const double sq = e > 0 ? q2[i] * w[4] : 0.0;  // |q|^2 (B0 / 2) g_e conj(g_e-1)
-        wr = fma(sq, fma(gr, pr[i], gi * pim[i]), wr);
-        wi = fma(sq, fma(gi, pr[i], -gr * pim[i]), wi);
-        pr[i] = gr;
-        pim[i] = gi;
+      }
+      const double sq = e > 0 ? q2[i] * w[4] : 0.0;  // |q|^2 (B0 / 2) g_e conj(g_e-1)
+      vr = fma(sq, fma(gr, pr[i], gi * pim[i]), vr);
+      vi = fma(sq, fma(gi, pr[i], -gr * pim[i]), vi);
+      pr[i] = gr;
+      pim[i] = gi;
+    }
+    const double* tp = tab + (int64_t)e * tw_;
+    if constexpr (GRID) {
+      slide(cell[e]);
+#pragma unroll
+      for (int m = 0; m < K; ++m) {
+        ar_[m] = fma(tp[m], wr, ar_[m]);
+        ai_[m] = fma(tp[m], wi, ai_[m]);
       }
     }
-    const double* tp = tab + (int64_t)e * tw_ + (WHAT == 0 ? 0 : K + m0);
+    tp += K + m0;
 #pragma unroll
-    for (int m = 0; m < K; ++m) {
-      const double t = (WHAT == 0 || m0 + m < mh) ? tp[m] : 0.0;
-      ar_[m] = fma(t, wr, ar_[m]);
-      ai_[m] = fma(t, wi, ai_[m]);
+    for (int m = 0; m < MH; ++m) {
+      const double t = m0 + m < mh ? tp[m] : 0.0;
+      hr[m] = fma(t, vr, hr[m]);
+      hi[m] = fma(t, vi, hi[m]);
     }
   };
-  if constexpr (WHAT == 0) {
-    const int32_t* __restrict__ blo = e0 + nch + 1;
-    const int32_t* __restrict__ bhi = blo + nch;
-    const int32_t* __restrict__ sfirst = bhi + nch;
-    const int32_t* __restrict__ slast = sfirst + nch;
-    const int b_lo = blo[ch], b_hi = bhi[ch];
-    int e = e_lo;
-    for (int b = b_lo; b < b_hi; ++b) {
-      const int be = bs[b + 1] < e_hi ? bs[b + 1] : e_hi;
-      for (; e < be; ++e) edge(e);
-      const int slot = b == b_hi - 1 ? slast[ch] : (b == b_lo ? sfirst[ch] : -1);
-      if (p < n) {  // rows fastest: a wave's 64 rows store 1 KB contiguously
-        double2* out = slot < 0 ? mom + (int64_t)b * n + p : part + (int64_t)slot * K * n + p;
-        const int64_t ms = slot < 0 ? (int64_t)n_blk * n : n;
-#pragma unroll
-        for (int m = 0; m < K; ++m) out[m * ms] = make_double2(ar_[m], ai_[m]);
-      }
-#pragma unroll
-      for (int m = 0; m < K; ++m) ar_[m] = ai_[m] = 0.0;
-    }
-  } else {
-    for (int e = e_lo; e < e_hi; ++e) edge(e);
-    if (p < n) {
-      double2* out = hpart + ((int64_t)ch * n + p) * mh + m0;
-#pragma unroll
-      for (int m = 0; m < K; ++m)
-        if (m0 + m < mh) out[m] = make_double2(ar_[m], ai_[m]);
-    }
+  const int32_t* __restrict__ blo = e0 + nch + 1;
+  const int32_t* __restrict__ bhi = blo + nch;
+  if (GRID) {
+    cur = blo[ch];
+    out += (bhi + nch)[ch];
   }
-}
-
-// Blocks the plan cuts: each sums its pieces part [slot][K][rows] in chunk
-// order into mom [K][n_blk][rows]; lane = row, one (cut block, order) per
-// grid row and layer (a block of the narrow windows' wide blocks can have
-// tens of pieces, so the orders run in parallel).
-template <int K>
-__global__ void __launch_bounds__(64) k_het_tmom_fix(int64_t n, int n_blk, const int32_t* __restrict__ fb,
-                                                     const int32_t* __restrict__ fs, const int32_t* __restrict__ fc,
-                                                     const double2* __restrict__ part, double2* __restrict__ mom) {
-  const int64_t p = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (p >= n) return;
-  const int i = blockIdx.y, m = blockIdx.z;
-  const int b = fb[i], s0 = fs[i], cnt = fc[i];
-  double2 v = part[((int64_t)s0 * K + m) * n + p];
-  for (int k = 1; k < cnt; ++k) v = c_add(v, part[((int64_t)(s0 + k) * K + m) * n + p]);
-  mom[((int64_t)m * n_blk + b) * n + p] = v;
-}
-
-template <int ND, int K>
-static void launch_het_tmom_k(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, int prec, const HetConst& hc,
-                              int what, int m0, double2* mom, double2* part, double2* hpart, double* hhc,
-                              hipStream_t st) {
-  const gw_het_state* h = ctx->het;
-  const TrigConsts T = make_trig_consts();
-  const dim3 grid((unsigned)((n + 63) / 64), (unsigned)h->tm_nch);
-  const int32_t* bs = h->tm_idx;
-  const int32_t* plan = h->tm_idx + h->tm_nblk + 1;
-#define GW_HET_TMOM(P, W)                                                                                     \
-  hipLaunchKernelGGL((k_het_tmom<ND, P, K, W>), grid, dim3(64), 0, st, coef, ld, n, (const double*)h->rec,        \
-                     h->n_bins, (const double*)h->tm_tab, h->tm_mh, bs, plan, h->tm_nch, h->tm_nblk, m0, hc, T, mom, \
-                     part, hpart, hhc)
-  if (prec == GW_PREC_FP64) {
-    if (what == 0) GW_HET_TMOM(0, 0); else GW_HET_TMOM(0, 1);
-  } else {
-    if (what == 0) GW_HET_TMOM(1, 0); else GW_HET_TMOM(1, 1);
-  }
-#undef GW_HET_TMOM
-  if (what == 0 && h->tm_nsplit > 0) {  // add the pieces of the cut blocks
-    const int32_t* fb = plan + (h->tm_nch + 1) + 4 * h->tm_nch;
-    hipLaunchKernelGGL((k_het_tmom_fix<K>), dim3((unsigned)((n + 63) / 64), (unsigned)h->tm_nsplit, K), dim3(64), 0,
-                       st, n, h->tm_nblk, fb, fb + h->tm_nsplit, fb + 2 * h->tm_nsplit, (const double2*)part, mom);
+  for (int e = e_lo; e < e_hi; ++e) edge(e);
+  if (GRID) slide(bhi[ch] - 1);
+  if (p < n) {
+    if (GRID) {
+#pragma unroll
+      for (int m = 0; m < K; ++m) out[m] = make_double2(ar_[m], ai_[m]);
+    }
+    double2* ho = hpart + ((int64_t)ch * n + p) * mh + m0;
+#pragma unroll
+    for (int m = 0; m < MH; ++m)
+      if (m0 + m < mh) ho[m] = make_double2(hr[m], hi[m]);
   }
 }
 
 template <int ND>
 static void launch_het_tmom_nd(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, int prec, const HetConst& hc,
-                               int what, int m0, double2* mom, double2* part, double2* hpart, double* hhc,
-                               hipStream_t st) {
-  if (ctx->het->tm_K == 12)
-    launch_het_tmom_k<ND, 12>(ctx, coef, ld, n, prec, hc, what, m0, mom, part, hpart, hhc, st);
+                               double2* part, double2* hpart, double* hhc, hipStream_t st) {
+  const gw_het_state* h = ctx->het;
+  const dim3 grid((unsigned)((n + 63) / 64), (unsigned)h->tm_nch);
+  auto launch = [&](auto kernel, int m0) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64), 0, st, coef, ld, n, (const double*)h->rec, h->n_bins,
+                       (const double*)h->tm_tab, h->tm_mh, h->tm_cell, h->tm_cell + h->n_edges, h->tm_nch, m0, hc,
+                       make_trig_consts(), (int64_t)h->tm_npts, part, hpart, hhc);
+  };
+  const bool fp64 = prec == GW_PREC_FP64;
+  if (h->tm_mh <= 8)
+    fp64 ? launch(k_het_tmom<ND, 0, true, 8>, 0) : launch(k_het_tmom<ND, 1, true, 8>, 0);
   else
-    launch_het_tmom_k<ND, 16>(ctx, coef, ld, n, prec, hc, what, m0, mom, part, hpart, hhc, st);
+    fp64 ? launch(k_het_tmom<ND, 0, true, 14>, 0) : launch(k_het_tmom<ND, 1, true, 14>, 0);
+  for (int m0 = 14; m0 < h->tm_mh; m0 += 14)
+    fp64 ? launch(k_het_tmom<ND, 0, false, 14>, m0) : launch(k_het_tmom<ND, 1, false, 14>, m0);
 }
 
 // Chunks of the moment kernel: edge ranges of about equal cost (an edge or
-// a block's moment stores count one unit each; gw_hetplan.h), the count
+// a cell's store count one unit each; gw_hetplan.h), the count
 // chosen for about 4096 (tile, chunk) waves (at most 256 chunks, each of at
 // least 8 units), or fixed by gw_set_het_tm_split.
-static int het_tm_chunks(const gw_ctx* ctx, int64_t n, int n_blk) {
+static int het_tm_chunks(const gw_ctx* ctx, int64_t n, int n_cell) {
   if (ctx->tm_nsk > 0) return ctx->tm_nsk;
   const int64_t tiles = (n + 63) / 64;
   int64_t want = (4096 + tiles - 1) / tiles;
-  const int64_t most = std::max<int64_t>(1, std::min<int64_t>(256, (ctx->het->n_edges + n_blk) / 8));
+  const int64_t most = std::max<int64_t>(1, std::min<int64_t>(256, (ctx->het->n_edges + n_cell) / 8));
   return (int)std::max<int64_t>(1, std::min(want, most));
 }
 
-// Row-independent tables of the time marginal for the grid (blocks of blk
-// fine bins, n_blk of them, the window's largest |u| = umax fine-grid cycles)
-// and nch edge chunks.
-static gw_status het_tm_tables(gw_ctx* ctx, int blk, int n_blk, double umax, int nch, int K) {
+// Row-independent tables of the time marginal for the grid and nch edge chunks.
+static gw_status het_tm_tables(gw_ctx* ctx, const TimeGridShape& g, int nch) {
   gw_het_state* h = ctx->het;
-  if (h->tm_tab && h->tm_blk == blk && h->tm_nblk == n_blk && h->tm_nch_req == nch && h->tm_umax == umax &&
-      h->tm_K == K)
+  if (h->tm_tab && h->tm_blk == g.blk && h->tm_nblk == g.n_blk && h->tm_nch_req == nch && h->tm_L == g.L &&
+      h->tm_jmax == g.jmax)
     return GW_OK;
+  const double umax = (double)g.jmax / ((double)g.N * (double)g.R);  // the window's largest |u|, fine-grid cycles
+  const int n_cell = 2 * g.n_blk;
   const int ne = h->n_edges;
   std::vector<int64_t> k(ne);
   for (int e = 0; e < ne; ++e) k[e] = (int64_t)llround(h->f_edges[e] / ctx->geom.df) - ctx->geom.k0;
@@ -1157,29 +1136,32 @@ static gw_status het_tm_tables(gw_ctx* ctx, int blk, int n_blk, double umax, int
   if (term * exp(x) > 1e-13)
     return set_error(GW_ENOTSUP, "heterodyned time marginal: bin widths up to %lld fine bins over a +-%.3g s window "
                                  "need more than %d norm terms", (long long)dmax, ctx->tm_window, kTgHMax);
-  const int tw_ = K + mh;
+  const int tw_ = kTgW + mh;
   std::vector<double> tab((size_t)ne * tw_, 0.0);
-  std::vector<int32_t> bs(n_blk + 1, 0);
-  const double cen = 0.5 * (blk - 1), hinv = 2.0 / blk;
+  std::vector<int32_t> cs(n_cell + 1, 0), cell(ne);
+  const TgWindow win(g.beta);
   for (int e = 0; e < ne; ++e) {
-    const int64_t b = k[e] / blk;
-    if (b < 0 || b >= n_blk) return set_error(GW_EINVAL, "heterodyned time marginal: edge outside the band");
-    bs[b + 1] += 1;
-    const double sv = ((double)(k[e] - b * blk) - cen) * hinv;
-    tgrid_basis_at(sv, K, tab.data() + (size_t)e * tw_);
+    const double x = (double)k[e] / g.cell;
+    if (k[e] < 0 || x >= n_cell) return set_error(GW_EINVAL, "heterodyned time marginal: edge outside the band");
+    cell[e] = (int32_t)x;
+    cs[cell[e] + 1] += 1;
+    win.weights(x - cell[e], tab.data() + (size_t)e * tw_);
     const double sg = e > 0 && hw > 0.0 ? ((double)(k[e] - k[e - 1]) - cw) / hw : 0.0;
     double tp = 1.0;
     for (int m = 0; m < mh; ++m) {
-      tab[(size_t)e * tw_ + K + m] = tp;
+      tab[(size_t)e * tw_ + kTgW + m] = tp;
       tp *= sg;
     }
   }
-  for (int b = 0; b < n_blk; ++b) bs[b + 1] += bs[b];
-  const HetTmPlan plan = het_tm_plan(bs, n_blk, ne, nch);
-  std::vector<int32_t> idx(bs);
-  for (const std::vector<int32_t>* v : {&plan.e0, &plan.blo, &plan.bhi, &plan.sfirst, &plan.slast, &plan.fb,
-                                        &plan.fs, &plan.fc})
-    idx.insert(idx.end(), v->begin(), v->end());
+  for (int b = 0; b < n_cell; ++b) cs[b + 1] += cs[b];
+  const HetTmPlan plan = het_tm_plan(cs, n_cell, ne, nch);
+  std::vector<int32_t> len(plan.nch());
+  for (int c = 0; c < plan.nch(); ++c) len[c] = plan.bhi[c] - plan.blo[c] + kTgW - 1;
+  const TgCoverPlan cov = tgrid_cover(plan.blo, len, g.n_g);
+  std::vector<int32_t> idx(cov.pts), first(plan.nch());
+  for (int c = 0; c < plan.nch(); ++c) first[c] = cov.shift[c] + plan.blo[c];
+  const std::vector<int32_t>* parts[] = {&cell, &plan.e0, &plan.blo, &plan.bhi, &first, &cov.shift};
+  for (const std::vector<int32_t>* v : parts) idx.insert(idx.end(), v->begin(), v->end());
   if (h->tm_tab) (void)hipFree(h->tm_tab);
   if (h->tm_idx) (void)hipFree(h->tm_idx);
   h->tm_tab = nullptr;
@@ -1191,17 +1173,18 @@ static gw_status het_tm_tables(gw_ctx* ctx, int blk, int n_blk, double umax, int
   if (s == GW_OK)
     s = check_hip(hipMemcpy(h->tm_idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice), "index");
   if (s != GW_OK) return s;
-  h->tm_blk = blk;
-  h->tm_nblk = n_blk;
+  h->tm_cov = TgCover{(const int4*)h->tm_idx, h->tm_idx + idx.size() - cov.shift.size(), cov.n_many};
+  h->tm_cell = h->tm_idx + cov.pts.size();
+  h->tm_blk = g.blk;
+  h->tm_nblk = g.n_blk;
+  h->tm_L = g.L;
+  h->tm_jmax = g.jmax;
   h->tm_mh = mh;
   h->tm_nch = plan.nch();
   h->tm_nch_req = nch;
-  h->tm_nslot = plan.nslot;
-  h->tm_nsplit = (int)plan.fb.size();
+  h->tm_npts = cov.n_pts;
   h->tm_hw = hw;
   h->tm_c2 = dmin + dmax;
-  h->tm_umax = umax;
-  h->tm_K = K;
   return GW_OK;
 }
 
@@ -1215,32 +1198,25 @@ gw_status loglike_het_tmarg_staged(gw_ctx* ctx, const double* theta, int64_t n, 
   if (!h) return set_error(GW_ESTATE, "loglike_batch: heterodyne_setup has not been called");
   TimeGridShape g;
   gw_status s = time_grid_shape(ctx, &g);
-  const int K = tgrid_orders(g.L, g.jmax);
-  if (s == GW_OK) s = tgrid_tables(ctx, g.L, g.jmax, K);
-  const int64_t chunk = tgrid_chunk_rows(n, g.n_blk, K);
+  if (s == GW_OK) s = tgrid_tables(ctx, g.L, g.jmax);
+  if (s != GW_OK) return s;
+  // rows per chunk for at most one wave of every chunk's window over each cell,
   // edge chunks sized for the rows of one launch
-  const int nch = het_tm_chunks(ctx, chunk, g.n_blk);
-  const double umax = (double)g.jmax / ((double)g.N * (double)g.R);
-  if (s == GW_OK) s = het_tm_tables(ctx, g.blk, g.n_blk, umax, nch, K);
+  const int64_t chunk = tgrid_chunk_rows(n, (int64_t)(kTgW + 1) * g.n_blk);
+  s = het_tm_tables(ctx, g, het_tm_chunks(ctx, chunk, 2 * g.n_blk));
   if (s != GW_OK) return s;
   const int mh = h->tm_mh;
-  // workspace: coefficients for all rows; per row chunk the moments
-  // [K][n_blk][rows] (rows fastest), the pieces of cut blocks [slot][K][rows],
-  // the norm moments [n_ch][rows][mh], hhc [rows] and, for a small launch,
-  // the order groups' partial grids (16-byte aligned)
-  const int64_t zp = tgrid_zpart_elems(n, chunk, K, 2 * g.jmax + 1);
+  // workspace: coefficients for all rows; per row chunk the grid sums
+  // [rows][points], the norm moments [n_ch][rows][mh] and hhc [rows]
   s = ensure_buffer(&ctx->coef, &ctx->coef_cap, (int64_t)C_NCOEF * n, "coefficient workspace");
   if (s == GW_OK)
     s = ensure_buffer(&ctx->tm_mom, &ctx->tm_mom_cap,
-                      chunk * K * g.n_blk * 2 + (int64_t)h->tm_nslot * K * chunk * 2 +
-                          (int64_t)h->tm_nch * chunk * mh * 2 + chunk + 1 + 2 * zp,
+                      chunk * h->tm_npts * 2 + (int64_t)h->tm_nch * chunk * mh * 2 + chunk,
                       "time-marginal workspace");
   if (s != GW_OK || !theta) return s;  // theta NULL: reserve only
-  double2* mom = (double2*)ctx->tm_mom;
-  double2* part = mom + chunk * K * g.n_blk;
-  double2* hpart = part + (int64_t)h->tm_nslot * K * chunk;
+  double2* part = (double2*)ctx->tm_mom;
+  double2* hpart = part + chunk * h->tm_npts;
   double* hhc = (double*)(hpart + (int64_t)h->tm_nch * chunk * mh);
-  double* zpart = zp > 0 ? hhc + (chunk + 1) / 2 * 2 : nullptr;
   s = launch_prologue(ctx, theta, n, GW_MARG_PHASE_TIME, ctx->coef, n, st, false);
   if (s != GW_OK) return s;
   HetConst hc;
@@ -1254,36 +1230,24 @@ gw_status loglike_het_tmarg_staged(gw_ctx* ctx, const double* theta, int64_t n, 
   for (int64_t r0 = 0; r0 < n && s == GW_OK; r0 += chunk) {
     const int64_t cn = n - r0 < chunk ? n - r0 : chunk;
     const int prof = prof_begin(ctx, st, 1);
-    for (int what = 0; what < 2; ++what)
-      for (int m0 = 0; m0 < (what == 0 ? 1 : mh); m0 += K) {
-        switch (ctx->n_det) {
-          case 1:
-            launch_het_tmom_nd<1>(ctx, ctx->coef + r0, n, cn, prec, hc, what, m0, mom, part, hpart, hhc, st);
-            break;
-          case 2:
-            launch_het_tmom_nd<2>(ctx, ctx->coef + r0, n, cn, prec, hc, what, m0, mom, part, hpart, hhc, st);
-            break;
-          case 3:
-            launch_het_tmom_nd<3>(ctx, ctx->coef + r0, n, cn, prec, hc, what, m0, mom, part, hpart, hhc, st);
-            break;
-          case 4:
-            launch_het_tmom_nd<4>(ctx, ctx->coef + r0, n, cn, prec, hc, what, m0, mom, part, hpart, hhc, st);
-            break;
-          default: return set_error(GW_ENOTSUP, "n_det not supported");
-        }
-        s = check_hip(hipGetLastError(), "time-marginal moment launch");
-        if (s != GW_OK) return s;
-      }
+    switch (ctx->n_det) {
+      case 1: launch_het_tmom_nd<1>(ctx, ctx->coef + r0, n, cn, prec, hc, part, hpart, hhc, st); break;
+      case 2: launch_het_tmom_nd<2>(ctx, ctx->coef + r0, n, cn, prec, hc, part, hpart, hhc, st); break;
+      case 3: launch_het_tmom_nd<3>(ctx, ctx->coef + r0, n, cn, prec, hc, part, hpart, hhc, st); break;
+      case 4: launch_het_tmom_nd<4>(ctx, ctx->coef + r0, n, cn, prec, hc, part, hpart, hhc, st); break;
+      default: return set_error(GW_ENOTSUP, "n_det not supported");
+    }
+    s = check_hip(hipGetLastError(), "time-marginal moment launch");
+    if (s != GW_OK) return s;
     prof_end(ctx, prof, st);
     TGridArgs a{};
-    a.mom = (const double*)mom;
-    a.mom_rs = 1;  // k_het_tmom writes rows fastest
-    a.mom_es = cn;
+    a.part = (const double*)part;
+    a.pitch = h->tm_npts;
+    a.cov[0] = a.cov[1] = h->tm_cov;  // one cover for all rows
     a.n = cn;
-    a.n_blk = g.n_blk;
+    a.n_g = g.n_g;
     a.L = g.L;
     a.jmax = g.jmax;
-    a.K = K;
     a.coef = ctx->coef + r0;
     a.ld = n;
     a.logl = logl + r0;
@@ -1296,9 +1260,8 @@ gw_status loglike_het_tmarg_staged(gw_ctx* ctx, const double* theta, int64_t n, 
     a.c2 = h->tm_c2;
     a.cden = 2 * g.N * (int64_t)g.R;
     a.zout = zout ? zout + r0 * nt * 3 : nullptr;
-    a.f0_num = (double)(2 * ctx->geom.k0 + g.blk - 1);
-    a.f0_den = (double)(2 * g.N) * (double)g.R;
-    a.zpart = zpart;
+    a.f0_num = g.f0_num;
+    a.f0_den = g.f0_den;
     const int gslot = prof_begin(ctx, st, 2);
     s = launch_tgrid(ctx, a, st);
     prof_end(ctx, gslot, st);

@@ -8,6 +8,7 @@
 
 #include "gw_ctx.h"
 #include "gw_nodes.h"
+#include "gw_tgrid.h"
 
 namespace gw {
 
@@ -268,64 +269,124 @@ gw_status nodes_wide_init(gw_ctx* ctx) {
   return node_table(ctx, w[0], place, &ctx->nodes_wide);
 }
 
-// Tables of the time marginal's moments.  Within a block the samples of
-// exp(-i phi s) G_i, |phi| <= phi_max (the shifts the moments are expanded
-// for), are what the sums over the grid see, so n nodes serve all K moments.
-// A node costs about twice what a bin of the walk does; a block on which that
-// saves nothing keeps its bins (no nodes).
-gw_status tm_nodes_init(gw_ctx* ctx, int blk, int n_blk, int K, double phi_max) {
-  TmNodes& t = ctx->tm_nodes;
-  if (t.tab.rec && t.blk == blk && t.K == K && t.phi_max == phi_max) return GW_OK;
-  tm_nodes_free(ctx);
-  const Geom& g = ctx->geom;
-  const int nf = (int)g.n_freq;
+// A wave's nodes, at least and at most, and the waves aimed at per 64 rows; a
+// cell of more than twice its nodes is split over four waves.  Fewer per wave
+// balance k_tspread better (1000 rows, 128 s: 72 us at 16, 75 at 48) but leave
+// k_tgrid more chunks to add (86 us against 68): 147 us a call at 48, 149 at
+// 32, 157 at 16; 50 to 1000 rows at 8 s are within 3 us either way.
+constexpr int kTmNodesMin = 12, kTmNodesMax = 48, kTmWaves = 160;
+// Most cells of a wave's nodes.
+constexpr int kTmCells = 64;
+
+// Tables of the time marginal: the nodes of the band for delays up to the
+// window and the light travel time, each spread onto the grid at its own
+// frequency, and their chunks.
+gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
+  TmGrid& t = ctx->tm_grid;
+  if (t.tab.rec && t.blk == g.blk && t.L == g.L && t.jmax == g.jmax) return GW_OK;
+  tm_grid_free(ctx);
+  const Geom& geom = ctx->geom;
+  const int nf = (int)geom.n_freq, nd = ctx->n_det;
   std::vector<PhaseCoef> w;
   gw_status s = node_waveforms(ctx, &w);
   if (s != GW_OK) return s;
-  const SlopeBound slope(g, w);
-  const NodeCount node_count;
-  const double tau = travel_time(g);
   std::vector<NodePlace> place;
-  std::vector<int32_t> idx(n_blk + 1, 0);  // first node of each block
-  for (int b = 0; b < n_blk; ++b) {
-    const int kb = b * blk, ke = std::min(kb + blk, nf);
-    const int n = node_count(kPi * (ke - 1 - kb) * g.df * (slope.over(kb, ke - 1) + tau) + phi_max);
-    if (n <= kNodeMax && 2 * n < ke - kb)
-      for (int j = 0; j < n; ++j) place.push_back(NodePlace{kb, ke, n, j});
-    idx[b + 1] = (int32_t)place.size();
+  partition(ctx, w, (double)g.J * g.delta + travel_time(geom), &place);
+  // Chebyshev nodes come from the top of their block down
+  for (size_t q = 0; q < place.size();) {
+    const size_t m = place[q].n;
+    if (place[q].n != place[q].ke - place[q].kb) std::reverse(place.begin() + q, place.begin() + q + m);
+    q += m;
   }
-  // blocks of many samples are split over a workgroup's waves (the lowest ones:
-  // the slopes fall with frequency), all of them where there are few
-  for (int b = 0; b < n_blk; ++b) {
-    const int bins = std::min((b + 1) * blk, nf) - b * blk, nodes = idx[b + 1] - idx[b];
-    if (nodes > kTmWaveNodes || (nodes == 0 && bins > 2 * kTmWaveNodes)) t.n_heavy = b + 1;
-    if (n_blk <= kTmFewBlocks) t.n_heavy = n_blk;
+  const int n = (int)place.size(), n_cell = 2 * g.n_blk;
+  std::vector<int32_t> cell(n), count(n_cell, 0);
+  for (int q = 0; q < n; ++q) {
+    cell[q] = std::min((int)((place[q].kb + node_offset(place[q])) / g.cell), n_cell - 1);
+    ++count[cell[q]];
   }
-  const double cen = 0.5 * (blk - 1), hinv = 2.0 / blk;
-  s = node_table(ctx, w[0], place, 1, [&](size_t q, double* v) {
-    *v = (node_offset(place[q]) - cen) * hinv;
+  const int most = std::max(kTmNodesMin, std::min(kTmNodesMax, n / kTmWaves));
+  std::vector<int32_t> a0, len, first;
+  int n_dense = 0;
+  for (int q = 0; q < n;) {
+    const int a = cell[q];
+    int e = q + count[a], top = a;
+    if (count[a] > 2 * most && n_dense == (int)a0.size()) {
+      // units of about equal nodes, at most 4 most each
+      const int units = (count[a] + 4 * most - 1) / (4 * most), each = (count[a] + units - 1) / units;
+      for (int u = 0; u < units; ++u) {
+        ++n_dense;
+        first.push_back(q + u * each);
+        a0.push_back(a);
+        len.push_back(kTgW);
+      }
+      q = e;
+      continue;
+    }
+    while (e < n && e - q + count[cell[e]] <= most && cell[e] - a < kTmCells) {
+      top = cell[e];
+      e += count[top];
+    }
+    first.push_back(q);
+    a0.push_back(a);
+    len.push_back(top - a + kTgW);
+    q = e;
+  }
+  first.push_back(n);
+  const TgCoverPlan cn = tgrid_cover(a0, len, g.n_g);
+  std::vector<int32_t> b0(g.n_blk), blen(g.n_blk, kTgW + 1);
+  for (int b = 0; b < g.n_blk; ++b) b0[b] = 2 * b;
+  const TgCoverPlan cb = tgrid_cover(b0, blen, g.n_g);
+  const TgWindow win(g.beta);
+  const int cell_bins = (g.blk + 1) / 2;
+  std::vector<double> bw((size_t)cell_bins * kTgW);
+  for (int k = 0; k < cell_bins; ++k) win.weights((double)k / g.cell, &bw[(size_t)k * kTgW]);
+  // one allocation of the integers, those read by fours first
+  const int nc = (int)a0.size();
+  std::vector<int32_t> idx;
+  for (int c = 0; c < nc; ++c)
+    for (const int32_t v : {first[c], first[c + 1], a0[c], cn.shift[c] + a0[c]}) idx.push_back(v);
+  size_t at[5];
+  const std::vector<int32_t>* parts[5] = {&cn.pts, &cb.pts, &cell, &cn.shift, &cb.shift};
+  for (int i = 0; i < 5; ++i) {
+    at[i] = idx.size();
+    idx.insert(idx.end(), parts[i]->begin(), parts[i]->end());
+  }
+  s = node_table(ctx, w[0], place, kTgW, [&](size_t q, double* v) {
+    win.weights((place[q].kb + node_offset(place[q])) / g.cell - cell[q], v);
   }, &t.tab);
-  if (s == GW_OK) s = check_hip(hipMalloc((void**)&t.idx, idx.size() * sizeof(int32_t)), "time-moment units");
+  if (s == GW_OK) s = check_hip(hipMalloc((void**)&t.idx, idx.size() * sizeof(int32_t)), "time-grid chunks");
   if (s == GW_OK)
-    s = check_hip(hipMemcpy(t.idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice), "units");
+    s = check_hip(hipMemcpy(t.idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice), "chunks");
+  if (s == GW_OK) s = check_hip(hipMalloc((void**)&t.bins_w, bw.size() * sizeof(double)), "time-grid weights");
+  if (s == GW_OK)
+    s = check_hip(hipMemcpy(t.bins_w, bw.data(), bw.size() * sizeof(double), hipMemcpyHostToDevice), "weights");
   if (s != GW_OK) {
-    tm_nodes_free(ctx);
+    tm_grid_free(ctx);
     return s;
   }
-  t.blk = blk;
-  t.K = K;
-  t.phi_max = phi_max;
+  t.chunk = (const int4*)t.idx;
+  t.cell = t.idx + at[2];
+  t.cov[0] = TgCover{(const int4*)(t.idx + at[0]), t.idx + at[3], cn.n_many};
+  t.cov[1] = TgCover{(const int4*)(t.idx + at[1]), t.idx + at[4], cb.n_many};
+  t.n_chunk = nc;
+  t.n_dense = n_dense;
+  t.n_pts = std::max(cn.n_pts, cb.n_pts);
+  t.blk = g.blk;
+  t.L = g.L;
+  t.jmax = g.jmax;
   return GW_OK;
 }
 
-void tm_nodes_free(gw_ctx* ctx) {
-  if (ctx->tm_nodes.tab.rec) (void)hipFree(ctx->tm_nodes.tab.rec);
-  if (ctx->tm_nodes.idx) (void)hipFree(ctx->tm_nodes.idx);
-  ctx->tm_nodes = TmNodes{};
+void tm_grid_free(gw_ctx* ctx) {
+  TmGrid& t = ctx->tm_grid;
+  if (t.tab.rec) (void)hipFree(t.tab.rec);
+  if (t.idx) (void)hipFree(t.idx);
+  if (t.bins_w) (void)hipFree(t.bins_w);
+  t = TmGrid{};
 }
 
 void nodes_free(gw_ctx* ctx) {
-  tm_nodes_free(ctx);
+  tm_grid_free(ctx);
   if (ctx->nodes_wide.rec) (void)hipFree(ctx->nodes_wide.rec);
   ctx->nodes_wide = NodeTable{};
   if (ctx->nodes.rec) (void)hipFree(ctx->nodes.rec);

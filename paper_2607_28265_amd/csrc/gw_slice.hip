@@ -973,9 +973,9 @@ struct SliceGraphKey {
   int32_t like, marg, prec, cache;
   const void *ws_mem, *coef, *partial, *zbuf, *het, *wc, *mlp;
   uint64_t mlp_scale, gen;
-  const void *tm_mom, *tm_ccoef, *tm_basis, *tm_tab, *tm_idx;
+  const void *tm_mom, *tm_dec, *tm_grid, *tm_tab, *tm_idx;
   int32_t het_wpb, het_grid, het_ech, full_tpb, full_chunks, full_kernel;
-  int32_t tm_nch, tm_nslot, tm_nsplit, fused, pinned, pad;
+  int32_t tm_nch, fused, pinned, pad;
   bool operator==(const SliceGraphKey& o) const { return memcmp(this, &o, sizeof(*this)) == 0; }
 };
 
@@ -1097,9 +1097,9 @@ static gw_status slice_graph(gw_ctx* ctx, gw_slice_ws* ws, int64_t k, int64_t n,
   key.pinned = pinned ? 1 : 0;
   if (a.marg == GW_MARG_PHASE_TIME) {
     key.tm_mom = ctx->tm_mom;
-    key.tm_ccoef = ctx->tm_ccoef;
-    key.tm_basis = ctx->tm_basis;
-    het_tm_key(ctx, &key.tm_tab, &key.tm_idx, &key.tm_nch, &key.tm_nslot, &key.tm_nsplit);
+    key.tm_dec = ctx->tm_dec;
+    key.tm_grid = ctx->tm_grid.idx;
+    het_tm_key(ctx, &key.tm_tab, &key.tm_idx, &key.tm_nch);
   }
   if (ws->have_graph && ws->key == key) return GW_OK;
   if (ws->exec) (void)hipGraphExecDestroy(ws->exec);

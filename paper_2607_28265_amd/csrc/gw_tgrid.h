@@ -85,67 +85,109 @@ __host__ __device__ inline void tg_pass2(double2* v, double2 w) {
   }
 }
 
-// J_n(x) by its power series (|x| <= pi / 2 here: the terms fall by at least
-// (x / 2)^2 / k at step k, so the sum settles in a dozen terms).
-inline double tgrid_bessel_jn(int n, double x) {
-  const long double h = 0.5L * (long double)x;
-  long double t = 1.0L;
-  for (int i = 1; i <= n; ++i) t *= h / (long double)i;
-  long double s = t;
-  for (int k = 1; k < 60; ++k) {
-    t *= -(h * h) / ((long double)k * (long double)(n + k));
+// exp(-i pi k / 16), k = 0 .. 15
+__host__ __device__ inline double2 w32(int k) {
+  constexpr double c[9] = {1.0,                 0.98078528040323044, 0.92387953251128674, 0.83146961230254524,
+                           0.70710678118654752, 0.55557023301960222, 0.38268343236508977, 0.19509032201612827, 0.0};
+  return k <= 8 ? make_double2(c[k], -c[8 - k]) : make_double2(-c[16 - k], -c[k - 8]);
+}
+
+// Kaiser-Bessel gridding (Beatty, Nishimura & Pauly 2005): a sample at grid
+// coordinate x is spread over kTgW grid points with weights
+// psi(x - g) = I0(beta sqrt(1 - (2 (x - g) / kTgW)^2)) / I0(beta),
+// whose transform sum_g psi(x - g) exp(-2 pi i g nu) is
+// psi_hat(nu) exp(-2 pi i x nu) up to the images at nu + 1, nu - 1, ...
+constexpr int kTgW = 14;
+constexpr int kTgLead = kTgW / 2 - 1;  // grid points before the sample's cell
+
+inline double tgrid_i0(double x) {
+  long double t = 1.0L, s = 1.0L;
+  const long double q = 0.25L * (long double)x * (long double)x;
+  for (int k = 1; k < 200 && t > 1e-22L * s; ++k) {
+    t *= q / ((long double)k * (long double)k);
     s += t;
-    if (fabsl(t) <= 1e-22L * fabsl(s)) break;
   }
   return (double)s;
 }
 
-// Expansion orders for a grid of |j| <= jmax on a length-L transform: 12 when
-// the dropped orders' bound 2 (phi / 2)^12 / 12! at phi = pi jmax / L is at
-// most 2e-11, else 16.
-inline int tgrid_orders(int L, int jmax) {
-  const double phi = 3.141592653589793 * (double)jmax / (double)L;
-  double b = 2.0;
-  for (int i = 1; i <= 12; ++i) b *= 0.5 * phi / (double)i;
-  return b <= 2e-11 ? 12 : 16;
-}
+// Shape for |nu| <= nu_max: close to the largest beta that keeps the images
+// at |nu| >= 1 - nu_max beyond the main lobe, 2 % below it (measured error
+// over all nu and x: 7e-15 of sum |y| at nu_max 1/8, 5e-14 at 1/5 (the default
+// window), 6e-13 at 1/4; 0.96 and 1.0 of it 7e-13 and 2e-12 there).
+inline double tgrid_beta(double nu_max) { return 0.98 * 3.141592653589793 * kTgW * (1.0 - nu_max); }
 
-// Coefficient table [K][256][16]: eps_m J_m(pi j / L) with the sign of (-i)^m
-// folded in (+ for m mod 4 in {0, 1}, - otherwise), for lane l's output slot
-// k3 at (m 256 + l) 16 + k3; zero where the slot's |j| exceeds jmax.
-inline void tgrid_coefficients(int L, int jmax, int K, std::vector<double>* out) {
-  int D1 = 1, D2 = 1;
-  out->assign((size_t)K * 16 * 256, 0.0);
-  if (!tgrid_plan(L, &D1, &D2)) return;
-  for (int lane = 0; lane < L / 16; ++lane)
-    for (int k3 = 0; k3 < 16; ++k3) {
-      const int X = tg_owned(L, D1, D2, lane, k3);
-      const int j = X <= jmax ? X : X - L;
-      if (j < -jmax || j > jmax) continue;
-      const double phi = 3.141592653589793 * (double)j / (double)L;
-      for (int m = 0; m < K; ++m) {
-        const double sgn = (m & 3) < 2 ? 1.0 : -1.0;
-        (*out)[((size_t)m * 256 + lane) * 16 + k3] = sgn * (m == 0 ? 1.0 : 2.0) * tgrid_bessel_jn(m, phi);
+// psi and psi_hat for one shape, and the kTgW weights of a sample at offset s
+// of its cell (0 <= s < 1): grid point m of the window is s + kTgLead - m away.
+// I0(beta sqrt(1 - u^2)) is analytic in u, so each weight is a Chebyshev series
+// in s (26 terms: the rest below 1e-17), a tenth of the work of its Bessel
+// series.
+struct TgWindow {
+  static constexpr int kTerms = 26;
+  double beta, i0_beta, c[kTerms][kTgW];
+
+  explicit TgWindow(double b) : beta(b), i0_beta(tgrid_i0(b)) {
+    double v[kTerms][kTgW];
+    for (int j = 0; j < kTerms; ++j)
+      for (int m = 0; m < kTgW; ++m) v[j][m] = psi(0.5 + 0.5 * cos(angle(1, j)) + kTgLead - m);
+    for (int k = 0; k < kTerms; ++k)
+      for (int m = 0; m < kTgW; ++m) {
+        double t = 0.0;
+        for (int j = 0; j < kTerms; ++j) t += v[j][m] * cos(angle(k, j));
+        c[k][m] = (k == 0 ? 1.0 : 2.0) / kTerms * t;
       }
-    }
-}
-
-// Chebyshev values T_m(s), m < K (T_0 = 1, T_1 = s, T_{m+1} = 2 s T_m - T_{m-1}).
-inline void tgrid_basis_at(double s, int K, double* t) {
-  double a = 1.0, b = s;
-  for (int m = 0; m < K; ++m) {
-    t[m] = a;
-    const double c = 2.0 * s * b - a;
-    a = b;
-    b = c;
   }
-}
+  static double angle(int k, int j) { return 3.141592653589793 * k * (j + 0.5) / kTerms; }
+  double psi(double x) const {
+    const double u = 2.0 * x / kTgW;
+    return u * u < 1.0 ? tgrid_i0(beta * sqrt(1.0 - u * u)) / i0_beta : 0.0;
+  }
+  double psi_hat(double nu) const {
+    const double x = 3.141592653589793 * kTgW * nu, a = sqrt(beta * beta - x * x);
+    return kTgW * sinh(a) / (a * i0_beta);
+  }
+  void weights(double s, double* w) const {
+    const double t = 2.0 * s - 1.0;
+    double p[kTgW] = {}, q[kTgW] = {};
+    for (int k = kTerms - 1; k > 0; --k)
+      for (int m = 0; m < kTgW; ++m) {
+        const double n = c[k][m] + 2.0 * t * p[m] - q[m];
+        q[m] = p[m];
+        p[m] = n;
+      }
+    for (int m = 0; m < kTgW; ++m) w[m] = c[0][m] + t * p[m] - q[m];
+  }
+};
 
-// The same at s = (j - (blk - 1) / 2) / (blk / 2) for j < blk: [blk][K].
-inline void tgrid_basis(int blk, int K, std::vector<double>* out) {
-  out->assign((size_t)blk * K, 0.0);
-  const double cen = 0.5 * (blk - 1), hinv = 2.0 / blk;
-  for (int j = 0; j < blk; ++j) tgrid_basis_at(((double)j - cen) * hinv, K, out->data() + (size_t)j * K);
+// Chunk c adds to grid points a0[c] .. a0[c] + len[c] - 1, stored from off[c]
+// on (off the running sum of len); a0 and a0 + len nondecreasing.  Per grid
+// point g < n_g (pts [n_g][4]): where the first and the second chunk that
+// reach it hold it (-1: none), then the third and the last of them; per chunk
+// off - a0 (shift).  n_many: leading points, some with more than four chunks,
+// which k_tgrid sums with four lanes each (at most 256 of them, else none).
+struct TgCoverPlan {
+  std::vector<int32_t> pts, shift;
+  int n_pts = 0, n_many = 0;
+};
+inline TgCoverPlan tgrid_cover(const std::vector<int32_t>& a0, const std::vector<int32_t>& len, int n_g) {
+  TgCoverPlan p;
+  const int nc = (int)a0.size();
+  for (int c = 0; c < nc; ++c) {
+    p.shift.push_back(p.n_pts - a0[c]);
+    p.n_pts += len[c];
+  }
+  p.pts.resize(4 * (size_t)n_g);
+  int lo = 0, hi = -1;
+  for (int g = 0; g < n_g; ++g) {
+    while (hi + 1 < nc && a0[hi + 1] <= g) ++hi;
+    while (lo <= hi && a0[lo] + len[lo] <= g) ++lo;
+    p.pts[4 * g] = lo <= hi ? p.shift[lo] + g : -1;
+    p.pts[4 * g + 1] = lo < hi ? p.shift[lo + 1] + g : -1;
+    p.pts[4 * g + 2] = lo + 2;
+    p.pts[4 * g + 3] = hi;
+    if (hi - lo >= 4) p.n_many = g + 1;
+  }
+  if (p.n_many > 256) p.n_many = 0;
+  return p;
 }
 
 }  // namespace gw
