@@ -1,9 +1,10 @@
 // Likelihood prescreen network 11 -> 256 -> 256 -> 256 -> 1 with exact GELU.
 //
-// Training (forward, backward, Adam) runs in FP32 on the vector ALUs through
-// one LDS-tiled GEMM kernel (64 x 64 tiles, 4 x 4 outputs per thread, split-K
-// with a fixed-order reduction for the weight gradients) and elementwise
-// kernels; the FP32 master weights live on the device.  Inference runs the
+// Training (forward, backward, Adam) runs in FP32 on the matrix cores: one
+// kernel takes a few rows forward and their deltas back, another forms the
+// weight gradients over row splits, summed in a fixed order; the FP32 master
+// weights live on the device.  The FP32 forward alone runs through an LDS-tiled
+// GEMM (64 x 64 tiles, 4 x 4 outputs per thread).  Inference runs the
 // hidden layers on the matrix cores: BF16 weights (round-to-nearest-even,
 // stored transposed so that one lane's K-run is contiguous) and BF16
 // activations feed v_mfma_f32_16x16x16_bf16 with FP32 accumulation; bias and
@@ -60,51 +61,29 @@ __global__ void k_mlp_stdin(const double* __restrict__ x, int64_t n, MlpScale sc
   xs[i] = ((float)x[i] - sc.xm[j]) * sc.xs_inv[j];
 }
 
-// C[z] = op(A) op(B) over the K range of split z (+ bias when z is the only
-// split); op(A)(i, k) = TA ? A[k lda + i] : A[i lda + k], likewise for B.
-template <bool TA, bool TB>
-__global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, int k_per, const float* __restrict__ A, int lda,
+// C = A B + bias (FP32 forward).
+__global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, const float* __restrict__ A, int lda,
                                               const float* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-                                              int64_t c_split_stride, const float* __restrict__ bias) {
+                                              const float* __restrict__ bias) {
   __shared__ float As[16][64 + 4];
   __shared__ float Bs[16][64 + 4];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const int kb = blockIdx.z * k_per;
-  const int ke = kb + k_per < K ? kb + k_per : K;
   float acc[4][4];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[r][c] = 0.0f;
-  for (int k0 = kb; k0 < ke; k0 += 16) {
+  for (int k0 = 0; k0 < K; k0 += 16) {
     for (int e = threadIdx.x; e < 1024; e += 256) {
-      int ii, kk;
-      if (TA) {
-        kk = e >> 6;
-        ii = e & 63;
-      } else {
-        ii = e >> 4;
-        kk = e & 15;
-      }
+      const int ii = e >> 4, kk = e & 15;
       const int gi = i0 + ii, gk = k0 + kk;
-      float v = 0.0f;
-      if (gi < M && gk < ke) v = TA ? A[(int64_t)gk * lda + gi] : A[(int64_t)gi * lda + gk];
-      As[kk][ii] = v;
+      As[kk][ii] = gi < M && gk < K ? A[(int64_t)gi * lda + gk] : 0.0f;
     }
     for (int e = threadIdx.x; e < 1024; e += 256) {
-      int jj, kk;
-      if (TB) {
-        jj = e >> 4;
-        kk = e & 15;
-      } else {
-        kk = e >> 6;
-        jj = e & 63;
-      }
+      const int kk = e >> 6, jj = e & 63;
       const int gj = j0 + jj, gk = k0 + kk;
-      float v = 0.0f;
-      if (gj < N && gk < ke) v = TB ? B[(int64_t)gj * ldb + gk] : B[(int64_t)gk * ldb + gj];
-      Bs[kk][jj] = v;
+      Bs[kk][jj] = gj < N && gk < K ? B[(int64_t)gk * ldb + gj] : 0.0f;
     }
     __syncthreads();
 #pragma unroll
@@ -121,7 +100,6 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, int k_per, co
     }
     __syncthreads();
   }
-  float* Cz = C + (int64_t)blockIdx.z * c_split_stride;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = i0 + ty * 4 + r;
@@ -129,18 +107,9 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, int k_per, co
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int j = j0 + tx * 4 + c;
-      if (j < N) Cz[(int64_t)i * ldc + j] = acc[r][c] + (bias ? bias[j] : 0.0f);
+      if (j < N) C[(int64_t)i * ldc + j] = acc[r][c] + bias[j];
     }
   }
-}
-
-// out[e] = sum_z part[z][e] in split order.
-__global__ void k_sum_splits(const float* __restrict__ part, int splits, int64_t count, float* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= count) return;
-  float s = 0.0f;
-  for (int z = 0; z < splits; ++z) s += part[(int64_t)z * count + e];
-  out[e] = s;
 }
 
 __global__ void k_gelu_fwd(const float* __restrict__ z, float* __restrict__ a, int64_t count) {
@@ -148,56 +117,326 @@ __global__ void k_gelu_fwd(const float* __restrict__ z, float* __restrict__ a, i
   if (e < count) a[e] = gelu_f(z[e]);
 }
 
-__global__ void k_gelu_bwd(float* __restrict__ d, const float* __restrict__ z, int64_t count) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < count) d[e] *= gelu_grad_f(z[e]);
+// ---------------------------------------------------------------------------
+// Loss and gradient of a batch, FP32 on the matrix cores, in four launches.
+// Bound by latency and by the weights each workgroup reads from L2.  1024 rows:
+// 26 us forward and deltas, 13 weight gradients, 4 each for the transposes and
+// the sum over splits; 440 us as 28 launches of a vector-ALU GEMM of 64 x 64
+// tiles (16 to 64 workgroups each), elementwise kernels and column sums.
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+// W2 and W3 transposed, for the backward products (32 x 32 tiles).
+__global__ void __launch_bounds__(256) k_transpose(const float* __restrict__ p, float* __restrict__ t) {
+  __shared__ float tile[32][33];
+  const float* __restrict__ src = p + (blockIdx.z == 0 ? OW2 : OW3);
+  float* __restrict__ dst = t + (int64_t)blockIdx.z * kH * kH;
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+  for (int r = y; r < 32; r += 8) tile[r][x] = src[(i0 + r) * kH + j0 + x];
+  __syncthreads();
+  for (int r = y; r < 32; r += 8) dst[(j0 + r) * kH + i0 + x] = tile[x][r];
 }
 
-// Loss 1/n sum (y - t)^2 on standardised targets and dy = 2 (y - t) / n; one
-// workgroup, fixed-order tree for the loss.
-__global__ void __launch_bounds__(256) k_mse(const float* __restrict__ y, const double* __restrict__ target,
-                                             int64_t n, MlpScale sc, float* __restrict__ dy,
-                                             float* __restrict__ loss) {
-  __shared__ float red[256];
-  float s = 0.0f;
-  const double iys = 1.0 / sc.ys;
-  for (int64_t i = threadIdx.x; i < n; i += 256) {
-    const float t = (float)((target[i] - sc.ym) * iys);
-    const float r = y[i] - t;
-    dy[i] = 2.0f * r / (float)n;
-    s += r * r;
+// Batch state between the launches: inputs [n][16] (standardised, zero
+// beyond kIn), activations and deltas of the hidden layers [n][kH] each, per
+// row dy and (y - t)^2.
+struct TrainView {
+  float *xs, *a1, *a2, *a3, *d1, *d2, *d3, *dy, *r2;
+};
+
+// The 4 R rows of a workgroup against 64 features per wave: lane = feature,
+// acc[r][q] of row 4 r + q over the kH inputs of act (LDS, [4 R][kH + 4]) and
+// w [kH][kH], by
+// the 4x4x1 matrix instruction (16 blocks of 4 rows x 4 features at one k; the
+// rows are the same in every block, so 4-row tiles keep all of its rate and
+// 1024 rows fill the 256 CUs).  Weights are read ahead, 64 k of them with few
+// rows (1024 rows: 26 us for k_train_rows, 34 at 16 k).
+template <int R>
+__device__ inline void rows_times(const float* __restrict__ act, const float* __restrict__ w, int j, f4v acc[R]) {
+  constexpr int kStride = kH + 4, kStep = R == 1 ? 64 : 16;
+  f4v part[R][4];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[r][q] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+  const float* __restrict__ row = act + (threadIdx.x & 3) * kStride;
+  float cur[kStep], nxt[kStep];
+#pragma unroll
+  for (int k = 0; k < kStep; ++k) cur[k] = w[(int64_t)k * kH + j];
+#pragma unroll
+  for (int k0 = 0; k0 < kH; k0 += kStep) {
+    const int kn = k0 + kStep < kH ? k0 + kStep : k0;
+#pragma unroll
+    for (int k = 0; k < kStep; ++k) nxt[k] = w[(int64_t)(kn + k) * kH + j];
+#pragma unroll
+    for (int k = 0; k < kStep; k += 4)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const f4v a = *(const f4v*)(row + 4 * r * kStride + k0 + k);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          part[r][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[q], cur[k + q], part[r][q], 0, 0, 0);
+      }
+#pragma unroll
+    for (int k = 0; k < kStep; ++k) cur[k] = nxt[k];
   }
-  red[threadIdx.x] = s;
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = (part[r][0] + part[r][1]) + (part[r][2] + part[r][3]);
+}
+
+// Forward and the deltas backward of 4 R rows per workgroup (wave = 64
+// features).  wt: W2, W3 transposed.
+template <int R>
+__global__ void __launch_bounds__(256) k_train_rows(const double* __restrict__ x, const double* __restrict__ target,
+                                                    int64_t n, MlpScale sc, const float* __restrict__ p,
+                                                    const float* __restrict__ wt, TrainView v) {
+  constexpr int kRows = 4 * R, kStride = kH + 4;
+  __shared__ __align__(16) float act[2][kRows * kStride];
+  __shared__ float ysum[4][kRows];
+  __shared__ float dys[kRows];
+  const int j = threadIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t i0 = (int64_t)blockIdx.x * kRows;
+  for (int e = threadIdx.x; e < kRows * 16; e += 256) {
+    const int r = e >> 4, k = e & 15;
+    const int64_t i = i0 + r;
+    const float f = i < n && k < kIn ? ((float)x[i * kIn + k] - sc.xm[k]) * sc.xs_inv[k] : 0.0f;
+    act[0][r * kStride + k] = f;
+    if (i < n) v.xs[i * 16 + k] = f;
+  }
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  f4v acc[R], z1[R], z2[R], z3[R];
+  // out = GELU(acc + b) to the next activation buffer and to memory
+  auto layer = [&](int from, float b, f4v* z, float* __restrict__ out) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        z[r][q] = acc[r][q] + b;
+        const float a = gelu_f(z[r][q]);
+        const int row = 4 * r + q;
+        act[from ^ 1][row * kStride + j] = a;
+        if (i0 + row < n) out[(i0 + row) * kH + j] = a;
+        acc[r][q] = a;
+      }
     __syncthreads();
+  };
+  {  // K = 11: the weights of the padding are zero by the input alone
+    f4v s[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    const float* __restrict__ row = act[0] + (threadIdx.x & 3) * kStride;
+#pragma unroll
+    for (int k = 0; k < kIn; ++k) {
+      const float w = p[OW1 + k * kH + j];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        s[r] = __builtin_amdgcn_mfma_f32_4x4x1f32(row[4 * r * kStride + k], w, s[r], 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = s[r];
   }
-  if (threadIdx.x == 0) *loss = red[0] / (float)n;
+  layer(0, p[OB1 + j], z1, v.a1);
+  rows_times<R>(act[1], p + OW2, j, acc);
+  layer(1, p[OB2 + j], z2, v.a2);
+  rows_times<R>(act[0], p + OW3, j, acc);
+  layer(0, p[OB3 + j], z3, v.a3);
+  // output, loss terms and dy: lanes, then waves, in a fixed order
+  const float w4 = p[OW4 + j];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float t = acc[r][q] * w4;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+      if (lane == 0) ysum[wave][4 * r + q] = t;
+    }
+  __syncthreads();
+  if (threadIdx.x < kRows) {
+    const int64_t i = i0 + threadIdx.x;
+    const int r = threadIdx.x;
+    float d = 0.0f;
+    if (i < n) {
+      const float y = ((ysum[0][r] + ysum[1][r]) + (ysum[2][r] + ysum[3][r])) + p[OB4];
+      const float e = y - (float)((target[i] - sc.ym) * (1.0 / sc.ys));
+      d = 2.0f * e / (float)n;
+      v.dy[i] = d;
+      v.r2[i] = e * e;
+    }
+    dys[r] = d;
+  }
+  __syncthreads();
+  auto delta = [&](int to, const f4v* z, float* __restrict__ out) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = 4 * r + q;
+        const float d = acc[r][q] * gelu_grad_f(z[r][q]);
+        act[to][row * kStride + j] = d;
+        if (i0 + row < n) out[(i0 + row) * kH + j] = d;
+      }
+    __syncthreads();
+  };
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[r][q] = dys[4 * r + q] * w4;
+  delta(0, z3, v.d3);
+  rows_times<R>(act[0], wt + kH * kH, j, acc);
+  delta(1, z2, v.d2);
+  rows_times<R>(act[1], wt, j, acc);
+  delta(0, z1, v.d1);
 }
 
-// db[j] = sum_i d[i][j]: workgroup = 64 columns x 4 waves; wave w sums rows
-// i = w mod 4 in four interleaved partial sums (i mod 16), the 16 partials
-// are added in a fixed order.
-__global__ void __launch_bounds__(256) k_colsum(const float* __restrict__ d, int64_t rows, int cols,
-                                               float* __restrict__ db) {
-  __shared__ float red[4][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
-  float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-  if (j < cols) {
-    int64_t i = w;
-    for (; i + 12 < rows; i += 16) {
-      a0 += d[i * cols + j];
-      a1 += d[(i + 4) * cols + j];
-      a2 += d[(i + 8) * cols + j];
-      a3 += d[(i + 12) * cols + j];
+// Weight gradients over the rows of split blockIdx.y, into part [split]
+// [kNPar + 1] (the last: the loss sum): one workgroup per 64 x 64 tile of dW3
+// and dW2 (32), per 64 columns of dW1 (4) and per 64 rows of dW4 (4).  A wave
+// takes a quarter of the split's rows; the 16x16x4 matrix instruction has the
+// rows as its k.  A lane's 16-byte read holds one value of four tiles: tile a
+// has the features 4 c + a, c < 16.  The tiles of dW3, dW2 at i0 = 0 and those of
+// dW1 carry the column sums of the deltas (the bias gradients) along.
+__global__ void __launch_bounds__(256) k_train_weights(int64_t n, int rows_per, TrainView v, float* __restrict__ part) {
+  __shared__ float red[3][64][65];
+  __shared__ float cred[3][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+  const int64_t s0 = (int64_t)blockIdx.y * rows_per;
+  const int64_t s1 = s0 + rows_per < n ? s0 + rows_per : n;
+  const int quarter = rows_per / 4;  // a multiple of 4
+  const int64_t r0 = s0 + wave * quarter < s1 ? s0 + wave * quarter : s1;
+  const int64_t r1 = r0 + quarter < s1 ? r0 + quarter : s1;
+  float* __restrict__ out = part + (int64_t)blockIdx.y * (kNPar + 1);
+  const int t = blockIdx.x;
+  f4v col = {0.0f, 0.0f, 0.0f, 0.0f};  // column sums of this lane's rows
+  // (wave 0 + wave 1) + wave 2 + wave 3, lanes by their row group first
+  auto group_sum = [&](f4v s) {
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], o, 64);
+    return s;
+  };
+  if (t < 36) {
+    const bool first = t >= 32;
+    const int m = t >> 4, i0 = first ? 0 : 64 * ((t >> 2) & 3), j0 = 64 * (t & 3);
+    const float* __restrict__ A = first ? v.xs : (m == 0 ? v.a2 : v.a1);
+    const float* __restrict__ D = first ? v.d1 : (m == 0 ? v.d3 : v.d2);
+    const int lda = first ? 16 : kH;
+    f4v acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+    for (int64_t r = r0; r < r1; r += 4) {
+      const int64_t i = r + g;
+      f4v av = zero, dv = zero;
+      if (i < r1) {
+        dv = *(const f4v*)(D + i * kH + j0 + 4 * c);
+        if (first)
+          av[0] = A[i * 16 + c];
+        else
+          av = *(const f4v*)(A + i * (int64_t)lda + i0 + 4 * c);
+      }
+      col += dv;
+      if (first) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[0], dv[b], acc[0][b], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], dv[b], acc[a][b], 0, 0, 0);
+      }
     }
-    for (; i < rows; i += 4) a0 += d[i * cols + j];
+    // tile (a, b): register q of this lane is row 4 g + q, column c; feature
+    // 4 row + a (the first layer: row), 4 c + b
+    col = group_sum(col);
+    if (wave > 0) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (!first || a == 0) red[wave - 1][first ? 4 * g + q : 4 * (4 * g + q) + a][4 * c + b] = acc[a][b][q];
+      if (g == 0)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) cred[wave - 1][4 * c + b] = col[b];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    float* __restrict__ W = out + (first ? OW1 : (m == 0 ? OW3 : OW2));
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int fi = first ? 4 * g + q : 4 * (4 * g + q) + a;
+        if (first && (a > 0 || fi >= kIn)) continue;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int fj = 4 * c + b;
+          W[(int64_t)(i0 + fi) * kH + j0 + fj] =
+              ((acc[a][b][q] + red[0][fi][fj]) + red[1][fi][fj]) + red[2][fi][fj];
+        }
+      }
+    if ((first || i0 == 0) && g == 0) {
+      float* __restrict__ B = out + (first ? OB1 : (m == 0 ? OB3 : OB2));
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int fj = 4 * c + b;
+        B[j0 + fj] = ((col[b] + cred[0][fj]) + cred[1][fj]) + cred[2][fj];
+      }
+    }
+    return;
   }
-  red[w][lane] = (a0 + a1) + (a2 + a3);
+  const int j0 = 64 * (t - 36);
+  float sd = 0.0f, sr = 0.0f;
+  for (int64_t r = r0; r < r1; r += 4) {
+    const int64_t i = r + g;
+    if (i < r1) {
+      const float d = v.dy[i];
+      const f4v a = *(const f4v*)(v.a3 + i * kH + j0 + 4 * c);
+      col += a * d;
+      sd += d;
+      sr += v.r2[i];
+    }
+  }
+  col = group_sum(col);
+  const f4v e = group_sum(f4v{sd, sr, 0.0f, 0.0f});
+  if (wave > 0 && g == 0) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) cred[wave - 1][4 * c + b] = col[b];
+    red[wave - 1][0][0] = e[0];
+    red[wave - 1][0][1] = e[1];
+  }
   __syncthreads();
-  if (w == 0 && j < cols) db[j] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+  if (wave > 0 || g > 0) return;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int fj = 4 * c + b;
+    out[OW4 + j0 + fj] = ((col[b] + cred[0][fj]) + cred[1][fj]) + cred[2][fj];
+  }
+  if (j0 == 0 && c == 0) {
+    out[OB4] = ((e[0] + red[0][0][0]) + red[1][0][0]) + red[2][0][0];
+    out[kNPar] = ((e[1] + red[0][0][1]) + red[1][0][1]) + red[2][0][1];
+  }
+}
+
+// g = sum of the splits in order; the loss is the mean of its terms.
+__global__ void __launch_bounds__(256) k_train_sum(const float* __restrict__ part, int splits, int64_t n,
+                                                   float* __restrict__ g, float* __restrict__ loss) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e > kNPar) return;
+  float s = 0.0f;
+#pragma unroll 8
+  for (int z = 0; z < splits; ++z) s += part[(int64_t)z * (kNPar + 1) + e];
+  if (e < kNPar)
+    g[e] = s;
+  else
+    *loss = s / (float)n;
 }
 
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
@@ -234,7 +473,7 @@ __global__ void k_to_bf16(const float* __restrict__ p, uint16_t* __restrict__ q)
 }
 
 // ---------------------------------------------------------------------------
-// BF16 MFMA inference: one workgroup (8 waves) per 128 rows.  Each layer is
+// BF16 MFMA inference: one workgroup (8 waves) per 32 RT rows.  Each layer is
 // computed transposed, out^T [feature][row] = W [feature][k] act^T [k][row],
 // with the 16x16x32 BF16 matrix instruction (FP32 accumulation): operand A is
 // a 16-feature x 32-k tile of the weights (read from memory, one k-step
@@ -242,12 +481,10 @@ __global__ void k_to_bf16(const float* __restrict__ p, uint16_t* __restrict__ q)
 // kActStride bf16 so that the 16 rows of a read fall in distinct banks); a
 // lane's 4 results are 4 consecutive features of one row, stored as one
 // 8-byte write.  Wave w owns features 64 (w mod 4) .. + 63 of rows
-// 64 (w / 4) .. + 63: 4 feature tiles x 4 row tiles.
+// 16 RT (w / 4) .. + 16 RT - 1: 4 feature tiles x RT row tiles.
 
 typedef short s8v __attribute__((ext_vector_type(8)));
-typedef float f4v __attribute__((ext_vector_type(4)));
 
-constexpr int kInferRows = 128;
 constexpr int kActStride = kH + 8;  // bf16 per activation row in LDS
 
 __device__ inline f4v mfma_bf16_16x16x32(s8v a, s8v b, f4v c) {
@@ -256,17 +493,19 @@ __device__ inline f4v mfma_bf16_16x16x32(s8v a, s8v b, f4v c) {
                                                  0);
 }
 
+template <int RT>
 __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x, int64_t n, MlpScale sc,
                                                    const uint16_t* __restrict__ q, const float* __restrict__ p,
                                                    double* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) uint16_t act[kInferRows * kActStride];  // [row][k]
-  __shared__ float red[4][kInferRows];
+  constexpr int kRows = 32 * RT;
+  __shared__ __attribute__((aligned(16))) uint16_t act[kRows * kActStride];  // [row][k]
+  __shared__ float red[4][kRows];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int fw = wave & 3, rw = wave >> 2;  // feature block, row half
-  const int64_t r0 = (int64_t)blockIdx.x * kInferRows;
+  const int64_t r0 = (int64_t)blockIdx.x * kRows;
   // standardised input, K padded to 32
-  for (int e = threadIdx.x; e < kInferRows * kInPad; e += 512) {
+  for (int e = threadIdx.x; e < kRows * kInPad; e += 512) {
     const int row = e / kInPad, k = e % kInPad;
     float v = 0.0f;
     if (k < kIn && r0 + row < n) v = ((float)x[(r0 + row) * kIn + k] - sc.xm[k]) * sc.xs_inv[k];
@@ -276,7 +515,7 @@ __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x,
   const int l16 = lane & 15;        // feature (A) / row (B) within a tile
   const int lk = (lane >> 4) * 8;   // this lane's 8 values of the 32-k step
   const int lf = (lane >> 4) * 4;   // first of this lane's 4 output features in a tile
-  f4v acc[4][4];                    // [feature tile][row tile]
+  f4v acc[4][RT];                   // [feature tile][row tile]
   for (int layer = 0; layer < 3; ++layer) {
     const int K = layer == 0 ? kInPad : kH;
     const uint16_t* __restrict__ W = q + (layer == 0 ? QW1 : (layer == 1 ? QW2 : QW3));
@@ -284,7 +523,7 @@ __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x,
 #pragma unroll
     for (int ft = 0; ft < 4; ++ft)
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt) acc[ft][rt] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int rt = 0; rt < RT; ++rt) acc[ft][rt] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
     const uint16_t* __restrict__ wrow = W + (int64_t)(fw * 64 + l16) * K + lk;
     s8v a_cur[4], a_nxt[4];
 #pragma unroll
@@ -295,8 +534,8 @@ __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x,
         for (int ft = 0; ft < 4; ++ft) a_nxt[ft] = *(const s8v*)(wrow + (int64_t)ft * 16 * K + k0 + 32);
       }
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt) {
-        const s8v b = *(const s8v*)&act[(rw * 64 + rt * 16 + l16) * kActStride + k0 + lk];
+      for (int rt = 0; rt < RT; ++rt) {
+        const s8v b = *(const s8v*)&act[((rw * RT + rt) * 16 + l16) * kActStride + k0 + lk];
 #pragma unroll
         for (int ft = 0; ft < 4; ++ft) acc[ft][rt] = mfma_bf16_16x16x32(a_cur[ft], b, acc[ft][rt]);
       }
@@ -310,7 +549,7 @@ __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x,
     for (int ft = 0; ft < 4; ++ft) {
       const float4 bc = *(const float4*)&bias[fw * 64 + ft * 16 + lf];
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt) {
+      for (int rt = 0; rt < RT; ++rt) {
         acc[ft][rt][0] = gelu_f(acc[ft][rt][0] + bc.x);
         acc[ft][rt][1] = gelu_f(acc[ft][rt][1] + bc.y);
         acc[ft][rt][2] = gelu_f(acc[ft][rt][2] + bc.z);
@@ -322,10 +561,10 @@ __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x,
 #pragma unroll
       for (int ft = 0; ft < 4; ++ft)
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
+        for (int rt = 0; rt < RT; ++rt) {
           const uint32_t lo = (uint32_t)to_bf16(acc[ft][rt][0]) | ((uint32_t)to_bf16(acc[ft][rt][1]) << 16);
           const uint32_t hi = (uint32_t)to_bf16(acc[ft][rt][2]) | ((uint32_t)to_bf16(acc[ft][rt][3]) << 16);
-          *(uint2*)&act[(rw * 64 + rt * 16 + l16) * kActStride + fw * 64 + ft * 16 + lf] = make_uint2(lo, hi);
+          *(uint2*)&act[((rw * RT + rt) * 16 + l16) * kActStride + fw * 64 + ft * 16 + lf] = make_uint2(lo, hi);
         }
       __syncthreads();
     }
@@ -342,7 +581,7 @@ __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x,
     w4[ft][3] = w.w;
   }
 #pragma unroll
-  for (int rt = 0; rt < 4; ++rt) {
+  for (int rt = 0; rt < RT; ++rt) {
     float v = 0.0f;
 #pragma unroll
     for (int ft = 0; ft < 4; ++ft)
@@ -350,10 +589,10 @@ __global__ void __launch_bounds__(512) k_mlp_infer(const double* __restrict__ x,
       for (int j = 0; j < 4; ++j) v = fmaf(acc[ft][rt][j], w4[ft][j], v);
     v += __shfl_xor(v, 16, 64);
     v += __shfl_xor(v, 32, 64);
-    if (lane < 16) red[fw][rw * 64 + rt * 16 + l16] = v;
+    if (lane < 16) red[fw][(rw * RT + rt) * 16 + l16] = v;
   }
   __syncthreads();
-  if (threadIdx.x < kInferRows && r0 + threadIdx.x < n) {
+  if (threadIdx.x < kRows && r0 + threadIdx.x < n) {
     const int t = threadIdx.x;
     const float y = ((red[0][t] + red[1][t]) + (red[2][t] + red[3][t])) + p[OB4];
     out[r0 + t] = sc.ym + sc.ys * (double)y;
@@ -463,10 +702,8 @@ struct gw_mlp {
   int64_t t = 0;
   MlpScale sc{};
   uint64_t sc_version = 0;  // bumped whenever sc changes (a captured launch bakes sc in)
-  float* ws = nullptr;  // training workspace
-  int64_t ws_rows = 0;
-  float* part = nullptr;  // split-K partials
-  int64_t part_cap = 0;
+  float* ws = nullptr;  // workspace of training and of the FP32 forward
+  int64_t ws_cap = 0;
   float* loss = nullptr;  // device scalar
   // prescreen workspace
   void* pre = nullptr;
@@ -476,128 +713,75 @@ struct gw_mlp {
 
 namespace {
 
-gw_status mlp_ws(gw_mlp* m, int64_t rows) {
-  if (rows <= m->ws_rows) return GW_OK;
+// Workspace of the FP32 forward and of training (floats).
+gw_status mlp_ws(gw_mlp* m, int64_t count) {
+  if (count <= m->ws_cap) return GW_OK;
   if (m->ws) (void)hipFree(m->ws);
   m->ws = nullptr;
-  m->ws_rows = 0;
-  const size_t per = kIn + 6 * kH + 2 + 2 * kH;
-  gw_status s = check_hip(hipMalloc((void**)&m->ws, (size_t)rows * per * sizeof(float)), "mlp workspace");
-  if (s == GW_OK) m->ws_rows = rows;
+  m->ws_cap = 0;
+  gw_status s = check_hip(hipMalloc((void**)&m->ws, (size_t)count * sizeof(float)), "mlp workspace");
+  if (s == GW_OK) m->ws_cap = count;
   return s;
-}
-
-struct Act {
-  float *xs, *z1, *a1, *z2, *a2, *z3, *a3, *y, *dy, *d0, *d1;
-};
-
-Act act_views(gw_mlp* m, int64_t rows) {
-  Act a;
-  float* w = m->ws;
-  a.xs = w; w += rows * kIn;
-  a.z1 = w; w += rows * kH;
-  a.a1 = w; w += rows * kH;
-  a.z2 = w; w += rows * kH;
-  a.a2 = w; w += rows * kH;
-  a.z3 = w; w += rows * kH;
-  a.a3 = w; w += rows * kH;
-  a.y = w; w += rows;
-  a.dy = w; w += rows;
-  a.d0 = w; w += rows * kH;
-  a.d1 = w;
-  return a;
-}
-
-// C = op(A) op(B) (+ bias); with splits > 1 the K range is split and the
-// partial products are summed in split order (bias not allowed then).
-gw_status gemm(gw_mlp* m, bool ta, bool tb, int M, int N, int K, const float* A, int lda, const float* B, int ldb,
-               float* C, int ldc, const float* bias, int splits, hipStream_t st) {
-  if (splits < 1) splits = 1;
-  const int k_per = ((K + splits - 1) / splits + 15) / 16 * 16;
-  splits = (K + k_per - 1) / k_per;
-  if (splits < 1) splits = 1;
-  float* out = C;
-  int64_t stride = 0;
-  if (splits > 1) {
-    const int64_t need = (int64_t)splits * M * N;
-    if (need > m->part_cap) {
-      if (m->part) (void)hipFree(m->part);
-      m->part = nullptr;
-      m->part_cap = 0;
-      gw_status s = check_hip(hipMalloc((void**)&m->part, need * sizeof(float)), "mlp partials");
-      if (s != GW_OK) return s;
-      m->part_cap = need;
-    }
-    out = m->part;
-    stride = (int64_t)M * N;
-    ldc = N;
-  }
-  dim3 grid((N + 63) / 64, (M + 63) / 64, splits);
-  if (ta && tb) return set_error(GW_ENOTSUP, "gemm: both transposed");
-  if (ta)
-    hipLaunchKernelGGL((k_gemm<true, false>), grid, dim3(256), 0, st, M, N, K, k_per, A, lda, B, ldb, out, ldc, stride,
-                       splits > 1 ? nullptr : bias);
-  else if (tb)
-    hipLaunchKernelGGL((k_gemm<false, true>), grid, dim3(256), 0, st, M, N, K, k_per, A, lda, B, ldb, out, ldc, stride,
-                       splits > 1 ? nullptr : bias);
-  else
-    hipLaunchKernelGGL((k_gemm<false, false>), grid, dim3(256), 0, st, M, N, K, k_per, A, lda, B, ldb, out, ldc,
-                       stride, splits > 1 ? nullptr : bias);
-  gw_status s = check_hip(hipGetLastError(), "gemm launch");
-  if (s != GW_OK || splits == 1) return s;
-  const int64_t cnt = (int64_t)M * N;
-  hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, m->part, splits, cnt, C);
-  return check_hip(hipGetLastError(), "split-K reduce launch");
 }
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-// FP32 forward of ``rows`` standardised inputs already in a.xs.
-gw_status forward32(gw_mlp* m, const Act& a, int64_t rows, hipStream_t st) {
+// FP32 forward of ``rows`` inputs into y (workspace a: one activation buffer
+// of rows kIn, then two of rows kH).
+gw_status forward32(gw_mlp* m, const double* x, int64_t rows, float* y, float* a, hipStream_t st) {
   const int R = (int)rows;
-  gw_status s = gemm(m, false, false, R, kH, kIn, a.xs, kIn, m->p + OW1, kH, a.z1, kH, m->p + OB1, 1, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_gelu_fwd, dim3(nblk(rows * kH)), dim3(256), 0, st, a.z1, a.a1, rows * kH);
-  if (s == GW_OK) s = gemm(m, false, false, R, kH, kH, a.a1, kH, m->p + OW2, kH, a.z2, kH, m->p + OB2, 1, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_gelu_fwd, dim3(nblk(rows * kH)), dim3(256), 0, st, a.z2, a.a2, rows * kH);
-  if (s == GW_OK) s = gemm(m, false, false, R, kH, kH, a.a2, kH, m->p + OW3, kH, a.z3, kH, m->p + OB3, 1, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_gelu_fwd, dim3(nblk(rows * kH)), dim3(256), 0, st, a.z3, a.a3, rows * kH);
-  if (s == GW_OK) s = gemm(m, false, false, R, 1, kH, a.a3, kH, m->p + OW4, 1, a.y, 1, m->p + OB4, 1, st);
-  if (s == GW_OK) s = check_hip(hipGetLastError(), "mlp forward");
-  return s;
+  float *xs = a, *h = xs + rows * kIn, *z = h + rows * kH;
+  auto gemm = [&](const float* in, int k, int64_t w, int64_t b, int cols, float* out) {
+    hipLaunchKernelGGL(k_gemm, dim3((cols + 63) / 64, (R + 63) / 64), dim3(256), 0, st, R, cols, k, in, k, m->p + w,
+                       cols, out, cols, m->p + b);
+  };
+  auto gelu = [&] {
+    hipLaunchKernelGGL(k_gelu_fwd, dim3(nblk(rows * kH)), dim3(256), 0, st, z, h, rows * kH);
+  };
+  hipLaunchKernelGGL(k_mlp_stdin, dim3(nblk(rows * kIn)), dim3(256), 0, st, x, rows, m->sc, xs);
+  gemm(xs, kIn, OW1, OB1, kH, z);
+  gelu();
+  gemm(h, kH, OW2, OB2, kH, z);
+  gelu();
+  gemm(h, kH, OW3, OB3, kH, z);
+  gelu();
+  gemm(h, kH, OW4, OB4, 1, y);
+  return check_hip(hipGetLastError(), "mlp forward");
 }
 
 // Loss and gradients of one batch into m->g.
 gw_status grad32(gw_mlp* m, const double* x, const double* y, int64_t n, hipStream_t st) {
-  gw_status s = mlp_ws(m, n);
+  // rows of a split of the weight gradients: 128 up to 32 splits (1024 rows: 320
+  // workgroups of 8 splits)
+  const int64_t rows_per = std::max<int64_t>(128, ((n + 31) / 32 + 15) / 16 * 16);
+  const int splits = (int)((n + rows_per - 1) / rows_per);
+  const int64_t per_row = 16 + 6 * kH + 2, wt_n = 2 * kH * kH, np = (n + 3) / 4 * 4;
+  gw_status s = mlp_ws(m, np * per_row + wt_n + (int64_t)splits * (kNPar + 1));
   if (s != GW_OK) return s;
-  Act a = act_views(m, n);
-  hipLaunchKernelGGL(k_mlp_stdin, dim3(nblk(n * kIn)), dim3(256), 0, st, x, n, m->sc, a.xs);
-  s = forward32(m, a, n, st);
-  if (s != GW_OK) return s;
-  hipLaunchKernelGGL(k_mse, dim3(1), dim3(256), 0, st, a.y, y, n, m->sc, a.dy, m->loss);
-  const int R = (int)n;
-  const int sp = (int)std::min<int64_t>(32, std::max<int64_t>(1, n / 256));
-  float* g = m->g;
-  // layer 4
-  s = gemm(m, true, false, kH, 1, R, a.a3, kH, a.dy, 1, g + OW4, 1, nullptr, sp, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_colsum, dim3(1), dim3(256), 0, st, a.dy, n, 1, g + OB4);
-  if (s == GW_OK) s = gemm(m, false, true, R, kH, 1, a.dy, 1, m->p + OW4, 1, a.d0, kH, nullptr, 1, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_gelu_bwd, dim3(nblk(n * kH)), dim3(256), 0, st, a.d0, a.z3, n * kH);
-  // layer 3
-  if (s == GW_OK) s = gemm(m, true, false, kH, kH, R, a.a2, kH, a.d0, kH, g + OW3, kH, nullptr, sp, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_colsum, dim3(kH / 64), dim3(256), 0, st, a.d0, n, kH, g + OB3);
-  if (s == GW_OK) s = gemm(m, false, true, R, kH, kH, a.d0, kH, m->p + OW3, kH, a.d1, kH, nullptr, 1, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_gelu_bwd, dim3(nblk(n * kH)), dim3(256), 0, st, a.d1, a.z2, n * kH);
-  // layer 2
-  if (s == GW_OK) s = gemm(m, true, false, kH, kH, R, a.a1, kH, a.d1, kH, g + OW2, kH, nullptr, sp, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_colsum, dim3(kH / 64), dim3(256), 0, st, a.d1, n, kH, g + OB2);
-  if (s == GW_OK) s = gemm(m, false, true, R, kH, kH, a.d1, kH, m->p + OW2, kH, a.d0, kH, nullptr, 1, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_gelu_bwd, dim3(nblk(n * kH)), dim3(256), 0, st, a.d0, a.z1, n * kH);
-  // layer 1
-  if (s == GW_OK) s = gemm(m, true, false, kIn, kH, R, a.xs, kIn, a.d0, kH, g + OW1, kH, nullptr, sp, st);
-  if (s == GW_OK) hipLaunchKernelGGL(k_colsum, dim3(kH / 64), dim3(256), 0, st, a.d0, n, kH, g + OB1);
-  if (s == GW_OK) s = check_hip(hipGetLastError(), "mlp backward");
-  return s;
+  TrainView v;
+  float* w = m->ws;
+  float* wt = w;
+  w += wt_n;
+  v.xs = w, w += np * 16;
+  for (float** q : {&v.a1, &v.a2, &v.a3, &v.d1, &v.d2, &v.d3}) *q = w, w += np * kH;
+  v.dy = w, w += np;
+  v.r2 = w, w += np;
+  float* part = w;
+  hipLaunchKernelGGL(k_transpose, dim3(kH / 32, kH / 32, 2), dim3(256), 0, st, (const float*)m->p, wt);
+  auto rows = [&](auto kernel, int64_t r) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + r - 1) / r)), dim3(256), 0, st, x, y, n, m->sc,
+                       (const float*)m->p, (const float*)wt, v);
+  };
+  // rows per workgroup: 4, up to four workgroups a CU; beyond, 16 share the
+  // weights' reads (3000 rows: 144 us a call of 4, 175 of 16; 8192: 215 and 200)
+  if (n <= 4096)
+    rows(k_train_rows<1>, 4);
+  else
+    rows(k_train_rows<4>, 16);
+  hipLaunchKernelGGL(k_train_weights, dim3(40, (unsigned)splits), dim3(256), 0, st, n, (int)rows_per, v, part);
+  hipLaunchKernelGGL(k_train_sum, dim3(nblk(kNPar + 1)), dim3(256), 0, st, (const float*)part, splits, n, m->g,
+                     m->loss);
+  return check_hip(hipGetLastError(), "mlp gradient");
 }
 
 uint64_t splitmix(uint64_t& s) {
@@ -625,8 +809,20 @@ gw_status mlp_prepare(gw_mlp* m, hipStream_t st) {
 
 gw_status mlp_infer(gw_mlp* m, const double* x, int64_t n, double* out, hipStream_t st) {
   if (n == 0) return GW_OK;
-  hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)((n + kInferRows - 1) / kInferRows)), dim3(512), 0, st, x, n, m->sc,
-                     m->q, m->p, out);
+  auto launch = [&](auto kernel, int64_t rows) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + rows - 1) / rows)), dim3(512), 0, st, x, n, m->sc,
+                       (const uint16_t*)m->q, (const float*)m->p, out);
+  };
+  // the fewest rows per workgroup that still is one workgroup a CU (a row's
+  // result is the same in each): 25, 31 and 42 us a call of 32, 64 and 128 rows
+  // up to that point; beyond it fewer rows read the weights more often (12,000
+  // rows: 37 us of 32, 31 of 64; 32,768: 72, 45, 43)
+  if (n <= 8192)
+    launch(k_mlp_infer<1>, 32);
+  else if (n <= 16384)
+    launch(k_mlp_infer<2>, 64);
+  else
+    launch(k_mlp_infer<4>, 128);
   return check_hip(hipGetLastError(), "mlp inference launch");
 }
 
@@ -691,7 +887,7 @@ gw_status gw_mlp_create(gw_ctx* ctx, uint64_t seed, gw_mlp** out) {
 gw_status gw_mlp_destroy(gw_mlp* m) {
   if (!m) return GW_OK;
   (void)hipSetDevice(m->ctx->device);
-  float* bufs[] = {m->p, m->g, m->m, m->v, m->ws, m->part, m->loss};
+  float* bufs[] = {m->p, m->g, m->m, m->v, m->ws, m->loss};
   for (float* b : bufs)
     if (b) (void)hipFree(b);
   if (m->q) (void)hipFree(m->q);
@@ -780,24 +976,15 @@ gw_status gw_mlp_forward(gw_mlp* m, const double* x, int64_t n, double* out, int
   gw_status s = check_hip(hipSetDevice(m->ctx->device), "hipSetDevice");
   if (s != GW_OK) return s;
   if (use_bf16) {
-    if (m->q_dirty) {
-      hipLaunchKernelGGL(k_to_bf16, dim3(nblk(kNQ)), dim3(256), 0, st, m->p, m->q);
-      s = check_hip(hipGetLastError(), "bf16 conversion launch");
-      if (s != GW_OK) return s;
-      m->q_dirty = false;
-    }
-    hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)((n + kInferRows - 1) / kInferRows)), dim3(512), 0, st, x, n, m->sc,
-                     m->q, m->p, out);
-    return check_hip(hipGetLastError(), "mlp inference launch");
+    s = mlp_prepare(m, st);
+    return s == GW_OK ? mlp_infer(m, x, n, out, st) : s;
   }
-  const int64_t chunk = 1 << 16;
-  s = mlp_ws(m, std::min(n, chunk));
+  const int64_t chunk = 1 << 16, most = std::min(n, chunk);
+  s = mlp_ws(m, most * (1 + kIn + 2 * kH));
   for (int64_t o = 0; o < n && s == GW_OK; o += chunk) {
     const int64_t r = std::min(chunk, n - o);
-    Act a = act_views(m, std::min(n, chunk));
-    hipLaunchKernelGGL(k_mlp_stdin, dim3(nblk(r * kIn)), dim3(256), 0, st, x + o * kIn, r, m->sc, a.xs);
-    s = forward32(m, a, r, st);
-    if (s == GW_OK) hipLaunchKernelGGL(k_unscale, dim3(nblk(r)), dim3(256), 0, st, a.y, r, m->sc, out + o);
+    s = forward32(m, x + o * kIn, r, m->ws, m->ws + most, st);
+    if (s == GW_OK) hipLaunchKernelGGL(k_unscale, dim3(nblk(r)), dim3(256), 0, st, m->ws, r, m->sc, out + o);
     if (s == GW_OK) s = check_hip(hipGetLastError(), "mlp forward");
   }
   return s;
