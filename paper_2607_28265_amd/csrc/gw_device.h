@@ -610,8 +610,8 @@ __device__ inline double wave_dist_lse_f32(double z1, double hh1, const double* 
   return bmax + log(wave_sum((double)s));
 }
 
-// Sliced forms of the distance marginal: one proposal per lane, and the
-// waves of a workgroup share the same 64 proposals, each wave taking a slice
+// Sliced form of the distance marginal, single precision: one proposal per lane,
+// and the waves of a workgroup share the same 64 proposals, each wave taking a slice
 // [j0, j1) of the grid.  All lanes of a wave walk their slice together, so
 // each grid record is a wave-uniform (scalar) load shared by 64 proposals
 // instead of a separate vector load per lane.  The caller combines the slice
@@ -626,39 +626,7 @@ __device__ inline double slice_dist_bound(double z1, double hh1, const double* _
   return bmax;
 }
 
-// sum_j exp(t_j - bmax) over the slice (FP64 form; terms more than 35
-// below the bound in FP32, as in wave_dist_lse).
-__device__ inline double slice_dist_sum(double z1, double hh1, double bmax, const double* __restrict__ tab, int j0,
-                                        int j1, const LogI0Consts& C) {
-  const double cut = bmax - 60.0, fine = bmax - 35.0;
-  const double iz = z1 > 0.0 ? 1.0 / z1 : 0.0;
-  const int tier = wave_i0_tier(z1, C), atier = wave_asym_tier(z1, C);
-  double s = 0.0;
-  for (int j = j0; j < j1; ++j) {
-    const double* r = tab + 4 * j;
-    const double a = fma(-hh1, r[2], r[3]);
-    const double x = z1 * r[1];
-    if (a + x < cut) continue;
-    if (a + x < fine) {
-      s += (double)dist_term_f32(a, x, bmax);
-      continue;
-    }
-    double v, e;
-    if (x < 20.0) {
-      v = i0_series_tier(tier, 0.25 * x * x);
-      e = a - bmax;
-    } else {
-      const double u = r[0] * iz;  // 1 / x
-      const double p = i0_asym_tier(atier, u);
-      v = p * sqrt(u * kInvTwoPi);
-      e = (a + x) - bmax;
-    }
-    s = fma(exp_nonpos(e, C.exp2_64), v, s);
-  }
-  return s;
-}
-
-// Same sum, single-precision form.
+// sum_j exp(t_j - bmax) over the slice.
 __device__ inline double slice_dist_sum_f32(double z1, double hh1, double bmax, const double* __restrict__ tab,
                                             int j0, int j1) {
   const double cut = bmax - 60.0;
@@ -693,9 +661,8 @@ __device__ inline double slice_dist_sum_f32(double z1, double hh1, double bmax, 
 // Workgroup-level driver: waves w = 0 .. nw-1 of the block share 64
 // proposals (lane = proposal); red is LDS scratch of nw x 64 doubles.
 // Returns the log-sum-exp in every lane of wave 0 (other waves return 0).
-template <int PREC>
 __device__ inline double block_dist_lse(double z1, double hh1, const double* __restrict__ tab, int n_dist, int nw,
-                                        double* red, const LogI0Consts& C) {
+                                        double* red) {
   const int lane = threadIdx.x & 63;
   // wave index, made visibly wave-uniform so that the grid loads are scalar
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -707,8 +674,7 @@ __device__ inline double block_dist_lse(double z1, double hh1, const double* __r
   double bmax = -INFINITY;
   for (int v = 0; v < nw; ++v) bmax = fmax(bmax, red[v * 64 + lane]);
   __syncthreads();
-  red[w * 64 + lane] = PREC == 0 ? slice_dist_sum(z1, hh1, bmax, tab, j0, j1, C)
-                                 : slice_dist_sum_f32(z1, hh1, bmax, tab, j0, j1);
+  red[w * 64 + lane] = slice_dist_sum_f32(z1, hh1, bmax, tab, j0, j1);
   __syncthreads();
   double s = 0.0;
   if (w == 0)

@@ -1272,9 +1272,8 @@ __global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ par
     if (j < 2 * nd) partial[((int64_t)c0 * 2 * nd + j) * n + p] = z[j];
 }
 
-// Distance marginal: one lane per proposal, waves splitting the grid (see block_dist_lse).
-// Small batches: one wave per proposal (see wave_dist_lse), which keeps many
-// waves busy when there are few proposals.
+// Distance marginal, small batches and FP64: one wave per proposal (see
+// wave_dist_lse), which keeps many waves busy when there are few proposals.
 template <int PREC>
 __global__ void __launch_bounds__(256) k_dist_marg_w(const double* __restrict__ zbuf, int64_t n,
                                                      const double* __restrict__ tab, int n_dist, double dd,
@@ -1294,16 +1293,14 @@ __global__ void __launch_bounds__(256) k_dist_marg_w(const double* __restrict__ 
   if (lane == 0) logl[p] = -0.5 * dd + v;
 }
 
-// Large batches: a workgroup of kDistWaves waves per 64 proposals, the grid
+// Large mixed batches: a workgroup of kDistWaves waves per 64 proposals, the grid
 // split between the waves (see block_dist_lse).
 constexpr int kDistWaves = 16;
 constexpr int64_t kDistSliced = 8192;  // batches from this size use the sliced form
 
-template <int PREC>
 __global__ void __launch_bounds__(1024) k_dist_marg(const double* __restrict__ zbuf, int64_t n,
                                                     const double* __restrict__ tab, int n_dist, double dd,
-                                                    const LogI0Consts* __restrict__ Cp, double* __restrict__ logl) {
-  const LogI0Consts& C = *Cp;
+                                                    double* __restrict__ logl) {
   __shared__ double red[kDistWaves * 64];
   const int lane = threadIdx.x & 63;
   const int64_t p = (int64_t)blockIdx.x * 64 + lane;
@@ -1311,7 +1308,7 @@ __global__ void __launch_bounds__(1024) k_dist_marg(const double* __restrict__ z
   const double z1 = zbuf[pc];
   const double hh1 = zbuf[n + pc];
   // invalid rows (z1 < 0) still take part in the block's barriers
-  const double v = block_dist_lse<PREC>(z1 < 0.0 ? 0.0 : z1, hh1, tab, n_dist, kDistWaves, red, C);
+  const double v = block_dist_lse(z1 < 0.0 ? 0.0 : z1, hh1, tab, n_dist, kDistWaves, red);
   if ((threadIdx.x >> 6) == 0 && p < n) logl[p] = z1 < 0.0 ? -INFINITY : -0.5 * dd + v;
 }
 
@@ -1665,16 +1662,14 @@ gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_
                      ctx->n_det, coef, ld, n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow, node_from);
   gw_status s = check_hip(hipGetLastError(), "epilogue launch");
   if (s != GW_OK || marg != 2) return s;
-  // large batches: lane = row (grid records are scalar loads shared by 64
-  // rows); small batches: wave = row
-  if (n >= kDistSliced) {
+  // large mixed batches: lane = row (grid records are scalar loads shared by
+  // 64 rows).  Small ones and FP64: wave = row; its lanes are neighbouring
+  // distances, which mostly take the same form of a term, while rows differ
+  // (9000 rows in FP64: 306 us a call against 377)
+  if (n >= kDistSliced && prec == GW_PREC_MIXED) {
     const int64_t dblocks = (n + 63) / 64;
-    if (prec == GW_PREC_MIXED)
-      hipLaunchKernelGGL(k_dist_marg<1>, dim3((unsigned)dblocks), dim3(64 * kDistWaves), 0, st, zbuf, n,
-                         ctx->dist_tab, ctx->n_dist, ctx->dd, C, logl);
-    else
-      hipLaunchKernelGGL(k_dist_marg<0>, dim3((unsigned)dblocks), dim3(64 * kDistWaves), 0, st, zbuf, n,
-                         ctx->dist_tab, ctx->n_dist, ctx->dd, C, logl);
+    hipLaunchKernelGGL(k_dist_marg, dim3((unsigned)dblocks), dim3(64 * kDistWaves), 0, st, zbuf, n, ctx->dist_tab,
+                       ctx->n_dist, ctx->dd, logl);
   } else {
     const int64_t dblocks = (n + 3) / 4;
     if (prec == GW_PREC_MIXED)

@@ -324,6 +324,21 @@ struct HetConst {
   double dd;
 };
 
+// exp(-2 pi i r), FP64, from tab [256] = (cos, sin)(2 pi k / 256) in LDS:
+// |a| <= pi / 256 about the nearest point, cos a - 1 and sin a by their Taylor
+// polynomials (first dropped terms 1.3e-20 and 8e-18).  19 vector operations
+// and a gather against 31 of sincos_cycles; k_het has LDS time to spare.
+__device__ inline void het_phasor_tab(double r, const double2* __restrict__ tab, double* gr, double* gi) {
+  const double q = rint(r * 256.0);
+  const double a = fma(q, -1.0 / 256.0, r) * kTwoPi;
+  const double2 t = tab[(int)q & 255];
+  const double a2 = a * a;
+  const double sn = fma(a * a2, fma(a2, 1.0 / 120.0, -1.0 / 6.0), a);
+  const double cm = a2 * fma(a2, fma(a2, -1.0 / 720.0, 1.0 / 24.0), -0.5);
+  *gr = fma(t.x, cm, fma(-t.y, sn, t.x));
+  *gi = -fma(t.y, cm, fma(t.x, sn, t.y));
+}
+
 template <int PREC>
 __device__ inline void het_phasor(double r, const TrigConsts& T, double* gr, double* gi) {
   if (PREC == 0) {
@@ -349,6 +364,14 @@ __device__ inline void het_phasor(double r, const TrigConsts& T, double* gr, dou
 // whole workgroup, then wave-uniform broadcast reads).  Per lane the partial
 // (Z_i, <h_i|h_i>) of the chunk's bins go to ab->part, without the
 // (A P_i) / (A0 P0_i) prefactor.
+//
+// FP64, 20,011 rows of 5000 bins, three detectors: 398 us, of which the vector
+// operations (107 an edge and row) take 270 at full rate and LDS 240; 552 us with
+// sincos_cycles and every row choosing the edge's weight.  Mixed, 65,536 rows of
+// 500 bins: 124 us (145), half of it LDS reads of the records (8 cycles per 16
+// bytes, broadcast or not).  Two rows a lane instead of one leave three waves a
+// SIMD (584 and 150 us), records as scalar loads wait for them (16,000 rows of
+// 5000 bins, mixed: 452 us a call against 396).
 constexpr int kLdsEdges = 128;
 
 template <int ND, int PREC>
@@ -357,6 +380,14 @@ __global__ void __launch_bounds__(256) k_het(const HetArgs* __restrict__ ab, con
   constexpr int RS = het_rs(ND);
   constexpr int BO = het_bin_off(ND);
   __shared__ double srec[kLdsEdges * RS];
+  __shared__ double2 tab[PREC == 0 ? 256 : 1];
+  if (PREC == 0) {
+    for (int k = threadIdx.x; k < 256; k += blockDim.x) {
+      double s, c;
+      sincospi((double)k / 128.0, &s, &c);
+      tab[k] = make_double2(c, s);
+    }
+  }
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int wpb = blockDim.x >> 6;
@@ -399,30 +430,35 @@ __global__ void __launch_bounds__(256) k_het(const HetArgs* __restrict__ ab, con
     for (int e0 = b0; e0 <= e_last; e0 += kLdsEdges) {
       const int ne = e_last - e0 + 1 < kLdsEdges ? e_last - e0 + 1 : kLdsEdges;
       __syncthreads();
-      for (int j = threadIdx.x; j < ne * RS; j += blockDim.x) srec[j] = rec[(int64_t)e0 * RS + j];
+      // Edges inside the chunk's bins (b0, b1] weigh C, its first the left-edge
+      // part C - R, its last the right-edge part R: set here, not per row (30 of
+      // 172 vector operations an edge in FP64)
+      for (int j = threadIdx.x; j < ne * RS; j += blockDim.x) {
+        const int e = e0 + j / RS, col = j % RS - (BO + 1);
+        const double* src = rec + (int64_t)e0 * RS + j;
+        double v = *src;
+        if ((e == b0 || e == b1) && col >= 0 && col % 6 < 2) v = e == b0 ? v - src[2] : src[2];
+        srec[j] = v;
+      }
       __syncthreads();
       if (!has) continue;
       for (int el = 0; el < ne; ++el) {
-        const int e = e0 + el;
         const double* r = srec + el * RS;
         const double d0 = phase_cycles(c, r[H_X], r[H_X2], r[H_XM5], r[H_LNF]) - r[H_PHI0];
         const double f = r[H_F];
-        // weight of this edge in the chunk's bins (b0, b1]: C inside, the
-        // left-edge part C - R at b0, the right-edge part R at b1 (uniform)
-        const int side = e == b0 ? 1 : (e == b1 ? 2 : 0);
 #pragma unroll
         for (int i = 0; i < ND; ++i) {
-          const double di = i == 0 ? d0 : fma(f, dt[i], d0) - r[H_PHI0 + i];
           double gr, gi;
-          het_phasor<PREC>(di, T, &gr, &gi);
+          const double di = i == 0 ? d0 : fma(f, dt[i], d0) - r[H_PHI0 + i];
+          if constexpr (PREC == 0) het_phasor_tab(di, tab, &gr, &gi);
+          else het_phasor<PREC>(di, T, &gr, &gi);
           const double* w = r + BO + 1 + 6 * i;
-          const double kr = side == 0 ? w[0] : (side == 1 ? w[0] - w[2] : w[2]);
-          const double ki = side == 0 ? w[1] : (side == 1 ? w[1] - w[3] : w[3]);
-          zr[i] = fma(kr, gr, fma(-ki, gi, zr[i]));
-          zi[i] = fma(kr, gi, fma(ki, gr, zi[i]));
-          // |r0|^2 = (1 + Re(g_e conj g_{e-1})) / 2 for unit phasors; the
-          // constant half is added once per row by the combine kernel
-          if (e > b0) hh[i] = fma(w[4], fma(gr, pr[i], gi * pi[i]), hh[i]);
+          zr[i] = fma(w[0], gr, fma(-w[1], gi, zr[i]));
+          zi[i] = fma(w[0], gi, fma(w[1], gr, zi[i]));
+          // |r0|^2 = (1 + Re(g_e conj g_{e-1})) / 2 for unit phasors (no bin
+          // ends at the first edge: its predecessor is zero); the constant half
+          // is added once per row by the combine kernel
+          hh[i] = fma(w[4], fma(gr, pr[i], gi * pi[i]), hh[i]);
           pr[i] = gr;
           pi[i] = gi;
         }
@@ -498,32 +534,40 @@ __device__ inline void het_finish_row(const HetArgs* __restrict__ ab, int64_t ro
   }
 }
 
-// Large batches: one lane per row (coalesced over rows), the edge-chunk
-// partials summed in chunk order.
+// Large batches: a workgroup of four waves per 64-row tile, lane = row; each
+// wave sums some of the 3 nd columns over the edge chunks in chunk order, eight
+// loads in flight, and wave 0 finishes the rows.  20,011 rows of 53 chunks: 22
+// us, 65 with a wave a tile and a load at a time.
 __global__ void __launch_bounds__(256) k_het_combine(const HetArgs* __restrict__ ab, const int64_t* __restrict__ pre,
                                                      int nd, int n_ech, int marg, HetConst hc) {
+  __shared__ double col[3 * kMaxDet][64];
   const int lane = threadIdx.x & 63;
-  const int wpb = blockDim.x >> 6;
-  const int64_t wid = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6);
-  const int64_t nwaves = (int64_t)gridDim.x * wpb;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t total = pre[ab->n_sub];
   const int64_t ld = ab->ld;
-  for (int64_t t = wid; t < total; t += nwaves) {
+  for (int64_t t = blockIdx.x; t < total; t += gridDim.x) {
     int64_t row0, row_end;
-    if (!tile_rows(ab, pre, t, &row0, &row_end)) continue;
-    const int64_t row = row0 + lane;
-    if (row >= row_end) continue;
-    double zr[kMaxDet], zi[kMaxDet], hh[kMaxDet];
-    for (int i = 0; i < nd; ++i) {
-      zr[i] = zi[i] = hh[i] = 0.0;
-      for (int e = 0; e < n_ech; ++e) {
-        const double* p = ab->part + ((int64_t)e * 3 * nd + 3 * i) * ld + row;
-        zr[i] += p[0];
-        zi[i] += p[ld];
-        hh[i] += p[2 * ld];
-      }
+    if (!tile_rows(ab, pre, t, &row0, &row_end)) continue;  // the same for the workgroup
+    const int64_t row = row0 + lane < row_end ? row0 + lane : row0;
+    const int64_t step = (int64_t)3 * nd * ld;
+    for (int c = wave; c < 3 * nd; c += 4) {
+      const double* __restrict__ p = ab->part + c * ld + row;
+      double s = 0.0;
+#pragma unroll 8
+      for (int e = 0; e < n_ech; ++e) s += p[e * step];
+      col[c][lane] = s;
     }
-    het_finish_row(ab, row, nd, marg, zr, zi, hh, hc);
+    __syncthreads();
+    if (wave == 0 && row0 + lane < row_end) {
+      double zr[kMaxDet], zi[kMaxDet], hh[kMaxDet];
+      for (int i = 0; i < nd; ++i) {
+        zr[i] = col[3 * i][lane];
+        zi[i] = col[3 * i + 1][lane];
+        hh[i] = col[3 * i + 2][lane];
+      }
+      het_finish_row(ab, row, nd, marg, zr, zi, hh, hc);
+    }
+    __syncthreads();
   }
 }
 
@@ -567,7 +611,7 @@ __global__ void __launch_bounds__(256) k_het_combine_w(const HetArgs* __restrict
   }
 }
 
-// Distance marginal over the work list, small batches: one wave per row
+// Distance marginal over the work list, small batches and FP64: one wave per row
 // (wave_dist_lse), which keeps many waves busy when there are few rows.
 template <int PREC>
 __global__ void __launch_bounds__(256) k_het_dist_w(const HetArgs* __restrict__ ab, const int64_t* __restrict__ pre,
@@ -657,18 +701,16 @@ __global__ void __launch_bounds__(256) k_het_combine_dist_w(const HetArgs* __res
   }
 }
 
-// Distance marginal over the work list, large batches: a workgroup per 64-row
+// Distance marginal over the work list, large mixed batches: a workgroup per 64-row
 // tile, lane = row, waves splitting the grid (block_dist_lse), so that grid
 // records are scalar loads shared by 64 rows.
 constexpr int64_t kDistRowsPerLane = 8192;  // batches from this size use the sliced form
 constexpr int kHetDistWaves = 8;  // waves per 64-row tile in the sliced form
 
-template <int PREC>
 __global__ void __launch_bounds__(64 * kHetDistWaves) k_het_dist(const HetArgs* __restrict__ ab,
                                                                  const int64_t* __restrict__ pre,
                                                                  const double* __restrict__ dtab, int n_dist,
-                                                                 double dd, const LogI0Consts* __restrict__ Cp) {
-  const LogI0Consts& C = *Cp;
+                                                                 double dd) {
   __shared__ double red[kHetDistWaves * 64];
   const int lane = threadIdx.x & 63;
   const int nw = blockDim.x >> 6;
@@ -683,7 +725,7 @@ __global__ void __launch_bounds__(64 * kHetDistWaves) k_het_dist(const HetArgs* 
     const int64_t rr = active ? row : (has ? row0 : 0);
     const double z1 = has ? ab->zbuf[rr] : 0.0;
     const double h1 = has ? ab->zbuf[ld + rr] : 0.0;
-    const double v = block_dist_lse<PREC>(z1 < 0.0 ? 0.0 : z1, h1, dtab, n_dist, nw, red, C);
+    const double v = block_dist_lse(z1 < 0.0 ? 0.0 : z1, h1, dtab, n_dist, nw, red);
     if ((threadIdx.x >> 6) == 0 && active) ab->logl[row] = z1 < 0.0 ? -INFINITY : -0.5 * dd + v;
   }
 }
@@ -841,19 +883,17 @@ static gw_status enqueue_het(gw_ctx* ctx, int marg, int prec, int n_ech, hipStre
     hipLaunchKernelGGL(k_het_combine_w, dim3(256 * 8), dim3(256), 0, st, h->args, h->tile_pre, ctx->n_det, n_ech,
                        marg, hc);
   else
-    hipLaunchKernelGGL(k_het_combine, dim3(256 * 4), dim3(256), 0, st, h->args, h->tile_pre, ctx->n_det, n_ech,
+    hipLaunchKernelGGL(k_het_combine, dim3(256 * 8), dim3(256), 0, st, h->args, h->tile_pre, ctx->n_det, n_ech,
                        marg, hc);
   s = check_hip(hipGetLastError(), "heterodyne combine launch");
   if (s != GW_OK || marg != 2) return s;
-  // large batches: lane = row (grid records are scalar loads shared by 64
-  // rows); small batches: wave = row
-  const bool sliced = h->n_rows_last >= kDistRowsPerLane;
-  if (sliced && prec == GW_PREC_MIXED)
-    hipLaunchKernelGGL(k_het_dist<1>, dim3(256 * 8), dim3(64 * kHetDistWaves), 0, st, h->args, h->tile_pre,
-                       ctx->dist_tab, ctx->n_dist, ctx->dd, ctx->i0c);
-  else if (sliced)
-    hipLaunchKernelGGL(k_het_dist<0>, dim3(256 * 8), dim3(64 * kHetDistWaves), 0, st, h->args, h->tile_pre,
-                       ctx->dist_tab, ctx->n_dist, ctx->dd, ctx->i0c);
+  // large mixed batches: lane = row (grid records are scalar loads shared by
+  // 64 rows).  Small ones and FP64: wave = row; its lanes are neighbouring
+  // distances, which take the same form of a term (skipped, FP32, series or
+  // asymptotic), while rows differ: 20,011 rows in FP64 take 85 us against 230
+  if (h->n_rows_last >= kDistRowsPerLane && prec == GW_PREC_MIXED)
+    hipLaunchKernelGGL(k_het_dist, dim3(256 * 8), dim3(64 * kHetDistWaves), 0, st, h->args, h->tile_pre,
+                       ctx->dist_tab, ctx->n_dist, ctx->dd);
   else if (prec == GW_PREC_MIXED)
     hipLaunchKernelGGL(k_het_dist_w<1>, dim3(256 * 8), dim3(256), 0, st, h->args, h->tile_pre, ctx->dist_tab,
                        ctx->n_dist, ctx->dd, ctx->i0c);
