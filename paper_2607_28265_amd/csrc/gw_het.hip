@@ -818,9 +818,13 @@ static int het_ech(const gw_ctx* ctx, int64_t n_rows) {
   // 64 chunks (one lane each in the combine) of at least 8 edges: a
   // sampler's 250-row batch of 500 bins takes 31.2 us a call at 62 chunks
   // against 36.0 at 31
+  // Large batches take at least 48 bins a chunk: its start and its partials
+  // (three per detector and row) weigh more than the waves it adds (mixed, 500
+  // bins: 12,000 rows 109 us at 62 chunks and 84 at 10, 30,000 rows 141 at 35
+  // and 133 at 10).
   const int64_t tiles = (n_rows + 63) / 64;
   int64_t e = (kHetWaves + tiles - 1) / tiles;
-  const int64_t emax = std::max<int64_t>(1, std::min<int64_t>(64, nb / 8));
+  const int64_t emax = std::max<int64_t>(1, std::min<int64_t>(64, nb / (n_rows >= kDistRowsPerLane ? 48 : 8)));
   e = std::max<int64_t>(1, std::min(e, emax));
   return (int)e;
 }
