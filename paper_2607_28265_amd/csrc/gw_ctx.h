@@ -39,8 +39,7 @@ struct TgCover {
 struct TmGrid {
   NodeTable tab;
   double* bins_w = nullptr;
-  int32_t* idx = nullptr;
-  const int32_t* cell = nullptr;
+  const int32_t *idx = nullptr, *cell = nullptr;  // in bins_w's allocation
   const int4* chunk = nullptr;
   TgCover cov[2];
   int n_chunk = 0, n_dense = 0, n_pts = 0;  // n_pts: points of a row, the larger of the two covers
@@ -61,6 +60,8 @@ struct gw_ctx {
   NodeTable nodes, nodes_wide;
   TmGrid tm_grid;
   gw::NodeCheck node_check{};
+  std::vector<double> node_slope;  // S(f), 64 points an octave
+  gw::PhaseCoef node_ref{};        // the nodes' reference waveform
   gw::NodeCheck* node_check_dev = nullptr;
   // distance grid
   double* dist_tab = nullptr;      // [n_dist][4]: d, 1/d, 1/(2 d^2), ln w

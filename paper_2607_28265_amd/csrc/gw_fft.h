@@ -16,8 +16,10 @@ namespace gw {
 
 __host__ __device__ inline double2 c_add(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __host__ __device__ inline double2 c_sub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+// multiply-adds written out: left to contraction, the forms of a kernel round
+// differently
 __host__ __device__ inline double2 c_mul(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+  return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 // a times -i
 __host__ __device__ inline double2 c_mul_mi(double2 a) { return make_double2(a.y, -a.x); }

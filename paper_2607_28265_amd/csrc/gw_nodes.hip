@@ -137,15 +137,16 @@ static double envelope(const std::vector<PhaseCoef>& w, double f) {
 
 // S(f) by bin: the envelope on a grid fine enough for the larger of two
 // neighbours to bound what lies between (power laws; 64 points an octave).
+static void slope_bound(const Geom& g, const std::vector<PhaseCoef>& w, std::vector<double>* e) {
+  const double k0 = (double)g.k0, f0 = k0 * g.df, top = (k0 + (double)(g.n_freq - 1)) / k0;
+  const int n = 2 + (int)(64.0 * log2(top > 1.0 ? top : 1.0));
+  e->resize(n + 1);
+  for (int j = 0; j <= n; ++j) (*e)[j] = envelope(w, f0 * exp2(j / 64.0));
+}
+
 struct SlopeBound {
-  std::vector<double> e;
+  const std::vector<double>& e;
   double k0;
-  SlopeBound(const Geom& g, const std::vector<PhaseCoef>& w) : k0((double)g.k0) {
-    const double f0 = k0 * g.df, top = (k0 + (double)(g.n_freq - 1)) / k0;
-    const int n = 2 + (int)(64.0 * log2(top > 1.0 ? top : 1.0));
-    e.resize(n + 1);
-    for (int j = 0; j <= n; ++j) e[j] = envelope(w, f0 * exp2(j / 64.0));
-  }
   double at(int k) const {
     const int j = std::min((int)(64.0 * log2((k0 + k) / k0)), (int)e.size() - 2);
     return fmax(e[j], e[j + 1]);
@@ -157,11 +158,11 @@ struct SlopeBound {
 // Partition of the band: from the lowest bin up, the block length (growing by
 // a quarter at a time, at most a sixth of its frequency, at most kNodeMax
 // nodes) with the fewest nodes per bin.
-static void partition(const gw_ctx* ctx, const std::vector<PhaseCoef>& w, double tau, std::vector<NodePlace>* out) {
+static void partition(const gw_ctx* ctx, double tau, std::vector<NodePlace>* out) {
   const Geom& g = ctx->geom;
   const int nf = (int)g.n_freq;
   const NodeCount node_count;
-  const SlopeBound slope(g, w);
+  const SlopeBound slope{ctx->node_slope, (double)g.k0};
   for (int k = 0; k < nf;) {
     double best = 0.9;
     int bl = std::min(8, nf - k), bn = bl;  // a node per bin
@@ -206,20 +207,19 @@ static gw_status node_table(gw_ctx* ctx, const PhaseCoef& ref, const std::vector
     r[4] = f;
     fill(q, r + node_rs(nd));
   }
+  // the places behind the records: one allocation and one copy
+  static_assert(sizeof(NodePlace) == 2 * sizeof(double), "two columns a place");
+  const size_t n_rec = rec.size();
+  rec.resize(n_rec + 2 * n);
+  if (n > 0) memcpy(&rec[n_rec], place.data(), n * sizeof(NodePlace));
   gw_status s = check_hip(hipMalloc((void**)&out->rec, rec.size() * sizeof(double)), "node records");
   if (s == GW_OK)
     s = check_hip(hipMemcpy(out->rec, rec.data(), rec.size() * sizeof(double), hipMemcpyHostToDevice), "records");
   if (s != GW_OK || n == 0) return s;
-  NodePlace* d = nullptr;
-  s = check_hip(hipMalloc((void**)&d, n * sizeof(NodePlace)), "node places");
-  if (s == GW_OK) s = check_hip(hipMemcpy(d, place.data(), n * sizeof(NodePlace), hipMemcpyHostToDevice), "places");
-  if (s == GW_OK) {
-    hipLaunchKernelGGL(k_node_weights, dim3((unsigned)n), dim3(256), 0, nullptr, (const NodePlace*)d,
-                       (const double*)ctx->bins, nd, ref, make_trig_consts(), rs, out->rec);
-    s = check_hip(hipGetLastError(), "node weights launch");
-  }
+  hipLaunchKernelGGL(k_node_weights, dim3((unsigned)n), dim3(256), 0, nullptr, (const NodePlace*)(out->rec + n_rec),
+                     (const double*)ctx->bins, nd, ref, make_trig_consts(), rs, out->rec);
+  s = check_hip(hipGetLastError(), "node weights launch");
   if (s == GW_OK) s = check_hip(hipStreamSynchronize(nullptr), "node weights");
-  if (d) (void)hipFree(d);
   if (s == GW_OK) out->n = (int)n;
   return s;
 }
@@ -252,21 +252,20 @@ gw_status nodes_init(gw_ctx* ctx) {
   // plus the light travel times; at most a quarter second
   c.tau_max = fmin(0.1 + 2.0 * travel_time(g), kTauCap);
   std::vector<NodePlace> place;
-  partition(ctx, w, c.tau_max, &place);
+  slope_bound(g, w, &ctx->node_slope);
+  ctx->node_ref = w[0];
+  partition(ctx, c.tau_max, &place);
   s = check_hip(hipMalloc((void**)&ctx->node_check_dev, sizeof(NodeCheck)), "node check");
   if (s == GW_OK) s = check_hip(hipMemcpy(ctx->node_check_dev, &c, sizeof(c), hipMemcpyHostToDevice), "node check");
-  if (s == GW_OK) s = node_table(ctx, w[0], place, &ctx->nodes);
+  if (s == GW_OK) s = node_table(ctx, ctx->node_ref, place, &ctx->nodes);
   return s;
 }
 
 gw_status nodes_wide_init(gw_ctx* ctx) {
   if (ctx->nodes_wide.rec) return GW_OK;
-  std::vector<PhaseCoef> w;
   std::vector<NodePlace> place;
-  const gw_status s = node_waveforms(ctx, &w);
-  if (s != GW_OK) return s;
-  partition(ctx, w, kTauCap, &place);
-  return node_table(ctx, w[0], place, &ctx->nodes_wide);
+  partition(ctx, kTauCap, &place);
+  return node_table(ctx, ctx->node_ref, place, &ctx->nodes_wide);
 }
 
 // A wave's nodes, at least and at most, and the waves aimed at per 64 rows; a
@@ -287,11 +286,8 @@ gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
   tm_grid_free(ctx);
   const Geom& geom = ctx->geom;
   const int nf = (int)geom.n_freq, nd = ctx->n_det;
-  std::vector<PhaseCoef> w;
-  gw_status s = node_waveforms(ctx, &w);
-  if (s != GW_OK) return s;
   std::vector<NodePlace> place;
-  partition(ctx, w, (double)g.J * g.delta + travel_time(geom), &place);
+  partition(ctx, (double)g.J * g.delta + travel_time(geom), &place);
   // Chebyshev nodes come from the top of their block down
   for (size_t q = 0; q < place.size();) {
     const size_t m = place[q].n;
@@ -340,7 +336,7 @@ gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
   const int cell_bins = (g.blk + 1) / 2;
   std::vector<double> bw((size_t)cell_bins * kTgW);
   for (int k = 0; k < cell_bins; ++k) win.weights((double)k / g.cell, &bw[(size_t)k * kTgW]);
-  // one allocation of the integers, those read by fours first
+  // one allocation: the weights, then the integers, those read by fours first
   const int nc = (int)a0.size();
   std::vector<int32_t> idx;
   for (int c = 0; c < nc; ++c)
@@ -351,19 +347,20 @@ gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
     at[i] = idx.size();
     idx.insert(idx.end(), parts[i]->begin(), parts[i]->end());
   }
-  s = node_table(ctx, w[0], place, kTgW, [&](size_t q, double* v) {
+  gw_status s = node_table(ctx, ctx->node_ref, place, kTgW, [&](size_t q, double* v) {
     win.weights((place[q].kb + node_offset(place[q])) / g.cell - cell[q], v);
   }, &t.tab);
-  if (s == GW_OK) s = check_hip(hipMalloc((void**)&t.idx, idx.size() * sizeof(int32_t)), "time-grid chunks");
+  const size_t n_bw = bw.size();
+  bw.resize(n_bw + (idx.size() + 1) / 2);
+  memcpy(&bw[n_bw], idx.data(), idx.size() * sizeof(int32_t));
+  if (s == GW_OK) s = check_hip(hipMalloc((void**)&t.bins_w, bw.size() * sizeof(double)), "time-grid tables");
   if (s == GW_OK)
-    s = check_hip(hipMemcpy(t.idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice), "chunks");
-  if (s == GW_OK) s = check_hip(hipMalloc((void**)&t.bins_w, bw.size() * sizeof(double)), "time-grid weights");
-  if (s == GW_OK)
-    s = check_hip(hipMemcpy(t.bins_w, bw.data(), bw.size() * sizeof(double), hipMemcpyHostToDevice), "weights");
+    s = check_hip(hipMemcpy(t.bins_w, bw.data(), bw.size() * sizeof(double), hipMemcpyHostToDevice), "tables");
   if (s != GW_OK) {
     tm_grid_free(ctx);
     return s;
   }
+  t.idx = (const int32_t*)(t.bins_w + n_bw);
   t.chunk = (const int4*)t.idx;
   t.cell = t.idx + at[2];
   t.cov[0] = TgCover{(const int4*)(t.idx + at[0]), t.idx + at[3], cn.n_many};
@@ -380,7 +377,6 @@ gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
 void tm_grid_free(gw_ctx* ctx) {
   TmGrid& t = ctx->tm_grid;
   if (t.tab.rec) (void)hipFree(t.tab.rec);
-  if (t.idx) (void)hipFree(t.idx);
   if (t.bins_w) (void)hipFree(t.bins_w);
   t = TmGrid{};
 }

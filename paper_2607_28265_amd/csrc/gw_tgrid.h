@@ -100,15 +100,20 @@ __host__ __device__ inline double2 w32(int k) {
 constexpr int kTgW = 14;
 constexpr int kTgLead = kTgW / 2 - 1;  // grid points before the sample's cell
 
-inline double tgrid_i0(double x) {
-  long double t = 1.0L, s = 1.0L;
-  const long double q = 0.25L * (long double)x * (long double)x;
-  for (int k = 1; k < 200 && t > 1e-22L * s; ++k) {
-    t *= q / ((long double)k * (long double)k);
-    s += t;
+// I0(x), 0 <= x <= 44, by its power series (85 terms: the rest below 1e-30).
+struct TgBessel {
+  double c[85];
+  TgBessel() {
+    c[0] = 1.0;
+    for (int k = 1; k < 85; ++k) c[k] = c[k - 1] / ((double)k * (double)k);
   }
-  return (double)s;
-}
+  double operator()(double x) const {
+    const double q = 0.25 * x * x;
+    double s = c[84];
+    for (int k = 83; k >= 0; --k) s = fma(s, q, c[k]);
+    return s;
+  }
+};
 
 // Shape for |nu| <= nu_max: close to the largest beta that keeps the images
 // at |nu| >= 1 - nu_max beyond the main lobe, 2 % below it (measured error
@@ -116,35 +121,38 @@ inline double tgrid_i0(double x) {
 // window), 6e-13 at 1/4; 0.96 and 1.0 of it 7e-13 and 2e-12 there).
 inline double tgrid_beta(double nu_max) { return 0.98 * 3.141592653589793 * kTgW * (1.0 - nu_max); }
 
-// psi and psi_hat for one shape, and the kTgW weights of a sample at offset s
-// of its cell (0 <= s < 1): grid point m of the window is s + kTgLead - m away.
+inline double tgrid_psi_hat(double nu, double beta, double i0_beta) {
+  const double x = 3.141592653589793 * kTgW * nu, a = sqrt(beta * beta - x * x);
+  return kTgW * sinh(a) / (a * i0_beta);
+}
+
+// The kTgW weights of a sample at offset s of its cell (0 <= s < 1): grid
+// point m of the window is s + kTgLead - m away.
 // I0(beta sqrt(1 - u^2)) is analytic in u, so each weight is a Chebyshev series
 // in s (26 terms: the rest below 1e-17), a tenth of the work of its Bessel
 // series.
 struct TgWindow {
   static constexpr int kTerms = 26;
-  double beta, i0_beta, c[kTerms][kTgW];
+  double c[kTerms][kTgW];
 
-  explicit TgWindow(double b) : beta(b), i0_beta(tgrid_i0(b)) {
+  explicit TgWindow(double beta) {
+    const TgBessel i0;
+    const double i0_beta = i0(beta);
     double v[kTerms][kTgW];
     for (int j = 0; j < kTerms; ++j)
-      for (int m = 0; m < kTgW; ++m) v[j][m] = psi(0.5 + 0.5 * cos(angle(1, j)) + kTgLead - m);
-    for (int k = 0; k < kTerms; ++k)
       for (int m = 0; m < kTgW; ++m) {
-        double t = 0.0;
-        for (int j = 0; j < kTerms; ++j) t += v[j][m] * cos(angle(k, j));
-        c[k][m] = (k == 0 ? 1.0 : 2.0) / kTerms * t;
+        const double u = 2.0 / kTgW * (0.5 + 0.5 * cos(angle(1, j)) + kTgLead - m);
+        v[j][m] = i0(beta * sqrt(1.0 - u * u)) / i0_beta;
       }
+    for (int k = 0; k < kTerms; ++k) {
+      for (int m = 0; m < kTgW; ++m) c[k][m] = 0.0;
+      for (int j = 0; j < kTerms; ++j) {
+        const double t = (k == 0 ? 1.0 : 2.0) / kTerms * cos(angle(k, j));
+        for (int m = 0; m < kTgW; ++m) c[k][m] += t * v[j][m];
+      }
+    }
   }
   static double angle(int k, int j) { return 3.141592653589793 * k * (j + 0.5) / kTerms; }
-  double psi(double x) const {
-    const double u = 2.0 * x / kTgW;
-    return u * u < 1.0 ? tgrid_i0(beta * sqrt(1.0 - u * u)) / i0_beta : 0.0;
-  }
-  double psi_hat(double nu) const {
-    const double x = 3.141592653589793 * kTgW * nu, a = sqrt(beta * beta - x * x);
-    return kTgW * sinh(a) / (a * i0_beta);
-  }
   void weights(double s, double* w) const {
     const double t = 2.0 * s - 1.0;
     double p[kTgW] = {}, q[kTgW] = {};

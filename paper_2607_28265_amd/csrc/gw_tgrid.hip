@@ -415,9 +415,9 @@ gw_status tgrid_tables(gw_ctx* ctx, int L, int jmax) {
   if (ctx->tm_dec && ctx->tm_dec_L == L && ctx->tm_dec_jmax == jmax) return GW_OK;
   int D1, D2;
   if (!tgrid_plan(L, &D1, &D2)) return set_error(GW_ENOTSUP, "time marginal: transform length %d not supported", L);
-  const TgWindow win(tgrid_beta((double)jmax / (2.0 * L)));
+  const double beta = tgrid_beta((double)jmax / (2.0 * L)), i0_beta = TgBessel()(beta);
   std::vector<double> h(jmax + 1);
-  for (int j = 0; j <= jmax; ++j) h[j] = 1.0 / win.psi_hat((double)j / (2.0 * L));
+  for (int j = 0; j <= jmax; ++j) h[j] = 1.0 / tgrid_psi_hat((double)j / (2.0 * L), beta, i0_beta);
   if (ctx->tm_dec) (void)hipFree(ctx->tm_dec);
   ctx->tm_dec = nullptr;
   ctx->tm_dec_L = 0;
