@@ -62,3 +62,22 @@ def test_large_full_batches_distance(prec, tol):
         ok = np.isfinite(ref)
         assert np.array_equal(np.isfinite(got), ok)
         assert np.max(np.abs(got - ref)[ok]) < tol
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 66])
+def test_small_full_batches_distance(n):
+    """Four rows a workgroup: ragged ends, rows over nodes and over bins."""
+    import paper_2607_28265_amd as gw
+    prob = gwsynth.make_problem(8.0, 20.0, 512.0, psd_scale=1e-47, n_det=2, n_dist=300)
+    th = gwsynth.prior_draws(gwsynth.SEEDS["injection"], 1)[0]
+    prob = with_injection(prob, th)
+    few, _ = _rows(th, 97)
+    few[1::7, 0] = 0.9  # outside the node tables
+    with gw.Context(prob) as ctx:
+        t = torch.from_numpy(few).cuda()
+        for prec, tol in ((0, 1e-9), (1, 1e-4)):
+            ref = ctx.loglike(t, marg=2, prec=prec).cpu().numpy()
+            got = ctx.loglike(t[:n].contiguous(), marg=2, prec=prec).cpu().numpy()
+            ok = np.isfinite(ref[:n])
+            assert np.array_equal(np.isfinite(got), ok)
+            assert np.max(np.abs(got - ref[:n])[ok]) < tol
