@@ -110,7 +110,7 @@ struct TgBessel {
   double operator()(double x) const {
     const double q = 0.25 * x * x;
     double s = c[84];
-    for (int k = 83; k >= 0; --k) s = fma(s, q, c[k]);
+    for (int k = 83; k >= 0; --k) s = s * q + c[k];
     return s;
   }
 };
