@@ -205,7 +205,6 @@ gw_status gw_ctx_create(const gw_problem* pr, int32_t device, gw_ctx** out) {
       tab[4 * j + 1] = 1.0 / d;
       tab[4 * j + 2] = 0.5 / (d * d);
       tab[4 * j + 3] = pr->dist_logw[j];
-      ctx->dist_r1max = fmax(ctx->dist_r1max, 1.0 / d);
     }
     st = check_hip(hipMalloc((void**)&ctx->dist_tab, tab.size() * sizeof(double)), "dist alloc");
     if (st == GW_OK)
@@ -213,9 +212,7 @@ gw_status gw_ctx_create(const gw_problem* pr, int32_t device, gw_ctx** out) {
                      "dist copy");
   }
   if (st == GW_OK) {
-    LogI0Consts c = make_log_i0_consts();
-    c.r1max = ctx->dist_r1max;
-    for (double dj : ctx->h_dist_grid) c.dmax = fmax(c.dmax, dj);
+    const LogI0Consts c = make_log_i0_consts();
     st = check_hip(hipMalloc((void**)&ctx->i0c, sizeof(LogI0Consts)), "ln I0 table alloc");
     if (st == GW_OK) st = check_hip(hipMemcpy(ctx->i0c, &c, sizeof(c), hipMemcpyHostToDevice), "ln I0 table copy");
   }

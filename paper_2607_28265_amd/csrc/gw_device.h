@@ -326,16 +326,12 @@ constexpr I0Coefs kI0 = make_i0_coefs();
 // Per-context constants of the distance marginal (kernels take them by
 // device pointer).
 struct LogI0Consts {
-  double r1max;  // largest 1/d of the distance grid (bounds x = |Z1| / d); 0 if unknown
-  double dmax;   // largest d of the grid (bounds u = 1/x = d / |Z1|); 0 if unknown
   double exp2_64[64];  // 2^(i/64), i < 64, rounded to FP64 (for exp_nonpos)
 };
 
 // The host fills exp2_64 from long-double 2^(i/64).
 inline LogI0Consts make_log_i0_consts() {
   LogI0Consts c;
-  c.r1max = 0.0;
-  c.dmax = 0.0;
   for (int i = 0; i < 64; ++i) c.exp2_64[i] = (double)exp2l((long double)i / 64.0L);
   return c;
 }
@@ -407,58 +403,28 @@ __device__ inline double i0_asym_k(double u) {
 
 __device__ inline double i0_asym(double u) { return i0_asym_k<24>(u); }
 
-// Series length for every u <= umax: the first dropped term c_K u^K is below
-// 1e-17 for K = 10, 13, 16 up to u = 0.01, 0.02, 0.03 (x >= 100, 50, 33);
-// otherwise the full 24 terms (below 1e-16 at u = 0.05, x = 20).
-__device__ inline int asym_tier(double umax) {
-  return umax <= 0.01 ? 0 : (umax <= 0.02 ? 1 : (umax <= 0.03 ? 2 : 3));
+// The series at the least length that serves every active lane.  Lanes hold
+// neighbouring grid points, whose arguments are alike, so this is far less than
+// the longest a row can need.  The first dropped term is below 1e-17: c_K u^K
+// for K = 10, 13, 16 up to u = 0.01, 0.02, 0.03 (x >= 100, 50, 33), otherwise the
+// full 24 terms (below 1e-16 at u = 0.05, x = 20).
+__device__ inline double i0_asym_wave(double u) {
+  if (!__any(u > 0.01)) return i0_asym_k<10>(u);
+  if (!__any(u > 0.02)) return i0_asym_k<13>(u);
+  if (!__any(u > 0.03)) return i0_asym_k<16>(u);
+  return i0_asym_k<24>(u);
 }
 
-__device__ inline double i0_asym_tier(int tier, double u) {
-  switch (tier) {
-    case 0: return i0_asym_k<10>(u);
-    case 1: return i0_asym_k<13>(u);
-    case 2: return i0_asym_k<16>(u);
-    default: return i0_asym_k<24>(u);
-  }
-}
-
-// Series length for every y <= ymax: the first dropped term y^K / (K!)^2 is
-// below 1e-17 (and I0 >= 1) for K = 8, 12, 16, 24 up to y = 0.106, 1.07, 4.00,
+// y^K / (K!)^2 (and I0 >= 1) for K = 8, 12, 16, 24 up to y = 0.106, 1.07, 4.00,
 // 18.8; otherwise the full 40 terms (enough for y <= 100, i.e. x < 20).
-__device__ inline int i0_tier(double ymax) {
-  return ymax <= 0.106 ? 0 : (ymax <= 1.07 ? 1 : (ymax <= 4.0 ? 2 : (ymax <= 18.8 ? 3 : 4)));
-}
-
-__device__ inline double i0_series_tier(int tier, double y) {
-  switch (tier) {
-    case 0: return i0_series<8>(y);
-    case 1: return i0_series<12>(y);
-    case 2: return i0_series<16>(y);
-    case 3: return i0_series<24>(y);
-    default: return i0_series<40>(y);
+__device__ inline double i0_series_wave(double y) {
+  if (!__any(y > 4.0)) {
+    if (!__any(y > 0.106)) return i0_series<8>(y);
+    if (!__any(y > 1.07)) return i0_series<12>(y);
+    return i0_series<16>(y);
   }
-}
-
-// Wave-uniform series tier for arguments up to x = z1 * r1max (z1 may differ
-// between lanes): the largest need over the wave.
-__device__ inline int wave_i0_tier(double z1, const LogI0Consts& C) {
-  if (!(C.r1max > 0.0)) return 4;
-  const double x = z1 * C.r1max;
-  double y = 0.25 * x * x;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) y = fmax(y, __shfl_xor(y, o, 64));
-  return __builtin_amdgcn_readfirstlane(i0_tier(y));
-}
-
-// Wave-uniform tier of the large-argument series for u = d / z1 up to
-// dmax / z1 (only arguments x >= 20, u <= 0.05, take that series).
-__device__ inline int wave_asym_tier(double z1, const LogI0Consts& C) {
-  if (!(C.dmax > 0.0)) return 3;
-  double u = z1 > 0.0 ? C.dmax / z1 : 1.0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) u = fmax(u, __shfl_xor(u, o, 64));
-  return __builtin_amdgcn_readfirstlane(asym_tier(u));
+  if (!__any(y > 18.8)) return i0_series<24>(y);
+  return i0_series<40>(y);
 }
 
 // ln I0(x) given x and u = 1/x (u is only used when x >= 20).
@@ -548,7 +514,6 @@ __device__ inline double wave_dist_lse(double z1, double hh1, const double* __re
   const double bmax = wave_dist_bound(z1, hh1, tab, n_dist, lane);
   const double cut = bmax - 60.0, fine = bmax - 35.0;
   const double iz = z1 > 0.0 ? 1.0 / z1 : 0.0;
-  const int tier = wave_i0_tier(z1, C), atier = wave_asym_tier(z1, C);
   double s = 0.0;
   for (int j = lane; j < n_dist; j += 64) {
     const double* r = tab + 4 * j;
@@ -561,11 +526,11 @@ __device__ inline double wave_dist_lse(double z1, double hh1, const double* __re
     }
     double v, e;
     if (x < 20.0) {
-      v = i0_series_tier(tier, 0.25 * x * x);
+      v = i0_series_wave(0.25 * x * x);
       e = a - bmax;
     } else {
       const double u = r[0] * iz;  // 1 / x
-      const double p = i0_asym_tier(atier, u);
+      const double p = i0_asym_wave(u);
       v = p * sqrt(u * kInvTwoPi);
       e = (a + x) - bmax;
     }

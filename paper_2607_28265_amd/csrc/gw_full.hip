@@ -1700,7 +1700,7 @@ gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_
                             double* zbuf, hipStream_t st, double node_from) {
   if (n == 0) return GW_OK;
   const int64_t blocks = (n + 63) / 64;
-  const LogI0Consts* C = ctx->i0c;  // device copy, r1max from the distance grid
+  const LogI0Consts* C = ctx->i0c;
   int groups = n_chunks, cstride = 1;
   if (n <= 2048 && n_chunks >= 64 && nch_node <= 0) {
     // few rows, many chunks: reduce groups of 8 chunks across the chip first

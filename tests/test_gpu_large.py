@@ -81,3 +81,22 @@ def test_small_full_batches_distance(n):
             ok = np.isfinite(ref[:n])
             assert np.array_equal(np.isfinite(got), ok)
             assert np.max(np.abs(got - ref[:n])[ok]) < tol
+
+
+@pytest.mark.parametrize("psd_scale", [1e-43, 1e-45, 1e-46, 1e-47, 1e-48, 1e-49])
+def test_fp64_distance_series_lengths(psd_scale):
+    """From x = |Z1| / d far below 1 to hundreds: every length of the two I0
+    series, against the oracle (the FP64 form's 1e-6)."""
+    import paper_2607_28265_amd as gw
+    from oracle import likelihood as L
+    from tests.gpu_common import oracle_many
+    prob = gwsynth.make_problem(4.0, 20.0, 256.0, psd_scale=psd_scale, n_dist=200)
+    th = gwsynth.prior_draws(gwsynth.SEEDS["injection"], 1)[0]
+    prob = with_injection(prob, th)
+    few, _ = _rows(th, 97)
+    ref = oracle_many(few, prob, L.PHASE_DIST)
+    ok = np.isfinite(ref)
+    with gw.Context(prob) as ctx:
+        got = ctx.loglike(torch.from_numpy(few).cuda(), marg=2, prec=0).cpu().numpy()
+        assert np.array_equal(np.isfinite(got), ok)
+        assert np.max(np.abs(got - ref)[ok]) < 1e-6
