@@ -39,14 +39,13 @@ PEAK_FP64_TFLOPS = 78.6  # MI355X FP64 vector, dense
 
 # HBM bytes per launch from two rocprofv3 PMC runs (FETCH_SIZE, WRITE_SIZE)
 # scaled by what the same counters read for a plain 256 MiB device copy
-# (FETCH_SIZE x 1.99982, WRITE_SIZE x 1.000): k_full<3, 1, false> at
-# 4096 x 259,585, and k_wmom<3> at 4096 rows on 2048 cached slots (12 orders).
+# (FETCH_SIZE x 1.99982, WRITE_SIZE x 1.000): k_full<3, 1, true> at
+# 4096 rows of the 128 s band over its nodes.
 # Valid only for the kernel sources they were taken on (hash below; retaken
 # when those files change, or carried over after checking that the compiled
-# code of both kernels is unchanged).
-TRAFFIC = {"sources_sha256": "78485f89754a80c14c8330dda9495618a08f1c73a5db95363cacc7f73b1b324d",
-           "k_full": {"read_bytes": 22404.2 * 1.99982 * 1024, "write_bytes": 49152.0 * 1024},
-           "k_wmom": {"read_bytes": 320487.9 * 1.99982 * 1024, "write_bytes": 23040.0 * 1024}}
+# code of the kernel is unchanged).
+TRAFFIC = {"sources_sha256": "cd9a8d888f005a3db1da7c3834a61dcb29f0b625ce167027e6f12db7890bace5",
+           "k_full": {"read_bytes": 2650.54 * 1.99982 * 1024, "write_bytes": 3072.0 * 1024}}
 TRAFFIC_SOURCES = ("paper_2607_28265_amd/csrc/gw_full.hip", "paper_2607_28265_amd/csrc/gw_device.h")
 
 
@@ -122,10 +121,10 @@ def time_steps(ctx, theta, out, steps, warmup, prec, marg, torch, gw, profile=Fa
 # minus the fiducial's (1); per detector the delay term of detectors 1 and 2
 # (1 FMA + 1 sub = 3 each), the phasor (mixed: the reduction to a fraction of
 # a cycle (1) and the Newton normalisation of the FP32 pair (7); FP64: the
-# software sin/cos, 47), the summed-by-parts weight product (4 FMA = 8) and
+# table method's 24), the summed-by-parts weight product (4 FMA = 8) and
 # the norm term (1 mul + 2 FMA = 5).  Mixed: 24 + 3 (8 + 8 + 5) + 2 x 3 = 93;
-# FP64: 24 + 3 (47 + 13) + 6 = 210.
-HET_FLOPS_PER_EDGE = {"mixed": 93.0, "fp64": 210.0}
+# FP64: 24 + 3 (24 + 13) + 6 = 141.
+HET_FLOPS_PER_EDGE = {"mixed": 93.0, "fp64": 141.0}
 
 
 def het_leg(gw, torch, prob, th_inj, steps, warmup):
@@ -181,7 +180,6 @@ def het_leg(gw, torch, prob, th_inj, steps, warmup):
         # phase+time marginal on 500 and 5000 bins and the same proposals
         delta, n_t, p_len, blk = gw.gw_time_grid_info(ctx.handle)
         L = p_len * 4
-        K = tgrid_orders(L, (n_t - 1) // 2)
         for n_bins in (500, 5000):
             ctx.heterodyne_setup(th_inj, n_bins)
             tm = {}
@@ -199,7 +197,7 @@ def het_leg(gw, torch, prob, th_inj, steps, warmup):
                 mom_ms, n_mom = time_kernel(gw, torch, ctx, run, reps, 1)
                 grid_ms, n_grid = time_kernel(gw, torch, ctx, run, reps, 2)
                 rows_per_launch = n * reps / max(n_grid, 1)
-                gflops = tgrid_flops_per_row(K, L) * rows_per_launch
+                gflops = tgrid_flops_per_row(L) * rows_per_launch
                 tm[name] = {"value": n / dt, "ms_per_batch": dt * 1e3,
                             "moments_ms_per_batch": mom_ms * n_mom / reps,
                             "k_tgrid_ms_per_batch": grid_ms * n_grid / reps,
@@ -508,56 +506,22 @@ def cache_leg(gw, torch, prob, steps, warmup, mixed_value):
                 ms, nl = gw._lib.gw_profile_read(ctx.handle)
                 gw._lib.gw_profile_enable(ctx.handle, False)
                 k_ms = ms / max(nl, 1)
-                # moment cache: blocks of B bins (256 at df = 1/128 Hz), 12 Chebyshev moments per block and
-                # detector, FP32 complex; algorithmic bytes = each used slot's moments once
-                blk = 4
-                while blk < 512 and math.pi * prob.df * (2 * blk) * 0.25 <= 1.61:
-                    blk *= 2
-                n_blk = -(-prob.n_freq // blk)
-                nbytes = n_slots * n_blk * 3 * 12 * 8
-                # per row, block and detector: 12 weighted moments (2 FMA each) + block factor and rotation
-                # (8 flop-pairs)
-                flops = n * n_blk * 3 * (12 * 2 + 8) * 2
-                r["kernel"] = "k_wmom<3>"
+                # fast rows sum over interpolation nodes, rows beyond their tables over the cached moments
+                r["kernel"] = "fast rows' sums over nodes and cached moments"
                 r["kernel_ms"] = k_ms
-                r["moment_block_bins"] = blk
-                r["roofline"] = {"bound": "hbm", "achieved": nbytes / (k_ms * 1e-3) / 1e9, "peak": 8000.0,
-                                 "unit": "GB/s", "frac": nbytes / (k_ms * 1e-3) / 1e9 / 8000.0,
-                                 "traffic": traffic_bytes("k_wmom"), "bytes_per_launch": nbytes,
-                                 "fp64_tflops": flops / (k_ms * 1e-3) / 1e12,
-                                 "fp64_frac": flops / (k_ms * 1e-3) / 1e12 / PEAK_FP64_TFLOPS}
             res[f"kind{kind}"] = r
         cache.close()
     res["unit"] = "logL evals/s"
-    res["workload"] = ("waveform cache on the 128 s grid: 2048 cached waveforms (block moments), 4096 rows (two "
-                       "per slot); kind 1 = sky/t_c/psi/iota/d_L moves on the cached moments, kind 2 = "
+    res["workload"] = ("waveform cache on the 128 s grid: 2048 cached waveforms, 4096 rows (two "
+                       "per slot); kind 1 = sky/t_c/psi/iota/d_L moves on the cached waveforms, kind 2 = "
                        "psi/iota/d_L moves on the cached overlaps; phase+distance marginalised")
     return res
 
 
-def tgrid_orders(L, jmax):
-    """Expansion orders the library takes for a grid (12 when the dropped
-    Chebyshev terms' bound 2 (phi/2)^12 / 12! at phi = pi jmax / L is at most
-    2e-11, else 16)."""
-    phi = math.pi * jmax / L
-    b = 2.0
-    for i in range(1, 13):
-        b *= 0.5 * phi / i
-    return 12 if b <= 2e-11 else 16
-
-
-# k_tmom (mixed, ND = 3), FP64 flops per (row, bin) on the recurrence path, from
-# the source: phase recurrence 3, cycle reduction 1, detector sums 3 x 4 FMA,
-# two delay rotations 2 x 6, y = g s 6, and K moment updates of 2 FMA each.
-def tmom_flops_per_bin(K):
-    return 3 + 1 + 24 + 12 + 6 + 4 * K
-
-
-# k_tgrid, FP64 flops per row: K transforms of L points at the conventional
-# 5 L log2 L, plus the weighted accumulation (2 FMA per point and order); the
-# grid epilogue (ln I0, log-sum-exp) is not counted.
-def tgrid_flops_per_row(K, L):
-    return K * (5 * L * math.log2(L) + 4 * L)
+# k_tgrid, FP64 flops per row: one transform of 2 L points at the conventional
+# 5 n log2 n; the grid epilogue (ln I0, log-sum-exp) is not counted.
+def tgrid_flops_per_row(L):
+    return 5 * 2 * L * math.log2(2 * L)
 
 
 def time_kernel(gw, torch, ctx, fn, steps, mode):
@@ -581,8 +545,6 @@ def tmarg_leg(gw, torch, ctx, theta, steps, warmup, mixed_value):
     delta, n_t, p_len, blk = gw.gw_time_grid_info(ctx.handle)
     R = 4
     L = p_len * R
-    jmax = (n_t - 1) // 2
-    K = tgrid_orders(L, jmax)
     res = {}
     for name, prec in (("mixed", gw.GW_PREC_MIXED), ("fp64", gw.GW_PREC_FP64)):
         run = lambda: ctx.loglike(theta, gw.GW_FULL, gw.GW_MARG_PHASE_TIME, prec, out=out)
@@ -596,22 +558,16 @@ def tmarg_leg(gw, torch, ctx, theta, steps, warmup, mixed_value):
         dt = (time.perf_counter() - t0) / steps
         mom_ms, _ = time_kernel(gw, torch, ctx, run, steps, 1)
         grid_ms, _ = time_kernel(gw, torch, ctx, run, steps, 2)
-        r = {"value": n / dt, "ms_per_batch": dt * 1e3, "k_tmom_ms": mom_ms, "k_tgrid_ms": grid_ms}
-        gflops = tgrid_flops_per_row(K, L) * n
+        r = {"value": n / dt, "ms_per_batch": dt * 1e3, "k_tspread_ms": mom_ms, "k_tgrid_ms": grid_ms}
+        gflops = tgrid_flops_per_row(L) * n
         r["k_tgrid_roofline"] = {"bound": "alu", "achieved": gflops / (grid_ms * 1e-3) / 1e12,
                                  "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                                  "frac": gflops / (grid_ms * 1e-3) / 1e12 / PEAK_FP64_TFLOPS,
-                                 "flops_per_row": tgrid_flops_per_row(K, L)}
-        if name == "mixed":
-            mflops = tmom_flops_per_bin(K) * n * prob_n_freq(ctx)
-            r["k_tmom_roofline"] = {"bound": "alu", "achieved": mflops / (mom_ms * 1e-3) / 1e12,
-                                    "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                                    "frac": mflops / (mom_ms * 1e-3) / 1e12 / PEAK_FP64_TFLOPS,
-                                    "flops_per_bin": tmom_flops_per_bin(K)}
+                                 "flops_per_row": tgrid_flops_per_row(L)}
         res[name] = r
     res["cost_vs_distance_marginal_mixed"] = mixed_value / res["mixed"]["value"]
     res.update({"unit": "logL evals/s", "batch": n, "grid_points": n_t, "delta_s": delta, "blocks_P": p_len,
-                "fft_len": L, "orders": K, "block_bins": blk,
+                "fft_len": 2 * L, "cell_bins": blk / 2,
                 "workload": "phase+time marginal on the 128 s full band, 4096 prior draws, t_c grid of a quarter "
                             "of the segment's sampling interval over +-0.1 s"})
     return res

@@ -480,8 +480,8 @@ gw_status slice_sweep(gw_ctx* ctx, const gw_sweep_args* args, void* stream);
  * block whose coordinates are all among {iota, psi} is projection-only: its
  * candidates reuse the overlaps z_i of the chain's current point and cost
  * O(1); a block among {iota, ra, dec, psi, t_c} is extrinsic: its candidates
- * reuse the chain's cached waveform, held as block moments (see
- * gw_wcache_loglike, kind 1), and only the detector delays change; any other
+ * reuse the chain's cached waveform (see gw_wcache_loglike, kind 1), and only
+ * the detector delays change; any other
  * block evaluates in full (prec as given).  Each sweep first evaluates every
  * chain's current point in full to seed the overlaps (k extra evaluations,
  * not counted in n_evals).  A chain's waveform is rebuilt lazily: when it is
@@ -581,7 +581,9 @@ gw_status gw_fiducial_search(gw_ctx* ctx, const gw_fiducial_args* args, double* 
  *     M_m = sum_j t_j^m u_ij g_j,   m < 16   (FP64 sums stored as FP32),
  * so that a delay tau_i contributes
  *     exp(-2 pi i f_c tau_i) sum_m (-i pi df B tau_i)^m / m! M_m
- * per block.  B is the largest power of two up to 512 with
+ * per block.  A slot whose phase the context's interpolation nodes cover
+ * (gw_full_nodes) holds no moments: fast rows on it with delays up to 0.25 s
+ * sum its waveform over the nodes.  B is the largest power of two up to 512 with
  * pi df B 0.25 s <= 1.61 (256 at df = 1/128 Hz), which keeps the first
  * dropped term below 1e-10 of the block's sum of |u g| for |tau_i| <= 0.25 s.
  *

@@ -2,18 +2,22 @@
 // phase/phasor/projection/overlap kernel and the FP64 epilogue with the
 // phase and distance marginalisations (Sec. III.A).
 //
-// Layout.  One lane owns one proposal; a workgroup owns ``tpb`` proposals
-// (one to four waves) and one contiguous chunk of frequency bins, which all
-// of its waves walk in step so that they share each bin record.  Every lane of a wave walks the same
-// bins in the same order, so the per-bin records (frequency powers and the
-// weighted data u_ik = 4 df d_ik* f^(-7/6) / S_ik) are wave-uniform and are
-// fetched with scalar loads into SGPRs; the proposal's phase coefficients live
-// in VGPRs.  Per bin a lane evaluates the TaylorF2 phase in FP64 (Horner in
-// x = f^(1/3); the mixed form only on the first bins of each run and by a
-// cubic recurrence in between, see PhaseRuns), one complex phasor
-// exp(-i Phi_0) for detector 0, and folds the
-// other detectors' linear time-shift phases into a Horner recurrence over the
-// bins of the chunk: S_i <- S_i rho_i + u_ik g_k with rho_i = exp(-2 pi i df
+// Rows that the node tables cover (gw_nodes.h) are summed over interpolation
+// nodes, the others over every bin, both in one launch.
+//
+// Layout.  One lane owns one proposal; the waves of a workgroup either hold 64
+// proposals each and walk one chunk in step, sharing each record, or share 64
+// proposals and a quarter of the chunk each (SPLIT).  Every lane of a wave walks
+// the same records in the same order, so the records (frequency powers and the
+// weighted data u_ik = 4 df d_ik* f^(-7/6) / S_ik, or their node weights) are
+// wave-uniform and are fetched with scalar loads into SGPRs; the proposal's
+// phase coefficients live in VGPRs.  Per node a lane evaluates the TaylorF2
+// phase in FP64 (Horner in x = f^(1/3)) relative to the reference and a phasor
+// per detector.  Per bin it evaluates the phase (the mixed form only on the
+// first bins of each run and by a cubic recurrence in between, see PhaseRuns),
+// one complex phasor exp(-i Phi_0) for detector 0, and folds the other
+// detectors' linear time-shift phases into a Horner recurrence over the bins of
+// the chunk: S_i <- S_i rho_i + u_ik g_k with rho_i = exp(-2 pi i df
 // (tau_i - tau_0)), which is multiplied by exp(-2 pi i f_start (tau_i - tau_0))
 // at the end.  The template norm <h|h> has a closed form (|h|^2 / S does not
 // depend on the phase), so only z_i = sum_k u_ik exp(-i Phi_ik) is summed.
