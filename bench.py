@@ -44,7 +44,7 @@ PEAK_FP64_TFLOPS = 78.6  # MI355X FP64 vector, dense
 # Valid only for the kernel sources they were taken on (hash below; retaken
 # when those files change, or carried over after checking that the compiled
 # code of the kernel is unchanged).
-TRAFFIC = {"sources_sha256": "cd9a8d888f005a3db1da7c3834a61dcb29f0b625ce167027e6f12db7890bace5",
+TRAFFIC = {"sources_sha256": "f76780f89494f32d19855c2b3e424f7f411e8e9368e86322c0342ac0778b0710",
            "k_full": {"read_bytes": 2650.54 * 1.99982 * 1024, "write_bytes": 3072.0 * 1024}}
 TRAFFIC_SOURCES = ("paper_2607_28265_amd/csrc/gw_full.hip", "paper_2607_28265_amd/csrc/gw_device.h")
 

@@ -1282,8 +1282,8 @@ __global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ par
 // k_epilogue, bit for bit), and each wave finishes one row: its lanes are
 // neighbouring distances (wave_dist_lse), which mostly take the same form of a
 // term, while rows differ.
-// Bound by latency: 11.6 us at 250 rows of the 128 s band, 12.3 + 7.6 as two
-// launches (36 us a call, now 30); 4096 rows 108 and 105.
+// Bound by latency: 9.9 us at 250 rows of the 128 s band, 12.3 + 7.6 as two
+// launches (36 us a call, now 27); 4096 rows 108 and 106.
 template <int PREC>
 __global__ void __launch_bounds__(256) k_epilogue_dist(const double* __restrict__ partial, int n_chunks, int cstride,
                                                        int nch_node, int nd, const double* __restrict__ coef,
