@@ -404,9 +404,11 @@ __global__ void __launch_bounds__(256 * W, 2) k_tgrid(TgKernelArgs a) {
   if (threadIdx.x == 0) {
     const double m = fmax(bound[0], bound[1]);
     double s = 0.0;
-    for (int r = 0; r < 2; ++r)
-      if (bound[r] > -INFINITY)
-        s += exp(bound[r] - m) * (((wsum[4 * r] + wsum[4 * r + 1]) + wsum[4 * r + 2]) + wsum[4 * r + 3]);
+    for (int r = 0; r < 2; ++r) {
+      const double t = ((wsum[4 * r] + wsum[4 * r + 1]) + wsum[4 * r + 2]) + wsum[4 * r + 3];
+      // no bound: no point, or none that is a number (then the sum is not one either)
+      s += bound[r] > -INFINITY ? exp(bound[r] - m) * t : t;
+    }
     a.logl[p] = valid ? -0.5 * a.dd + m + log(s) - log((double)nt) : -INFINITY;
   }
 }

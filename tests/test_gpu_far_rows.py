@@ -61,3 +61,25 @@ def test_het_phases_of_many_cycles(gw, col, values):
             ref = oracle_het_many(th, prob, het, marg)
             got = ctx.loglike(torch.from_numpy(th).cuda(), gw.GW_HET, marg, 0).cpu().numpy()
             assert np.all(np.abs(got - ref) < 1e-6 + room)
+
+
+@pytest.mark.parametrize("like", ["full", "het"])
+@pytest.mark.parametrize("window,n", [(0.0, 6), (0.1, 6), (0.1, 300)])  # one grid point; both workgroup shapes
+def test_time_marginal_of_overlaps_that_are_not_numbers(gw, like, window, n):
+    # a distance so small that the overlap or the norm overflows: log L is not a
+    # number, as with the phase marginal, and the rows beside it are as ever
+    prob, inj = _problem((8.0, 20.0, 512.0))
+    th = np.tile(_far(6, [100.0, 1e-320, 200.0, 1e-200, 50.0, 1e-310]), (n // 6, 1))
+    bad = np.tile([False, True, False, True, False, True], n // 6)
+    with gw.Context(prob) as ctx:
+        gw.gw_set_time_window(ctx.handle, window)
+        ctx.heterodyne_setup(inj, 300)
+        which = gw.GW_FULL if like == "full" else gw.GW_HET
+        t = torch.from_numpy(th).cuda()
+        good = torch.from_numpy(th[~bad]).cuda()
+        for prec in (0, 1):
+            assert np.array_equal(np.isnan(ctx.loglike(t, which, L.PHASE, prec).cpu().numpy()), bad)
+            got = ctx.loglike(t, which, L.PHASE_TIME, prec).cpu().numpy()
+            assert np.array_equal(np.isnan(got), bad)
+            want = ctx.loglike(good, which, L.PHASE_TIME, prec).cpu().numpy()
+            assert np.max(np.abs(got[~bad] - want)) < 512 * EPS * np.max(np.abs(want))
