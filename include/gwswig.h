@@ -576,37 +576,37 @@ gw_status gw_fiducial_search(gw_ctx* ctx, const gw_fiducial_args* args, double* 
  * Waveform cache (Sec. III.B, Sec. III.A): the slow / fast likelihood pair.
  * A slot holds one point's overlaps z_i = sum_k u_ik exp(-2 pi i Phi_ik)
  * and its intrinsic waveform g_k = exp(-2 pi i Psi(f_k)) (Psi the TaylorF2
- * phase without the linear time term) as block moments: for blocks of B bins
- * with centre f_c and t_j = (j - (B - 1)/2) / (B/2),
- *     M_m = sum_j t_j^m u_ij g_j,   m < 16   (FP64 sums stored as FP32),
- * so that a delay tau_i contributes
- *     exp(-2 pi i f_c tau_i) sum_m (-i pi df B tau_i)^m / m! M_m
- * per block.  A slot whose phase the context's interpolation nodes cover
- * (gw_full_nodes) holds no moments: fast rows on it with delays up to 0.25 s
- * sum its waveform over the nodes.  B is the largest power of two up to 512 with
+ * phase without the linear time term): the phase's coefficients and, where the
+ * context's interpolation nodes (gw_full_nodes) do not cover that phase, block
+ * moments.  For blocks of B bins with centre f_c and t_j = (j - (B - 1)/2) / (B/2),
+ *     M_m = sum_j T_m(t_j) u_ij g_j,   m < 12   (FP64 sums stored as FP32,
+ * T_m the Chebyshev polynomials), so that a delay tau_i contributes
+ *     exp(-2 pi i f_c tau_i) sum_m eps_m (-i)^m J_m(pi df B tau_i) M_m
+ * per block (eps_0 = 1, eps_m = 2).  B is the largest power of two up to 512 with
  * pi df B 0.25 s <= 1.61 (256 at df = 1/128 Hz), which keeps the first
- * dropped term below 1e-10 of the block's sum of |u g| for |tau_i| <= 0.25 s.
+ * dropped term below 3e-10 of the block's sum of |u g| for |tau_i| <= 0.25 s.
+ * Which of the two a slot holds is decided when it is written, and stored.
  *
  * gw_wcache_update (slow): full-band log L of theta (device [n, 13]; marg,
  *   prec as for loglike_batch) into logl (device [n]), and row r's overlaps
- *   and moments into slot slots[r] (device int32 [n]).  When a slot appears
+ *   and waveform into slot slots[r] (device int32 [n]).  When a slot appears
  *   more than once the largest row index wins; a slot outside 0 .. n_slots-1
  *   stores nothing and gives log L = NaN.
  * gw_wcache_loglike (fast): log L of rows that differ from the point of
- *   their slot slots[r] only in extrinsic parameters, without generating a
- *   waveform:
- *     kind 1: ra, dec, psi, iota, t_c (and d_L) may differ; the moments are
- *             summed with each detector's delay t_c + dt_i (16 terms per
- *             block, FP64 arithmetic); rows with |t_c + dt_i| > 0.25 s get
- *             NaN;
+ *   their slot slots[r] only in extrinsic parameters:
+ *     kind 1: ra, dec, psi, iota, t_c (and d_L) may differ; the slot's waveform
+ *             is summed with each detector's delay t_c + dt_i, over the nodes
+ *             or over the moments (FP64 arithmetic); rows with
+ *             |t_c + dt_i| > 0.25 s get NaN;
  *     kind 2: only psi, iota (and d_L) may differ; the cached overlaps are
  *             reprojected, O(1) per row.
- *   Intrinsic parameters (Mc, q, chi1, chi2, Lambda1, Lambda2) and, for
- *   marg = GW_MARG_NONE, phi_c must equal the slot's; nothing checks this.
- *   Slots outside 0 .. n_slots-1 give log L = NaN.
- * Device memory: n_slots x (n_freq / B) x n_det x 128 bytes (at most
- * 128 GiB) plus the overlaps.  Errors as loglike_batch; GW_EINVAL for kind
- * not 1 or 2.
+ *   The phase is the slot's whatever the row's own intrinsic parameters (Mc, q,
+ *   chi1, chi2, Lambda1, Lambda2) and phi_c say; the amplitude follows the
+ *   row's Mc.  They should be equal; nothing checks this.
+ *   Slots outside 0 .. n_slots-1 and slots never written give log L = NaN.
+ * Device memory: n_slots x (n_freq / B) x n_det x 96 bytes (at most
+ * 128 GiB) plus the overlaps and the coefficients.  Errors as loglike_batch;
+ * GW_EINVAL for kind not 1 or 2.
  */
 typedef struct gw_wcache gw_wcache;
 gw_status gw_wcache_create(gw_ctx* ctx, int64_t n_slots, gw_wcache** out);

@@ -130,6 +130,21 @@ gw_status ensure_buffer(double** buf, int64_t* cap, int64_t need, const char* wh
 // ``nodes``: with the row check of the node tables (column C_NODE, else 0).
 gw_status launch_prologue(gw_ctx* ctx, const double* theta, int64_t n, int marg, double* coef,
                           int64_t ld, hipStream_t st, bool nodes = true);
+// A waveform cache's slots: rec [n][kSlotRec], the phase coefficients of the
+// slot's waveform (columns kSlotCols) and what the slot holds, decided once when
+// it is written.
+constexpr int kSlotRec = 12;
+constexpr int kSlotCols[kSlotRec - 1] = {C_A0, C_A2, C_A3, C_A4, C_A5, C_A6, C_A7, C_A10, C_A12, C_B5, C_B6};
+constexpr double kSlotEmpty = 0.0, kSlotNodes = 1.0, kSlotMoments = 2.0;
+struct SlotWaves {
+  const double* rec = nullptr;
+  int64_t n = 0;
+};
+// The prologue of a cache's fast rows: row p takes the phase coefficients of
+// slot slot_of[p] (zero when that is no slot) and C_NODE from what the slot holds
+// (kNodeNoSlot: nothing).
+gw_status launch_prologue_slots(gw_ctx* ctx, const double* theta, int64_t n, int marg, const int32_t* slot_of,
+                                const SlotWaves& slots, double* coef, int64_t ld, hipStream_t st);
 gw_status launch_full(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n, int prec,
                       int tpb, int n_chunks, double* partial, hipStream_t st);
 // Chunks (the first of n_chunks) that hold the partial sums of the rows summed
@@ -154,7 +169,8 @@ gw_status launch_template(gw_ctx* ctx, const double* coef, int64_t ld, int64_t n
 // launch_wcache_fast: rows that a node table covers (C_NODE at least
 // kNodeWide) summed over its nodes into nch_node chunks, the others over the
 // moments of slot slot_of[p] (slot 0 when that is outside 0 .. n_slots - 1)
-// into n_chunks = wcache_fast_chunks chunks; the epilogue is told kNodeWide.
+// into n_chunks = wcache_fast_chunks chunks, or NaN when their slot is one of
+// kSlotNodes (C_NODE = kNodePhase); the epilogue is told kNodeWide.
 // launch_epilogue_cached combines partials (rows with zsrc[p] >= 0 take their
 // sums from zc[zsrc[p]]) and writes every row's sums to zrow when not NULL.
 // launch_wmom_build rebuilds the slots slots[i] >= 0, i < *count <= max_count,

@@ -35,9 +35,14 @@ namespace gw {
 // what a launch of few rows waits for), then all four waves share the row
 // check of the node tables (gw_nodes.h), a quarter of its frequencies each.
 // At 250 rows 5 us, 6.5 us with one wave doing both halves and no check.
+//
+// SLOT: a waveform cache's fast rows, whose phase is their slot's: wave 0 copies
+// the coefficients that the slot was written with, and there is nothing to check.
+template <bool SLOT>
 __global__ void __launch_bounds__(256) k_prologue(const double* __restrict__ theta, int64_t n, int marg,
                                                   Geom geom, double* __restrict__ coef, int64_t ld,
-                                                  const NodeCheck* __restrict__ chk) {
+                                                  const NodeCheck* __restrict__ chk,
+                                                  const int32_t* __restrict__ slot_of, SlotWaves slots) {
   __shared__ double pc[11][64];
   __shared__ double tau[64];
   __shared__ int in[4][64];
@@ -46,7 +51,15 @@ __global__ void __launch_bounds__(256) k_prologue(const double* __restrict__ the
   const bool live = p < n;
   if (wave < 2 && live) {
     const Row row = load_row(theta + p * 13, marg);
-    if (wave == 0) {
+    if (SLOT && wave == 0) {
+      const int32_t s = slot_of[p];
+      const bool ok = s >= 0 && s < slots.n;
+      const double* __restrict__ w = slots.rec + (int64_t)(ok ? s : 0) * kSlotRec;
+#pragma unroll
+      for (int j = 0; j < kSlotRec - 1; ++j) coef[kSlotCols[j] * ld + p] = ok ? w[j] : 0.0;
+      const double holds = ok ? w[kSlotRec - 1] : kSlotEmpty;
+      in[0][lane] = holds == kSlotEmpty ? -1 : holds == kSlotNodes;
+    } else if (wave == 0) {
       const PhaseCoef c = prologue_phase(row, marg, coef + p, ld);
       const double v[11] = {c.a0, c.a2, c.a3, c.a4, c.a6, c.a7, c.a10, c.a12, c.b5, c.b6, row.ok ? 1.0 : 0.0};
 #pragma unroll
@@ -60,7 +73,7 @@ __global__ void __launch_bounds__(256) k_prologue(const double* __restrict__ the
     return;
   }
   __syncthreads();
-  if (live) {
+  if (!SLOT && live) {
     // a row that is not physical has zero coefficients: any table takes it
     PhaseCoef c{};
     c.a0 = pc[0][lane];
@@ -83,10 +96,10 @@ __global__ void __launch_bounds__(256) k_prologue(const double* __restrict__ the
   }
   __syncthreads();
   if (wave == 0 && live) {
-    const bool good = in[0][lane] && in[1][lane] && in[2][lane] && in[3][lane];
+    const bool good = in[0][lane] && (SLOT || (in[1][lane] && in[2][lane] && in[3][lane]));
     const double t = tau[lane];
-    coef[C_NODE * ld + p] =
-        !good ? 0.0 : (t <= chk->tau_max ? kNodeFull : (t <= kTauCap ? kNodeWide : kNodePhase));
+    const double node = !good ? 0.0 : (t <= chk->tau_max ? kNodeFull : (t <= kTauCap ? kNodeWide : kNodePhase));
+    coef[C_NODE * ld + p] = SLOT && in[0][lane] < 0 ? kNodeNoSlot : node;
   }
 }
 
@@ -837,7 +850,8 @@ __global__ void __launch_bounds__(256) k_wmom(const double* __restrict__ coef, i
   int64_t p = live ? idx : cnt - 1;
   if (rows) p = rows[p];
   // rows that the caller sums over the nodes (the workgroup's waves share their rows)
-  const bool mine = live && !(skip_nodes && coef[C_NODE * ld + p] >= kNodeWide);
+  const double node = skip_nodes ? coef[C_NODE * ld + p] : 0.0;
+  const bool mine = live && !(node >= kNodeWide);
   if (!__any(mine)) return;
   int64_t slot = slot_of ? (int64_t)slot_of[p] : p / rows_per_slot;
   if (slot < 0 || slot >= n_slots) slot = 0;  // a row without a valid slot (the caller discards it)
@@ -852,7 +866,7 @@ __global__ void __launch_bounds__(256) k_wmom(const double* __restrict__ coef, i
 
   const double tau0 = coef[C_TAU0 * ld + p];
   double zr[ND], zi[ND], er[ND], ei[ND], rr[ND], ri[ND], tc[ND][kWMom];
-  bool in_range = true;
+  bool in_range = node < kNodePhase;  // beyond: a slot without moments
 #pragma unroll
   for (int i = 0; i < ND; ++i) {
     const double tau = i == 0 ? tau0 : tau0 + coef[(C_DT1 + i - 1) * ld + p];
@@ -1415,8 +1429,17 @@ gw_status launch_prologue(gw_ctx* ctx, const double* theta, int64_t n, int marg,
                           hipStream_t st, bool nodes) {
   if (n == 0) return GW_OK;
   const int64_t blocks = (n + 63) / 64;
-  hipLaunchKernelGGL(k_prologue, dim3((unsigned)blocks), dim3(256), 0, st, theta, n, marg, ctx->geom, coef, ld,
-                     nodes ? (const NodeCheck*)ctx->node_check_dev : nullptr);
+  hipLaunchKernelGGL(k_prologue<false>, dim3((unsigned)blocks), dim3(256), 0, st, theta, n, marg, ctx->geom, coef, ld,
+                     nodes ? (const NodeCheck*)ctx->node_check_dev : nullptr, nullptr, SlotWaves{});
+  return check_hip(hipGetLastError(), "prologue launch");
+}
+
+gw_status launch_prologue_slots(gw_ctx* ctx, const double* theta, int64_t n, int marg, const int32_t* slot_of,
+                                const SlotWaves& slots, double* coef, int64_t ld, hipStream_t st) {
+  if (n == 0) return GW_OK;
+  const int64_t blocks = (n + 63) / 64;
+  hipLaunchKernelGGL(k_prologue<true>, dim3((unsigned)blocks), dim3(256), 0, st, theta, n, marg, ctx->geom, coef, ld,
+                     (const NodeCheck*)ctx->node_check_dev, slot_of, slots);
   return check_hip(hipGetLastError(), "prologue launch");
 }
 

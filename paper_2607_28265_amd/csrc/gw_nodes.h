@@ -44,6 +44,8 @@ constexpr double kTauCap = 0.25;   // s, delays of the wide table and of the wav
 // the tables are built for, and its delays within neither table's, the wide
 // table's (kTauCap) or the context's own (tau_max).  Zero: the phase does not.
 constexpr double kNodePhase = 1.0, kNodeWide = 2.0, kNodeFull = 3.0;
+// A waveform cache's row whose slot holds no waveform.
+constexpr double kNodeNoSlot = -1.0;
 
 // The row check's frequencies: x = f^(1/3), ln f, x^-8, x^-3, R'(f), S(f).
 struct NodeCheck {

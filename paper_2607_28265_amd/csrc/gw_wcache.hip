@@ -15,6 +15,7 @@ struct gw_wcache {
   int64_t slot_f2 = 0;
   float2* wc = nullptr;  // [n_slots][slot_f2] block moments (FP32 complex)
   double* zc = nullptr;  // [n_slots][2 n_det] sums z_i of each slot's point
+  double* rec = nullptr;  // [n_slots][kSlotRec] each slot's phase coefficients and what it holds
   int32_t* owner = nullptr;  // [n_slots]: -1 between calls
   // per-call workspace: zrow [cap][2 kMaxDet], sl [cap] (checked slots), and
   // the slots whose moments are wanted with their rows, bslot and brow [cap],
@@ -48,20 +49,28 @@ __global__ void k_wc_slots(const int32_t* __restrict__ slots, int64_t n, int64_t
   if (ok) atomicMax(&owner[s], (int32_t)r);
 }
 
-// The claiming row of each slot stores its sums, zc[sl[r]] = zrow[r], and asks
-// for the slot's moments when no node table covers its phase: the fast rows of
-// the other slots are summed over the nodes.  (The list's order does not
-// matter: each slot's moments come from its own row.)
+// The claiming row of each slot stores its sums, zc[sl[r]] = zrow[r], and its
+// phase coefficients, and asks for the slot's moments when no node table covers
+// its phase: the fast rows of the other slots are summed over the nodes.  What
+// the slot holds is stored with it, so that the fast rows ask for nothing else.
+// (The list's order does not matter: each slot's moments come from its own row.)
 __global__ void k_wc_store(const double* __restrict__ zrow, const int32_t* __restrict__ sl,
                            const int32_t* __restrict__ owner, const double* __restrict__ coef, int64_t n, int nd,
-                           bool nodes, double* __restrict__ zc, int32_t* __restrict__ bslot,
+                           bool nodes, double* __restrict__ zc, double* __restrict__ rec,
+                           int32_t* __restrict__ bslot,
                            int32_t* __restrict__ brow, int32_t* __restrict__ bcount) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n) return;
   const int32_t s = sl[r];
   if (s < 0 || owner[s] != (int32_t)r) return;
   for (int j = 0; j < 2 * nd; ++j) zc[(int64_t)s * 2 * nd + j] = zrow[r * 2 * nd + j];
-  if (nodes && coef[C_NODE * n + r] >= kNodePhase) return;
+  double* __restrict__ w = rec + (int64_t)s * kSlotRec;
+#pragma unroll
+  for (int j = 0; j < kSlotRec - 1; ++j) w[j] = coef[kSlotCols[j] * n + r];
+  // a row that is not physical has zero coefficients, which moments serve
+  const bool covered = nodes && coef[C_VALID * n + r] != 0.0 && coef[C_NODE * n + r] >= kNodePhase;
+  w[kSlotRec - 1] = covered ? kSlotNodes : kSlotMoments;
+  if (covered) return;
   const int32_t q = atomicAdd(bcount, 1);
   bslot[q] = s;
   brow[q] = (int32_t)r;
@@ -83,10 +92,10 @@ __global__ void k_wc_clip(const int32_t* __restrict__ slots, int64_t n, int64_t 
   if (r < n) sl[r] = slots[r] >= 0 && slots[r] < n_slots ? slots[r] : -1;
 }
 
-// Rows whose slot is out of range get log L = NaN.
-__global__ void k_wc_mark(const int32_t* __restrict__ slots, int64_t n, int64_t n_slots, double* __restrict__ logl) {
+// Rows whose slot is out of range or was never written get log L = NaN.
+__global__ void k_wc_mark(const double* __restrict__ coef, int64_t n, double* __restrict__ logl) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n && (slots[r] < 0 || slots[r] >= n_slots)) logl[r] = __builtin_nan("");
+  if (r < n && coef[C_NODE * n + r] == kNodeNoSlot) logl[r] = __builtin_nan("");
 }
 
 gw_status wc_reserve(gw_wcache* c, int64_t n) {
@@ -144,6 +153,9 @@ gw_status gw_wcache_create(gw_ctx* ctx, int64_t n_slots, gw_wcache** out) {
   s = check_hip(hipMalloc((void**)&c->wc, (size_t)n_slots * f2 * sizeof(float2)), "waveform cache");
   if (s == GW_OK)
     s = check_hip(hipMalloc((void**)&c->zc, (size_t)n_slots * 2 * ctx->n_det * sizeof(double)), "cached sums");
+  if (s == GW_OK)
+    s = check_hip(hipMalloc((void**)&c->rec, (size_t)n_slots * kSlotRec * sizeof(double)), "slot records");
+  if (s == GW_OK) s = check_hip(hipMemset(c->rec, 0, (size_t)n_slots * kSlotRec * sizeof(double)), "slot records");
   if (s == GW_OK) s = check_hip(hipMalloc((void**)&c->owner, (size_t)n_slots * sizeof(int32_t)), "slot claims");
   if (s == GW_OK) {
     hipLaunchKernelGGL(k_wc_fill, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, nullptr, c->owner, n_slots,
@@ -154,6 +166,7 @@ gw_status gw_wcache_create(gw_ctx* ctx, int64_t n_slots, gw_wcache** out) {
   if (s != GW_OK) {
     if (c->wc) (void)hipFree(c->wc);
     if (c->zc) (void)hipFree(c->zc);
+    if (c->rec) (void)hipFree(c->rec);
     if (c->owner) (void)hipFree(c->owner);
     delete c;
     return s;
@@ -167,6 +180,7 @@ gw_status gw_wcache_destroy(gw_wcache* c) {
   (void)hipSetDevice(c->ctx->device);
   if (c->wc) (void)hipFree(c->wc);
   if (c->zc) (void)hipFree(c->zc);
+  if (c->rec) (void)hipFree(c->rec);
   if (c->owner) (void)hipFree(c->owner);
   if (c->mem) (void)hipFree(c->mem);
   delete c;
@@ -197,7 +211,7 @@ gw_status gw_wcache_update(gw_wcache* c, const double* theta, const int32_t* slo
                                logl, nullptr, nullptr, c->zrow, st);
   if (s == GW_OK) {
     hipLaunchKernelGGL(k_wc_store, dim3(blocks), dim3(256), 0, st, c->zrow, c->sl, c->owner, ctx->coef, n, ctx->n_det,
-                       ctx->nodes.n > 0, c->zc, c->bslot, c->brow, c->bcount);
+                       ctx->nodes.n > 0, c->zc, c->rec, c->bslot, c->brow, c->bcount);
     s = check_hip(hipGetLastError(), "cached sums launch");
   }
   if (s == GW_OK) s = launch_wmom_build(ctx, ctx->coef, n, c->bslot, c->bcount, n, 1, c->brow, prec, c->wc, st);
@@ -221,7 +235,7 @@ gw_status gw_wcache_loglike(gw_wcache* c, const double* theta, const int32_t* sl
   int tpb, nch;
   cached_shape(ctx, &tpb, &nch);
   const unsigned blocks = (unsigned)((n + 255) / 256);
-  s = launch_prologue(ctx, theta, n, marg, ctx->coef, n, st);
+  s = launch_prologue_slots(ctx, theta, n, marg, slots, SlotWaves{c->rec, c->n_slots}, ctx->coef, n, st);
   if (s != GW_OK) return s;
   // out-of-range slots read slot 0 and are marked NaN afterwards
   if (kind == 2) {  // the slots' sums, no reduction
@@ -237,7 +251,7 @@ gw_status gw_wcache_loglike(gw_wcache* c, const double* theta, const int32_t* sl
                             ctx->zbuf, st, kNodeWide);
   }
   if (s == GW_OK) {
-    hipLaunchKernelGGL(k_wc_mark, dim3(blocks), dim3(256), 0, st, slots, n, c->n_slots, logl);
+    hipLaunchKernelGGL(k_wc_mark, dim3(blocks), dim3(256), 0, st, ctx->coef, n, logl);
     s = check_hip(hipGetLastError(), "slot check launch");
   }
   return s;
