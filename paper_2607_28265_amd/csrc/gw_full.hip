@@ -1291,7 +1291,7 @@ __global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ par
 }
 
 // Epilogue and distance marginal of small batches and FP64 in one launch: a
-// workgroup per four rows.  Thread (column group, w, row) sums the chunks
+// workgroup per four rows, from row p0 on.  Thread (column group, w, row) sums the chunks
 // c = w (mod 16) in order, the sixteen sums are added in order (as in
 // k_epilogue, bit for bit), and each wave finishes one row: its lanes are
 // neighbouring distances (wave_dist_lse), which mostly take the same form of a
@@ -1305,14 +1305,14 @@ __global__ void __launch_bounds__(256) k_epilogue_dist(const double* __restrict_
                                                        double* __restrict__ zbuf, const int32_t* __restrict__ zsrc,
                                                        const double* __restrict__ zc, double* __restrict__ zrow,
                                                        double node_from, const double* __restrict__ tab, int n_dist,
-                                                       const LogI0Consts* __restrict__ Cp) {
+                                                       const LogI0Consts* __restrict__ Cp, int64_t p0) {
   __shared__ double red[2 * kMaxDet][16][4];
   __shared__ double zf[2 * kMaxDet][4];
   const LogI0Consts& C = *Cp;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   {
     const int r = threadIdx.x & 3, w = (threadIdx.x >> 2) & 15;
-    const int64_t p = (int64_t)blockIdx.x * 4 + r;
+    const int64_t p = p0 + (int64_t)blockIdx.x * 4 + r;
     const int64_t pc = p < n ? p : n - 1;
     const int own = row_chunks(coef, ld, pc, n_chunks * cstride, nch_node, node_from);
     const int last = (own + cstride - 1) / cstride < n_chunks ? (own + cstride - 1) / cstride : n_chunks;
@@ -1328,7 +1328,7 @@ __global__ void __launch_bounds__(256) k_epilogue_dist(const double* __restrict_
   __syncthreads();
   if ((int)threadIdx.x < 8 * nd) {
     const int r = threadIdx.x & 3, j = threadIdx.x >> 2;
-    const int64_t p = (int64_t)blockIdx.x * 4 + r;
+    const int64_t p = p0 + (int64_t)blockIdx.x * 4 + r;
     double z = red[j][0][r];
 #pragma unroll
     for (int w = 1; w < 16; ++w) z += red[j][w][r];
@@ -1340,7 +1340,7 @@ __global__ void __launch_bounds__(256) k_epilogue_dist(const double* __restrict_
     zf[j][r] = z;
   }
   __syncthreads();
-  const int64_t p = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t p = p0 + (int64_t)blockIdx.x * 4 + wave;
   if (p >= n) return;
   double Zr = 0.0, Zi = 0.0;
   for (int i = 0; i < nd; ++i) {
@@ -1457,32 +1457,46 @@ static NodeTabs node_tabs(const gw_ctx* ctx, bool wide = false) {
   return t;
 }
 
+// A launch takes fewer than 2^32 threads: with more, the runtime reports no
+// error and the rows beyond are not computed.
+constexpr int64_t kMaxThreads = (int64_t)1 << 32;
+
+static gw_status check_launch(int64_t blocks, int threads) {
+  return blocks * threads < kMaxThreads ? GW_OK : set_error(GW_EINVAL, "batch too large for one launch");
+}
+
 // The automatic shape splits a chunk over the four waves of a 64-row
 // workgroup; a shape set by the caller and the matrix-core form keep their
-// rows per workgroup, whose waves walk the chunk in step.
-static bool full_split(const gw_ctx* ctx) { return ctx->full_tpb <= 0 && ctx->full_kernel != 2; }
+// rows per workgroup, whose waves walk the chunk in step.  So does a batch that
+// would take too many threads split (134 million rows in eight chunks): a wave
+// then walks a chunk by itself, a quarter of them.
+static bool full_split(const gw_ctx* ctx, int64_t n, int64_t n_chunks) {
+  return ctx->full_tpb <= 0 && ctx->full_kernel != 2 && (n + 63) / 64 * n_chunks * 256 < kMaxThreads;
+}
+
+static int full_chunks(const gw_ctx* ctx, int64_t n, bool split, int tpb) {
+  if (ctx->full_chunks > 0) return ctx->full_chunks;
+  // For the rows that walk every bin: aim for ~4096 workgroups of 4 waves
+  // (~2048 waves for under 2048 rows), keep at least 32 bins per wave.  At
+  // 4096 x 259,585 with 4-wave workgroups, 16,384 waves ran 12 % faster than
+  // 8192: several waves per SIMD in flight, and a short tail.
+  const int64_t nptile = split ? (n + 63) / 64 : (n + tpb - 1) / tpb;
+  const int64_t target = split ? (n >= 2048 ? 4096 : 512) : (tpb >= 256 ? 4096 : 2048);
+  const int64_t least = split ? 128 : 32;
+  int64_t want = (target + nptile - 1) / nptile;
+  want = (want + 7) / 8 * 8;
+  const int64_t maxc = ctx->geom.n_freq / least > 8 ? ctx->geom.n_freq / least : 8;
+  if (want > maxc) want = maxc / 8 * 8 > 0 ? maxc / 8 * 8 : 8;
+  if (want < 8) want = 8;
+  return (int)want;
+}
 
 void full_launch_shape(const gw_ctx* ctx, int64_t n, int* tpb_out, int* chunks_out) {
-  const bool split = full_split(ctx);
-  const int tpb = ctx->full_tpb > 0 ? ctx->full_tpb : (split || n >= 2048 ? 256 : 64);
-  int ch = ctx->full_chunks;
-  const int64_t nptile = split ? (n + 63) / 64 : (n + tpb - 1) / tpb;
-  if (ch <= 0) {
-    // For the rows that walk every bin: aim for ~4096 workgroups of 4 waves
-    // (~2048 waves for under 2048 rows), keep at least 32 bins per wave.  At
-    // 4096 x 259,585 with 4-wave workgroups, 16,384 waves ran 12 % faster than
-    // 8192: several waves per SIMD in flight, and a short tail.
-    const int64_t target = split ? (n >= 2048 ? 4096 : 512) : (tpb >= 256 ? 4096 : 2048);
-    const int64_t least = split ? 128 : 32;
-    int64_t want = (target + nptile - 1) / nptile;
-    want = (want + 7) / 8 * 8;
-    const int64_t maxc = ctx->geom.n_freq / least > 8 ? ctx->geom.n_freq / least : 8;
-    if (want > maxc) want = maxc / 8 * 8 > 0 ? maxc / 8 * 8 : 8;
-    if (want < 8) want = 8;
-    ch = (int)want;
-  }
-  *tpb_out = tpb;
-  *chunks_out = ch;
+  *tpb_out = 256;
+  *chunks_out = full_chunks(ctx, n, true, 256);
+  if (full_split(ctx, n, *chunks_out)) return;
+  *tpb_out = ctx->full_tpb > 0 ? ctx->full_tpb : (n >= 2048 ? 256 : 64);
+  *chunks_out = full_chunks(ctx, n, false, *tpb_out);
 }
 
 bool use_mfma(const gw_ctx* ctx, int prec);
@@ -1496,10 +1510,11 @@ static gw_status launch_full_nd(gw_ctx* ctx, const double* coef, int64_t ld, int
   const PhaseRuns PR = make_phase_runs(ctx->geom);
   const TrigFit F = make_trig_fit();
   const int nch_node = node_chunks(ctx, n, prec, n_chunks);
-  const bool split = full_split(ctx);
+  const bool split = full_split(ctx, n, n_chunks);
   const int64_t nptile = split ? (n + 63) / 64 : (n + tpb - 1) / tpb;
   const int64_t blocks = nptile * n_chunks;
-  if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
+  const gw_status fits = check_launch(blocks, split ? 256 : tpb);
+  if (fits != GW_OK) return fits;
   const NodeTabs tabs = node_tabs(ctx);
   const bool fp64 = prec == GW_PREC_FP64;
   auto launch = [&](auto kernel) {
@@ -1523,7 +1538,8 @@ static gw_status launch_mfma_nd(gw_ctx* ctx, const double* coef, int64_t ld, int
   const int chunk_len = (per + blk - 1) / blk * blk;
   const int64_t nptile = (n + tpb - 1) / tpb;
   const int64_t blocks = nptile * n_chunks;
-  if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
+  const gw_status fits = check_launch(blocks, tpb);
+  if (fits != GW_OK) return fits;
   hipLaunchKernelGGL((k_full_mfma<ND>), dim3((unsigned)blocks), dim3(tpb), 0, st, coef, ld, n, ctx->bins,
                      ctx->wtab, ctx->geom.k0, ctx->geom.df, nf, (int)ctx->mom_pad, blk, chunk_len, n_chunks,
                      ctx->pgain_re, ctx->pgain_im, partial);
@@ -1555,7 +1571,7 @@ static int node_chunk_count(const gw_ctx* ctx, int64_t n, int n_chunks, int spli
 
 int node_chunks(const gw_ctx* ctx, int64_t n, int prec, int n_chunks) {
   if (ctx->nodes.n <= 0 || ctx->full_kernel == 1 || use_mfma(ctx, prec)) return 0;
-  return node_chunk_count(ctx, n, n_chunks, full_split(ctx) ? 4 : 1);
+  return node_chunk_count(ctx, n, n_chunks, full_split(ctx, n, n_chunks) ? 4 : 1);
 }
 
 int cached_node_chunks(const gw_ctx* ctx, int64_t n, int n_chunks, bool always) {
@@ -1739,17 +1755,26 @@ gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_
     if (s != GW_OK) return s;
   }
   if (marg == 2 && (n < kDistSliced || prec != GW_PREC_MIXED)) {
-    auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, partial, groups, cstride, nch_node,
-                         ctx->n_det, coef, ld, n, ctx->dd, logl, zbuf, zsrc, zc, zrow, node_from, ctx->dist_tab,
-                         ctx->n_dist, C);
-    };
-    prec == GW_PREC_MIXED ? launch(k_epilogue_dist<1>) : launch(k_epilogue_dist<0>);
-    return check_hip(hipGetLastError(), "epilogue launch");
+    // 64 threads a row: launches of at most 2^25 rows
+    constexpr int64_t kRows = kMaxThreads / 128;
+    for (int64_t p0 = 0; p0 < n; p0 += kRows) {
+      const int64_t rows = n - p0 < kRows ? n - p0 : kRows;
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, partial, groups, cstride,
+                           nch_node, ctx->n_det, coef, ld, n, ctx->dd, logl, zbuf, zsrc, zc, zrow, node_from,
+                           ctx->dist_tab, ctx->n_dist, C, p0);
+      };
+      prec == GW_PREC_MIXED ? launch(k_epilogue_dist<1>) : launch(k_epilogue_dist<0>);
+      gw_status s = check_hip(hipGetLastError(), "epilogue launch");
+      if (s != GW_OK) return s;
+    }
+    return GW_OK;
   }
+  gw_status s = check_launch(blocks, 1024);
+  if (s != GW_OK) return s;
   hipLaunchKernelGGL(k_epilogue, dim3((unsigned)blocks), dim3(1024), 0, st, partial, groups, cstride, nch_node,
                      ctx->n_det, coef, ld, n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow, node_from);
-  gw_status s = check_hip(hipGetLastError(), "epilogue launch");
+  s = check_hip(hipGetLastError(), "epilogue launch");
   if (s != GW_OK || marg != 2) return s;
   // large mixed batches: lane = row (grid records are scalar loads shared by
   // 64 rows)
@@ -1780,7 +1805,8 @@ static gw_status launch_rows_nd(gw_ctx* ctx, const double* coef, int64_t n, int 
                                 hipStream_t st) {
   const int nf = (int)ctx->geom.n_freq;
   const int64_t blocks = (n + 63) / 64 * n_chunks;
-  if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
+  const gw_status fits = check_launch(blocks, 256);
+  if (fits != GW_OK) return fits;
   const int chunk_len = (int)((nf + n_chunks - 1) / n_chunks);
   const bool fp64 = prec == GW_PREC_FP64;
   auto launch = [&](auto kernel) {
@@ -1819,7 +1845,8 @@ static gw_status launch_wmom(gw_ctx* ctx, const double* coef, int64_t n, int cm,
   const int blk = wmom_block(ctx);
   const int n_blk = (int)((ctx->geom.n_freq + blk - 1) / blk);
   const int64_t blocks = (n + 63) / 64 * cm;
-  if (blocks > 0x7fffffff) return set_error(GW_EINVAL, "batch too large for one launch");
+  const gw_status fits = check_launch(blocks, 256);
+  if (fits != GW_OK) return fits;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, coef, n, n, ctx->geom.k0, ctx->geom.df, blk,
                        n_blk, cm, n_out, make_trig_consts(), rows, count, rows_per_slot, slot_of, n_slots, mom,
