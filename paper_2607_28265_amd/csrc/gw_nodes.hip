@@ -295,40 +295,12 @@ gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
     q += m;
   }
   const int n = (int)place.size(), n_cell = 2 * g.n_blk;
-  std::vector<int32_t> cell(n), count(n_cell, 0);
-  for (int q = 0; q < n; ++q) {
+  std::vector<int32_t> cell(n);
+  for (int q = 0; q < n; ++q)
     cell[q] = std::min((int)((place[q].kb + node_offset(place[q])) / g.cell), n_cell - 1);
-    ++count[cell[q]];
-  }
   const int most = std::max(kTmNodesMin, std::min(kTmNodesMax, n / kTmWaves));
-  std::vector<int32_t> a0, len, first;
-  int n_dense = 0;
-  for (int q = 0; q < n;) {
-    const int a = cell[q];
-    int e = q + count[a], top = a;
-    if (count[a] > 2 * most && n_dense == (int)a0.size()) {
-      // units of about equal nodes, at most 4 most each
-      const int units = (count[a] + 4 * most - 1) / (4 * most), each = (count[a] + units - 1) / units;
-      for (int u = 0; u < units; ++u) {
-        ++n_dense;
-        first.push_back(q + u * each);
-        a0.push_back(a);
-        len.push_back(kTgW);
-      }
-      q = e;
-      continue;
-    }
-    while (e < n && e - q + count[cell[e]] <= most && cell[e] - a < kTmCells) {
-      top = cell[e];
-      e += count[top];
-    }
-    first.push_back(q);
-    a0.push_back(a);
-    len.push_back(top - a + kTgW);
-    q = e;
-  }
-  first.push_back(n);
-  const TgCoverPlan cn = tgrid_cover(a0, len, g.n_g);
+  const TgChunkPlan chunks = tgrid_chunks(cell, n_cell, most, kTmCells);
+  const TgCoverPlan cn = tgrid_cover(chunks.a0, chunks.len, g.n_g);
   std::vector<int32_t> b0(g.n_blk), blen(g.n_blk, kTgW + 1);
   for (int b = 0; b < g.n_blk; ++b) b0[b] = 2 * b;
   const TgCoverPlan cb = tgrid_cover(b0, blen, g.n_g);
@@ -337,10 +309,11 @@ gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
   std::vector<double> bw((size_t)cell_bins * kTgW);
   for (int k = 0; k < cell_bins; ++k) win.weights((double)k / g.cell, &bw[(size_t)k * kTgW]);
   // one allocation: the weights, then the integers, those read by fours first
-  const int nc = (int)a0.size();
+  const int nc = chunks.n();
   std::vector<int32_t> idx;
   for (int c = 0; c < nc; ++c)
-    for (const int32_t v : {first[c], first[c + 1], a0[c], cn.shift[c] + a0[c]}) idx.push_back(v);
+    for (const int32_t v : {chunks.first[c], chunks.first[c + 1], chunks.a0[c], cn.shift[c] + chunks.a0[c]})
+      idx.push_back(v);
   size_t at[5];
   const std::vector<int32_t>* parts[5] = {&cn.pts, &cb.pts, &cell, &cn.shift, &cb.shift};
   for (int i = 0; i < 5; ++i) {
@@ -366,7 +339,7 @@ gw_status tm_grid_init(gw_ctx* ctx, const TimeGridShape& g) {
   t.cov[0] = TgCover{(const int4*)(t.idx + at[0]), t.idx + at[3], cn.n_many};
   t.cov[1] = TgCover{(const int4*)(t.idx + at[1]), t.idx + at[4], cb.n_many};
   t.n_chunk = nc;
-  t.n_dense = n_dense;
+  t.n_dense = chunks.n_dense;
   t.n_pts = std::max(cn.n_pts, cb.n_pts);
   t.blk = g.blk;
   t.L = g.L;

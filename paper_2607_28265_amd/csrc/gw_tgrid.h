@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "gw_fft.h"
+#include "gw_tgplan.h"
 
 namespace gw {
 
@@ -93,11 +94,10 @@ __host__ __device__ inline double2 w32(int k) {
 }
 
 // Kaiser-Bessel gridding (Beatty, Nishimura & Pauly 2005): a sample at grid
-// coordinate x is spread over kTgW grid points with weights
+// coordinate x is spread over kTgW grid points (gw_tgplan.h) with weights
 // psi(x - g) = I0(beta sqrt(1 - (2 (x - g) / kTgW)^2)) / I0(beta),
 // whose transform sum_g psi(x - g) exp(-2 pi i g nu) is
 // psi_hat(nu) exp(-2 pi i x nu) up to the images at nu + 1, nu - 1, ...
-constexpr int kTgW = 14;
 constexpr int kTgLead = kTgW / 2 - 1;  // grid points before the sample's cell
 
 // I0(x), 0 <= x <= 44, by its power series (85 terms: the rest below 1e-30).
@@ -165,37 +165,5 @@ struct TgWindow {
     for (int m = 0; m < kTgW; ++m) w[m] = c[0][m] + t * p[m] - q[m];
   }
 };
-
-// Chunk c adds to grid points a0[c] .. a0[c] + len[c] - 1, stored from off[c]
-// on (off the running sum of len); a0 and a0 + len nondecreasing.  Per grid
-// point g < n_g (pts [n_g][4]): where the first and the second chunk that
-// reach it hold it (-1: none), then the third and the last of them; per chunk
-// off - a0 (shift).  n_many: leading points, some with more than four chunks,
-// which k_tgrid sums with four lanes each (at most 256 of them, else none).
-struct TgCoverPlan {
-  std::vector<int32_t> pts, shift;
-  int n_pts = 0, n_many = 0;
-};
-inline TgCoverPlan tgrid_cover(const std::vector<int32_t>& a0, const std::vector<int32_t>& len, int n_g) {
-  TgCoverPlan p;
-  const int nc = (int)a0.size();
-  for (int c = 0; c < nc; ++c) {
-    p.shift.push_back(p.n_pts - a0[c]);
-    p.n_pts += len[c];
-  }
-  p.pts.resize(4 * (size_t)n_g);
-  int lo = 0, hi = -1;
-  for (int g = 0; g < n_g; ++g) {
-    while (hi + 1 < nc && a0[hi + 1] <= g) ++hi;
-    while (lo <= hi && a0[lo] + len[lo] <= g) ++lo;
-    p.pts[4 * g] = lo <= hi ? p.shift[lo] + g : -1;
-    p.pts[4 * g + 1] = lo < hi ? p.shift[lo + 1] + g : -1;
-    p.pts[4 * g + 2] = lo + 2;
-    p.pts[4 * g + 3] = hi;
-    if (hi - lo >= 4) p.n_many = g + 1;
-  }
-  if (p.n_many > 256) p.n_many = 0;
-  return p;
-}
 
 }  // namespace gw
