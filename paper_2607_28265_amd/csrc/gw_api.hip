@@ -29,15 +29,20 @@ gw_status check_hip(hipError_t e, const char* what) {
 }
 
 // Optional fault injection for error-path tests: GW_FAULT=alloc makes every
-// workspace allocation fail.
-static bool fault_alloc() {
+// workspace allocation fail, GW_FAULT=tables the filling of a table that has been
+// allocated.
+static bool fault(const char* which) {
   const char* f = getenv("GW_FAULT");
-  return f && strcmp(f, "alloc") == 0;
+  return f && strcmp(f, which) == 0;
+}
+
+gw_status fault_tables(const char* what) {
+  return fault("tables") ? set_error(GW_EDEVICE, "%s: injected failure", what) : GW_OK;
 }
 
 gw_status ensure_buffer(double** buf, int64_t* cap, int64_t need, const char* what) {
   if (need <= *cap) return GW_OK;
-  if (fault_alloc()) return set_error(GW_ENOMEM, "%s: injected allocation failure", what);
+  if (fault("alloc")) return set_error(GW_ENOMEM, "%s: injected allocation failure", what);
   if (*buf) {
     hipError_t e = hipFree(*buf);
     *buf = nullptr;

@@ -125,6 +125,8 @@ namespace gw {
 gw_status set_error(gw_status st, const char* fmt, ...);
 gw_status check_hip(hipError_t e, const char* what);
 gw_status ensure_buffer(double** buf, int64_t* cap, int64_t need, const char* what);
+// An injected failure (tests of the error paths), else GW_OK.
+gw_status fault_tables(const char* what);
 
 // Launch helpers (all asynchronous on ``st``).
 // ``nodes``: with the row check of the node tables (column C_NODE, else 0).

@@ -1217,11 +1217,18 @@ static gw_status het_tm_tables(gw_ctx* ctx, const TimeGridShape& g, int nch) {
   h->tm_idx = nullptr;
   gw_status s = check_hip(hipMalloc((void**)&h->tm_tab, tab.size() * sizeof(double)), "time-marginal tables");
   if (s == GW_OK) s = check_hip(hipMalloc((void**)&h->tm_idx, idx.size() * sizeof(int32_t)), "time-marginal index");
+  if (s == GW_OK) s = fault_tables("time-marginal tables");
   if (s == GW_OK)
     s = check_hip(hipMemcpy(h->tm_tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice), "tables");
   if (s == GW_OK)
     s = check_hip(hipMemcpy(h->tm_idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice), "index");
-  if (s != GW_OK) return s;
+  if (s != GW_OK) {  // no tables: a half of them would pass for the last grid's
+    if (h->tm_tab) (void)hipFree(h->tm_tab);
+    if (h->tm_idx) (void)hipFree(h->tm_idx);
+    h->tm_tab = nullptr;
+    h->tm_idx = nullptr;
+    return s;
+  }
   h->tm_cov = TgCover{(const int4*)h->tm_idx, h->tm_idx + idx.size() - cov.shift.size(), cov.n_many};
   h->tm_cell = h->tm_idx + cov.pts.size();
   h->tm_blk = g.blk;

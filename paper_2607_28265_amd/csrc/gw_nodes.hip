@@ -212,16 +212,25 @@ static gw_status node_table(gw_ctx* ctx, const PhaseCoef& ref, const std::vector
   const size_t n_rec = rec.size();
   rec.resize(n_rec + 2 * n);
   if (n > 0) memcpy(&rec[n_rec], place.data(), n * sizeof(NodePlace));
-  gw_status s = check_hip(hipMalloc((void**)&out->rec, rec.size() * sizeof(double)), "node records");
+  // published whole or not at all
+  NodeTable t;
+  gw_status s = check_hip(hipMalloc((void**)&t.rec, rec.size() * sizeof(double)), "node records");
+  if (s == GW_OK) s = fault_tables("node records");
   if (s == GW_OK)
-    s = check_hip(hipMemcpy(out->rec, rec.data(), rec.size() * sizeof(double), hipMemcpyHostToDevice), "records");
-  if (s != GW_OK || n == 0) return s;
-  hipLaunchKernelGGL(k_node_weights, dim3((unsigned)n), dim3(256), 0, nullptr, (const NodePlace*)(out->rec + n_rec),
-                     (const double*)ctx->bins, nd, ref, make_trig_consts(), rs, out->rec);
-  s = check_hip(hipGetLastError(), "node weights launch");
-  if (s == GW_OK) s = check_hip(hipStreamSynchronize(nullptr), "node weights");
-  if (s == GW_OK) out->n = (int)n;
-  return s;
+    s = check_hip(hipMemcpy(t.rec, rec.data(), rec.size() * sizeof(double), hipMemcpyHostToDevice), "records");
+  if (s == GW_OK && n > 0) {
+    hipLaunchKernelGGL(k_node_weights, dim3((unsigned)n), dim3(256), 0, nullptr, (const NodePlace*)(t.rec + n_rec),
+                       (const double*)ctx->bins, nd, ref, make_trig_consts(), rs, t.rec);
+    s = check_hip(hipGetLastError(), "node weights launch");
+    if (s == GW_OK) s = check_hip(hipStreamSynchronize(nullptr), "node weights");
+  }
+  if (s != GW_OK) {
+    if (t.rec) (void)hipFree(t.rec);
+    return s;
+  }
+  t.n = (int)n;
+  *out = t;
+  return GW_OK;
 }
 
 static gw_status node_table(gw_ctx* ctx, const PhaseCoef& ref, const std::vector<NodePlace>& place, NodeTable* out) {
