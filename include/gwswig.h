@@ -671,7 +671,8 @@ gw_status gw_prescreen_batch(gw_ctx* ctx, gw_mlp* mlp, const double* x, int64_t 
  * GW_FULL) or heterodyned (GW_HET) kernels on the caller's batch ``theta``
  * (device [n, 13]), ``reps`` timed calls each after one warm-up, keeps the
  * fastest in the context and returns it: best_shape[0..2] = (proposals per
- * workgroup, frequency chunks, 0) for the full band or (waves per workgroup,
+ * workgroup, frequency chunks, 0) for the full band (zeros: the automatic
+ * shape, one of the candidates) or (waves per workgroup,
  * persistent workgroups, edge chunks with 0 = heuristic) for the heterodyned
  * form; *best_ms the mean time of one call.  Synchronises the stream.  Errors
  * as loglike_batch.

@@ -12,6 +12,10 @@ import os
 
 from . import _lib
 
+# The set of shapes that gw_autotune chooses from, per likelihood; changed with it,
+# so that a shape stored as the fastest of another set is not applied.
+_CANDIDATES = {_lib.GW_FULL: 2, _lib.GW_HET: 1}
+
 
 def _cache_path() -> str:
     return os.environ.get("GW_AUTOTUNE_CACHE", os.path.expanduser("~/.cache/gwswig_autotune.json"))
@@ -20,7 +24,8 @@ def _cache_path() -> str:
 def _key(ctx, like, n, marg, prec, extra) -> str:
     import torch
     dev = torch.cuda.get_device_name(ctx.device) if torch.cuda.is_available() else "none"
-    return json.dumps([dev, like, int(n), int(ctx.n_freq), int(ctx.n_det), marg, prec, extra])
+    key = [dev, like, int(n), int(ctx.n_freq), int(ctx.n_det), marg, prec, extra]
+    return json.dumps(key if _CANDIDATES[like] == 1 else key + [_CANDIDATES[like]])
 
 
 def _load() -> dict:

@@ -1584,7 +1584,8 @@ gw_status gw_graph_info(const gw_ctx* ctx, int32_t* n_graphs, double* last_insta
 }
 
 // Autotuner: time every candidate launch shape on the caller's batch and keep
-// the fastest in the context.  Candidates: full band, proposals per workgroup
+// the fastest in the context.  Candidates: full band, the automatic shape (the
+// one in which a workgroup's waves share 64 rows) and proposals per workgroup
 // {64, 128, 256} x frequency chunks {8 .. 512} (multiples of 8, at least 16
 // bins per chunk); heterodyned, waves per workgroup {1, 2, 4} x persistent
 // grid {8, 16, 32, 64} waves per CU x edge chunks {heuristic, 8, 16, 32}.
@@ -1610,6 +1611,7 @@ gw_status gw_autotune(gw_ctx* ctx, const double* theta, int64_t n, int32_t like,
   };
   std::vector<Cand> cands;
   if (like == GW_FULL) {
+    cands.push_back({0, 0, 0});
     for (int tpb : {64, 128, 256})
       for (int ch : {8, 16, 32, 64, 128, 256, 512})
         if (ctx->geom.n_freq / ch >= 16) cands.push_back({tpb, ch, 0});
