@@ -506,7 +506,7 @@ def cache_leg(gw, torch, prob, steps, warmup, mixed_value):
                 ms, nl = gw._lib.gw_profile_read(ctx.handle)
                 gw._lib.gw_profile_enable(ctx.handle, False)
                 k_ms = ms / max(nl, 1)
-                # fast rows sum over interpolation nodes, rows beyond their tables over the cached moments
+                # both launches: slots within the interpolation nodes' tables, slots of moments
                 r["kernel"] = "fast rows' sums over nodes and cached moments"
                 r["kernel_ms"] = k_ms
             res[f"kind{kind}"] = r

@@ -1852,7 +1852,6 @@ static gw_status launch_wmom(gw_ctx* ctx, const double* coef, int64_t n, int cm,
                        n_blk, cm, n_out, make_trig_consts(), rows, count, rows_per_slot, slot_of, n_slots, mom,
                        wmom_slot_f2(ctx), skip_nodes, partial);
   };
-  const int slot = prof_begin(ctx, st, 1);
   switch (ctx->n_det) {
     case 1: launch(k_wmom<1>); break;
     case 2: launch(k_wmom<2>); break;
@@ -1860,7 +1859,6 @@ static gw_status launch_wmom(gw_ctx* ctx, const double* coef, int64_t n, int cm,
     case 4: launch(k_wmom<4>); break;
     default: return set_error(GW_ENOTSUP, "n_det %d not supported", ctx->n_det);
   }
-  prof_end(ctx, slot, st);
   return check_hip(hipGetLastError(), "cached-waveform kernel launch");
 }
 
@@ -1874,7 +1872,10 @@ gw_status launch_cached(gw_ctx* ctx, const double* coef, int64_t n, int prec, in
   // the epilogue sums rows that the node tables cover over nch_node chunks,
   // the fast ones among them
   const int cm = wmom_chunks(ctx, nch_node > 0 ? nch_node : n_chunks);
-  return launch_wmom(ctx, coef, n, cm, n_chunks, fast_rows, counts + 1, 2, nullptr, n, mom, false, partial, st);
+  const int slot = prof_begin(ctx, st, 1);
+  s = launch_wmom(ctx, coef, n, cm, n_chunks, fast_rows, counts + 1, 2, nullptr, n, mom, false, partial, st);
+  prof_end(ctx, slot, st);
+  return s;
 }
 
 gw_status launch_all_rows(gw_ctx* ctx, const double* coef, int64_t n, int prec, int n_chunks, int nch_node,
@@ -1893,10 +1894,13 @@ gw_status launch_wcache_fast(gw_ctx* ctx, const double* coef, int64_t n, int pre
                              hipStream_t st) {
   if (n == 0) return GW_OK;
   gw_status s = GW_OK;
+  const int slot = prof_begin(ctx, st, 1);  // both forms: a row is summed by one of them
   if (nch_node > 0) s = launch_rows(ctx, coef, n, prec, nch_node, nch_node, nullptr, nullptr, true, partial, st);
-  if (s != GW_OK) return s;
-  return launch_wmom(ctx, coef, n, n_chunks, n_chunks, nullptr, nullptr, 1, slot_of, n_slots, mom, nch_node > 0,
-                     partial, st);
+  if (s == GW_OK)
+    s = launch_wmom(ctx, coef, n, n_chunks, n_chunks, nullptr, nullptr, 1, slot_of, n_slots, mom, nch_node > 0,
+                    partial, st);
+  prof_end(ctx, slot, st);
+  return s;
 }
 
 template <int ND>
