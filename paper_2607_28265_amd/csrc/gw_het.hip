@@ -826,10 +826,14 @@ static int het_ech(const gw_ctx* ctx, int64_t n_rows) {
   // Large batches take at least 48 bins a chunk: its start and its partials
   // (three per detector and row) weigh more than the waves it adds (mixed, 500
   // bins: 12,000 rows 109 us at 62 chunks and 84 at 10, 30,000 rows 141 at 35
-  // and 133 at 10).
+  // and 133 at 10); but with few bins as many as make 1024 items, one a SIMD, of
+  // at least 12 bins (FP64, 9000 rows: 50 bins 41 us in one chunk, 28 in four;
+  // 100 bins 42 in two, 30 in eight).
   const int64_t tiles = (n_rows + 63) / 64;
   int64_t e = (kHetWaves + tiles - 1) / tiles;
-  const int64_t emax = std::max<int64_t>(1, std::min<int64_t>(64, nb / (n_rows >= kDistRowsPerLane ? 48 : 8)));
+  int64_t emax = std::min<int64_t>(64, nb / 8);
+  if (n_rows >= kDistRowsPerLane) emax = std::min<int64_t>(64, std::max(nb / 48, std::min(nb / 12, 1024 / tiles)));
+  emax = std::max<int64_t>(1, emax);
   e = std::max<int64_t>(1, std::min(e, emax));
   return (int)e;
 }
