@@ -1178,8 +1178,9 @@ __device__ inline int row_chunks(const double* __restrict__ coef, int64_t ld, in
   return nch_node > 0 && coef[C_NODE * ld + p] >= node_from ? nch_node : n_chunks;
 }
 
+template <int ND>
 __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ partial, int n_chunks, int cstride,
-                                                  int nch_node, int nd, const double* __restrict__ coef, int64_t ld, int64_t n,
+                                                  int nch_node, const double* __restrict__ coef, int64_t ld, int64_t n,
                                                   double dd, int marg, double* __restrict__ logl,
                                                   double* __restrict__ zbuf, const int32_t* __restrict__ zsrc,
                                                   const double* __restrict__ zc, double* __restrict__ zrow,
@@ -1188,45 +1189,48 @@ __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ pa
   const int wave = threadIdx.x >> 6;
   const int64_t p = (int64_t)blockIdx.x * 64 + lane;
   const int64_t pc = p < n ? p : n - 1;
-  double z[2 * kMaxDet];
+  double z[2 * ND];
 #pragma unroll
-  for (int j = 0; j < 2 * kMaxDet; ++j) z[j] = 0.0;
+  for (int j = 0; j < 2 * ND; ++j) z[j] = 0.0;
+  // the row's chunks, and those of any row of the wave; four chunks in flight (the
+  // 512 chunks of 64 rows of 128 s on the bins: 67 us a chunk at a time)
   const int own = row_chunks(coef, ld, pc, n_chunks * cstride, nch_node, node_from);
-  for (int c = wave; c < n_chunks && __any(c * cstride < own); c += 16) {
-    if (c * cstride < own) {
+  const int last = (own + cstride - 1) / cstride < n_chunks ? (own + cstride - 1) / cstride : n_chunks;
+  const int most = __any(last == n_chunks) ? n_chunks : __builtin_amdgcn_readfirstlane(last);
+#pragma unroll 4
+  for (int c = wave; c < most; c += 16) {
+    const double* __restrict__ src = partial + (int64_t)c * cstride * 2 * ND * n + pc;
+    double v[2 * ND];
 #pragma unroll
-      for (int j = 0; j < 2 * kMaxDet; ++j)
-        if (j < 2 * nd) z[j] += partial[((int64_t)c * cstride * 2 * nd + j) * n + pc];
-    }
+    for (int j = 0; j < 2 * ND; ++j) v[j] = src[j * n];
+#pragma unroll
+    for (int j = 0; j < 2 * ND; ++j) z[j] += c < last ? v[j] : 0.0;
   }
-  __shared__ double red[15][2 * kMaxDet][64];
+  __shared__ double red[15][2 * ND][64];
   if (wave > 0) {
 #pragma unroll
-    for (int j = 0; j < 2 * kMaxDet; ++j) red[wave - 1][j][lane] = z[j];
+    for (int j = 0; j < 2 * ND; ++j) red[wave - 1][j][lane] = z[j];
   }
   __syncthreads();
   if (wave != 0 || p >= n) return;
   for (int w = 0; w < 15; ++w)
 #pragma unroll
-    for (int j = 0; j < 2 * kMaxDet; ++j) z[j] += red[w][j][lane];
+    for (int j = 0; j < 2 * ND; ++j) z[j] += red[w][j][lane];
   if (zsrc) {
     const int32_t sl = zsrc[p];
     if (sl >= 0) {
 #pragma unroll
-      for (int j = 0; j < 2 * kMaxDet; ++j)
-        if (j < 2 * nd) z[j] = zc[(int64_t)sl * 2 * nd + j];
+      for (int j = 0; j < 2 * ND; ++j) z[j] = zc[(int64_t)sl * 2 * ND + j];
     }
   }
   if (zrow) {
 #pragma unroll
-    for (int j = 0; j < 2 * kMaxDet; ++j)
-      if (j < 2 * nd) zrow[p * 2 * nd + j] = z[j];
+    for (int j = 0; j < 2 * ND; ++j) zrow[p * 2 * ND + j] = z[j];
   }
   const bool valid = coef[C_VALID * ld + p] != 0.0;
   double Zr = 0.0, Zi = 0.0, plain = 0.0;
 #pragma unroll
-  for (int i = 0; i < kMaxDet; ++i) {
-    if (i >= nd) break;
+  for (int i = 0; i < ND; ++i) {
     const double zr = z[2 * i], zi = z[2 * i + 1];
     const double ar = coef[(C_APRE + i) * ld + p];
     const double ai = coef[(C_APIM + i) * ld + p];
@@ -1772,8 +1776,17 @@ gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_
   }
   gw_status s = check_launch(blocks, 1024);
   if (s != GW_OK) return s;
-  hipLaunchKernelGGL(k_epilogue, dim3((unsigned)blocks), dim3(1024), 0, st, partial, groups, cstride, nch_node,
-                     ctx->n_det, coef, ld, n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow, node_from);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(1024), 0, st, partial, groups, cstride, nch_node, coef, ld,
+                       n, ctx->dd, marg, logl, zbuf, zsrc, zc, zrow, node_from);
+  };
+  switch (ctx->n_det) {
+    case 1: launch(k_epilogue<1>); break;
+    case 2: launch(k_epilogue<2>); break;
+    case 3: launch(k_epilogue<3>); break;
+    case 4: launch(k_epilogue<4>); break;
+    default: return set_error(GW_ENOTSUP, "n_det %d not supported", ctx->n_det);
+  }
   s = check_hip(hipGetLastError(), "epilogue launch");
   if (s != GW_OK || marg != 2) return s;
   // large mixed batches: lane = row (grid records are scalar loads shared by
