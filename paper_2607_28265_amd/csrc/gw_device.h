@@ -38,6 +38,7 @@ enum CoefCol {
   C_TAU0 = 25,       // total time shift of detector 0 (t_c + dt_0), s
   C_AMP = 26,        // amplitude A
   C_NODE = 27,       // full band: what of the row the node tables cover (gw_nodes.h)
+  C_TILE = 28,       // full band, first row of 64: which of them the tables cover (tile_row)
   C_NCOEF = 32
 };
 
@@ -64,7 +65,7 @@ struct PhaseCoef {
 // Per-proposal prologue in two halves that share nothing but the row, so that
 // two waves can take one each: the phase coefficients (masses, spins, tides),
 // and the sky, delays and amplitude.  Together they write every column but
-// C_NODE into out[] (stride ``ld``); a row that is not physical gets zeros.
+// C_NODE and C_TILE into out[] (stride ``ld``); a row that is not physical gets zeros.
 // marg: 0 plain, 1 phase-marginalised (phi_c := 0), 2 phase+distance
 // (phi_c := 0, d_L := 1 Mpc), 3 phase+time (phi_c := 0, t_c := 0).
 struct Row {
@@ -170,7 +171,7 @@ __device__ inline double prologue_sky(const Row& row, int marg, const Geom& g, d
     out[C_A8 * ld] = 0.0;
 #pragma unroll
     for (int c = C_DT1; c < C_NCOEF; ++c)
-      if (c != C_NODE) out[c * ld] = 0.0;
+      if (c != C_NODE && c != C_TILE) out[c * ld] = 0.0;
     return ta;
   }
   const double mc = row.v[0], iota = row.v[7], ra = row.v[8], dec = row.v[9], psi = row.v[10];
@@ -227,7 +228,7 @@ __device__ inline double prologue_sky(const Row& row, int marg, const Geom& g, d
   out[C_TAU0 * ld] = tau0;
   out[C_AMP * ld] = amp;
 #pragma unroll
-  for (int c = C_NODE + 1; c < C_NCOEF; ++c) out[c * ld] = 0.0;
+  for (int c = C_TILE + 1; c < C_NCOEF; ++c) out[c * ld] = 0.0;
   return ta;
 }
 

@@ -100,6 +100,8 @@ __global__ void __launch_bounds__(256) k_prologue(const double* __restrict__ the
     const double t = tau[lane];
     const double node = !good ? 0.0 : (t <= chk->tau_max ? kNodeFull : (t <= kTauCap ? kNodeWide : kNodePhase));
     coef[C_NODE * ld + p] = SLOT && in[0][lane] < 0 ? kNodeNoSlot : node;
+    const uint64_t tile = __ballot(node >= (marg == 3 ? kNodePhase : kNodeFull));
+    if (lane == 0) coef[C_TILE * ld + p] = __longlong_as_double((int64_t)tile);
   }
 }
 
@@ -163,11 +165,15 @@ __device__ inline void phasor(double r, const TrigConsts& T, double* gr, double*
 // SPLIT (the automatic launch shape, and row lists): 64 rows to a workgroup,
 // whose four waves split the chunk's nodes or bins between them (each with its
 // own start phase), their sums added in wave order: a quarter of the partial
-// sums for the same number of waves.  With ``rows`` the rows are
-// rows[0 .. *count) (at most n, in any order) instead of 0 .. n - 1, and
-// workgroups past the count exit at once.  Rows with C_NODE = tabs.row are
-// summed over the nodes (of table blockIdx.y), the others over the bins, or
-// with nodes_only not at all (the caller sums them its own way).
+// sums for the same number of waves.  Tiles hold rows by kind (tile_row).  With
+// ``rows`` the rows are rows[0 .. *count) (at most n, in any order) instead of
+// 0 .. n - 1, and workgroups past the count exit at once.  Rows with C_NODE =
+// tabs.row are summed over the nodes (of table blockIdx.y), the others over the
+// bins, or with nodes_only not at all (the caller sums them its own way).
+// The first nch_node chunks of workgroups take the node chunks, the next n_chunks
+// the bins', so a tile of both kinds waits for the longer of the two and not for
+// their sum (64 rows of 32 s, half of each kind: 48 us a call with both in one wave,
+// 32 so; 27 and 22 of either kind alone).
 template <int ND, int PREC, bool SPLIT>
 __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, int64_t ld, int64_t n,
                                               const double* __restrict__ bins, int64_t k0, double df,
@@ -183,29 +189,36 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
   const int tpb = SPLIT ? 64 : blockDim.x;
   const int nptile = (int)((n + tpb - 1) / tpb);
   int chunk, ptile;
-  decode_block(blockIdx.x, nptile, n_chunks, &chunk, &ptile);
-  int64_t p, pc;
-  bool live;
-  if constexpr (SPLIT) {
-    const int64_t cnt = rows ? *count : n;
-    if ((int64_t)ptile * tpb >= cnt) return;  // uniform over the workgroup
-    const int64_t idx = (int64_t)ptile * tpb + (threadIdx.x & 63);
-    live = idx < cnt;
-    p = live ? idx : cnt - 1;
-    if (rows) p = rows[p];
-    pc = p;
-  } else {
-    p = (int64_t)ptile * tpb + threadIdx.x;
-    pc = p < n ? p : n - 1;
-    live = p < n;
-  }
-
+  decode_block(blockIdx.x, nptile, nodes_only ? nch_node : nch_node + n_chunks, &chunk, &ptile);
+  const bool over_nodes = chunk < nch_node;
+  if (!over_nodes) chunk -= nch_node;
   // Rows that the node tables cover (gw_nodes.h) take the sums over the nodes,
-  // in the first nch_node chunks; the others the walk over every bin below.
-  // A wave with rows of both kinds does both.
-  const bool on_nodes = nch_node > 0 && coef[C_NODE * ld + pc] == node_row;
-  const bool any_node = chunk < nch_node && __any(on_nodes), any_bins = !nodes_only && __any(!on_nodes);
-  if (!any_node && !any_bins) return;  // the waves of a SPLIT workgroup share their rows
+  // the others the walk over every bin below.  The waves of a SPLIT workgroup
+  // share their rows.
+  int64_t p;
+  bool live, covered;
+  if (SPLIT && !rows && nch_node > 0 && !nodes_only) {  // (with nodes_only there are more than two kinds)
+    const TileRow r = tile_row(coef, ld, n, ptile, threadIdx.x & 63);
+    live = r.p < n;
+    p = live ? r.p : n - 1;
+    covered = r.covered;
+  } else {
+    if (SPLIT && rows) {
+      const int64_t cnt = *count;
+      if ((int64_t)ptile * tpb >= cnt) return;  // uniform over the workgroup
+      const int64_t idx = (int64_t)ptile * tpb + (threadIdx.x & 63);
+      live = idx < cnt;
+      p = rows[live ? idx : cnt - 1];
+    } else {
+      p = (int64_t)ptile * tpb + (SPLIT ? threadIdx.x & 63 : threadIdx.x);
+      live = p < n;
+      if (!live) p = n - 1;
+    }
+    covered = nch_node > 0 && coef[C_NODE * ld + p] == node_row;
+  }
+  const bool mine = live && covered == over_nodes;
+  if (!__any(mine)) return;
+  const int64_t pc = p;
 
   PhaseCoef c;
   c.a0 = coef[C_A0 * ld + pc];
@@ -238,7 +251,7 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
     zr[i] = 0.0;
     zi[i] = 0.0;
   }
-  if (any_bins) {
+  if (!over_nodes) {
     double rr[ND], ri[ND];  // rho_i
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
@@ -425,7 +438,7 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
       }
     }
   }
-  if (any_node) {
+  if (over_nodes) {
     // the nodes of this wave's share of the chunk, in pairs with the next
     // record in flight, as for the bins below
     constexpr int NS = node_rs(ND);
@@ -439,12 +452,9 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
       je = b2 + sub < je ? b2 + sub : je;
       jb = b2;
     }
-    double sr[ND], si[ND], dt[ND];
+    double dt[ND];
 #pragma unroll
-    for (int i = 0; i < ND; ++i) {
-      sr[i] = si[i] = 0.0;
-      dt[i] = i == 0 ? 0.0 : coef[(C_DT1 + i - 1) * ld + pc];
-    }
+    for (int i = 0; i < ND; ++i) dt[i] = i == 0 ? 0.0 : coef[(C_DT1 + i - 1) * ld + pc];
     auto step = [&](const double* __restrict__ rec) {
       const double r0 = node_phase(c, rec[0], rec[1], rec[2], rec[3], rec[5]);
 #pragma unroll
@@ -452,10 +462,10 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
         double gr, gi;
         node_phasor<PREC>(i == 0 ? r0 : fma(rec[4], dt[i], r0), T, F, &gr, &gi);
         const double wr = rec[6 + 2 * i], wi = rec[7 + 2 * i];
-        sr[i] = fma(wr, gr, sr[i]);
-        sr[i] = fma(-wi, gi, sr[i]);
-        si[i] = fma(wr, gi, si[i]);
-        si[i] = fma(wi, gr, si[i]);
+        zr[i] = fma(wr, gr, zr[i]);
+        zr[i] = fma(-wi, gi, zr[i]);
+        zi[i] = fma(wr, gi, zi[i]);
+        zi[i] = fma(wi, gr, zi[i]);
       }
     };
     if (je > jb) {
@@ -474,16 +484,11 @@ __global__ void __launch_bounds__(256) k_full(const double* __restrict__ coef, i
       }
       if (j < je) step(ra);
     }
-#pragma unroll
-    for (int i = 0; i < ND; ++i) {
-      zr[i] = on_nodes ? sr[i] : zr[i];
-      zi[i] = on_nodes ? si[i] : zi[i];
-    }
   }
   if constexpr (SPLIT) {
     if (!wave_sums_combine<ND>(zr, zi)) return;
   }
-  if (live && (on_nodes ? chunk < nch_node : !nodes_only)) {
+  if (mine) {
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       partial[((int64_t)chunk * 2 * ND + 2 * i) * n + p] = zr[i];
@@ -1472,10 +1477,10 @@ static gw_status check_launch(int64_t blocks, int threads) {
 // The automatic shape splits a chunk over the four waves of a 64-row
 // workgroup; a shape set by the caller and the matrix-core form keep their
 // rows per workgroup, whose waves walk the chunk in step.  So does a batch that
-// would take too many threads split (134 million rows in eight chunks): a wave
-// then walks a chunk by itself, a quarter of them.
+// would take too many threads split (67 million rows in eight chunks, and eight of
+// nodes): a wave then walks a chunk by itself, a quarter of them.
 static bool full_split(const gw_ctx* ctx, int64_t n, int64_t n_chunks) {
-  return ctx->full_tpb <= 0 && ctx->full_kernel != 2 && (n + 63) / 64 * n_chunks * 256 < kMaxThreads;
+  return ctx->full_tpb <= 0 && ctx->full_kernel != 2 && (n + 63) / 64 * 2 * n_chunks * 256 < kMaxThreads;
 }
 
 static int full_chunks(const gw_ctx* ctx, int64_t n, bool split, int tpb) {
@@ -1516,7 +1521,7 @@ static gw_status launch_full_nd(gw_ctx* ctx, const double* coef, int64_t ld, int
   const int nch_node = node_chunks(ctx, n, prec, n_chunks);
   const bool split = full_split(ctx, n, n_chunks);
   const int64_t nptile = split ? (n + 63) / 64 : (n + tpb - 1) / tpb;
-  const int64_t blocks = nptile * n_chunks;
+  const int64_t blocks = nptile * (nch_node + n_chunks);
   const gw_status fits = check_launch(blocks, split ? 256 : tpb);
   if (fits != GW_OK) return fits;
   const NodeTabs tabs = node_tabs(ctx);
@@ -1817,7 +1822,7 @@ static gw_status launch_rows_nd(gw_ctx* ctx, const double* coef, int64_t n, int 
                                 const int32_t* rows, const int32_t* count, bool wide, double* partial,
                                 hipStream_t st) {
   const int nf = (int)ctx->geom.n_freq;
-  const int64_t blocks = (n + 63) / 64 * n_chunks;
+  const int64_t blocks = (n + 63) / 64 * (wide ? nch_node : nch_node + n_chunks);
   const gw_status fits = check_launch(blocks, 256);
   if (fits != GW_OK) return fits;
   const int chunk_len = (int)((nf + n_chunks - 1) / n_chunks);

@@ -64,6 +64,70 @@ struct NodeTabs {
 // per detector.
 __host__ __device__ constexpr int node_rs(int nd) { return 6 + 2 * nd; }
 
+// Rows to a tile of 64 lanes, covered rows apart from the others: a wave that
+// holds both kinds pays for both, and two rows in a hundred beyond the tables put
+// one into most tiles (20,000 such rows of 8 s, plain mixed: 216 us a call, 149 so;
+// 99 with none of them beyond, 144 with all).  In a group of kTileGroup tiles the covered rows come first, each kind in
+// order, so one tile at most is mixed.  k_prologue leaves each tile's mask of
+// covered rows in C_TILE of its first row; a group of one kind is taken as it lies.
+constexpr int kTileGroup = 16;
+
+struct TileRow {
+  int64_t p;     // n: no row
+  bool covered;
+};
+
+// The row of lane ``lane`` of tile ``tile`` (of the n rows at coef, stride ld).  All
+// lanes of the wave together.
+__device__ inline TileRow tile_row(const double* __restrict__ coef, int64_t ld, int64_t n, int64_t tile, int lane) {
+  const int64_t base = tile / kTileGroup * kTileGroup * 64;
+  const int rows = n - base < kTileGroup * 64 ? (int)(n - base) : kTileGroup * 64;
+  int k = (int)(tile % kTileGroup) * 64 + lane;
+  const bool none = k >= rows;  // (no lane leaves: the words below come from all)
+  // lane i: the masks of tile i of the group
+  uint64_t in = 0, out = 0;
+  if (lane * 64 < rows) {
+    in = (uint64_t)__double_as_longlong(coef[C_TILE * ld + base + 64 * lane]);
+    const int left = rows - 64 * lane;
+    out = ~in & (left >= 64 ? ~0ull : (1ull << left) - 1);
+  }
+  const bool any_in = __any(in != 0), any_out = __any(out != 0);
+  if (!any_in || !any_out) return TileRow{none ? n : base + k, !none && any_in};
+  int covered = __popcll(in);
+#pragma unroll
+  for (int o = 1; o < kTileGroup; o <<= 1) covered += __shfl_xor(covered, o, 64);
+  covered = __builtin_amdgcn_readfirstlane(covered);
+  const bool kind = k < covered;
+  if (!kind) k -= covered;
+  // the k-th row of its kind: its tile, then its bit
+  uint64_t word = 0;
+  int at = -1;
+#pragma unroll
+  for (int i = 0; i < kTileGroup; ++i) {
+    const uint32_t il = __builtin_amdgcn_readlane((uint32_t)in, i), ih = __builtin_amdgcn_readlane((uint32_t)(in >> 32), i);
+    const uint32_t ol = __builtin_amdgcn_readlane((uint32_t)out, i), oh = __builtin_amdgcn_readlane((uint32_t)(out >> 32), i);
+    const uint64_t w = kind ? (uint64_t)ih << 32 | il : (uint64_t)oh << 32 | ol;
+    const int c = __popcll(w);
+    if (at < 0 && k < c) {
+      at = i;
+      word = w;
+    } else if (at < 0) {
+      k -= c;
+    }
+  }
+  int bit = 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const int c = __popcll(word & ((1ull << o) - 1));
+    if (k >= c) {
+      k -= c;
+      word >>= o;
+      bit += o;
+    }
+  }
+  return TileRow{none ? n : base + 64 * at + bit, !none && kind};
+}
+
 // d Psi / d f without the linear time term, in cycles per Hz.
 __device__ inline double phase_slope(const PhaseCoef& c, double x, double lnf, double xm8, double xm3) {
   // sum_j a_j (j - 5) / 3 x^(j - 8) + (b5 + b6 x) / f + b6 ln f / (3 x^2)
