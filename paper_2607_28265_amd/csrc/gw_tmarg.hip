@@ -191,19 +191,21 @@ __global__ void __launch_bounds__(256, 4) k_tspread(const double* __restrict__ c
   }
 }
 
-// The other rows (all: every row), over the bins.  Lane = row, a wave per
-// (64-row tile, block of two cells); a tile with no such row leaves at once (5 us
-// for 16 tiles of 128 s).  A kernel of its own: together with the nodes it took
-// three waves a SIMD, 1070 us for 1000 such rows against 880 (twelve moments of
-// each block and their transforms: 923).  The block's bins are walked from the
-// top down (wave-uniform records), the window of kTgW points moving down once.  FP64: the
-// phase of every bin by its full series.  Mixed: the phase by the cubic
-// recurrence in the runs of the full-band walk (gw_phase.h: a bin's phase
-// depends on its run alone, so it is the same here as in the distance-marginal
-// reduction), FP32 hardware sin/cos, FP64 sums.
-// e_i = (A P_i) exp(-2 pi i f_k dtau_i) starts at the block's top bin and
+// The other rows (all: every row), over the bins.  Lane = row, the tiles by kind of
+// row (tile_row).  A wave takes a block's upper cell, then its lower one, adding the
+// upper one's points to it from memory, or, in a launch of few waves (PAIR), two
+// waves a cell each, the lower one's adding the upper one's from LDS: the same sums
+// (64 rows of 128 s, mixed: 439 us a call in one wave, 239 in two).  A tile with no
+// such row leaves at once (5 us for 16 tiles of 128 s, 8 in pairs).  A kernel of its
+// own: in one launch with the nodes, parted by workgroup, both spill (1000 rows within
+// the tables: 290 us a call against 148).  The cell's bins are walked from the top
+// down (wave-uniform records).  FP64: the phase of every bin by its full series.
+// Mixed: the phase by the cubic recurrence in the runs of the full-band walk
+// (gw_phase.h: a bin's phase depends on its run alone, so it is the same here as in
+// the distance-marginal reduction), FP32 hardware sin/cos, FP64 sums.
+// e_i = (A P_i) exp(-2 pi i f_k dtau_i) starts at the cell's top bin and
 // steps down by conj(rho_i), rho_i = exp(-2 pi i df dtau_i).
-template <int ND, int PREC>
+template <int ND, int PREC, bool PAIR>
 __global__ void __launch_bounds__(256, 4) k_tbins(const double* __restrict__ coef, int64_t ld, int64_t n, bool all,
                                                   const double* __restrict__ bins, int64_t k0, double df, int n_freq,
                                                   int blk, int n_blk, TrigConsts T, PhaseRuns R, double pg_re,
@@ -211,48 +213,32 @@ __global__ void __launch_bounds__(256, 4) k_tbins(const double* __restrict__ coe
                                                   double2* __restrict__ part) {
   constexpr int RS = 4 + 2 * ND;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the tiles of a unit are rotated by the unit: those without such a row leave, and
+  // the rest then fall on all XCDs and on all of an XCD's engines, to which
+  // workgroups are dealt in turn (500 of 1000 rows of 128 s: 946 us with every second
+  // workgroup of an XCD one that leaves, 1030 for all rows)
   const int nptile = (int)((n + 63) / 64);
-  const int unit = blockIdx.x / nptile, ptile = blockIdx.x - unit * nptile;
-  const int64_t p = (int64_t)ptile * 64 + lane;
-  const int64_t pc = p < n ? p : n - 1;
-  const bool mine = p < n && (all || !(coef[C_NODE * ld + pc] >= kNodePhase));
-  if (__ballot(mine) == 0) return;
-  double2* __restrict__ row = part + p * pitch;
+  const int unit = blockIdx.x / nptile;
+  int ptile = blockIdx.x - unit * nptile + ((unit + (unit >> 2)) & 15);
+  while (ptile >= nptile) ptile -= nptile;
+  const TileRow r = all ? TileRow{(int64_t)ptile * 64 + lane, false} : tile_row(coef, ld, n, ptile, lane);
+  const int64_t p = r.p, pc = p < n ? p : n - 1;
+  const bool mine = p < n && !r.covered;
+  if (!__any(mine)) return;
   const PhaseCoef c = tm_phase_coef(coef, ld, pc);
   constexpr int K = kTgW;
-  const int b = 4 * unit + wv;
-  if (b >= n_blk) return;
-  const int kb = b * blk, ke = kb + blk < n_freq ? kb + blk : n_freq;
-  const int mid = kb + (blk + 1) / 2;  // the upper cell's first bin
-  double2* out = row + (int64_t)b * (K + 1);
-  // the highest point, which the upper cell alone reaches
-  auto put_top = [&](double vr, double vi) {
-    if (PREC == 1) {
-      const double tr = vr * pg_re - vi * pg_im;
-      vi = vr * pg_im + vi * pg_re;
-      vr = tr;
-    }
-    if (mine) out[K] = make_double2(vr, vi);
-  };
-  if (ke <= mid) put_top(0.0, 0.0);
+  const int b = PAIR ? 2 * unit + (wv >> 1) : 4 * unit + wv;
+  const int b0 = b * blk, b1 = b0 + blk < n_freq ? b0 + blk : n_freq, mid = b0 + (blk + 1) / 2;
+  int kb = 0, ke = 0;  // the cell's bins
   double mr[K], mi[K];
-#pragma unroll
-  for (int m = 0; m < K; ++m) mr[m] = mi[m] = 0.0;
   double er[ND], ei[ND], rr[ND], ri[ND];
 #pragma unroll
   for (int i = 0; i < ND; ++i) {
-    const double apr = coef[(C_APRE + i) * ld + pc], api = coef[(C_APIM + i) * ld + pc];
-    er[i] = apr;
-    ei[i] = api;
     rr[i] = 1.0;
     ri[i] = 0.0;
     if (i > 0) {
-      const double dt = coef[(C_DT1 + i - 1) * ld + pc];
       double s, co;
-      sincos_cycles((double)(k0 + ke - 1) * df * dt, T, &s, &co);
-      er[i] = apr * co + api * s;
-      ei[i] = api * co - apr * s;
-      sincos_cycles(df * dt, T, &s, &co);
+      sincos_cycles(df * coef[(C_DT1 + i - 1) * ld + pc], T, &s, &co);
       rr[i] = co;
       ri[i] = s;  // conj(rho_i): the walk descends
     }
@@ -275,111 +261,156 @@ __global__ void __launch_bounds__(256, 4) k_tbins(const double* __restrict__ coe
       }
     }
     const double yr = gr * sr - gi * si, yi = gr * si + gi * sr;
-    if (k == mid - 1 && ke > mid) {  // into the lower cell
-      put_top(mr[K - 1], mi[K - 1]);
-#pragma unroll
-      for (int m = K - 1; m > 0; --m) {
-        mr[m] = mr[m - 1];
-        mi[m] = mi[m - 1];
-      }
-      mr[0] = mi[0] = 0.0;
-    }
     // the grid weights of the bin's offset in its cell (the same for every
     // cell and proposal: wave-uniform scalar loads)
-    const double* __restrict__ tq = basis + (int64_t)(k >= mid ? k - mid : k - kb) * K;
+    const double* __restrict__ tq = basis + (int64_t)(k - kb) * K;
 #pragma unroll
     for (int m = 0; m < K; ++m) {
       mr[m] = fma(tq[m], yr, mr[m]);
       mi[m] = fma(tq[m], yi, mi[m]);
     }
   };
-  if constexpr (PREC == 0) {
-    for (int k = ke - 1; k >= kb; --k) {
-      const double* __restrict__ rec = bins + (int64_t)k * RS;
-      double gr, gi;
-      tm_phasor<0>(phase_cycles(c, rec[0], rec[1], rec[2], rec[3]), T, &gr, &gi);
-      visit(k, gr, gi);
-    }
-  } else {
-    // One run at a time: its top (up to) four bins evaluated directly give
-    // the backward differences; every bin of the run in this block is then
-    // visited from one call site (direct phases for the top bins, the
-    // recurrence below them), which keeps the loop body small.  A block
-    // that starts inside a run advances the recurrence through the run's
-    // bins above it without visiting them.
-    const double lin_step = -c.a8 * df;  // linear phase change per bin of the descending walk
-    int k = ke - 1;
-    while (k >= kb) {
-      int L = 0, s = 0;
+  auto cell = [&](bool upper) {
+    kb = upper ? mid : b0;
+    ke = upper ? b1 : (b1 < mid ? b1 : mid);  // no bins beyond the band
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int sj = k & ~(R.len[j] - 1);
-        if (L == 0 && sj >= R.k_min[j]) {
-          L = R.len[j];
-          s = sj;
+    for (int m = 0; m < K; ++m) mr[m] = mi[m] = 0.0;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const double apr = coef[(C_APRE + i) * ld + pc], api = coef[(C_APIM + i) * ld + pc];
+      er[i] = apr;
+      ei[i] = api;
+      if (i > 0) {
+        double s, co;
+        sincos_cycles((double)(k0 + ke - 1) * df * coef[(C_DT1 + i - 1) * ld + pc], T, &s, &co);
+        er[i] = apr * co + api * s;
+        ei[i] = api * co - apr * s;
+      }
+    }
+    if constexpr (PREC == 0) {
+      for (int k = ke - 1; k >= kb; --k) {
+        const double* __restrict__ rec = bins + (int64_t)k * RS;
+        double gr, gi;
+        tm_phasor<0>(phase_cycles(c, rec[0], rec[1], rec[2], rec[3]), T, &gr, &gi);
+        visit(k, gr, gi);
+      }
+    } else {
+      // One run at a time: its top (up to) four bins evaluated directly give
+      // the backward differences; every bin of the run in this block is then
+      // visited from one call site (direct phases for the top bins, the
+      // recurrence below them), which keeps the loop body small.  A block
+      // that starts inside a run advances the recurrence through the run's
+      // bins above it without visiting them.
+      const double lin_step = -c.a8 * df;  // linear phase change per bin of the descending walk
+      int k = ke - 1;
+      while (k >= kb) {
+        int L = 0, s = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int sj = k & ~(R.len[j] - 1);
+          if (L == 0 && sj >= R.k_min[j]) {
+            L = R.len[j];
+            s = sj;
+          }
         }
-      }
-      // a bin below the lowest level is a run of one, evaluated directly
-      const int top = L == 0 ? k : (s + L - 1 < n_freq - 1 ? s + L - 1 : n_freq - 1);
-      if (L == 0) s = k;
-      const int nd = top - s + 1 < 4 ? top - s + 1 : 4;
-      double r0 = 0.0, r1 = 0.0, r2 = 0.0, r3 = 0.0;  // direct phases of bins top, top - 1, ...
-      double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0, lin = 0.0;
+        // a bin below the lowest level is a run of one, evaluated directly
+        const int top = L == 0 ? k : (s + L - 1 < n_freq - 1 ? s + L - 1 : n_freq - 1);
+        if (L == 0) s = k;
+        const int nd = top - s + 1 < 4 ? top - s + 1 : 4;
+        double r0 = 0.0, r1 = 0.0, r2 = 0.0, r3 = 0.0;  // direct phases of bins top, top - 1, ...
+        double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0, lin = 0.0;
 #pragma nounroll
-      for (int j = 0; j < nd; ++j) {
-        const double* __restrict__ rc = bins + (int64_t)(top - j) * RS;
-        const double nl = phase_nonlinear(c, rc[0], rc[1], rc[2], rc[3]);
-        lin = fma(c.a8, rc[0] * rc[1], c.a5);
-        const double d1 = nl - n0;
-        const double d2 = d1 - n1;
-        n3 = d2 - n2;
-        n2 = d2;
-        n1 = d1;
-        n0 = nl;
-        const double ph = nl + lin;
-        r0 = j == 0 ? ph : r0;
-        r1 = j == 1 ? ph : r1;
-        r2 = j == 2 ? ph : r2;
-        r3 = j == 3 ? ph : r3;
-      }
-      double p0 = n0 + lin, p1 = n1 + lin_step, p2 = n2;
-      const double p3 = n3;
-      int kk = top - nd;
-      for (; kk > k; --kk) {  // above the walk's first bin: advance only
-        p2 += p3;
-        p1 += p2;
-        p0 += p1;
-      }
-      const int lo = s > kb ? s : kb;
-      for (kk = k; kk >= lo; --kk) {
-        const int j = top - kk;
-        double ph;
-        if (j < nd) {
-          ph = j == 0 ? r0 : (j == 1 ? r1 : (j == 2 ? r2 : r3));
-        } else {
+        for (int j = 0; j < nd; ++j) {
+          const double* __restrict__ rc = bins + (int64_t)(top - j) * RS;
+          const double nl = phase_nonlinear(c, rc[0], rc[1], rc[2], rc[3]);
+          lin = fma(c.a8, rc[0] * rc[1], c.a5);
+          const double d1 = nl - n0;
+          const double d2 = d1 - n1;
+          n3 = d2 - n2;
+          n2 = d2;
+          n1 = d1;
+          n0 = nl;
+          const double ph = nl + lin;
+          r0 = j == 0 ? ph : r0;
+          r1 = j == 1 ? ph : r1;
+          r2 = j == 2 ? ph : r2;
+          r3 = j == 3 ? ph : r3;
+        }
+        double p0 = n0 + lin, p1 = n1 + lin_step, p2 = n2;
+        const double p3 = n3;
+        int kk = top - nd;
+        for (; kk > k; --kk) {  // above the walk's first bin: advance only
           p2 += p3;
           p1 += p2;
           p0 += p1;
-          ph = p0;
         }
-        double gr, gi;
-        tm_phasor<1>(ph, T, &gr, &gi);
-        visit(kk, gr, gi);
+        const int lo = s > kb ? s : kb;
+        for (kk = k; kk >= lo; --kk) {
+          const int j = top - kk;
+          double ph;
+          if (j < nd) {
+            ph = j == 0 ? r0 : (j == 1 ? r1 : (j == 2 ? r2 : r3));
+          } else {
+            p2 += p3;
+            p1 += p2;
+            p0 += p1;
+            ph = p0;
+          }
+          double gr, gi;
+          tm_phasor<1>(ph, T, &gr, &gi);
+          visit(kk, gr, gi);
+        }
+        k = s - 1;
       }
-      k = s - 1;
     }
-  }
-  if (PREC == 1) {  // remove the mean bias of the hardware phasor
+    if (PREC == 1) {  // remove the mean bias of the hardware phasor
 #pragma unroll
-    for (int m = 0; m < K; ++m) {
-      const double tr = mr[m] * pg_re - mi[m] * pg_im;
-      mi[m] = mr[m] * pg_im + mi[m] * pg_re;
-      mr[m] = tr;
+      for (int m = 0; m < K; ++m) {
+        const double tr = mr[m] * pg_re - mi[m] * pg_im;
+        mi[m] = mr[m] * pg_im + mi[m] * pg_re;
+        mr[m] = tr;
+      }
     }
-  }
-  if (mine) {
+  };
+  if constexpr (PAIR) {
+    __shared__ double red[2][2 * K][64];
+    const bool upper = wv & 1;
+    cell(upper);
+    if (upper) {
 #pragma unroll
-    for (int m = 0; m < K; ++m) out[m] = make_double2(mr[m], mi[m]);
+      for (int m = 0; m < K; ++m) {
+        red[wv >> 1][2 * m][lane] = mr[m];
+        red[wv >> 1][2 * m + 1][lane] = mi[m];
+      }
+    }
+    __syncthreads();
+    if (upper || !mine || b >= n_blk) return;
+    double2* __restrict__ out = part + p * pitch + (int64_t)b * (K + 1);
+    const double (*hi)[64] = red[wv >> 1];
+    out[0] = make_double2(mr[0], mi[0]);
+#pragma unroll
+    for (int m = 1; m < K; ++m)
+      out[m] = make_double2(mr[m] + hi[2 * m - 2][lane], mi[m] + hi[2 * m - 1][lane]);
+    out[K] = make_double2(hi[2 * K - 2][lane], hi[2 * K - 1][lane]);
+  } else {
+    if (b >= n_blk) return;
+    double2* out = part + p * pitch + (int64_t)b * (K + 1);
+#pragma nounroll
+    for (int upper = 1; upper >= 0; --upper) {
+      cell(upper);
+      if (!mine) continue;
+      if (upper) {
+#pragma unroll
+        for (int m = 0; m < K; ++m) out[m + 1] = make_double2(mr[m], mi[m]);
+      } else {
+        out[0] = make_double2(mr[0], mi[0]);
+#pragma unroll
+        for (int m = 1; m < K; ++m) {
+          const double2 hi = out[m];
+          out[m] = make_double2(mr[m] + hi.x, mi[m] + hi.y);
+        }
+      }
+    }
   }
 }
 
@@ -398,13 +429,19 @@ static void launch_tspread(gw_ctx* ctx, const double* coef, int64_t ld, int64_t 
     };
     fp64 ? launch(k_tspread<ND, 0>) : launch(k_tspread<ND, 1>);
   }
+  // in pairs while the waves then still run all at once (four a SIMD)
+  const bool pair = nptile * 2 * n_blk <= 4096;
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(nptile * ((n_blk + 3) / 4))), dim3(256), 0, st, coef, ld, n, !nodes,
-                       ctx->bins, ctx->geom.k0, ctx->geom.df, (int)ctx->geom.n_freq, blk, n_blk, make_trig_consts(),
+    const int units = pair ? (n_blk + 1) / 2 : (n_blk + 3) / 4;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(nptile * units)), dim3(256), 0, st, coef, ld, n, !nodes, ctx->bins,
+                       ctx->geom.k0, ctx->geom.df, (int)ctx->geom.n_freq, blk, n_blk, make_trig_consts(),
                        make_phase_runs(ctx->geom), fp64 ? 1.0 : ctx->pgain_re, fp64 ? 0.0 : ctx->pgain_im,
                        (const double*)t.bins_w, (int64_t)t.n_pts, part);
   };
-  fp64 ? launch(k_tbins<ND, 0>) : launch(k_tbins<ND, 1>);
+  if (pair)
+    fp64 ? launch(k_tbins<ND, 0, true>) : launch(k_tbins<ND, 1, true>);
+  else
+    fp64 ? launch(k_tbins<ND, 0, false>) : launch(k_tbins<ND, 1, false>);
 }
 
 gw_status time_grid_shape(const gw_ctx* ctx, TimeGridShape* g) {
@@ -450,7 +487,10 @@ gw_status loglike_tmarg_staged(gw_ctx* ctx, const double* theta, int64_t n, int 
   if (s == GW_OK) s = tm_grid_init(ctx, g);
   if (s != GW_OK) return s;
   const TmGrid& t = ctx->tm_grid;
-  const int64_t chunk = tgrid_chunk_rows(n, t.n_pts);
+  // whole groups of tiles (tile_row)
+  constexpr int64_t kGroup = 64 * kTileGroup;
+  int64_t chunk = tgrid_chunk_rows(n, t.n_pts);
+  if (chunk < n) chunk = chunk > kGroup ? chunk / kGroup * kGroup : kGroup;
   const int nt = 2 * g.jmax + 1;
   s = ensure_buffer(&ctx->coef, &ctx->coef_cap, (int64_t)C_NCOEF * n, "coefficient workspace");
   if (s == GW_OK) s = ensure_buffer(&ctx->tm_mom, &ctx->tm_mom_cap, chunk * t.n_pts * 2, "time-grid sums");
