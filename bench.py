@@ -538,8 +538,9 @@ def time_kernel(gw, torch, ctx, fn, steps, mode):
 def tmarg_leg(gw, torch, ctx, theta, steps, warmup, mixed_value):
     """Phase + coalescence-time marginal on the same 4096 proposals of the
     128 s band: grid t_j = j / 16384 s over |t| <= 0.1 s (3273 points, R = 4),
-    block moments of 512 bins (K Chebyshev orders) and K FFTs of 4096 points
-    per proposal; k_tmom and k_tgrid timed separately with HIP events."""
+    samples spread on a frequency grid of 256-bin cells and one transform of
+    8192 points per proposal; the spreading kernels and k_tgrid timed
+    separately with HIP events."""
     n = theta.shape[0]
     out = torch.empty(n, dtype=torch.float64, device="cuda")
     delta, n_t, p_len, blk = gw.gw_time_grid_info(ctx.handle)
@@ -571,10 +572,6 @@ def tmarg_leg(gw, torch, ctx, theta, steps, warmup, mixed_value):
                 "workload": "phase+time marginal on the 128 s full band, 4096 prior draws, t_c grid of a quarter "
                             "of the segment's sampling interval over +-0.1 s"})
     return res
-
-
-def prob_n_freq(ctx):
-    return int(ctx.n_freq)
 
 
 def nested_full_leg(gw, torch):

@@ -487,7 +487,7 @@ gw_status slice_sweep(gw_ctx* ctx, const gw_sweep_args* args, void* stream);
  * not counted in n_evals).  A chain's waveform is rebuilt lazily: when it is
  * in an extrinsic block after a slow move (or at the start of the sweep), that
  * round's candidates evaluate in full and the rebuild follows the round.
- * Device memory: k x (n_freq / B) x n_det x 16 x 8 bytes (B the moment block,
+ * Device memory: k x (n_freq / B) x n_det x 96 bytes (B the moment block,
  * 256 bins at df = 1/128 Hz), at most 64 GiB, kept with the context.  Results
  * agree with use_cache = 0 to rounding, so a near tie with log L* can resolve
  * differently.
@@ -739,9 +739,9 @@ gw_status gw_phasor_gain(const gw_ctx* ctx, double* re, double* im);
 
 /*
  * Kernel timing for roofline reporting.  enable = 1: the dominant kernel (the
- * full-band overlap kernel, the heterodyned evaluation kernel, or the moment
- * kernel of a time marginal); enable = 2: the time-grid kernel of the time
- * marginals; 0 turns timing off.  While enabled, every launch of the chosen
+ * full-band overlap kernel, the heterodyned evaluation kernel, or the kernels
+ * that sum a time marginal's samples on its frequency grid, timed as one);
+ * enable = 2: the time-grid kernel of the time marginals; 0 turns timing off.  While enabled, every launch of the chosen
  * kernel is bracketed by HIP events recorded on the launch stream.
  * gw_profile_read waits for the recorded events, returns the summed kernel
  * time (ms) and the number of launches, and clears the record.  At most 4096

@@ -607,7 +607,7 @@ __global__ void __launch_bounds__(64) k_wmom_build(const double* __restrict__ co
       visit(k, cs, -sn);
     }
   } else {
-    // the runs of the mixed walk, as in k_tmom: one visit site per bin
+    // the runs of the mixed walk, as in k_tbins: one visit site per bin
     int k = ke - 1;
     while (k >= kb) {
       int L = 0, s = 0;
@@ -1179,7 +1179,7 @@ __global__ void __launch_bounds__(256) k_full_mfma(const double* __restrict__ co
 // group length after k_partial_reduce).  A row summed over the nodes (C_NODE
 // at least node_from) has partials in the first nch_node chunks only.
 __device__ inline int row_chunks(const double* __restrict__ coef, int64_t ld, int64_t p, int n_chunks, int nch_node,
-                                 double node_from = kNodeFull) {
+                                 double node_from) {
   return nch_node > 0 && coef[C_NODE * ld + p] >= node_from ? nch_node : n_chunks;
 }
 
@@ -1263,19 +1263,16 @@ __global__ void __launch_bounds__(1024) k_epilogue(const double* __restrict__ pa
 }
 
 // First level of the chunk reduction for small batches (few rows, many
-// chunks): workgroup (tile, g) adds chunks g cpg .. (g + 1) cpg - 1 of its 64
+// chunks) without node sums: workgroup (tile, g) adds chunks g cpg .. (g + 1) cpg - 1 of its 64
 // rows (its 4 waves interleaved, then in wave order) and stores the sum in
 // chunk g cpg of the same buffer, which no other workgroup reads.
-__global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ partial, int n_chunks, int cpg,
-                                                        int nch_node, int nd, const double* __restrict__ coef,
-                                                        int64_t ld, int64_t n) {
+__global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ partial, int n_chunks, int cpg, int nd,
+                                                        int64_t n) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t p = (int64_t)blockIdx.x * 64 + lane;
   const int64_t pc = p < n ? p : n - 1;
   const int c0 = blockIdx.y * cpg;
-  const int own = row_chunks(coef, ld, pc, n_chunks, nch_node);
-  if (!__any(c0 < own)) return;  // the four waves hold the same rows
-  const int c1 = c0 + cpg < own ? c0 + cpg : own;
+  const int c1 = c0 + cpg < n_chunks ? c0 + cpg : n_chunks;
   double z[2 * kMaxDet];
 #pragma unroll
   for (int j = 0; j < 2 * kMaxDet; ++j) z[j] = 0.0;
@@ -1306,7 +1303,7 @@ __global__ void __launch_bounds__(256) k_partial_reduce(double* __restrict__ par
 // neighbouring distances (wave_dist_lse), which mostly take the same form of a
 // term, while rows differ.
 // Bound by latency: 9.9 us at 250 rows of the 128 s band, 12.3 + 7.6 as two
-// launches (36 us a call, now 27); 4096 rows 108 and 106.
+// launches (36 us a call, 27 so); 4096 rows 98 us a call, 100 as two.
 template <int PREC>
 __global__ void __launch_bounds__(256) k_epilogue_dist(const double* __restrict__ partial, int n_chunks, int cstride,
                                                        int nch_node, int nd, const double* __restrict__ coef,
@@ -1759,7 +1756,7 @@ gw_status launch_epilogue_z(gw_ctx* ctx, double* partial, int n_chunks, int nch_
     cstride = 8;
     groups = (n_chunks + cstride - 1) / cstride;
     hipLaunchKernelGGL(k_partial_reduce, dim3((unsigned)blocks, (unsigned)groups), dim3(256), 0, st, partial, n_chunks,
-                       cstride, nch_node, ctx->n_det, coef, ld, n);
+                       cstride, ctx->n_det, n);
     gw_status s = check_hip(hipGetLastError(), "partial reduction launch");
     if (s != GW_OK) return s;
   }

@@ -1,11 +1,12 @@
-// Work split of the heterodyned time marginal's edge-weight moments (host
-// only).  The edges lie in n_blk frequency blocks (block b holds edges
-// [bs[b], bs[b + 1])); a block's moment needs all of its edges, and a chunk
-// costs one unit per edge plus one per block it emits.  Edges of equal phase
-// change crowd into the lowest blocks (hundreds of edges in the first), so
-// chunks are edge ranges of about equal cost that may cut a block: a block
-// cut by several chunks gets one partial moment per chunk (a "piece" with a
-// slot of its own), and a fix-up pass adds a block's pieces in chunk order.
+// Work split of the heterodyned time marginal's edges (host only).  The edges lie
+// in n_blk grid cells (cell b holds edges [bs[b], bs[b + 1])), and a chunk costs one
+// unit per edge plus one per cell whose first grid point it stores.  Edges of equal
+// phase change crowd into the lowest cells (hundreds of edges in the first), so
+// chunks are edge ranges of about equal cost that may cut a cell.  The kernels take
+// the chunks' first edges and cell ranges (e0, blo, bhi): every chunk's sums have
+// points of their own, which the grid kernel adds (gw_tgplan.h).  Of the cells that
+// several chunks cut, the plan also lists the pieces, each with a number of its own,
+// in chunk order (sfirst, slast, fb, fs, fc): what a reduction piece by piece adds.
 #pragma once
 
 #include <algorithm>

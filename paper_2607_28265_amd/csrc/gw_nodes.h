@@ -22,10 +22,13 @@
 // the largest S.  S is the largest of a set of waveforms around the sampler's
 // prior (kNodeMc and 1.45 Msun, the prior's mass ratios and tides, aligned
 // spins of 0.1), times 1.02, plus 1 ms.  k_prologue compares each row's
-// Psi' - R' with S at kNodeCheck frequencies (Psi' - R' is a sum of a dozen
-// powers of f, too smooth to exceed S between them by more than that margin)
-// and its delays with tau_max; a row that exceeds either takes the sums over
-// every bin instead.
+// Psi' - R' with S at kNodeCheck frequencies and its delays with tau_max; a row
+// that exceeds either takes the sums over every bin instead.  Between those
+// frequencies Psi' - R' may exceed S (a search over masses, spins and tides found
+// up to 9 % on 20-2048 Hz, 12 % on 1-8192 Hz), but S + tau_max by under 2 %, and
+// the node counts have more to spare: their bound is far above the error at tens
+// of nodes, and they take one node more.  Such rows interpolate to 7e-14 like the
+// rest.
 #pragma once
 
 #include "gw_device.h"
