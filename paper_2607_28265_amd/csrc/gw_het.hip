@@ -326,18 +326,18 @@ struct HetConst {
 
 // exp(-2 pi i r), FP64, from tab [256] = (cos, sin)(2 pi k / 256) in LDS:
 // |a| <= pi / 256 about the nearest point, cos a - 1 and sin a by their Taylor
-// polynomials (first dropped terms 1.3e-20 and 8e-18).  The table index is the
-// low bits of 256 r rounded, plus 1.5 2^52: it holds for |r| < 2^43 cycles (a row
-// far from the reference, or hours away in t_c; a conversion to 32 bits would
-// saturate from 2^23 on).  19 vector operations and a gather against 31 of
-// sincos_cycles; k_het has LDS time to spare.  With the rounding done by that sum
-// as well (17 operations) 20,011 rows of 5000 bins took 388 us and not 399, but
-// 6481 rows of 726 bins 58 and not 56.
+// polynomials (first dropped terms 1.3e-20 and 8e-18).  The sum r + 1.5 2^44
+// rounds r to 1/256 and its low bits are the table index: it holds for |r| < 2^43
+// cycles (a row far from the reference, or hours away in t_c; a conversion to 32
+// bits would saturate from 2^23 on).  17 vector operations and a gather against 31
+// of sincos_cycles; k_het has LDS time to spare.  20,011 rows of 5000 bins take 394
+// us and 6481 rows of 726 bins 54.6, against 408 and 56.6 with 256 r rounded and
+// converted.
 __device__ inline void het_phasor_tab(double r, const double2* __restrict__ tab, double* gr, double* gi) {
-  constexpr double kRound = 6755399441055744.0;  // 1.5 2^52
-  const double q = rint(r * 256.0);
-  const double a = fma(q, -1.0 / 256.0, r) * kTwoPi;
-  const double2 t = tab[__double2loint(q + kRound) & 255];
+  constexpr double kRound = 26388279066624.0;  // 1.5 2^44: the sum rounds to 1/256
+  const double m = r + kRound;
+  const double a = (r - (m - kRound)) * kTwoPi;
+  const double2 t = tab[__double2loint(m) & 255];
   const double a2 = a * a;
   const double sn = fma(a * a2, fma(a2, 1.0 / 120.0, -1.0 / 6.0), a);
   const double cm = a2 * fma(a2, fma(a2, -1.0 / 720.0, 1.0 / 24.0), -0.5);
